@@ -26,6 +26,9 @@ KernelEntry** kernel_table(int* count) {
 // else the shape's variant 0.  want = 0 leaves the choice to the library: variant 0, except that a plan
 // without split tiles (whole_tile_iters = its k-iterations per tile, 0 for plans with split tiles) gets
 // the variant marked for such plans where the shape has one and the tiles are deep enough.
+// whole_tile_iters is also 0 for problems on the register-staged path: its loads are bound by the vector L1,
+// and two waves per SIMD hide that better (3841 x 4225 x 4097, data-parallel, eight waves / four waves:
+// 224 / 252 us with 256 x 256, 232 / 258 us with 256 x 128, 238 / 262 us with 128 x 128).
 KernelEntry* find_kernel(int dtype, int bm, int bn, int bk, int fixup = SK_FIXUP_FLAGS, int want = 0, int whole_tile_iters = 0) {
     int n;
     KernelEntry** t = kernel_table(&n);
@@ -40,6 +43,14 @@ KernelEntry* find_kernel(int dtype, int bm, int bn, int bk, int fixup = SK_FIXUP
     return exact ? exact : fallback;
 }
 
+
+// k-iterations per tile as find_kernel wants them.
+int whole_tile_iters(const sk_plan_t* plan) {
+    const sk_plan_header& h = plan->h;
+    const int piece = h.in_dtype == SK_FP8_E4M3 ? 16 : 8;          // elements of a 16-byte piece
+    const bool staged = h.K % piece != 0 || h.N % piece != 0;
+    return plan->needs_fixup || staged ? 0 : h.iters_per_tile;
+}
 
 // Helpers of the atomic fix-up: clear the fp32 image, and turn it into a 16-bit D afterwards.
 __global__ void zero_image_kernel(float4* p, size_t n4, float* tail, int n_tail) {
@@ -98,7 +109,7 @@ extern "C" int sk_plan_kernel_info(const sk_plan_t* plan, int32_t* threads, int3
     if (!plan) return SK_ERR_INVALID_ARG;
     const sk_plan_header& h = plan->h;
     const bool atomic = plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup;
-    const KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, plan->needs_fixup ? 0 : plan->h.iters_per_tile);
+    const KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, whole_tile_iters(plan));
     if (!e) return SK_ERR_UNSUPPORTED;
     if (threads) *threads = e->threads;
     if (lds_bytes) *lds_bytes = e->lds_bytes;
@@ -120,7 +131,7 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
         return SK_ERR_UNSUPPORTED;
     // plans without split tiles run the plain kernel under either fix-up mode
     const bool atomic = plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup;
-    KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, plan->needs_fixup ? 0 : plan->h.iters_per_tile);
+    KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, whole_tile_iters(plan));
     if (!e) return SK_ERR_UNSUPPORTED;
     if (plan->needs_fixup && !workspace && !(atomic && h.out_dtype == SK_F32)) return SK_ERR_WORKSPACE;
     const bool aligned = (h.K % e->piece_elems == 0) && (h.N % e->piece_elems == 0);   // whole 16-byte pieces per row

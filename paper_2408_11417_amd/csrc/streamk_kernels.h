@@ -158,8 +158,12 @@ struct Cfg {
     // sits in the instruction-by-instruction loop, so they carry no such switch
     static constexpr bool MAY_STREAM_B = BM <= 64;
     static_assert(!FINE || PIN_ORDER, "the instruction-by-instruction order needs two operand sets");
-    // register-staged path: room to hold the next stage's pieces (4 registers each) during the matrix-core work
-    static constexpr bool STAGE_AHEAD = NW >= 8 ? 2 * FRAG_REGS + ACC_REGS + 4 * (CA + CB) + 64 <= 256 : 2 * FRAG_REGS + 4 * (CA + CB) + 64 <= 224;
+    // register-staged path: a stage's pieces (4 registers each).  STAGED_FINE: the instruction-by-instruction
+    // MAC loop with one stage in registers, where the two operand sets leave room for it; the other tiles hold
+    // STAGES_HELD stages in registers, about 64 registers of loads in flight.
+    static constexpr int PIECES = CA + CB;
+    static constexpr bool STAGED_FINE = FINE && KK % 2 == 0 && 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 5 * PIECES + 32 <= 256;
+    static constexpr int STAGES_HELD = 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 4 * PIECES + 64 > 256 ? 0 : PIECES <= 5 ? 4 : PIECES <= 8 ? 2 : 1;
     // vector stores one wave issues in the epilogue of an unsplit interior tile with 16-bit output (an fp32
     // output issues more): what may still be in flight when the next tile's first stage is waited for
     static constexpr int EPILOGUE_STORES = MI * NI * (MF == 32 ? ACC / 8 : ACC / 4);
@@ -262,41 +266,57 @@ __device__ __forceinline__ uint4 load_piece(const unsigned char* __restrict__ ba
     return v;
 }
 
-// Register-staged fill of one stage with zero fill at every edge (same LDS image as the DMA path),
-// in two halves: fetch the stage's pieces into registers, and later park them in LDS.
+// Register-staged fill of one stage (same LDS image as the DMA path), piece by piece: fetch a piece
+// into registers, and later park it in LDS.  Piece j of thread t is LDS position j * THREADS + t of the
+// stage's A or B tile; the swizzle is applied by choosing which global piece goes there, as on the DMA path.
+// INSIDE pieces are fetched with one under-aligned 16-byte load at a precomputed offset, no checks: rows beyond
+// M are clamped, and a piece that reaches beyond column N - 1 of B runs on into the next row - it only feeds
+// output columns that are never stored.  The caller vouches that the k-iteration is below inside_k(), that
+// is, lies wholly inside K with at least one row of B behind it (so that running on stays inside B).
+// Everything else goes through load_piece, with zero fill beyond K.
 template <class C, bool ALIGNED> struct StagedFill {
-    uint4 ra[C::CA], rb[C::CB];
-    __device__ __forceinline__ void fetch(const GemmArgs& g, int m0, int n0, int kit) {
-        const int tid = threadIdx.x;
-        const unsigned char* A = static_cast<const unsigned char*>(g.A);
-        const unsigned char* B = static_cast<const unsigned char*>(g.B);
-        const int k0 = kit * C::BK;
+    uint32_t a_off[C::CA], b_off[C::CB];         // byte offsets from A / B at k-iteration 0
+    int m0, n0;
+    static __device__ __forceinline__ int inside_k(const GemmArgs& g) { return g.N >= C::PE ? (g.K - 1) / C::BK : 0; }
+    __device__ __forceinline__ void init(const GemmArgs& g, int m0_, int n0_) {
+        m0 = m0_;
+        n0 = n0_;
 #pragma unroll
-        for (int i = 0; i < C::CA; i++) {
-            const int p = tid + i * C::THREADS;
-            if (C::A_PIECES % C::THREADS == 0 || p < C::A_PIECES)
-                ra[i] = load_piece<C::ES, ALIGNED>(A, m0 + p / C::CPA, k0 + (p % C::CPA) * C::PE, g.M, g.K);
+        for (int j = 0; j < C::CA; j++) {
+            const int p = threadIdx.x + j * C::THREADS, r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
+            const int row = m0 + r < g.M ? m0 + r : g.M - 1;
+            a_off[j] = ((uint32_t)row * (uint32_t)g.K + (uint32_t)(C::PE * c)) * C::ES;
         }
 #pragma unroll
-        for (int i = 0; i < C::CB; i++) {
-            const int p = tid + i * C::THREADS;
-            if (C::B_PIECES % C::THREADS == 0 || p < C::B_PIECES)
-                rb[i] = load_piece<C::ES, ALIGNED>(B, k0 + p / C::CPB, n0 + (p % C::CPB) * C::PE, g.K, g.N);
+        for (int j = 0; j < C::CB; j++) {
+            const int p = threadIdx.x + j * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8>(k);
+            const int col = n0 + C::PE * c;
+            b_off[j] = ((uint32_t)k * (uint32_t)g.N + (uint32_t)(col < g.N ? col : 0)) * C::ES;
         }
     }
-    __device__ __forceinline__ void park(unsigned char* a_stage, unsigned char* b_stage) const {
-        const int tid = threadIdx.x;
-        uint4* sA = reinterpret_cast<uint4*>(a_stage);
-        uint4* sB = reinterpret_cast<uint4*>(b_stage);
-#pragma unroll
-        for (int i = 0; i < C::CA; i++) {
-            const int p = tid + i * C::THREADS, r = p / C::CPA;
-            if (C::A_PIECES % C::THREADS == 0 || p < C::A_PIECES) sA[r * C::CPA + ((p % C::CPA) ^ swz_a<C::CPA>(r))] = ra[i];
+    static __device__ __forceinline__ uint4 load_inside(const char* base, uint32_t off) {
+        const u32x4 w = ALIGNED ? *reinterpret_cast<const u32x4*>(base + off)
+                      : C::ES == 2 ? reinterpret_cast<const Piece2*>(base + off)->v : reinterpret_cast<const Piece1*>(base + off)->v;
+        return make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    // piece q of the stage of k-iteration kit: the B pieces first, then the A pieces
+    template <bool INSIDE> __device__ __forceinline__ uint4 fetch(const GemmArgs& g, int kit, int q) const {
+        if (q < C::CB) {
+            if (INSIDE) return load_inside(static_cast<const char*>(g.B) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)) * (uint32_t)g.N, b_off[q]);
+            const int p = threadIdx.x + q * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8>(k);
+            return load_piece<C::ES, ALIGNED>(static_cast<const unsigned char*>(g.B), kit * C::BK + k, n0 + c * C::PE, g.K, g.N);
         }
-#pragma unroll
-        for (int i = 0; i < C::CB; i++) {
-            const int p = tid + i * C::THREADS, k = p / C::CPB;
-            if (C::B_PIECES % C::THREADS == 0 || p < C::B_PIECES) sB[k * C::CPB + ((p % C::CPB) ^ swz_b<C::FP8>(k))] = rb[i];
+        const int j = q - C::CB;
+        if (INSIDE) return load_inside(static_cast<const char*>(g.A) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)), a_off[j]);
+        const int p = threadIdx.x + j * C::THREADS, r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
+        return load_piece<C::ES, ALIGNED>(static_cast<const unsigned char*>(g.A), m0 + r, kit * C::BK + c * C::PE, g.M, g.K);
+    }
+    static __device__ __forceinline__ void park(unsigned char* a_stage, unsigned char* b_stage, int q, uint4 v) {
+        const int p = threadIdx.x + (q < C::CB ? q : q - C::CB) * C::THREADS;
+        if (q < C::CB) {
+            if (C::B_PIECES % C::THREADS == 0 || p < C::B_PIECES) reinterpret_cast<uint4*>(b_stage)[p] = v;
+        } else {
+            if (C::A_PIECES % C::THREADS == 0 || p < C::A_PIECES) reinterpret_cast<uint4*>(a_stage)[p] = v;
         }
     }
 };
@@ -531,6 +551,127 @@ __device__ __forceinline__ void mac_prefetch(const GemmArgs& g, int m0, int n0, 
         issue_requests<C, false, NT>(g, dm, lds0, k_begin, nk, full_k, j, (j + C::NSA) % C::NSA, (j + 2 * C::NSB) % C::NSB, 0, 1);
 }
 
+// MAC loop of one segment on the register-staged path (rows of A or B that do not start on 16-byte
+// boundaries: the LDS-DMA loads need aligned addresses).  Two LDS slots, stage s in slot s & 1.
+//
+// STAGED_FINE: the pipeline of the DMA path with registers in place of the deeper ring.  Trip i =
+// [barrier that hands over stage i+1, one k-step before stage i ends] [last k-step of stage i, k-steps
+// 0 .. KK-2 of stage i+1], written out slot by slot: one matrix-core instruction, its share of the next
+// k-step's LDS reads, and one piece parked (stage i+2, into the slot that the barrier has freed) whose
+// registers then take the same piece of stage i+3.  A load therefore has a whole trip to land.
+// What bounds it is the vector L1: under-aligned 16-byte loads move about 25 bytes per clock and CU where
+// aligned ones move 52 (a microbenchmark of this access pattern), and a 256 x 256 x 64 stage is 64 KB.
+template <class C, bool ALIGNED, bool TR>
+__device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n0, int k_begin, int k_end, unsigned char* smem,
+                                                const FragMap<C>& fm, typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI]) {
+    const int nk = k_end - k_begin;
+    StagedFill<C, ALIGNED> sf;
+    sf.init(g, m0, n0);
+    const int inside = StagedFill<C, ALIGNED>::inside_k(g);
+    auto a_slot = [&](int s) { return smem + (s & 1) * C::A_BYTES; };
+    auto b_slot = [&](int s) { return smem + C::B_RING + (s & 1) * C::B_BYTES; };
+    if constexpr (C::STAGED_FINE) {
+        constexpr int NM = C::MI * C::NI, SLOTS = C::KK * NM, PS = SLOTS * 7 / 8 > 0 ? SLOTS * 7 / 8 : 1;
+        uint4 st[C::PIECES];
+#pragma unroll
+        for (int q = 0; q < C::PIECES; q++) st[q] = k_begin < inside ? sf.template fetch<true>(g, k_begin, q) : sf.template fetch<false>(g, k_begin, q);
+#pragma unroll
+        for (int q = 0; q < C::PIECES; q++) sf.park(a_slot(0), b_slot(0), q, st[q]);
+        if (nk > 1) {
+#pragma unroll
+            for (int q = 0; q < C::PIECES; q++) st[q] = k_begin + 1 < inside ? sf.template fetch<true>(g, k_begin + 1, q) : sf.template fetch<false>(g, k_begin + 1, q);
+        }
+        Frags<C> f[2];
+        auto step = [&](int i, int k_step, auto mma, auto read, const Frags<C>& cur, Frags<C>& nxt, int kk_next, auto steady) {
+            constexpr int R = Frags<C>::READS, NRS = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
+            constexpr bool STEADY = decltype(steady)::value;
+#pragma unroll
+            for (int s = 0; s < NM; s++) {
+                const int mi = s / C::NI, ni = s % C::NI, slot = k_step * NM + s;
+                if (decltype(mma)::value)
+                    acc[mi][ni] = TR ? Mfma<C::DT, C::MF>::run(cur.b[ni], cur.a[mi], acc[mi][ni]) : Mfma<C::DT, C::MF>::run(cur.a[mi], cur.b[ni], acc[mi][ni]);
+                if (decltype(read)::value && s < NRS) {
+#pragma unroll
+                    for (int r = s * R / NRS; r < (s + 1) * R / NRS; r++) nxt.load_one(a_slot(i + 1), b_slot(i + 1), fm, kk_next, r);
+                }
+                if (slot < PS) {
+#pragma unroll
+                    for (int q = slot * C::PIECES / PS; q < (slot + 1) * C::PIECES / PS; q++) {
+                        if (STEADY || i + 2 < nk) sf.park(a_slot(i), b_slot(i), q, st[q]);
+                        if (STEADY) st[q] = sf.template fetch<true>(g, k_begin + i + 3, q);
+                        else if (i + 3 < nk) st[q] = k_begin + i + 3 < inside ? sf.template fetch<true>(g, k_begin + i + 3, q) : sf.template fetch<false>(g, k_begin + i + 3, q);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto trip = [&](int i, auto first, auto next, auto steady) {
+            constexpr bool FIRST = decltype(first)::value, NEXT = decltype(next)::value;
+            if (NEXT) __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);
+            step(i, 0, std::integral_constant<bool, !FIRST>(), std::integral_constant<bool, NEXT>(), f[1], f[0], 0, steady);
+            if (NEXT) {
+#pragma unroll
+                for (int kk = 0; kk < C::KK - 1; kk++) step(i, kk + 1, std::true_type(), std::true_type(), f[kk & 1], f[(kk + 1) & 1], kk + 1, steady);
+            }
+        };
+        // trips 0 .. n_steady-1 fetch a stage that exists and is inside: no checks in their body
+        const int n_steady = (inside - k_begin < nk ? inside - k_begin : nk) - 3;
+        trip(-1, std::true_type(), std::true_type(), std::false_type());
+        int i = 0;
+        for (; i < n_steady; i++) trip(i, std::false_type(), std::true_type(), std::true_type());
+        for (; i < nk - 1; i++) trip(i, std::false_type(), std::true_type(), std::false_type());
+        trip(nk - 1, std::false_type(), std::false_type(), std::false_type());
+    } else {
+        // The other tiles: HELD stages in registers, requested HELD k-iterations ahead of their use (HELD = 0: the
+        // two operand sets leave no room, a stage is requested right before it is parked).
+        constexpr int HELD = C::STAGES_HELD, H = HELD > 0 ? HELD : 1;
+        uint4 st[H][C::PIECES];
+        auto fetch_stage = [&](int kit, uint4 (&dst)[C::PIECES]) {
+            if (kit < inside) {
+#pragma unroll
+                for (int q = 0; q < C::PIECES; q++) dst[q] = sf.template fetch<true>(g, kit, q);
+            } else {
+#pragma unroll
+                for (int q = 0; q < C::PIECES; q++) dst[q] = sf.template fetch<false>(g, kit, q);
+            }
+        };
+        auto consume = [&](int s, uint4 (&src)[C::PIECES], auto steady) {
+            if (HELD == 0) fetch_stage(k_begin + s, src);
+#pragma unroll
+            for (int q = 0; q < C::PIECES; q++) sf.park(a_slot(s), b_slot(s), q, src[q]);
+            if (HELD > 0) {
+                if (decltype(steady)::value) {
+#pragma unroll
+                    for (int q = 0; q < C::PIECES; q++) src[q] = sf.template fetch<true>(g, k_begin + s + H, q);
+                } else if (s + H < nk) {
+                    fetch_stage(k_begin + s + H, src);
+                }
+            }
+            __syncthreads();      // also: every wave is done with the other slot (stage s-1)
+            mac_stage<C, TR>(a_slot(s), b_slot(s), fm, acc);
+        };
+        if (HELD > 0) {
+#pragma unroll
+            for (int h = 0; h < H; h++)
+                if (h < nk) fetch_stage(k_begin + h, st[h]);
+        }
+        // whole rounds of H stages whose requests are all inside, then the rest
+        const int n_steady = HELD == 0 ? 0 : (inside - k_begin < nk ? inside - k_begin : nk) - H;
+        int s = 0;
+        for (; s + H <= n_steady; s += H) {
+#pragma unroll
+            for (int h = 0; h < H; h++) consume(s + h, st[h], std::true_type());
+        }
+        for (; s < nk; s += H) {
+#pragma unroll
+            for (int h = 0; h < H; h++)
+                if (s + h < nk) consume(s + h, st[h], std::false_type());
+        }
+    }
+    __syncthreads();                             // all reads done before the next segment refills
+}
+
 // MAC loop of one segment (Algorithm 1's MAC-loop call): k-iterations [k_begin, k_end) of one tile.
 //
 // Software pipeline of the LDS-DMA path.  Stage s (one k-iteration) lives in A ring slot s % NSA and
@@ -669,21 +810,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
         }
         __syncthreads();                             // all reads done before the next segment refills
     } else {
-        // Register-staged path, two LDS slots.  Where registers allow (STAGE_AHEAD) the pieces of
-        // stage k+1 are requested before the matrix-core work of stage k and parked after it.
-        StagedFill<C, ALIGNED> sf;
-        if (C::STAGE_AHEAD) sf.fetch(g, m0, n0, k_begin);
-        for (int k = k_begin; k < k_end; k++) {
-            const int slot = (k - k_begin) & 1;
-            unsigned char* a_stage = smem + slot * C::A_BYTES;
-            unsigned char* b_stage = smem + C::B_RING + slot * C::B_BYTES;
-            if (!C::STAGE_AHEAD) sf.fetch(g, m0, n0, k);
-            sf.park(a_stage, b_stage);
-            __syncthreads();      // also: every wave is done with the other slot (stage k-1)
-            if (C::STAGE_AHEAD && k + 1 < k_end) sf.fetch(g, m0, n0, k + 1);
-            mac_stage<C, TR>(a_stage, b_stage, fm, acc);
-        }
-        __syncthreads();
+        mac_loop_staged<C, ALIGNED, TR>(g, m0, n0, k_begin, k_end, smem, fm, acc);
     }
 }
 

@@ -137,6 +137,33 @@ def test_ragged_and_unaligned_shapes(shape):
     _run_and_compare(A, B, inputs.F16, sk.SK_POLICY_ALL_SK, (128, 128, 32), grid=256)
 
 
+@pytest.mark.parametrize("blk,variant", [((256, 256, 64), 0), ((256, 256, 64), 1), ((256, 128, 64), 0), ((256, 128, 64), 1), ((128, 128, 64), 0),
+                                         ((128, 128, 64), 1), ((128, 128, 32), 0), ((64, 128, 64), 0), ((32, 128, 64), 0), ((16, 128, 64), 0)])
+def test_unaligned_rows_every_tile_integer_exact(blk, variant):
+    # rows of A and B off the 16-byte grid: K from one iteration up to more than the stages held in registers, K a
+    # whole number of iterations (the last row of B ends the matrix) and just off it, N just below and above a tile
+    for iters, dk, dn in ((1, 0, 1), (2, 1, -1), (3, -1, 3), (5, 0, -3), (7, 5, 7)):
+        M, N, K = blk[0] + 9, 2 * blk[1] + dn, iters * blk[2] + dk
+        A, B = inputs.small_int_pair(M, N, K, inputs.BF16, 60 + iters)
+        ref = G.gemm_fp64(A, B, G.BF16)
+        for policy in (sk.SK_POLICY_DP, sk.SK_POLICY_ALL_SK):
+            _run_and_compare(A, B, inputs.BF16, policy, blk, grid=8, out_dtype=sk.SK_F32, ref=ref, exact=True, variant=variant)
+
+
+def test_unaligned_rows_keep_columns_apart():
+    # a 16-byte piece at the end of a row of B runs on into the next row: what it finds there must not reach D
+    M, N, K = 70, 261, 257
+    A, B = inputs.small_int_pair(M, N, K, inputs.BF16, 66)
+    ref = G.gemm_fp64(A, B, G.BF16)
+    B[1:, :8] = 0x7FC0                                          # NaN in the first columns of every row but the first
+    for blk in ((256, 256, 64), (128, 128, 64), (64, 128, 64), (32, 128, 64), (16, 128, 64)):
+        r = Runner(M, N, K, sk.SK_POLICY_DP, blk, 8, inputs.BF16, sk.SK_F32)
+        r.run(to_device(A), to_device(B))
+        d = r.result()
+        r.close()
+        assert np.isnan(d[:, :8]).all() and np.array_equal(d[:, 8:], ref[:, 8:])
+
+
 def test_bit_identical_run_to_run_and_flag_reuse():
     c = inputs.config1()
     dA, dB = to_device(c["A"]), to_device(c["B"])
