@@ -147,13 +147,15 @@ typedef struct {
     int32_t tile_order;                   /* sk_tile_order                                   */
     int32_t fixup, batch_order, segment_order;  /* sk_fixup, sk_batch_order, sk_segment_order: the
                                              defaults, or what the sk_plan_set_* calls chose */
-    int32_t xcd_remap;                    /* 1: the kernel renumbers the workgroups so that each of the 8 XCDs
-                                             runs grid/8 consecutive ones (neighbours in the schedule, which share
-                                             operand blocks, then share an L2); 0: hardware order, consecutive
-                                             workgroups on different XCDs - chosen when the tile grid is a single
-                                             row of tiles at most 64 rows high, where B is streamed once in narrow
-                                             column blocks and spreading neighbouring blocks over the XCDs
-                                             measured 8-10 % faster */
+    int32_t xcd_remap;                    /* which workgroups of the schedule share one of the 8 XCDs (and its L2).
+                                             1: each XCD runs grid/8 consecutive ones (neighbours in the schedule, which
+                                             share operand blocks and exchange partial tiles); 2: the workgroups sorted by
+                                             their slice of the tiles' K range, in eight consecutive parts - chosen when
+                                             at least 4 workgroups share every tile and the XCDs would otherwise
+                                             fetch 20 MB or more of the same operand blocks each; 0: hardware order,
+                                             consecutive workgroups on different XCDs - chosen when the tile grid is a
+                                             single row of 16-bit tiles at most 64 (32) rows high and B is at least
+                                             48 (16) MB, which is then streamed once in narrow column blocks */
 } sk_plan_header;
 
 /* Work of one workgroup x: global Stream-K iterations [sk_iter_begin, sk_iter_end)

@@ -51,13 +51,14 @@ struct GemmArgs {
     uint32_t spin_limit;
     int out_dtype;
     int dp_first;          // 1: a workgroup runs its data-parallel tiles before its Stream-K iterations
-    int xcd_remap;         // 1: consecutive logical workgroup ids share an XCD (see logical_wg)
+    int xcd_remap;         // which logical workgroup ids share an XCD (see logical_wg)
     int k_aligned;         // 1: a workgroup runs the whole tiles of its Stream-K range first, then the head of its last
                            //    tile (k from 0), then the tail of its first one, and the workgroup holding a tile's
                            //    last iteration reduces and stores it
     int stream_b;          // 1: B is read exactly once (one row of tiles) and is large: the low tiles request it non-temporally
     // divisors of the index arithmetic: ipt, ipw, tiles_n, SK_GROUP_ROWS * tiles_n, rows of the last (short) band
     sk_fast_div div_ipt, div_ipw, div_tiles_n, div_band, div_last_rows;
+    sk_fast_div div_tiles, div_extra;   // of logical_wg: tiles, grid mod tiles
 };
 
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, sk_fast_div f) { return (uint32_t)(((uint64_t)n * f.mul) >> f.shift); }
@@ -229,12 +230,29 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);   // lgkmcnt / expcnt not waited
 }
 
-// Hardware workgroup ids go round-robin over the 8 XCDs; give each XCD a contiguous block of
-// logical workgroup ids so that neighbours in the schedule (which share tiles and A row-blocks)
-// share an L2.  Plans with a single row of low tiles keep the hardware order: their workgroups
-// only stream B, and neighbouring column blocks read from different XCDs reach a higher HBM rate.
-__device__ __forceinline__ int logical_wg(int hw, int grid, int remap) {
-    return (remap && grid % 8 == 0) ? (hw % 8) * (grid / 8) + hw / 8 : hw;
+// Hardware workgroup ids go round-robin over the 8 XCDs.  Which logical ids (positions in the schedule) an
+// XCD runs decides what its L2 can share (sk_plan chooses, see there):
+//   1  a contiguous block of logical ids: neighbours in the schedule share tiles and A row-blocks;
+//   2  for plans in which several workgroups share every tile: the ids sorted by their piece of the
+//      tile's K range, then by tile, and a contiguous block of that - an XCD then reads one slice of K of
+//      every tile it touches, and the tiles that share an A row-block or B column-block share its slice in L2;
+//   0  the hardware order.
+__device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
+    if (g.xcd_remap == 0 || g.grid % 8 != 0) return hw;
+    const int q = (hw % 8) * (g.grid / 8) + hw / 8;
+    if (g.xcd_remap == 1) return q;
+    // workgroups ceil(t * grid / tiles) .. ceil((t + 1) * grid / tiles) - 1 share tile t, about: `each` or
+    // one more; the tiles with one more are t = floor(i * tiles / extra), i = 0 .. extra - 1.
+    const int each = (int)fast_div((uint32_t)g.grid, g.div_tiles), extra = g.grid - each * g.tiles;
+    int t, j;
+    if (q < each * g.tiles) {
+        j = (int)fast_div((uint32_t)q, g.div_tiles);
+        t = q - j * g.tiles;
+    } else {
+        j = each;
+        t = (int)fast_div((uint32_t)((q - each * g.tiles) * g.tiles), g.div_extra);
+    }
+    return (int)fast_div((uint32_t)(t * g.grid + g.tiles - 1), g.div_tiles) + j;
 }
 
 // 16 bytes whose address is only known to be a multiple of the element size (rows of a matrix whose
@@ -1067,7 +1085,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
     typedef typename Mfma<C::DT, C::MF>::Acc Acc;
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
     const int wm = wave / C::WN, wn = wave % C::WN;
-    const int x = logical_wg(blockIdx.x, g.grid, g.xcd_remap);
+    const int x = logical_wg(blockIdx.x, g);
     // transposed accumulator blocks (vector stores) where D's rows are 16-byte aligned; the atomic
     // fix-up and the element-wise stores of unaligned problems want the lanes side by side in a row
     constexpr bool TR = ALIGNED && !ATOMIC;

@@ -2,6 +2,7 @@
 // persistent kernel walks, and expands them into the canonical segment list.
 // Integer arithmetic only; no device contact.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <limits>
@@ -115,6 +116,41 @@ const TileCost* model_constants(int bm, int bn, int in_dtype) {
     return nullptr;
 }
 int model_bk(int blk_k, int in_dtype) { return in_dtype == SK_FP8_E4M3 ? blk_k / 2 : blk_k; }
+
+// Which logical workgroups an XCD runs (sk_plan_header.xcd_remap; the three maps are logical_wg's).  Measured on
+// 1667 (size, tile) pairs whose tiles are all split, 16 and 8 bits, under each map:
+//  - the contiguous map (1) is the fastest in general: the workgroups of a tile then exchange their partials
+//    inside one L2 (64 x 128 tiles of 8 workgroups, 512 x 512 x 8192: 14.4 us against 18.3 with either other map);
+//  - with at least 4 workgroups per tile each XCD reads the whole K range of its few tiles, so operand blocks
+//    shared with other XCDs' tiles are fetched once per XCD; sorted by K slice (2) they are fetched once.
+//    Where that saves 20 MB or more it pays for the longer exchange: 3 % at 20 - 40 MB, 8 - 12 % above, up to
+//    1.5x (384 x 240 x 52832, 64 x 128 tiles: 48.1 -> 31.6 us); below 20 MB it loses 3 - 9 %;
+//  - a single row of low 16-bit tiles over a large B streams B once and shares only the small A: the hardware
+//    order (0), neighbouring column blocks on different XCDs, gains 2 - 6 % from 48 MB of B on (32 rows and
+//    less: from 16 MB on) and loses 2 - 20 % below.  8-bit tiles lose 3 - 20 % with it at any size.
+int choose_remap(const sk_plan_header& h) {
+    const double es = h.in_dtype == SK_FP8_E4M3 ? 1 : 2;
+    if (h.tiles_m == 1 && h.blk_m <= 64 && es == 2) {
+        const double b_bytes = (double)h.K * (double)h.N * es;
+        if (b_bytes >= (h.blk_m <= 32 ? 16e6 : 48e6)) return 0;
+    }
+    if (h.dp_tiles == 0 && h.tiles <= h.grid && h.grid <= 4096 && 4ll * h.iters_per_wg <= h.iters_per_tile) {
+        const double per_xcd = h.grid / 8.0 * h.iters_per_wg / h.iters_per_tile;   // tiles of one XCD under the contiguous map
+        const double all = (double)h.tiles_m * h.blk_m + (double)h.tiles_n * h.blk_n;      // operand rows and columns
+        double fetched;
+        if (per_xcd >= 1) {
+            double rows = per_xcd < SK_GROUP_ROWS ? per_xcd : SK_GROUP_ROWS;
+            if (rows > h.tiles_m) rows = h.tiles_m;
+            double cols = std::ceil(per_xcd / rows);
+            if (cols > h.tiles_n) cols = h.tiles_n;
+            fetched = 8 * std::min(rows * h.blk_m + cols * h.blk_n, all);
+        } else {
+            fetched = (double)h.tiles * (h.blk_m + h.blk_n);
+        }
+        if ((fetched - all) * (double)h.K * es >= 20e6) return 2;
+    }
+    return 1;
+}
 
 }  // namespace
 
@@ -271,18 +307,13 @@ extern "C" int sk_plan(int64_t M, int64_t N, int64_t K, int policy, const sk_con
     h.fixup = SK_FIXUP_FLAGS;
     h.batch_order = SK_STREAMK_FIRST;
     h.segment_order = SK_SEGMENTS_K_ALIGNED;
-    // A single row of low tiles streams B once, in column blocks that are narrow stripes of the same
-    // memory rows, and shares only the small A: there the hardware order (neighbouring column
-    // blocks on different XCDs) measured 8 - 10 % faster (M <= 64, N = K = 8192: 28.5 against
-    // 31.5 us).  Everything else measured faster renumbered - a single column of tiles, two rows
-    // of tiles, and also a single row of 128-row tiles (M = 128: 42 against 48 us).
-    h.xcd_remap = (tiles_m == 1 && blk[0] <= 64) ? 0 : 1;
     h.sk_tiles = (int32_t)sk_tiles;
     h.dp_tiles = (int32_t)(tiles - sk_tiles);
     h.sk_iters = sk_tiles * ipt;
     const int64_t ipw = ceil_div(h.sk_iters, grid);   // Algorithm 1: iterations per workgroup, on the split region
     if (ipw > imax) return SK_ERR_INVALID_ARG;
     h.iters_per_wg = (int32_t)ipw;
+    h.xcd_remap = choose_remap(h);
     h.dp_waves = (int32_t)ceil_div(h.dp_tiles, grid);
     h.has_kernel = sk_kernel_available(in_dtype, blk[0], blk[1], blk[2]) ? 1 : 0;
 

@@ -164,6 +164,20 @@ def test_unaligned_rows_keep_columns_apart():
         assert np.isnan(d[:, :8]).all() and np.array_equal(d[:, 8:], ref[:, 8:])
 
 
+@pytest.mark.parametrize("shape,blk", [((64, 512, 52000), (32, 128, 64)), ((96, 768, 30000), (32, 128, 64)), ((112, 400, 30016), (64, 128, 64)),
+                                       ((33, 777, 40000), (16, 128, 64))])
+def test_workgroups_sorted_by_k_slice_integer_exact(shape, blk):
+    # the K-slice numbering of the workgroups: as many per tile as divide the grid, and some tiles with one more
+    M, N, K = shape
+    A, B = inputs.small_int_pair(M, N, K, inputs.BF16, 74, lo=-1, hi=1)
+    ref = G.gemm_fp64(A, B, G.BF16)
+    plan = sk.sk_plan(M, N, K, sk.SK_POLICY_ALL_SK, blk)
+    assert sk.sk_plan_info(plan)["xcd_remap"] == 2
+    sk.sk_plan_destroy(plan)
+    for k_aligned in (True, False):
+        _run_and_compare(A, B, inputs.BF16, sk.SK_POLICY_ALL_SK, blk, out_dtype=sk.SK_F32, ref=ref, exact=True, launches=3, k_aligned=k_aligned)
+
+
 def test_bit_identical_run_to_run_and_flag_reuse():
     c = inputs.config1()
     dA, dB = to_device(c["A"]), to_device(c["B"])
