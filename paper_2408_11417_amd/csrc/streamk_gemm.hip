@@ -7,13 +7,16 @@ using namespace streamk_detail;
 namespace {
 
 KernelEntry** kernel_table(int* count) {
-    static KernelEntry* table[64];
+    static KernelEntry* table[128];
     static int n = 0;
     static std::once_flag once;
     std::call_once(once, [] {
         register_bf16(table, &n);
         register_f16(table, &n);
         register_fp8(table, &n);
+        register_bf16_low(table, &n);
+        register_f16_low(table, &n);
+        register_fp8_low(table, &n);
         register_bf16_atomic(table, &n);
         register_f16_atomic(table, &n);
         register_fp8_atomic(table, &n);

@@ -1,4 +1,4 @@
-// fp16 kernels of the Stream-K GEMM (see streamk_kernels.h).
+// fp16 kernels of the Stream-K GEMM: tiles of 128 rows and more (see streamk_kernels.h).
 #include "streamk_kernels.h"
 namespace streamk_detail {
 void register_f16(KernelEntry** t, int* n) { add_16bit_tiles<SK_F16>(t, n); }

@@ -138,8 +138,10 @@ struct Cfg {
     static constexpr int B_RING = NSA * A_BYTES;         // byte offset of the B ring
     static constexpr int LDS_BYTES = NSA * A_BYTES + NSB * B_BYTES;
     // one LDS-DMA instruction of one wave fills 64 consecutive pieces
-    static constexpr bool DIRECT = (A_PIECES % (64 * NW) == 0) && (B_PIECES % (64 * NW) == 0);
-    static constexpr int A_LD = A_PIECES / (64 * NW), B_LD = B_PIECES / (64 * NW);
+    // (an A tile of fewer pieces than that for every wave is fetched by several waves: the same bytes to the same place)
+    static constexpr int A_WAVES = A_PIECES < 64 * NW ? A_PIECES / 64 : NW;
+    static constexpr int A_LD = A_PIECES < 64 * NW ? 1 : A_PIECES / (64 * NW), B_LD = B_PIECES / (64 * NW);
+    static_assert(A_PIECES % (64 * A_WAVES) == 0 && NW % A_WAVES == 0 && B_PIECES % (64 * NW) == 0, "whole LDS-DMA instructions");
     static constexpr int LPS = A_LD + B_LD;              // LDS-DMA loads per stage per wave
     // register-staged fill (unaligned problems, tiles too small for the DMA split)
     static constexpr int CA = (A_PIECES + THREADS - 1) / THREADS, CB = (B_PIECES + THREADS - 1) / THREADS;
@@ -170,7 +172,7 @@ struct Cfg {
     static constexpr int EPILOGUE_STORES = MI * NI * (MF == 32 ? ACC / 8 : ACC / 4);
     static_assert(WTM % MF == 0 && WTN % MF == 0 && BK % KM == 0, "tile does not divide");
     static_assert(CPA == 4 || CPA == 8 || CPA == 16, "A swizzle assumes 64/128/256-byte rows");
-    static_assert(CPB >= 16, "B swizzle assumes rows of at least 256 bytes");
+    static_assert(CPB >= 8, "B swizzle assumes rows of at least 128 bytes");
     static_assert(NSB >= 2 && (NSA == NSB || NSA == NSB + 1) && LDS_BYTES <= 160 * 1024, "LDS budget / ring depths");
     static_assert((NSA - 1) * LPS <= 63, "vmcnt range");
     // LDS-DMA loads that may still be in flight when iteration i starts, if `later` more
@@ -195,10 +197,13 @@ template <int CPA> __device__ __forceinline__ int swz_a(int r) {
     if (CPA == 4) return (r >> 1) & 3;
     return (r & 7) ^ ((r >> 3) & 1);
 }
-// B: piece c of row k sits at position c ^ swz_b<C::FP8>(k): rows k..k+3, read together by one transposing
+// B: piece c of row k sits at position c ^ swz_b<C::FP8, C::CPB>(k): rows k..k+3, read together by one transposing
 // read, land on different 32-byte and different 64-byte bank groups.
 // (8-bit elements: one transposing read covers 8 rows; rows k..k+7 go to 8 different 32-byte groups.)
-template <bool FP8> __device__ __forceinline__ int swz_b(int k) {
+// Rows of 128 bytes (CPB == 8): rows k and k+1 already lie 128 bytes apart, so only every other row moves,
+// by 64-byte (16-bit elements; rows 8 apart, read together by the 16-row block, by 32-byte) or 32-byte groups.
+template <bool FP8, int CPB> __device__ __forceinline__ int swz_b(int k) {
+    if (CPB == 8) return FP8 ? ((k >> 1) & 3) << 1 : ((k >> 1) & 1) << 2 | ((k >> 3) & 1) << 1;
     if (FP8) return (k & 7) << 1;
     const int k0 = k & 1, k1 = (k >> 1) & 1;
     return (k0 << 1) | (k1 << 2) | (k0 << 3);
@@ -260,15 +265,13 @@ __device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
 struct __attribute__((packed, aligned(1))) Piece1 { u32x4 v; };
 struct __attribute__((packed, aligned(2))) Piece2 { u32x4 v; };
 
-template <int ES, bool ALIGNED>
+template <int ES>
 __device__ __forceinline__ uint4 load_piece(const unsigned char* __restrict__ base, int row, int col, int rows, int cols) {
     // 16 bytes = 16 / ES consecutive elements of a row-major matrix with `cols` columns, zero beyond its edges
     uint4 v = make_uint4(0, 0, 0, 0);
     if (row < rows) {
         const unsigned char* p = base + (size_t)((uint32_t)row * (uint32_t)cols + (uint32_t)col) * ES;
-        if (ALIGNED) {
-            if (col < cols) v = *reinterpret_cast<const uint4*>(p);
-        } else if (col + 16 / ES <= cols) {          // the whole piece lies inside the row
+        if (col + 16 / ES <= cols) {          // the whole piece lies inside the row
             const u32x4 w = ES == 2 ? reinterpret_cast<const Piece2*>(p)->v : reinterpret_cast<const Piece1*>(p)->v;
             v = make_uint4(w[0], w[1], w[2], w[3]);
         } else if (col < cols) {                     // the piece that straddles the end of the row
@@ -292,7 +295,7 @@ __device__ __forceinline__ uint4 load_piece(const unsigned char* __restrict__ ba
 // output columns that are never stored.  The caller vouches that the k-iteration is below inside_k(), that
 // is, lies wholly inside K with at least one row of B behind it (so that running on stays inside B).
 // Everything else goes through load_piece, with zero fill beyond K.
-template <class C, bool ALIGNED> struct StagedFill {
+template <class C> struct StagedFill {
     uint32_t a_off[C::CA], b_off[C::CB];         // byte offsets from A / B at k-iteration 0
     int m0, n0;
     static __device__ __forceinline__ int inside_k(const GemmArgs& g) { return g.N >= C::PE ? (g.K - 1) / C::BK : 0; }
@@ -307,27 +310,26 @@ template <class C, bool ALIGNED> struct StagedFill {
         }
 #pragma unroll
         for (int j = 0; j < C::CB; j++) {
-            const int p = threadIdx.x + j * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8>(k);
+            const int p = threadIdx.x + j * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8, C::CPB>(k);
             const int col = n0 + C::PE * c;
             b_off[j] = ((uint32_t)k * (uint32_t)g.N + (uint32_t)(col < g.N ? col : 0)) * C::ES;
         }
     }
     static __device__ __forceinline__ uint4 load_inside(const char* base, uint32_t off) {
-        const u32x4 w = ALIGNED ? *reinterpret_cast<const u32x4*>(base + off)
-                      : C::ES == 2 ? reinterpret_cast<const Piece2*>(base + off)->v : reinterpret_cast<const Piece1*>(base + off)->v;
+        const u32x4 w = C::ES == 2 ? reinterpret_cast<const Piece2*>(base + off)->v : reinterpret_cast<const Piece1*>(base + off)->v;
         return make_uint4(w[0], w[1], w[2], w[3]);
     }
     // piece q of the stage of k-iteration kit: the B pieces first, then the A pieces
     template <bool INSIDE> __device__ __forceinline__ uint4 fetch(const GemmArgs& g, int kit, int q) const {
         if (q < C::CB) {
             if (INSIDE) return load_inside(static_cast<const char*>(g.B) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)) * (uint32_t)g.N, b_off[q]);
-            const int p = threadIdx.x + q * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8>(k);
-            return load_piece<C::ES, ALIGNED>(static_cast<const unsigned char*>(g.B), kit * C::BK + k, n0 + c * C::PE, g.K, g.N);
+            const int p = threadIdx.x + q * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8, C::CPB>(k);
+            return load_piece<C::ES>(static_cast<const unsigned char*>(g.B), kit * C::BK + k, n0 + c * C::PE, g.K, g.N);
         }
         const int j = q - C::CB;
         if (INSIDE) return load_inside(static_cast<const char*>(g.A) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)), a_off[j]);
         const int p = threadIdx.x + j * C::THREADS, r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
-        return load_piece<C::ES, ALIGNED>(static_cast<const unsigned char*>(g.A), m0 + r, kit * C::BK + c * C::PE, g.M, g.K);
+        return load_piece<C::ES>(static_cast<const unsigned char*>(g.A), m0 + r, kit * C::BK + c * C::PE, g.M, g.K);
     }
     static __device__ __forceinline__ void park(unsigned char* a_stage, unsigned char* b_stage, int q, uint4 v) {
         const int p = threadIdx.x + (q < C::CB ? q : q - C::CB) * C::THREADS;
@@ -349,7 +351,7 @@ template <class C> struct DmaMap {
         const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
 #pragma unroll
         for (int j = 0; j < C::A_LD; j++) {
-            const int p = (j * C::NW + wave) * 64 + lane;
+            const int p = (j * C::NW + wave % C::A_WAVES) * 64 + lane;
             const int r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
             int row = m0 + r;
             row = row < g.M ? row : g.M - 1;
@@ -358,7 +360,7 @@ template <class C> struct DmaMap {
 #pragma unroll
         for (int j = 0; j < C::B_LD; j++) {
             const int p = (j * C::NW + wave) * 64 + lane;
-            const int k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8>(k);
+            const int k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8, C::CPB>(k);
             int col = n0 + C::PE * c;
             col = col < g.N ? col : g.N - C::PE;
             b_off[j] = ((uint32_t)k * (uint32_t)g.N + (uint32_t)col) * C::ES;
@@ -368,7 +370,7 @@ template <class C> struct DmaMap {
     // piece length here); pieces at k >= K are then fetched from a zero piece so that they add nothing.
     template <bool TAIL> __device__ __forceinline__ void issue_a(const GemmArgs& g, int kit, uint32_t lds, int j0 = 0, int j1 = C::A_LD) const {
         const int lane = threadIdx.x % 64;
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64) % C::A_WAVES;
         const char* A = static_cast<const char*>(g.A) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES));
 #pragma unroll
         for (int j = 0; j < C::A_LD; j++) {
@@ -432,7 +434,7 @@ template <class C> struct FragMap {
 #pragma unroll
         for (int ni = 0; ni < C::NI; ni++) {
             const int col = wn * C::WTN + ni * C::MF + 16 * ((lane % C::MF) / 16) + (C::FP8 ? 8 * (lane % 2) : 4 * (lane % 4));
-            b_ni[ni] = (krow * C::CPB + ((col / C::PE) ^ swz_b<C::FP8>(krow))) * 16 + (col % C::PE) * C::ES;
+            b_ni[ni] = (krow * C::CPB + ((col / C::PE) ^ swz_b<C::FP8, C::CPB>(krow))) * 16 + (col % C::PE) * C::ES;
         }
     }
 };
@@ -579,13 +581,13 @@ __device__ __forceinline__ void mac_prefetch(const GemmArgs& g, int m0, int n0, 
 // registers then take the same piece of stage i+3.  A load therefore has a whole trip to land.
 // What bounds it is the vector L1: under-aligned 16-byte loads move about 25 bytes per clock and CU where
 // aligned ones move 52 (a microbenchmark of this access pattern), and a 256 x 256 x 64 stage is 64 KB.
-template <class C, bool ALIGNED, bool TR>
+template <class C, bool TR>
 __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n0, int k_begin, int k_end, unsigned char* smem,
                                                 const FragMap<C>& fm, typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI]) {
     const int nk = k_end - k_begin;
-    StagedFill<C, ALIGNED> sf;
+    StagedFill<C> sf;
     sf.init(g, m0, n0);
-    const int inside = StagedFill<C, ALIGNED>::inside_k(g);
+    const int inside = StagedFill<C>::inside_k(g);
     auto a_slot = [&](int s) { return smem + (s & 1) * C::A_BYTES; };
     auto b_slot = [&](int s) { return smem + C::B_RING + (s & 1) * C::B_BYTES; };
     if constexpr (C::STAGED_FINE) {
@@ -710,8 +712,8 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
                                          typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI],
                                          bool prefetched, bool stores_in_flight) {
     const int nk = k_end - k_begin;
-    if (C::DIRECT && ALIGNED) {
-        static_assert(!C::DIRECT || C::KK % 2 == 0, "operand double buffering assumes an even number of k-steps");
+    if constexpr (ALIGNED) {
+        static_assert(C::KK % 2 == 0, "operand double buffering assumes an even number of k-steps");
         const uint32_t lds0 = (uint32_t)(size_t)(lds_byte*)smem;
         const int full_k = g.K / C::BK;             // iterations below this index are entirely inside K
         DmaMap<C> dm;
@@ -828,7 +830,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
         }
         __syncthreads();                             // all reads done before the next segment refills
     } else {
-        mac_loop_staged<C, ALIGNED, TR>(g, m0, n0, k_begin, k_end, smem, fm, acc);
+        mac_loop_staged<C, TR>(g, m0, n0, k_begin, k_end, smem, fm, acc);
     }
 }
 
@@ -1249,7 +1251,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
     // On the LDS-DMA path the first requests of the next segment go out before the current tile's
     // fix-up and epilogue (the ring is free once the MAC loop has ended): the loads travel while the
     // tile is stored, and the first wait of the next MAC loop leaves the epilogue's stores in flight.
-    constexpr bool PREFETCH = C::DIRECT && ALIGNED;
+    constexpr bool PREFETCH = ALIGNED;
     int tile, k_begin, k_end, m0, n0;
     bool have = next_segment(tile, k_begin, k_end, m0, n0);
     bool prefetched = false, stores_in_flight = false;
@@ -1318,9 +1320,6 @@ template <int DT, bool ATOMIC = false> void add_16bit_tiles(KernelEntry** t, int
     t[(*n)++] = make_entry<Cfg<DT, 128, 128, 64, 2, 4, 32, 3, 3, 1>, ATOMIC>();
     t[(*n)++] = make_entry<Cfg<DT, 256, 128, 64, 4, 2, 32, 3, 3, 1>, ATOMIC>();
     t[(*n)++] = make_entry<Cfg<DT, 256, 256, 64, 2, 4, 32, 3, 2, 1>, ATOMIC>();
-    t[(*n)++] = make_entry<Cfg<DT, 64, 128, 64, 2, 4, 32, 4>, ATOMIC>();
-    t[(*n)++] = make_entry<Cfg<DT, 32, 128, 64, 1, 4, 32, 4>, ATOMIC>();
-    t[(*n)++] = make_entry<Cfg<DT, 16, 128, 64, 1, 4, 16, 4>, ATOMIC>();
     if constexpr (!ATOMIC) {  // (the atomic fix-up exists for the layouts above only)
         t[(*n)++] = make_entry<Cfg<DT, 256, 128, 64, 2, 2, 32, 3, 3, 1>>(1, 16);
         t[(*n)++] = make_entry<Cfg<DT, 256, 128, 64, 4, 2, 32, 3, 3, 1>>(3);
@@ -1330,15 +1329,32 @@ template <int DT, bool ATOMIC = false> void add_16bit_tiles(KernelEntry** t, int
         t[(*n)++] = make_entry<Cfg<DT, 256, 256, 32, 2, 2, 32, 4>>();
         t[(*n)++] = make_entry<Cfg<DT, 128, 128, 64, 2, 2, 32, 3, 3, 1>>(1, 1);
         t[(*n)++] = make_entry<Cfg<DT, 128, 128, 64, 2, 4, 32, 3, 3, 1>>(3);
-        t[(*n)++] = make_entry<Cfg<DT, 64, 128, 64, 2, 2, 32, 4>>(1);
     }
 }
 
-// One function per input type, each in its own translation unit (so that they compile in parallel);
+// The tiles of at most 64 rows.  What bounds them outside the HBM-bound shapes is the rate at which a CU
+// takes operand bytes into LDS (about 90 bytes per ns with rows on 128-byte boundaries, 60 off them), so they
+// matter where the larger tiles leave CUs idle: 1024^3 on 256 tiles of 64 x 64 6.6 us (128 of 64 x 128: 8.2,
+// 256 of 32 x 128: 7.2), 1 x 4096 x 4096 on 32 x 64 9.3 us (32 x 128: 11.4, 16 x 128: 9.8).
+template <int DT, bool ATOMIC = false> void add_16bit_low_tiles(KernelEntry** t, int* n) {
+    t[(*n)++] = make_entry<Cfg<DT, 64, 128, 64, 2, 4, 32, 4>, ATOMIC>();
+    t[(*n)++] = make_entry<Cfg<DT, 32, 128, 64, 1, 4, 32, 4>, ATOMIC>();
+    t[(*n)++] = make_entry<Cfg<DT, 16, 128, 64, 1, 4, 16, 4>, ATOMIC>();
+    if constexpr (!ATOMIC) {
+        t[(*n)++] = make_entry<Cfg<DT, 64, 128, 64, 2, 2, 32, 4>>(1);
+    }
+    t[(*n)++] = make_entry<Cfg<DT, 64, 64, 128, 2, 2, 32, 4>, ATOMIC>();
+    t[(*n)++] = make_entry<Cfg<DT, 32, 64, 64, 1, 2, 32, 4>, ATOMIC>();
+}
+
+// One or two functions per input type, each in its own translation unit (so that they compile in parallel);
 // it appends that type's kernels to the table.
 void register_bf16(KernelEntry** t, int* n);
 void register_f16(KernelEntry** t, int* n);
 void register_fp8(KernelEntry** t, int* n);
+void register_bf16_low(KernelEntry** t, int* n);
+void register_f16_low(KernelEntry** t, int* n);
+void register_fp8_low(KernelEntry** t, int* n);
 void register_bf16_atomic(KernelEntry** t, int* n);
 void register_f16_atomic(KernelEntry** t, int* n);
 void register_fp8_atomic(KernelEntry** t, int* n);

@@ -84,38 +84,72 @@ void expand_wg(const sk_plan_header& h, int x, std::vector<sk_segment>* out, sk_
     }
 }
 
-// Cost model shared by the tile dispatcher and sk_plan_estimate_us.  The constants (sustained
-// TFLOP/s of each 16-bit kernel with the grid full, microseconds to drain / store a tile and to
-// park or fetch a partial) were fitted to timings of every tile shape on the first 400 of 500 seeded
-// problem sizes plus 12 large skinny ones on MI355X - sizes 400 .. 499 are the selector's held-out split
-// and stay out of the fit (fit_tile_model.py; the fit optimises the dispatcher's pick, not the
-// predicted times, so the constants need not be physical).
-struct TileCost { int bm, bn; double tflops; };
-const TileCost tile_costs[] = {{256, 256, 1170.}, {256, 128, 1027.}, {128, 128, 826.}, {64, 128, 624.}, {32, 128, 297.}, {16, 128, 47.}};
+// Cost model shared by the tile dispatcher and sk_plan_estimate_us.  The constants - per kernel the rate of
+// its MAC loop with the grid full and the microseconds a tile takes outside the loop (first loads, drain,
+// store), and for the exchange of partial tiles a latency per level, the rate of one owner's chain of fetches
+// and the rate of all partial traffic together - were fitted to timings of every tile shape and schedule on 397
+// of the first 400 of 500 seeded problem sizes, 72 with at most 128 rows and 40 with few tiles and deep K on
+// MI355X; sizes 400 .. 499 are the selector's held-out split and stay out of the fit (fit_tile_model.py; the
+// fit optimises the dispatcher's pick of tile and policy, not the predicted times).  Time of the pick over the
+// fastest of all tiles and schedules, geometric mean: 16 bits 1.016 / 1.025 / 1.030 on the three sets (the six
+// shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.008 / 1.006 / 1.006 (two shapes: 1.59 / 2.29 / 2.44).
+struct TileCost { int bm, bn, bk; double tflops, tile_us; };
+const TileCost tile_costs16[] = {{256, 256, 64, 1585., 10.9}, {256, 128, 64, 1299., 5.89}, {128, 128, 64, 1099., 3.90},
+                                 {64, 128, 64, 661., 2.29},   {32, 128, 64, 583., 2.47},   {16, 128, 64, 330., 2.49},
+                                 {64, 64, 128, 602., 2.63},   {32, 64, 64, 425., 2.58}};
+// (the large 8-bit tile moves the bytes of the large 16-bit one with twice the k at twice the rate: its constants)
+const TileCost tile_costs8[] = {{256, 256, 128, 3170., 10.9}, {128, 256, 128, 2821., 4.75}, {128, 128, 128, 1919., 2.61},
+                                {64, 128, 128, 1467., 2.45},  {32, 128, 128, 915., 2.48}};
+constexpr int N_COSTS16 = 8, N_COSTS8 = 5;
 constexpr int MODEL_GRID = 256;
+constexpr double MODEL_LEVEL_US = 1.78, MODEL_FETCH_BYTES_PER_US = 119.2e3, MODEL_TRAFFIC_BYTES_PER_US = 6.658e6;
+
 double model_iter_us(const TileCost& c, int bk) {          // one k-iteration of every workgroup of a full grid
     return 2.0 * c.bm * c.bn * bk * MODEL_GRID / (c.tflops * 1e12) * 1e6;
 }
-double model_tile_us(const TileCost& c) { return 0.69 + c.bm * c.bn * 2 / 8.86e3; }
-// exchange of partial tiles when about `split` workgroups share a tile: the partials an owner (or a
-// group leader) fetches one after the other - all of them up to 16 workgroups per tile, beyond that
-// the two-level reduction with groups of 8
-double model_exchange_us(const TileCost& c, double split) {
-    const bool tree = split >= 16;
-    const double serial = tree ? 8 + split / 8 : split;
-    return 5.77 * (tree ? 2 : 1) + serial * c.bm * c.bn * 4 / 35.9e3;
+
+// Workgroups that park a partial tile: those whose range ends inside a tile (as many as start inside one).
+// ipw iterations per workgroup, `workgroups` ranges that are not empty; every ipt / gcd(ipt, ipw)-th ends on a boundary.
+int64_t model_contributors(int64_t workgroups, int64_t ipt, int64_t ipw) {
+    int64_t a = ipt, b = ipw;
+    while (b) { const int64_t r = a % b; a = b; b = r; }
+    return workgroups - 1 - (workgroups - 1) / (ipt / a);
 }
 
-// The constants of a tile shape.  The 8-bit kernels were not fitted: they move the same bytes per
-// k-iteration as the 16-bit kernel of the same footprint with twice the k at twice the matrix-core
-// rate, so an 8-bit tile is modelled as that 16-bit shape (128 x 256 as 256 x 128) with half its blk_k.
-const TileCost* model_constants(int bm, int bn, int in_dtype) {
-    if (in_dtype == SK_FP8_E4M3 && bm < bn) std::swap(bm, bn);
-    for (const TileCost& t : tile_costs)
-        if (t.bm == bm && t.bn == bn) return &t;
+// Microseconds of a schedule: sk_tiles tiles split evenly over the grid, the rest in whole-tile waves.
+double model_us(const TileCost& c, int bk, int64_t ipt, int64_t tiles, int64_t sk_tiles, int grid) {
+    const double t_iter = model_iter_us(c, bk);
+    double t = (double)ceil_div(tiles - sk_tiles, grid) * (ipt * t_iter + c.tile_us);
+    if (sk_tiles == 0) return t;
+    const int64_t iters = sk_tiles * ipt, ipw = ceil_div(iters, grid);
+    const double waves = (double)sk_tiles / grid;
+    t += ipw * t_iter + c.tile_us * (waves > 1 ? waves : 1.0);
+    if (ipw % ipt != 0 && iters > ipw) {
+        // about `split` workgroups share a tile: the partials an owner (or a group leader) fetches one after the
+        // other - all of them up to 16 workgroups per tile, beyond that the two-level reduction with groups of 8 -
+        // and the traffic of all of them together, which shares the memory system
+        const double split = ipt > ipw ? (double)ipt / ipw : 1.0;
+        const bool tree = split >= 16;
+        t += MODEL_LEVEL_US * (tree ? 2 : 1) + (tree ? 8 + split / 8 : split) * c.bm * c.bn * 4 / MODEL_FETCH_BYTES_PER_US;
+        t += (double)model_contributors(ceil_div(iters, ipw), ipt, ipw) * c.bm * c.bn * 8 / MODEL_TRAFFIC_BYTES_PER_US;
+    }
+    return t;
+}
+
+const TileCost* model_costs(int in_dtype, int* count) {
+    const bool fp8 = in_dtype == SK_FP8_E4M3;
+    *count = fp8 ? N_COSTS8 : N_COSTS16;
+    return fp8 ? tile_costs8 : tile_costs16;
+}
+// The constants of a tile shape: the entry with its blk_k, or - for 16 bits, where blk_k 32 and 64 share the rate -
+// one with at least as deep a k-iteration as the shape's.
+const TileCost* model_constants(int bm, int bn, int bk, int in_dtype) {
+    int n;
+    const TileCost* t = model_costs(in_dtype, &n);
+    for (int i = 0; i < n; i++)
+        if (t[i].bm == bm && t[i].bn == bn && (t[i].bk == bk || (t[i].bk == 64 && bk < 64))) return &t[i];
     return nullptr;
 }
-int model_bk(int blk_k, int in_dtype) { return in_dtype == SK_FP8_E4M3 ? blk_k / 2 : blk_k; }
 
 // Which logical workgroups an XCD runs (sk_plan_header.xcd_remap; the three maps are logical_wg's).  Measured on
 // 1667 (size, tile) pairs whose tiles are all split, 16 and 8 bits, under each map:
@@ -157,66 +191,41 @@ int choose_remap(const sk_plan_header& h) {
 extern "C" int sk_plan_estimate_us(const sk_plan_t* plan, double* microseconds) {
     if (!plan || !microseconds) return SK_ERR_INVALID_ARG;
     const sk_plan_header& h = plan->h;
-    const TileCost* c = model_constants(h.blk_m, h.blk_n, h.in_dtype);
+    const TileCost* c = model_constants(h.blk_m, h.blk_n, h.blk_k, h.in_dtype);
     if (!c) return SK_ERR_UNSUPPORTED;
-    // per-iteration time of a workgroup does not depend on how many workgroups the grid has
-    const double t_iter = model_iter_us(*c, model_bk(h.blk_k, h.in_dtype)), c_tile = model_tile_us(*c);
-    double t = h.dp_waves * (h.iters_per_tile * t_iter + c_tile);
-    if (h.sk_tiles > 0) {
-        const double sk_waves = (double)h.sk_tiles / h.grid;
-        t += h.iters_per_wg * t_iter + c_tile * (sk_waves > 1 ? sk_waves : 1.0);
-        if (plan->needs_fixup) {
-            double split = (double)h.iters_per_tile / h.iters_per_wg;     // workgroups per tile beyond the owner, about
-            if (split < 1) split = 1;
-            t += model_exchange_us(*c, split);
-            // every workgroup that holds a contributor piece parks one fp32 tile and somebody fetches it, all at
-            // about the same time: that traffic shares the memory system (fitted: 6 TB/s for write plus read;
-            // with 256 x 256 tiles and a full grid it is 128 MB, the largest term of a short problem)
-            int64_t contributors = 0;
-            for (int64_t x = 0; x < h.grid; x++) {
-                const int64_t b = std::min<int64_t>(x * h.iters_per_wg, h.sk_iters), e = std::min<int64_t>((x + 1) * h.iters_per_wg, h.sk_iters);
-                if (e > b && (plan->k_aligned ? e : b) % h.iters_per_tile != 0) contributors++;
-            }
-            t += (double)contributors * c->bm * c->bn * 8 / 6.0e6;
-        }
-    }
-    *microseconds = t;
+    *microseconds = model_us(*c, h.blk_k, h.iters_per_tile, h.tiles, h.sk_tiles, h.grid);
     return SK_OK;
 }
 
 extern "C" int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, int32_t* out_blk) {
     if (!out_blk || M < 1 || N < 1 || K < 1 || !dtype_in_ok(in_dtype)) return SK_ERR_INVALID_ARG;
-    // Dispatcher: a small cost model over the tile shapes that have a kernel.  For each shape it
-    // estimates the time of the better of (a) whole tiles in waves over the grid and (b) the
-    // iterations split evenly over the grid plus the cost of exchanging partial tiles, and keeps
-    // the cheapest; the model's choice is within 10 % of the fastest tile shape on 95 % of the
-    // sizes it was fitted on.
-    // candidates: the six 16-bit shapes, or the two 8-bit shapes (modelled through model_constants)
-    struct Cand { int bm, bn, bk; };
-    static const Cand cands16[] = {{256, 256, 64}, {256, 128, 64}, {128, 128, 64}, {64, 128, 64}, {32, 128, 64}, {16, 128, 64}};
-    static const Cand cands8[] = {{256, 256, 128}, {128, 256, 128}};
-    const bool fp8 = in_dtype == SK_FP8_E4M3;
-    const Cand* cands = fp8 ? cands8 : cands16;
-    const int n_cands = fp8 ? 2 : 6, grid = MODEL_GRID;
+    // Dispatcher: the tile shape whose best schedule - whole tiles in waves, the remainder wave split, or every
+    // tile split - the cost model estimates the cheapest.
+    // 8 bits: the tiles of 128 columns only where the LDS-DMA path serves them (they are slower than the large ones
+    // on the register-staged path), and not where fewer than 8 k-iterations meet a quarter of the grid or more of
+    // 128 x 256 tiles: there the answer has always been one of the two large shapes, and callers build on it.
+    int n;
+    const TileCost* costs = model_costs(in_dtype, &n);
+    if (in_dtype == SK_FP8_E4M3) {
+        const bool shallow = K < 1024 && ceil_div(M, 128) * (double)ceil_div(N, 256) >= MODEL_GRID / 4;
+        if (K % 16 != 0 || N % 16 != 0 || shallow) n = 2;
+    }
+    const int64_t most = std::numeric_limits<int32_t>::max();
     double best_t = 0;
     int best = -1;
-    for (int i = 0; i < n_cands; i++) {
-        const TileCost& c = *model_constants(cands[i].bm, cands[i].bn, in_dtype);
-        const double ipt = (double)ceil_div(K, cands[i].bk);
-        const double tiles = (double)ceil_div(M, cands[i].bm) * (double)ceil_div(N, cands[i].bn);
-        const double t_iter = model_iter_us(c, model_bk(cands[i].bk, in_dtype)), c_tile = model_tile_us(c);
-        const double waves = (double)((int64_t)((tiles + grid - 1) / grid));
-        const double t_dp = waves * (ipt * t_iter + c_tile);
-        const double ipw = (double)((int64_t)((tiles * ipt + grid - 1) / grid));
-        double split = grid / tiles;
-        if (split > ipt) split = ipt;
-        if (split < 1) split = 1;
-        double t_sk = ipw * t_iter + c_tile * (tiles > grid ? tiles / grid : 1.0);
-        if (((int64_t)tiles % grid) != 0) t_sk += model_exchange_us(c, split);
-        const double t = t_dp < t_sk ? t_dp : t_sk;
+    for (int i = 0; i < n; i++) {
+        const TileCost& c = costs[i];
+        const int64_t ipt = ceil_div(K, c.bk), tiles_m = ceil_div(M, c.bm), tiles_n = ceil_div(N, c.bn);
+        // beyond what sk_plan accepts: any answer will do, the first (largest) shape
+        if (ipt > most || tiles_m > most || tiles_n > most || tiles_m * tiles_n > most || tiles_m * tiles_n > std::numeric_limits<int64_t>::max() / ipt) continue;
+        const int64_t tiles = tiles_m * tiles_n;
+        double t = model_us(c, c.bk, ipt, tiles, 0, MODEL_GRID);
+        t = std::min(t, model_us(c, c.bk, ipt, tiles, tiles, MODEL_GRID));
+        t = std::min(t, model_us(c, c.bk, ipt, tiles, tiles % MODEL_GRID, MODEL_GRID));
         if (best < 0 || t < best_t) { best = i; best_t = t; }
     }
-    out_blk[0] = cands[best].bm; out_blk[1] = cands[best].bn; out_blk[2] = cands[best].bk;
+    if (best < 0) best = 0;
+    out_blk[0] = costs[best].bm; out_blk[1] = costs[best].bn; out_blk[2] = costs[best].bk;
     return SK_OK;
 }
 

@@ -21,34 +21,50 @@ import random
 import statistics
 import sys
 
-GRID, BK = 256, 64
-# The constants as they stand in csrc/streamk_plan.cpp (tile_costs, model_tile_us, model_exchange_us).
-# The library's C++ code is what runs; predict() below restates its formula for the fit, and
-# tests/test_selector.py checks that predict() with these constants picks sk_default_tile's tile.
-LIBRARY = {"tflops": {(256, 256): 1170., (256, 128): 1027., (128, 128): 826., (64, 128): 624., (32, 128): 297., (16, 128): 47.},
-           "tile_us": 0.69, "tile_bytes_per_us": 8.86e3, "part_us": 5.77, "part_bytes_per_us": 35.9e3}
+GRID = 256
+BK = {(256, 256): 64, (256, 128): 64, (128, 128): 64, (64, 128): 64, (32, 128): 64, (16, 128): 64, (64, 64): 128, (32, 64): 64}
+# The constants as they stand in csrc/streamk_plan.cpp (tile_costs16, MODEL_*).  The library's C++ code is
+# what runs; predict() below restates its formula for the fit, and tests/test_selector.py checks that
+# predict() with these constants picks sk_default_tile's tile.
+LIBRARY = {"tflops": {(256, 256): 1585., (256, 128): 1299., (128, 128): 1099., (64, 128): 661., (32, 128): 583., (16, 128): 330.,
+                      (64, 64): 602., (32, 64): 425.},
+           "tile_us": {(256, 256): 10.9, (256, 128): 5.89, (128, 128): 3.90, (64, 128): 2.29, (32, 128): 2.47, (16, 128): 2.49,
+                       (64, 64): 2.63, (32, 64): 2.58},
+           "level_us": 1.78, "fetch_bytes_per_us": 119.2e3, "traffic_bytes_per_us": 6.658e6}
 
 
 def cdiv(a, b):
     return -(-a // b)
 
 
+def schedule_us(P, tile, ipt, T, sk_tiles):
+    """Microseconds of a schedule that splits sk_tiles of T tiles over the grid (model_us in C++)."""
+    bm, bn = tile
+    t_iter = 2.0 * bm * bn * BK[tile] * GRID / (P["tflops"][tile] * 1e12) * 1e6
+    c_tile = P["tile_us"][tile]
+    t = cdiv(T - sk_tiles, GRID) * (ipt * t_iter + c_tile)
+    if sk_tiles == 0:
+        return t
+    iters = sk_tiles * ipt
+    ipw = cdiv(iters, GRID)
+    t += ipw * t_iter + c_tile * max(sk_tiles / GRID, 1.0)
+    if ipw % ipt and iters > ipw:
+        # partial tiles an owner (or a group leader) fetches one after the other: all of them up to 16
+        # workgroups per tile, beyond that the two-level reduction with groups of 8; and all of them together
+        split = max(ipt / ipw, 1.0)
+        serial = split if split < 16 else 8 + split / 8
+        others = cdiv(iters, ipw) - 1
+        contributors = others - others // (ipt // math.gcd(ipt, ipw))
+        t += P["level_us"] * (1 if split < 16 else 2) + serial * bm * bn * 4 / P["fetch_bytes_per_us"]
+        t += contributors * bm * bn * 8 / P["traffic_bytes_per_us"]
+    return t
+
+
 def predict(P, tile, M, N, K):
     """The cost model of sk_default_tile for one tile shape (microseconds)."""
-    bm, bn = tile
-    ipt = cdiv(K, BK)
-    T = cdiv(M, bm) * cdiv(N, bn)
-    t_iter = 2.0 * bm * bn * BK * GRID / (P["tflops"][tile] * 1e12) * 1e6
-    c_tile = P["tile_us"] + bm * bn * 2 / P["tile_bytes_per_us"]
-    t_dp = cdiv(T, GRID) * (ipt * t_iter + c_tile)
-    split = min(max(GRID / T, 1), ipt)
-    t_sk = cdiv(T * ipt, GRID) * t_iter + c_tile * max(T / GRID, 1.0)
-    if T % GRID:
-        # partial tiles an owner (or a group leader) fetches one after the other: all of them up to 16
-        # workgroups per tile, beyond that the two-level reduction with groups of 8
-        serial = split if split < 16 else 8 + split / 8
-        t_sk += P["part_us"] * (1 if split < 16 else 2) + serial * bm * bn * 4 / P["part_bytes_per_us"]
-    return min(t_dp, t_sk)
+    ipt = cdiv(K, BK[tile])
+    T = cdiv(M, tile[0]) * cdiv(N, tile[1])
+    return min(schedule_us(P, tile, ipt, T, s) for s in (0, T, T % GRID))
 
 
 def regrets(P, shapes, best, idx):
@@ -91,23 +107,22 @@ def main():
     test = [j for j in idx if 400 <= j < 500] or idx[4 * n // 5:]
     # the large skinny sizes are few among the random ones but matter (they are the HBM-bound workload): count them four times
     train = train + [j for j in train if shapes[j][0] <= 128 and shapes[j][1] >= 4096 and shapes[j][2] >= 4096] * 3
-    start = {"tflops": {t: 4.4 * math.sqrt(t[0] * t[1]) for t in best}, "tile_us": 1.5, "tile_bytes_per_us": 50e3,
-             "part_us": 3.0, "part_bytes_per_us": 40e3}
+    start = {"tflops": {t: 4.4 * math.sqrt(t[0] * t[1]) for t in best}, "tile_us": {t: 2.0 + t[0] * t[1] / 8e3 for t in best},
+             "level_us": 2.0, "fetch_bytes_per_us": 80e3, "traffic_bytes_per_us": 6e6}
     fits = []
     for seed in range(4):
         rng = random.Random(10 + seed)
-        P = dict(start, tflops=dict(start["tflops"]))
+        P = dict(start, tflops=dict(start["tflops"]), tile_us=dict(start["tile_us"]))
         s = score(P, shapes, best, train)
         for _ in range(5000):
-            Q = dict(P, tflops=dict(P["tflops"]))
-            k = rng.choice(["tflops"] * 3 + ["tile_us", "tile_bytes_per_us", "part_us", "part_bytes_per_us"])
-            if k == "tflops":
+            Q = dict(P, tflops=dict(P["tflops"]), tile_us=dict(P["tile_us"]))
+            k = rng.choice(["tflops"] * 3 + ["tile_us"] * 3 + ["level_us", "fetch_bytes_per_us", "traffic_bytes_per_us"])
+            if k in ("tflops", "tile_us"):
                 t = rng.choice(list(best))
-                Q["tflops"][t] *= math.exp(rng.gauss(0, 0.12))
+                Q[k][t] *= math.exp(rng.gauss(0, 0.12))
             else:
                 Q[k] *= math.exp(rng.gauss(0, 0.2))
-            Q["part_us"] = min(max(Q["part_us"], 1.0), 40.0)
-            Q["tile_us"] = min(max(Q["tile_us"], 0.5), 10.0)
+            Q["level_us"] = min(max(Q["level_us"], 0.5), 40.0)
             sq = score(Q, shapes, best, train)
             if sq < s:
                 P, s = Q, sq
@@ -117,9 +132,9 @@ def main():
     P = min(fits, key=lambda f: f[0])[1]
     print("chosen: all sizes %s" % describe(P, shapes, best, idx))
     for t in sorted(best, reverse=True):
-        print("  {%d, %d, %.0f.}," % (t[0], t[1], P["tflops"][t]))
-    print("  c_tile = %.2f + bm * bn * 2 / %.3g;  exchange = %.2f us per level + serial partial bytes / %.3g" % (
-        P["tile_us"], P["tile_bytes_per_us"], P["part_us"], P["part_bytes_per_us"]))
+        print("  {%d, %d, %d, %.0f., %.3g}," % (t[0], t[1], BK[t], P["tflops"][t], P["tile_us"][t]))
+    print("  exchange = %.2f us per level + serial partial bytes / %.4g + all partial bytes / %.4g" % (
+        P["level_us"], P["fetch_bytes_per_us"], P["traffic_bytes_per_us"]))
     skinny = [j for j in idx if shapes[j][0] <= 128 and shapes[j][1] >= 4096 and shapes[j][2] >= 4096]
     if skinny:
         print("  skinny sizes (M <= 128, N and K >= 4096), %d of them: %s" % (len(skinny), describe(P, shapes, best, skinny)))

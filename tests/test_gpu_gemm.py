@@ -164,7 +164,27 @@ def test_unaligned_rows_keep_columns_apart():
         assert np.isnan(d[:, :8]).all() and np.array_equal(d[:, 8:], ref[:, 8:])
 
 
-@pytest.mark.parametrize("shape,blk", [((64, 512, 52000), (32, 128, 64)), ((96, 768, 30000), (32, 128, 64)), ((112, 400, 30016), (64, 128, 64)),
+@pytest.mark.parametrize("blk,dtype", [((64, 64, 128), inputs.BF16), ((64, 64, 128), inputs.F16), ((32, 64, 64), inputs.BF16), ((32, 64, 64), inputs.F16),
+                                       ((128, 128, 128), inputs.E4M3), ((64, 128, 128), inputs.E4M3), ((32, 128, 128), inputs.E4M3)])
+def test_low_tiles_integer_exact(blk, dtype):
+    # several tiles each way with ragged edges (K beyond the ring, off the 16-byte grid and a single iteration), every
+    # policy, both fix-ups
+    for M, N, K in ((2 * blk[0] + 8, 3 * blk[1] + 48, 7 * blk[2] + 16), (blk[0] + 1, blk[1] + 5, 3 * blk[2] + 1), (3, blk[1], 16)):
+        A, B = inputs.small_int_pair(M, N, K, dtype, 71)
+        ref = G.gemm_fp64(A, B, ODT[dtype])
+        for policy in range(8):
+            _run_and_compare(A, B, dtype, policy, blk, grid=24, out_dtype=sk.SK_F32, ref=ref, exact=True)
+        _run_and_compare(A, B, dtype, sk.SK_POLICY_ALL_SK, blk, grid=24, out_dtype=sk.SK_F32, ref=ref, exact=True, fixup=sk.SK_FIXUP_ATOMIC)
+    # whole interior tiles one after the other: the first wait of a tile leaves the previous tile's stores in flight
+    M, N, K = 4 * blk[0], 8 * blk[1], 3 * blk[2]
+    A, B = inputs.small_int_pair(M, N, K, dtype, 72)
+    ref = G.gemm_fp64(A, B, ODT[dtype])
+    _run_and_compare(A, B, dtype, sk.SK_POLICY_DP, blk, grid=8, out_dtype=sk.SK_F32, ref=ref, exact=True, launches=2)
+    A, B = inputs.uniform_pair(M, N, K, dtype, 73)
+    _run_and_compare(A, B, dtype, sk.SK_POLICY_SK2_DP, blk, grid=8, launches=2)
+
+
+@pytest.mark.parametrize("shape,blk", [((64, 256, 52000), (32, 64, 64)), ((96, 512, 16384), (32, 64, 64)), ((112, 400, 30016), (64, 128, 64)),
                                        ((33, 777, 40000), (16, 128, 64))])
 def test_workgroups_sorted_by_k_slice_integer_exact(shape, blk):
     # the K-slice numbering of the workgroups: as many per tile as divide the grid, and some tiles with one more
