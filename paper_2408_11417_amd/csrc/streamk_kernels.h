@@ -950,67 +950,121 @@ __device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), f16x2));
 }
 
-// Convert and store one accumulator block.
+// The other 8-lane half of a lane's 16-lane row.
+__device__ __forceinline__ uint32_t swap_lane8(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128 /* row_ror:8 */, 0xf, 0xf, true);
+}
+
+// Convert and store NB accumulator blocks that lie side by side (the transposed blocks in pairs where a wave has an
+// even number of them, see STORE_BLOCKS).
 // TR (transposed blocks; used when rows of D start on 16-byte boundaries and N is a multiple of 8):
 // lane l holds row `row` (= block row l % MF) and in registers 4q..4q+3 the columns
-// col0 + 4*KG*q + {0..3}, col0 already including 4 * (l / MF).  16-bit outputs of the 32 x 32 block
-// exchange register pairs between lanes l and l + 32, after which a lane owns 8 consecutive columns
-// = one 16-byte store; fp32 outputs store 4 columns = 16 bytes per q.  A group of 4 (8) columns
+// col0 + 4*KG*q + {0..3}, col0 already including 4 * (l / MF).  A group of 4 (8) columns
 // starting at a multiple of 4 (8) is then inside N as a whole or not at all.
+// 32 x 32 blocks are packed into 16 bytes per lane and group (16-bit outputs exchange register pairs between lanes
+// l and l + 32 for that), and the groups are exchanged between the 16-lane rows and the 8-lane halves so that
+// one store instruction writes 8 rows of 128 bytes.  What that is for: the same bytes written as 32 rows of 32 bytes,
+// 16 of 64, 8 of 128 or 4 of 256 reach 2.6 / 3.9 / 5.2 / 5.6 TB/s (a kernel that only stores 256 x 256 tiles of an
+// 8192 x 8192 16-bit matrix).  A single 32-column block of 16-bit values only has 64 bytes per row.
 // Not TR: lane l holds column `col0` (= block column l % MF) and in register r the row
 // row + 4*KG*(r/4) + r%4, `row` already including 4 * (l / MF); stored element by element, the
 // lanes of one store instruction side by side in a row of D.
-template <class C, int OUT, bool EDGE, bool TR>
-__device__ __forceinline__ void store_block(const GemmArgs& g, int row, int col0, const typename Mfma<C::DT, C::MF>::Acc& blk) {
+template <class C, int OUT, bool TR> constexpr int STORE_BLOCKS = TR && C::MF == 32 && OUT != SK_F32 && C::NI % 2 == 0 ? 2 : 1;
+template <class C, int OUT, bool EDGE, bool TR, int NB>
+__device__ __forceinline__ void store_blocks(const GemmArgs& g, int row, int col0, const typename Mfma<C::DT, C::MF>::Acc (&blks)[NB]) {
     constexpr int Q = C::ACC / 4, QS = 4 * C::KG;    // register groups per lane, distance between their rows / columns
     if constexpr (!TR) {
+        static_assert(NB == 1, "pairs of transposed blocks only");
 #pragma unroll
         for (int r = 0; r < C::ACC; r++) {
             const int rr = row + (r / 4) * QS + r % 4;
             if (!EDGE || (rr < g.M && col0 < g.N)) {
                 const size_t o = (size_t)((uint32_t)rr * (uint32_t)g.N + (uint32_t)col0);
-                if (OUT == SK_F32) static_cast<float*>(g.D)[o] = blk[r];
-                else if (OUT == SK_BF16) static_cast<u16*>(g.D)[o] = to_bf16_bits(blk[r]);
-                else static_cast<_Float16*>(g.D)[o] = (_Float16)blk[r];
+                if (OUT == SK_F32) static_cast<float*>(g.D)[o] = blks[0][r];
+                else if (OUT == SK_BF16) static_cast<u16*>(g.D)[o] = to_bf16_bits(blks[0][r]);
+                else static_cast<_Float16*>(g.D)[o] = (_Float16)blks[0][r];
             }
         }
         return;
     }
-    const bool row_ok = !EDGE || row < g.M;
-    const uint32_t row_off = (uint32_t)row * (uint32_t)g.N;
-    if constexpr (OUT == SK_F32) {
+    auto pack = [](float lo, float hi) { return OUT == SK_BF16 ? pack_bf16(lo, hi) : pack_f16(lo, hi); };
+    if constexpr (C::MF == 32) {
+        // v[i]: 16 bytes of row l % 32 at 16-byte slot (l / 32) + 2 * i of its 64 or 128 bytes
+        constexpr int ES = OUT == SK_F32 ? 4 : 2, COLS = 16 / ES, G = OUT == SK_F32 ? 4 : 2 * NB;
+        u32x4 v[G];
+#pragma unroll
+        for (int i = 0; i < G; i++) {
+            if constexpr (OUT == SK_F32) {
+                v[i] = __builtin_bit_cast(u32x4, f32x4{blks[0][4 * i], blks[0][4 * i + 1], blks[0][4 * i + 2], blks[0][4 * i + 3]});
+            } else {
+                const auto& blk = blks[i / 2];
+                const int q = 8 * (i % 2);
+                const u32x2 d0 = __builtin_amdgcn_permlane32_swap(pack(blk[q], blk[q + 1]), pack(blk[q + 4], blk[q + 5]), false, false);
+                const u32x2 d1 = __builtin_amdgcn_permlane32_swap(pack(blk[q + 2], blk[q + 3]), pack(blk[q + 6], blk[q + 7]), false, false);
+                v[i] = u32x4{d0[0], d1[0], d0[1], d1[1]};
+            }
+        }
+        const int lane = threadIdx.x % 64;
+        if constexpr (C::BM <= 32) {
+            // the lowest tiles are bound by the length of the chain at the end of the kernel, not by the store rate: no
+            // exchange (23 x 4096 x 8128 to fp32: 16.6 us with it, 16.5 without)
+#pragma unroll
+            for (int i = 0; i < G; i++) {
+                const int col = col0 - 4 * (lane / 32) + COLS * (lane / 32 + 2 * i);
+                if (!EDGE || (row < g.M && col < g.N))
+                    *reinterpret_cast<u32x4*>(static_cast<char*>(g.D) + (size_t)((uint32_t)row * (uint32_t)g.N + (uint32_t)col) * ES) = v[i];
+            }
+            return;
+        }
+        const bool upper8 = (lane & 8) != 0;
+        // w[h][i]: row 16 * h + l % 16 at slot (l / 32) + 2 * (l / 16 % 2) + 4 * i
+        u32x4 w[2][G / 2];
+#pragma unroll
+        for (int i = 0; i < G / 2; i++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const u32x2 x = __builtin_amdgcn_permlane16_swap(v[2 * i][e], v[2 * i + 1][e], false, false);
+                w[0][i][e] = x[0];
+                w[1][i][e] = x[1];
+            }
+        constexpr int ROWS = G == 4 ? 8 : 16;                // rows of one store instruction
+        const int slot = lane / 32 + 2 * (lane / 16 % 2) + (G == 4 ? 4 * (lane / 8 % 2) : 0);
+        const int first = row - lane % 32 + lane % ROWS, col = col0 - 4 * (lane / 32) + COLS * slot;
+        auto put = [&](int r, const u32x4& x) {
+            if (!EDGE || (r < g.M && col < g.N))
+                *reinterpret_cast<u32x4*>(static_cast<char*>(g.D) + (size_t)((uint32_t)r * (uint32_t)g.N + (uint32_t)col) * ES) = x;
+        };
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            if constexpr (G == 4) {
+                u32x4 lo, hi;                                // rows 16 * h + l % 8 and 8 further down, slot + 4 in the upper lanes
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const uint32_t got = swap_lane8(upper8 ? w[h][0][e] : w[h][1][e]);
+                    lo[e] = upper8 ? got : w[h][0][e];
+                    hi[e] = upper8 ? w[h][1][e] : got;
+                }
+                put(first + 16 * h, lo);
+                put(first + 16 * h + 8, hi);
+            } else {
+                put(first + 16 * h, w[h][0]);
+            }
+        }
+    } else {
+        static_assert(NB == 1, "pairs of 32 x 32 blocks only");
+        const bool row_ok = !EDGE || row < g.M;
+        const uint32_t row_off = (uint32_t)row * (uint32_t)g.N;
 #pragma unroll
         for (int q = 0; q < Q; q++) {
             const int col = col0 + q * QS;
-            if (row_ok && (!EDGE || col < g.N))
-                *reinterpret_cast<f32x4*>(static_cast<float*>(g.D) + (size_t)(row_off + (uint32_t)col)) =
-                    f32x4{blk[4 * q], blk[4 * q + 1], blk[4 * q + 2], blk[4 * q + 3]};
-        }
-    } else {
-        uint32_t w[Q][2];
-#pragma unroll
-        for (int q = 0; q < Q; q++) {
-            w[q][0] = OUT == SK_BF16 ? pack_bf16(blk[4 * q], blk[4 * q + 1]) : pack_f16(blk[4 * q], blk[4 * q + 1]);
-            w[q][1] = OUT == SK_BF16 ? pack_bf16(blk[4 * q + 2], blk[4 * q + 3]) : pack_f16(blk[4 * q + 2], blk[4 * q + 3]);
-        }
-        if constexpr (C::MF == 32) {
-            // groups q (lanes below 32 keep theirs) and q + 1 (lanes from 32 up keep theirs): after the
-            // exchange a lane holds columns 8 * (q + l / 32) .. + 7 of its row, relative to the block
-            const int half = threadIdx.x % 64 / 32;
-#pragma unroll
-            for (int q = 0; q < Q; q += 2) {
-                const u32x2 d0 = __builtin_amdgcn_permlane32_swap(w[q][0], w[q + 1][0], false, false);
-                const u32x2 d1 = __builtin_amdgcn_permlane32_swap(w[q][1], w[q + 1][1], false, false);
-                const int col = col0 - 4 * half + 8 * (q + half);
-                if (row_ok && (!EDGE || col < g.N))
-                    *reinterpret_cast<u32x4*>(static_cast<u16*>(g.D) + (size_t)(row_off + (uint32_t)col)) = u32x4{d0[0], d1[0], d0[1], d1[1]};
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < Q; q++) {
-                const int col = col0 + q * QS;
-                if (row_ok && (!EDGE || col < g.N))
-                    *reinterpret_cast<u32x2*>(static_cast<u16*>(g.D) + (size_t)(row_off + (uint32_t)col)) = u32x2{w[q][0], w[q][1]};
+            const auto& blk = blks[0];
+            if (row_ok && (!EDGE || col < g.N)) {
+                if constexpr (OUT == SK_F32)
+                    *reinterpret_cast<f32x4*>(static_cast<float*>(g.D) + (size_t)(row_off + (uint32_t)col)) =
+                        f32x4{blk[4 * q], blk[4 * q + 1], blk[4 * q + 2], blk[4 * q + 3]};
+                else
+                    *reinterpret_cast<u32x2*>(static_cast<u16*>(g.D) + (size_t)(row_off + (uint32_t)col)) =
+                        u32x2{pack(blk[4 * q], blk[4 * q + 1]), pack(blk[4 * q + 2], blk[4 * q + 3])};
             }
         }
     }
@@ -1018,13 +1072,14 @@ __device__ __forceinline__ void store_block(const GemmArgs& g, int row, int col0
 
 // Epilogue of a tile's owner (or of an unsplit tile, n_contrib = 0): add the parked partials of the
 // contributors part0, part0 + part_stride, ... (a fixed order: away from the owner in k), convert and store.  OUT selects the
-// output type, EDGE adds the bounds checks, TR says that the blocks are transposed (see store_block).
+// output type, EDGE adds the bounds checks, TR says that the blocks are transposed (see store_blocks).
 // row0 / col0: the lane's (first) row and (first) column in the wave's first block.  The big tiles
-// work one block at a time, which keeps their register need flat.
+// work one block (or pair of blocks) at a time, which keeps their register need flat.
 template <class C, int OUT, bool EDGE, bool TR>
 __device__ __forceinline__ void reduce_and_store(const GemmArgs& g, int row0, int col0, const float* part0, int n_contrib,
                                                  ptrdiff_t part_stride, const typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI]) {
     typedef typename Mfma<C::DT, C::MF>::Acc Acc;
+    constexpr int NB = STORE_BLOCKS<C, OUT, TR>;
     // Tiles with few accumulators per lane fetch a contributor's whole share at once (one round trip
     // per contributor instead of one per block and contributor); the big tiles have no registers for that.
     constexpr bool WHOLE = C::ACC_REGS <= 64;
@@ -1036,23 +1091,26 @@ __device__ __forceinline__ void reduce_and_store(const GemmArgs& g, int row0, in
             for (int ni = 0; ni < C::NI; ni++) sum[mi][ni] = acc[mi][ni];
         add_partials<C>(sum, part0, n_contrib, part_stride);
     }
+    // (unrolled by instantiation: written as loops the four-wave kernels' bodies exceed the compiler's limit for
+    // unrolling, and accumulators indexed at run time would live in memory)
+    for_each_below<C::MI * C::NI / NB>([&](auto index) {
+        constexpr int mi = decltype(index)::value * NB / C::NI, ni = decltype(index)::value * NB % C::NI;
+        Acc blks[NB];
 #pragma unroll
-    for (int mi = 0; mi < C::MI; mi++)
-#pragma unroll
-        for (int ni = 0; ni < C::NI; ni++) {
-            Acc blk;
+        for (int b = 0; b < NB; b++) {
             if constexpr (WHOLE) {
-                blk = sum[mi][ni];
+                blks[b] = sum[mi][ni + b];
             } else {
-                blk = acc[mi][ni];
-                const float* src = part0 + ((mi * C::NI + ni) * C::ACC) * C::THREADS;
+                blks[b] = acc[mi][ni + b];
+                const float* src = part0 + ((mi * C::NI + ni + b) * C::ACC) * C::THREADS;
                 // two contributors' shares of this block per round trip (all the registers allow), added in
                 // the same fixed order as one by one
-                add_block_partials<C, 32 / C::ACC>(blk, src, n_contrib, part_stride);
+                add_block_partials<C, 32 / C::ACC>(blks[b], src, n_contrib, part_stride);
             }
-            store_block<C, OUT, EDGE, TR>(g, row0 + mi * C::MF, col0 + ni * C::MF, blk);
-            __builtin_amdgcn_sched_barrier(0);
         }
+        store_blocks<C, OUT, EDGE, TR, NB>(g, row0 + mi * C::MF, col0 + ni * C::MF, blks);
+        __builtin_amdgcn_sched_barrier(0);
+    });
 }
 
 // Atomic fix-up (the accumulation step of Algorithm 1): a segment that covers only part of the tile's

@@ -122,9 +122,10 @@ double model_us(const TileCost& c, int bk, int64_t ipt, int64_t tiles, int64_t s
     double t = (double)ceil_div(tiles - sk_tiles, grid) * (ipt * t_iter + c.tile_us);
     if (sk_tiles == 0) return t;
     const int64_t iters = sk_tiles * ipt, ipw = ceil_div(iters, grid);
-    const double waves = (double)sk_tiles / grid;
+    const bool split_tiles = ipw % ipt != 0 && iters > ipw;
+    const double waves = split_tiles ? (double)sk_tiles / grid : (double)(ipw / ipt);       // tiles a workgroup stores
     t += ipw * t_iter + c.tile_us * (waves > 1 ? waves : 1.0);
-    if (ipw % ipt != 0 && iters > ipw) {
+    if (split_tiles) {
         // about `split` workgroups share a tile: the partials an owner (or a group leader) fetches one after the
         // other - all of them up to 16 workgroups per tile, beyond that the two-level reduction with groups of 8 -
         // and the traffic of all of them together, which shares the memory system

@@ -47,8 +47,9 @@ def schedule_us(P, tile, ipt, T, sk_tiles):
         return t
     iters = sk_tiles * ipt
     ipw = cdiv(iters, GRID)
-    t += ipw * t_iter + c_tile * max(sk_tiles / GRID, 1.0)
-    if ipw % ipt and iters > ipw:
+    split_tiles = ipw % ipt != 0 and iters > ipw
+    t += ipw * t_iter + c_tile * max(sk_tiles / GRID if split_tiles else ipw // ipt, 1.0)
+    if split_tiles:
         # partial tiles an owner (or a group leader) fetches one after the other: all of them up to 16
         # workgroups per tile, beyond that the two-level reduction with groups of 8; and all of them together
         split = max(ipt / ipw, 1.0)
