@@ -31,17 +31,18 @@ LIBRARY = {"tflops": {(256, 256): 1585., (256, 128): 1299., (128, 128): 1099., (
            "tile_us": {(256, 256): 10.9, (256, 128): 5.89, (128, 128): 3.90, (64, 128): 2.29, (32, 128): 2.47, (16, 128): 2.49,
                        (64, 64): 2.63, (32, 64): 2.58},
            "level_us": 1.78, "fetch_bytes_per_us": 119.2e3, "traffic_bytes_per_us": 6.658e6}
+STAGED_TILE = 1.6      # MODEL_STAGED_TILE: problems whose rows are off the 16-byte grid
 
 
 def cdiv(a, b):
     return -(-a // b)
 
 
-def schedule_us(P, tile, ipt, T, sk_tiles):
+def schedule_us(P, tile, ipt, T, sk_tiles, staged=False):
     """Microseconds of a schedule that splits sk_tiles of T tiles over the grid (model_us in C++)."""
     bm, bn = tile
     t_iter = 2.0 * bm * bn * BK[tile] * GRID / (P["tflops"][tile] * 1e12) * 1e6
-    c_tile = P["tile_us"][tile]
+    c_tile = P["tile_us"][tile] * (STAGED_TILE if staged else 1.0)
     t = cdiv(T - sk_tiles, GRID) * (ipt * t_iter + c_tile)
     if sk_tiles == 0:
         return t
@@ -65,7 +66,7 @@ def predict(P, tile, M, N, K):
     """The cost model of sk_default_tile for one tile shape (microseconds)."""
     ipt = cdiv(K, BK[tile])
     T = cdiv(M, tile[0]) * cdiv(N, tile[1])
-    return min(schedule_us(P, tile, ipt, T, s) for s in (0, T, T % GRID))
+    return min(schedule_us(P, tile, ipt, T, s, N % 8 != 0 or K % 8 != 0) for s in (0, T, T % GRID))
 
 
 def regrets(P, shapes, best, idx):
