@@ -91,18 +91,18 @@ void expand_wg(const sk_plan_header& h, int x, std::vector<sk_segment>* out, sk_
 // of the first 400 of 500 seeded problem sizes, 72 with at most 128 rows and 40 with few tiles and deep K on
 // MI355X; sizes 400 .. 499 are the selector's held-out split and stay out of the fit (fit_tile_model.py; the
 // fit optimises the dispatcher's pick of tile and policy, not the predicted times).  Time of the pick over the
-// fastest of all tiles and schedules, geometric mean: 16 bits 1.016 / 1.025 / 1.030 on the three sets (the six
-// shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.008 / 1.006 / 1.006 (two shapes: 1.59 / 2.29 / 2.44).
+// fastest of all tiles and schedules, geometric mean: 16 bits 1.016 / 1.028 / 1.027 on the three sets (the six
+// shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.009 / 1.007 / 1.015 (two shapes: 1.59 / 2.29 / 2.44).
 struct TileCost { int bm, bn, bk; double tflops, tile_us; };
-const TileCost tile_costs16[] = {{256, 256, 64, 1585., 10.9}, {256, 128, 64, 1299., 5.89}, {128, 128, 64, 1099., 3.90},
-                                 {64, 128, 64, 661., 2.29},   {32, 128, 64, 583., 2.47},   {16, 128, 64, 330., 2.49},
-                                 {64, 64, 128, 602., 2.63},   {32, 64, 64, 425., 2.58}};
+const TileCost tile_costs16[] = {{256, 256, 64, 1590., 10.40}, {256, 128, 64, 1307., 5.61}, {128, 128, 64, 1062., 4.33},
+                                 {64, 128, 64, 745., 2.91}, {32, 128, 64, 478., 2.73}, {16, 128, 64, 287., 2.68},
+                                 {64, 64, 128, 500., 3.08}, {32, 64, 64, 364., 2.76}};
 // (the large 8-bit tile moves the bytes of the large 16-bit one with twice the k at twice the rate: its constants)
-const TileCost tile_costs8[] = {{256, 256, 128, 3170., 10.9}, {128, 256, 128, 2821., 4.75}, {128, 128, 128, 1919., 2.61},
+const TileCost tile_costs8[] = {{256, 256, 128, 3180., 10.40}, {128, 256, 128, 2821., 4.75}, {128, 128, 128, 1919., 2.61},
                                 {64, 128, 128, 1467., 2.45},  {32, 128, 128, 915., 2.48}};
 constexpr int N_COSTS16 = 8, N_COSTS8 = 5;
 constexpr int MODEL_GRID = 256;
-constexpr double MODEL_LEVEL_US = 1.78, MODEL_FETCH_BYTES_PER_US = 119.2e3, MODEL_TRAFFIC_BYTES_PER_US = 6.658e6;
+constexpr double MODEL_LEVEL_US = 1.68, MODEL_FETCH_BYTES_PER_US = 107e3, MODEL_TRAFFIC_BYTES_PER_US = 6.953e6;
 
 double model_iter_us(const TileCost& c, int bk) {          // one k-iteration of every workgroup of a full grid
     return 2.0 * c.bm * c.bn * bk * MODEL_GRID / (c.tflops * 1e12) * 1e6;

@@ -26,11 +26,11 @@ BK = {(256, 256): 64, (256, 128): 64, (128, 128): 64, (64, 128): 64, (32, 128): 
 # The constants as they stand in csrc/streamk_plan.cpp (tile_costs16, MODEL_*).  The library's C++ code is
 # what runs; predict() below restates its formula for the fit, and tests/test_selector.py checks that
 # predict() with these constants picks sk_default_tile's tile.
-LIBRARY = {"tflops": {(256, 256): 1585., (256, 128): 1299., (128, 128): 1099., (64, 128): 661., (32, 128): 583., (16, 128): 330.,
-                      (64, 64): 602., (32, 64): 425.},
-           "tile_us": {(256, 256): 10.9, (256, 128): 5.89, (128, 128): 3.90, (64, 128): 2.29, (32, 128): 2.47, (16, 128): 2.49,
-                       (64, 64): 2.63, (32, 64): 2.58},
-           "level_us": 1.78, "fetch_bytes_per_us": 119.2e3, "traffic_bytes_per_us": 6.658e6}
+LIBRARY = {"tflops": {(256, 256): 1590., (256, 128): 1307., (128, 128): 1062., (64, 128): 745., (32, 128): 478., (16, 128): 287.,
+                      (64, 64): 500., (32, 64): 364.},
+           "tile_us": {(256, 256): 10.40, (256, 128): 5.61, (128, 128): 4.33, (64, 128): 2.91, (32, 128): 2.73, (16, 128): 2.68,
+                       (64, 64): 3.08, (32, 64): 2.76},
+           "level_us": 1.68, "fetch_bytes_per_us": 107e3, "traffic_bytes_per_us": 6.953e6}
 STAGED_TILE = 1.6      # MODEL_STAGED_TILE: problems whose rows are off the 16-byte grid
 
 
