@@ -55,7 +55,7 @@ struct GemmArgs {
     int k_aligned;         // 1: a workgroup runs the whole tiles of its Stream-K range first, then the head of its last
                            //    tile (k from 0), then the tail of its first one, and the workgroup holding a tile's
                            //    last iteration reduces and stores it
-    int stream_b;          // 1: B is read exactly once (one row of tiles) and is large: the low tiles request it non-temporally
+    int stream_b;          // 1: B is read exactly once (one row of tiles) and is large: MAY_STREAM_B tiles request it non-temporally
     // divisors of the index arithmetic: ipt, ipw, tiles_n, SK_GROUP_ROWS * tiles_n, rows of the last (short) band
     sk_fast_div div_ipt, div_ipw, div_tiles_n, div_band, div_last_rows;
     sk_fast_div div_tiles, div_extra;   // of logical_wg: tiles, grid mod tiles
@@ -1309,7 +1309,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
     // On the LDS-DMA path the first requests of the next segment go out before the current tile's
     // fix-up and epilogue (the ring is free once the MAC loop has ended): the loads travel while the
     // tile is stored, and the first wait of the next MAC loop leaves the epilogue's stores in flight.
-    constexpr bool PREFETCH = ALIGNED;
+    constexpr bool PREFETCH = ALIGNED, MAY_NT = ALIGNED && C::MAY_STREAM_B;
     int tile, k_begin, k_end, m0, n0;
     bool have = next_segment(tile, k_begin, k_end, m0, n0);
     bool prefetched = false, stores_in_flight = false;
@@ -1319,8 +1319,9 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         for (int mi = 0; mi < C::MI; mi++)
 #pragma unroll
             for (int ni = 0; ni < C::NI; ni++) acc[mi][ni] = Acc{};
-        // B requested non-temporally or not: decided once per launch, two copies of the loop in the low tiles
-        if (C::MAY_STREAM_B && g.stream_b) mac_loop<C, ALIGNED, TR, C::MAY_STREAM_B>(g, m0, n0, k_begin, k_end, smem, fm, acc, prefetched, stores_in_flight);
+        // B requested non-temporally or not: decided once per launch, two copies of the loop in the tiles that may
+        // (the register-staged path has no such requests, so its kernels carry one copy)
+        if (MAY_NT && g.stream_b) mac_loop<C, ALIGNED, TR, MAY_NT>(g, m0, n0, k_begin, k_end, smem, fm, acc, prefetched, stores_in_flight);
         else mac_loop<C, ALIGNED, TR, false>(g, m0, n0, k_begin, k_end, smem, fm, acc, prefetched, stores_in_flight);
 
         // this segment's numbers for the fix-up and the epilogue; then look ahead
@@ -1331,7 +1332,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         if (prefetched) {
             DmaMap<C> ahead;
             ahead.init(g, m0, n0);
-            if (C::MAY_STREAM_B && g.stream_b) mac_prefetch<C, C::MAY_STREAM_B>(g, m0, n0, k_begin, k_end, smem, ahead);
+            if (MAY_NT && g.stream_b) mac_prefetch<C, MAY_NT>(g, m0, n0, k_begin, k_end, smem, ahead);
             else mac_prefetch<C, false>(g, m0, n0, k_begin, k_end, smem, ahead);
         }
         stores_in_flight = finish_segment(cur_tile, cur_k_begin, cur_k_end, cur_m0, cur_n0, acc) && prefetched;
