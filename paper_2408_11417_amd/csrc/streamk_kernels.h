@@ -265,71 +265,109 @@ __device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
 struct __attribute__((packed, aligned(1))) Piece1 { u32x4 v; };
 struct __attribute__((packed, aligned(2))) Piece2 { u32x4 v; };
 
+// Element by element: a piece of a matrix of less than 16 bytes, zero beyond its edges.
 template <int ES>
 __device__ __forceinline__ uint4 load_piece(const unsigned char* __restrict__ base, int row, int col, int rows, int cols) {
-    // 16 bytes = 16 / ES consecutive elements of a row-major matrix with `cols` columns, zero beyond its edges
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (row < rows) {
-        const unsigned char* p = base + (size_t)((uint32_t)row * (uint32_t)cols + (uint32_t)col) * ES;
-        if (col + 16 / ES <= cols) {          // the whole piece lies inside the row
-            const u32x4 w = ES == 2 ? reinterpret_cast<const Piece2*>(p)->v : reinterpret_cast<const Piece1*>(p)->v;
-            v = make_uint4(w[0], w[1], w[2], w[3]);
-        } else if (col < cols) {                     // the piece that straddles the end of the row
-            unsigned char e[16];
+    unsigned char e[16];
+    const unsigned char* p = base + (size_t)((uint32_t)row * (uint32_t)cols + (uint32_t)col) * ES;
 #pragma unroll
-            for (int i = 0; i < 16; i++) e[i] = (col + i / ES < cols) ? p[i] : (unsigned char)0;
-            v.x = e[0] | (uint32_t)e[1] << 8 | (uint32_t)e[2] << 16 | (uint32_t)e[3] << 24;
-            v.y = e[4] | (uint32_t)e[5] << 8 | (uint32_t)e[6] << 16 | (uint32_t)e[7] << 24;
-            v.z = e[8] | (uint32_t)e[9] << 8 | (uint32_t)e[10] << 16 | (uint32_t)e[11] << 24;
-            v.w = e[12] | (uint32_t)e[13] << 8 | (uint32_t)e[14] << 16 | (uint32_t)e[15] << 24;
-        }
-    }
-    return v;
+    for (int i = 0; i < 16; i++) e[i] = row < rows && col + i / ES < cols ? p[i] : (unsigned char)0;
+    return make_uint4(e[0] | (uint32_t)e[1] << 8 | (uint32_t)e[2] << 16 | (uint32_t)e[3] << 24,
+                      e[4] | (uint32_t)e[5] << 8 | (uint32_t)e[6] << 16 | (uint32_t)e[7] << 24,
+                      e[8] | (uint32_t)e[9] << 8 | (uint32_t)e[10] << 16 | (uint32_t)e[11] << 24,
+                      e[12] | (uint32_t)e[13] << 8 | (uint32_t)e[14] << 16 | (uint32_t)e[15] << 24);
+}
+
+// Bytes `skip` .. 15 of a piece moved down to byte 0 on, zeros behind them.
+__device__ __forceinline__ uint4 shift_piece(uint4 v, uint32_t skip) {
+    uint32_t t[4] = {__builtin_amdgcn_alignbyte(v.y, v.x, skip & 3), __builtin_amdgcn_alignbyte(v.z, v.y, skip & 3),
+                     __builtin_amdgcn_alignbyte(v.w, v.z, skip & 3), __builtin_amdgcn_alignbyte(0, v.w, skip & 3)};
+    if (skip & 4) { t[0] = t[1]; t[1] = t[2]; t[2] = t[3]; t[3] = 0; }
+    if (skip & 8) { t[0] = t[2]; t[1] = t[3]; t[2] = 0; t[3] = 0; }
+    return make_uint4(t[0], t[1], t[2], t[3]);
 }
 
 // Register-staged fill of one stage (same LDS image as the DMA path), piece by piece: fetch a piece
 // into registers, and later park it in LDS.  Piece j of thread t is LDS position j * THREADS + t of the
 // stage's A or B tile; the swizzle is applied by choosing which global piece goes there, as on the DMA path.
-// INSIDE pieces are fetched with one under-aligned 16-byte load at a precomputed offset, no checks: rows beyond
-// M are clamped, and a piece that reaches beyond column N - 1 of B runs on into the next row - it only feeds
-// output columns that are never stored.  The caller vouches that the k-iteration is below inside_k(), that
-// is, lies wholly inside K with at least one row of B behind it (so that running on stays inside B).
-// Everything else goes through load_piece, with zero fill beyond K.
+// A piece is one under-aligned 16-byte load.  Rows beyond M and columns beyond N fetch the start of the iteration's
+// first row instead - every lane the same aligned 16 bytes, a third of the vector L1's time - and a piece that reaches
+// beyond column N - 1 of B runs on into the next row: both only feed output elements that are never stored.
+// The k-iterations below `inside` lie wholly inside K with at least one row of B behind them (so that running on
+// stays inside B).  The others - the last one, as a rule - are fetched from where 16 bytes still lie inside the matrix
+// and cut to what is inside K before they are parked: fetch<CHECKED> and cut() work for every k-iteration of matrices
+// of 16 bytes or more.  Short segments run hardly anything else: with element loads here and the checks in every
+// slot of the loop, 8-bit problems of one k-iteration took 11.3 us, now 9.1; 12 x 5481 x 8461 67.7, now 35.8;
+// 5001 x 5003 x 65 in bf16 40.8, now 28.8.
 template <class C> struct StagedFill {
     uint32_t a_off[C::CA], b_off[C::CB];         // byte offsets from A / B at k-iteration 0
-    int m0, n0;
-    static __device__ __forceinline__ int inside_k(const GemmArgs& g) { return g.N >= C::PE ? (g.K - 1) / C::BK : 0; }
-    __device__ __forceinline__ void init(const GemmArgs& g, int m0_, int n0_) {
-        m0 = m0_;
-        n0 = n0_;
+    uint32_t a_end, b_end;                       // byte offset of the last 16 bytes of A / B
+    int inside;
+    int a_col;                                   // column of this lane's A pieces inside the k-iteration (the same for all)
+    static_assert(C::THREADS % C::CPA == 0 && (C::THREADS / C::CPA) % 16 == 0, "a thread's A pieces lie in one column");
+    static __device__ __forceinline__ bool tiny(const GemmArgs& g) {
+        return (uint64_t)g.M * (uint32_t)g.K * C::ES < 16 || (uint64_t)g.N * (uint32_t)g.K * C::ES < 16;
+    }
+    __device__ __forceinline__ void init(const GemmArgs& g, int m0, int n0) {
+        inside = g.N >= C::PE ? (g.K - 1) / C::BK : 0;
+        a_end = (uint32_t)g.M * (uint32_t)g.K * C::ES - 16;
+        b_end = (uint32_t)g.N * (uint32_t)g.K * C::ES - 16;
+        a_col = C::PE * ((threadIdx.x % C::CPA) ^ swz_a<C::CPA>(threadIdx.x / C::CPA));
 #pragma unroll
         for (int j = 0; j < C::CA; j++) {
-            const int p = threadIdx.x + j * C::THREADS, r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
-            const int row = m0 + r < g.M ? m0 + r : g.M - 1;
-            a_off[j] = ((uint32_t)row * (uint32_t)g.K + (uint32_t)(C::PE * c)) * C::ES;
+            const int r = (threadIdx.x + j * C::THREADS) / C::CPA;
+            a_off[j] = m0 + r < g.M ? ((uint32_t)(m0 + r) * (uint32_t)g.K + (uint32_t)a_col) * C::ES : 0;
         }
 #pragma unroll
         for (int j = 0; j < C::CB; j++) {
             const int p = threadIdx.x + j * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8, C::CPB>(k);
             const int col = n0 + C::PE * c;
-            b_off[j] = ((uint32_t)k * (uint32_t)g.N + (uint32_t)(col < g.N ? col : 0)) * C::ES;
+            b_off[j] = col < g.N ? ((uint32_t)k * (uint32_t)g.N + (uint32_t)col) * C::ES : 0;
         }
     }
-    static __device__ __forceinline__ uint4 load_inside(const char* base, uint32_t off) {
+    static __device__ __forceinline__ uint4 load16(const char* base, uint32_t off) {
         const u32x4 w = C::ES == 2 ? reinterpret_cast<const Piece2*>(base + off)->v : reinterpret_cast<const Piece1*>(base + off)->v;
         return make_uint4(w[0], w[1], w[2], w[3]);
     }
+    // byte offset of piece q at k-iteration kit (modulo 2^32: one beyond the matrix may come out anywhere)
+    __device__ __forceinline__ uint32_t offset(const GemmArgs& g, int kit, int q) const {
+        const uint32_t it = (uint32_t)kit * (uint32_t)(C::BK * C::ES);
+        return q < C::CB ? b_off[q] + it * (uint32_t)g.N : a_off[q - C::CB] + it;
+    }
     // piece q of the stage of k-iteration kit: the B pieces first, then the A pieces
-    template <bool INSIDE> __device__ __forceinline__ uint4 fetch(const GemmArgs& g, int kit, int q) const {
-        if (q < C::CB) {
-            if (INSIDE) return load_inside(static_cast<const char*>(g.B) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)) * (uint32_t)g.N, b_off[q]);
-            const int p = threadIdx.x + q * C::THREADS, k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8, C::CPB>(k);
-            return load_piece<C::ES>(static_cast<const unsigned char*>(g.B), kit * C::BK + k, n0 + c * C::PE, g.K, g.N);
+    template <bool CHECKED> __device__ __forceinline__ uint4 fetch(const GemmArgs& g, int kit, int q) const {
+        const char* m = static_cast<const char*>(q < C::CB ? g.B : g.A);
+        if (CHECKED) {
+            // (nothing inside K: the start of the matrix, aligned; a little beyond the end of the matrix: its last 16 bytes)
+            const uint32_t off = offset(g, kit, q), end = q < C::CB ? b_end : a_end;
+            const bool some = (q < C::CB || kit * C::BK + a_col < g.K) && (off <= end || off - end < 16);
+            return load16(m, some ? (off < end ? off : end) : 0u);
         }
-        const int j = q - C::CB;
-        if (INSIDE) return load_inside(static_cast<const char*>(g.A) + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)), a_off[j]);
-        const int p = threadIdx.x + j * C::THREADS, r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
-        return load_piece<C::ES>(static_cast<const unsigned char*>(g.A), m0 + r, kit * C::BK + c * C::PE, g.M, g.K);
+        if (q < C::CB) return load16(m + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)) * (uint32_t)g.N, b_off[q]);
+        return load16(m + (size_t)((uint32_t)kit * (uint32_t)(C::BK * C::ES)), a_off[q - C::CB]);
+    }
+    // Before the pieces of a stage that was fetched CHECKED are parked: keep what is inside K.  (A piece with nothing
+    // inside K may have come from anywhere: nothing of it is kept.)
+    __device__ __forceinline__ void cut(const GemmArgs& g, int kit, uint4 (&st)[C::PIECES]) const {
+        if (kit < inside) return;
+        int tid = threadIdx.x, col = a_col;      // (opaque: masks and rows are worked out here, not ahead of the loop and kept)
+        asm volatile("" : "+v"(tid), "+v"(col));
+        uint32_t mask[4];                        // of the bytes of an A piece
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int n = (g.K - kit * C::BK - col) * C::ES - 4 * j;
+            mask[j] = n >= 4 ? ~0u : n <= 0 ? 0u : (1u << (8 * n)) - 1u;
+        }
+#pragma unroll
+        for (int q = 0; q < C::PIECES; q++) {
+            const uint32_t off = offset(g, kit, q), end = q < C::CB ? b_end : a_end;
+            if (off > end && off - end < 16) st[q] = shift_piece(st[q], off - end);
+            if (q < C::CB) {
+                if (kit * C::BK + (tid + q * C::THREADS) / C::CPB >= g.K) st[q] = make_uint4(0, 0, 0, 0);
+            } else {
+                st[q] = make_uint4(st[q].x & mask[0], st[q].y & mask[1], st[q].z & mask[2], st[q].w & mask[3]);
+            }
+        }
     }
     static __device__ __forceinline__ void park(unsigned char* a_stage, unsigned char* b_stage, int q, uint4 v) {
         const int p = threadIdx.x + (q < C::CB ? q : q - C::CB) * C::THREADS;
@@ -337,6 +375,19 @@ template <class C> struct StagedFill {
             if (C::B_PIECES % C::THREADS == 0 || p < C::B_PIECES) reinterpret_cast<uint4*>(b_stage)[p] = v;
         } else {
             if (C::A_PIECES % C::THREADS == 0 || p < C::A_PIECES) reinterpret_cast<uint4*>(a_stage)[p] = v;
+        }
+    }
+    // The stage of k-iteration kit of a problem with a matrix of less than 16 bytes.
+    static __device__ __forceinline__ void fill_tiny(const GemmArgs& g, int m0, int n0, int kit, unsigned char* a_stage, unsigned char* b_stage) {
+#pragma unroll 1
+        for (int p = threadIdx.x; p < C::A_PIECES; p += C::THREADS) {
+            const int r = p / C::CPA, c = (p % C::CPA) ^ swz_a<C::CPA>(r);
+            reinterpret_cast<uint4*>(a_stage)[p] = load_piece<C::ES>(static_cast<const unsigned char*>(g.A), m0 + r, kit * C::BK + c * C::PE, g.M, g.K);
+        }
+#pragma unroll 1
+        for (int p = threadIdx.x; p < C::B_PIECES; p += C::THREADS) {
+            const int k = p / C::CPB, c = (p % C::CPB) ^ swz_b<C::FP8, C::CPB>(k);
+            reinterpret_cast<uint4*>(b_stage)[p] = load_piece<C::ES>(static_cast<const unsigned char*>(g.B), kit * C::BK + k, n0 + c * C::PE, g.K, g.N);
         }
     }
 };
@@ -585,31 +636,40 @@ template <class C, bool TR>
 __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n0, int k_begin, int k_end, unsigned char* smem,
                                                 const FragMap<C>& fm, typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI]) {
     const int nk = k_end - k_begin;
-    StagedFill<C> sf;
-    sf.init(g, m0, n0);
-    const int inside = StagedFill<C>::inside_k(g);
     auto a_slot = [&](int s) { return smem + (s & 1) * C::A_BYTES; };
     auto b_slot = [&](int s) { return smem + C::B_RING + (s & 1) * C::B_BYTES; };
+    if (StagedFill<C>::tiny(g)) {                // (K is at most 15 then: a single k-iteration)
+        for (int k = k_begin; k < k_end; k++) {
+            StagedFill<C>::fill_tiny(g, m0, n0, k, a_slot(0), b_slot(0));
+            __syncthreads();
+            mac_stage<C, TR>(a_slot(0), b_slot(0), fm, acc);
+            __syncthreads();
+        }
+        return;
+    }
+    StagedFill<C> sf;
+    sf.init(g, m0, n0);
+    const int inside = sf.inside;
     if constexpr (C::STAGED_FINE) {
         constexpr int NM = C::MI * C::NI, SLOTS = C::KK * NM, PS = SLOTS * 7 / 8 > 0 ? SLOTS * 7 / 8 : 1;
         uint4 st[C::PIECES];
 #pragma unroll
-        for (int q = 0; q < C::PIECES; q++) st[q] = k_begin < inside ? sf.template fetch<true>(g, k_begin, q) : sf.template fetch<false>(g, k_begin, q);
+        for (int q = 0; q < C::PIECES; q++) st[q] = sf.template fetch<true>(g, k_begin, q);
+        sf.cut(g, k_begin, st);
 #pragma unroll
         for (int q = 0; q < C::PIECES; q++) sf.park(a_slot(0), b_slot(0), q, st[q]);
         if (nk > 1) {
 #pragma unroll
-            for (int q = 0; q < C::PIECES; q++) st[q] = k_begin + 1 < inside ? sf.template fetch<true>(g, k_begin + 1, q) : sf.template fetch<false>(g, k_begin + 1, q);
+            for (int q = 0; q < C::PIECES; q++) st[q] = sf.template fetch<true>(g, k_begin + 1, q);
         }
         Frags<C> f[2];
-        auto step = [&](int i, int k_step, auto mma, auto read, const Frags<C>& cur, Frags<C>& nxt, int kk_next, auto steady) {
+        auto step = [&](int i, int k_step, auto read, const Frags<C>& cur, Frags<C>& nxt, int kk_next, auto steady) {
             constexpr int R = Frags<C>::READS, NRS = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
             constexpr bool STEADY = decltype(steady)::value;
 #pragma unroll
             for (int s = 0; s < NM; s++) {
                 const int mi = s / C::NI, ni = s % C::NI, slot = k_step * NM + s;
-                if (decltype(mma)::value)
-                    acc[mi][ni] = TR ? Mfma<C::DT, C::MF>::run(cur.b[ni], cur.a[mi], acc[mi][ni]) : Mfma<C::DT, C::MF>::run(cur.a[mi], cur.b[ni], acc[mi][ni]);
+                acc[mi][ni] = TR ? Mfma<C::DT, C::MF>::run(cur.b[ni], cur.a[mi], acc[mi][ni]) : Mfma<C::DT, C::MF>::run(cur.a[mi], cur.b[ni], acc[mi][ni]);
                 if (decltype(read)::value && s < NRS) {
 #pragma unroll
                     for (int r = s * R / NRS; r < (s + 1) * R / NRS; r++) nxt.load_one(a_slot(i + 1), b_slot(i + 1), fm, kk_next, r);
@@ -618,52 +678,53 @@ __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n
 #pragma unroll
                     for (int q = slot * C::PIECES / PS; q < (slot + 1) * C::PIECES / PS; q++) {
                         if (STEADY || i + 2 < nk) sf.park(a_slot(i), b_slot(i), q, st[q]);
-                        if (STEADY) st[q] = sf.template fetch<true>(g, k_begin + i + 3, q);
-                        else if (i + 3 < nk) st[q] = k_begin + i + 3 < inside ? sf.template fetch<true>(g, k_begin + i + 3, q) : sf.template fetch<false>(g, k_begin + i + 3, q);
+                        if (STEADY || i + 3 < nk) st[q] = sf.template fetch<!STEADY>(g, k_begin + i + 3, q);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto trip = [&](int i, auto first, auto next, auto steady) {
-            constexpr bool FIRST = decltype(first)::value, NEXT = decltype(next)::value;
+        auto trip = [&](int i, auto next, auto steady) {
+            constexpr bool NEXT = decltype(next)::value;
             if (NEXT) __syncthreads();
+            if (NEXT && !decltype(steady)::value && i + 2 < nk) sf.cut(g, k_begin + i + 2, st);
             __builtin_amdgcn_sched_barrier(0);
-            step(i, 0, std::integral_constant<bool, !FIRST>(), std::integral_constant<bool, NEXT>(), f[1], f[0], 0, steady);
+            step(i, 0, std::integral_constant<bool, NEXT>(), f[1], f[0], 0, steady);
             if (NEXT) {
 #pragma unroll
-                for (int kk = 0; kk < C::KK - 1; kk++) step(i, kk + 1, std::true_type(), std::true_type(), f[kk & 1], f[(kk + 1) & 1], kk + 1, steady);
+                for (int kk = 0; kk < C::KK - 1; kk++) step(i, kk + 1, std::true_type(), f[kk & 1], f[(kk + 1) & 1], kk + 1, steady);
             }
         };
         // trips 0 .. n_steady-1 fetch a stage that exists and is inside: no checks in their body
         const int n_steady = (inside - k_begin < nk ? inside - k_begin : nk) - 3;
-        trip(-1, std::true_type(), std::true_type(), std::false_type());
-        int i = 0;
-        for (; i < n_steady; i++) trip(i, std::false_type(), std::true_type(), std::true_type());
-        for (; i < nk - 1; i++) trip(i, std::false_type(), std::true_type(), std::false_type());
-        trip(nk - 1, std::false_type(), std::false_type(), std::false_type());
+        // trip -1 multiplies zeros: it runs the checked trips' code, which a short segment then fetches once
+        f[1] = Frags<C>{};
+        int i = -1;
+        do {
+            trip(i, std::true_type(), std::false_type());
+            i++;
+            for (; i < n_steady; i++) trip(i, std::true_type(), std::true_type());
+        } while (i < nk - 1);
+        trip(nk - 1, std::false_type(), std::false_type());
     } else {
         // The other tiles: HELD stages in registers, requested HELD k-iterations ahead of their use (HELD = 0: the
         // two operand sets leave no room, a stage is requested right before it is parked).
         constexpr int HELD = C::STAGES_HELD, H = HELD > 0 ? HELD : 1;
         uint4 st[H][C::PIECES];
         auto fetch_stage = [&](int kit, uint4 (&dst)[C::PIECES]) {
-            if (kit < inside) {
 #pragma unroll
-                for (int q = 0; q < C::PIECES; q++) dst[q] = sf.template fetch<true>(g, kit, q);
-            } else {
-#pragma unroll
-                for (int q = 0; q < C::PIECES; q++) dst[q] = sf.template fetch<false>(g, kit, q);
-            }
+            for (int q = 0; q < C::PIECES; q++) dst[q] = sf.template fetch<true>(g, kit, q);
         };
         auto consume = [&](int s, uint4 (&src)[C::PIECES], auto steady) {
+            constexpr bool STEADY = decltype(steady)::value;
             if (HELD == 0) fetch_stage(k_begin + s, src);
+            if (!STEADY) sf.cut(g, k_begin + s, src);
 #pragma unroll
             for (int q = 0; q < C::PIECES; q++) sf.park(a_slot(s), b_slot(s), q, src[q]);
             if (HELD > 0) {
-                if (decltype(steady)::value) {
+                if (STEADY) {
 #pragma unroll
-                    for (int q = 0; q < C::PIECES; q++) src[q] = sf.template fetch<true>(g, k_begin + s + H, q);
+                    for (int q = 0; q < C::PIECES; q++) src[q] = sf.template fetch<false>(g, k_begin + s + H, q);
                 } else if (s + H < nk) {
                     fetch_stage(k_begin + s + H, src);
                 }

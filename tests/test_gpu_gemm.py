@@ -164,6 +164,32 @@ def test_unaligned_rows_keep_columns_apart():
         assert np.isnan(d[:, :8]).all() and np.array_equal(d[:, 8:], ref[:, 8:])
 
 
+@pytest.mark.parametrize("blk,dtype,variant", [((256, 256, 64), inputs.BF16, 0), ((256, 256, 64), inputs.BF16, 1), ((128, 128, 64), inputs.F16, 0),
+                                               ((64, 128, 64), inputs.BF16, 0), ((16, 128, 64), inputs.F16, 0), ((32, 64, 64), inputs.BF16, 0),
+                                               ((256, 256, 128), inputs.E4M3, 0), ((256, 256, 128), inputs.E4M3, 1), ((128, 256, 128), inputs.E4M3, 0),
+                                               ((32, 128, 128), inputs.E4M3, 0)])
+def test_unaligned_ends_of_the_matrices_integer_exact(blk, dtype, variant):
+    # matrices below 16 bytes, rows shorter than one piece, a last k-iteration of 1 .. blk_k - 1 elements whose pieces
+    # would reach beyond the end of A or B, few rows and columns of a tile; neighbours of the operands hold NaN
+    def surrounded(bits):
+        buf = np.full(bits.size + 64, 0x7F if dtype == inputs.E4M3 else 0x7FFF, dtype=bits.dtype)
+        buf[32:32 + bits.size] = bits.ravel()
+        return to_device(buf)[32:]
+
+    sizes = [(1, 1, 1), (3, 2, 1), (1, 7, 1), (2, 3, 5), (5, 1, 9), (9, 15, 7), (300, 1, 3), (1, 300, 3), (17, 5, 130), (12, 261, blk[2] + 1),
+             (33, 9, blk[2] - 1), (33, 7, 2 * blk[2] + 3), (70, 131, 3 * blk[2] - 7), (5, 37, 4 * blk[2] + 17)]
+    for M, N, K in sizes:
+        A, B = inputs.small_int_pair(M, N, K, dtype, 80)
+        ref = G.gemm_fp64(A, B, ODT[dtype])
+        for policy in (sk.SK_POLICY_DP, sk.SK_POLICY_ALL_SK):
+            r = Runner(M, N, K, policy, blk, 6, dtype, sk.SK_F32, variant=variant)
+            dA, dB = surrounded(A), surrounded(B)
+            r.run(dA, dB)
+            d = r.result()
+            r.close()
+            assert np.array_equal(d, ref), (M, N, K, policy)
+
+
 @pytest.mark.parametrize("blk,dtype", [((64, 64, 128), inputs.BF16), ((64, 64, 128), inputs.F16), ((32, 64, 64), inputs.BF16), ((32, 64, 64), inputs.F16),
                                        ((128, 128, 128), inputs.E4M3), ((64, 128, 128), inputs.E4M3), ((32, 128, 128), inputs.E4M3)])
 def test_low_tiles_integer_exact(blk, dtype):
