@@ -119,7 +119,9 @@ typedef enum { SK_SEGMENTS_ASCENDING = 0, SK_SEGMENTS_K_ALIGNED = 1 } sk_segment
 typedef enum { SK_ORDER_ROW_MAJOR = 0, SK_ORDER_GROUPED = 1 } sk_tile_order;
 
 /* Tile shape, grid and types.  A zero field means "library default": the tile
- * is then chosen from (M, N, K), grid = 256 (one workgroup per compute unit),
+ * is then chosen from (M, N, K) - where blk_m, blk_n or blk_k is given, among the
+ * tiles that fit it and have a kernel, if there are any -, grid = 256 (one
+ * workgroup per compute unit),
  * in_dtype = SK_BF16, out_dtype = in_dtype (SK_BF16 for fp8 inputs),
  * tile_order = chosen per plan (see sk_tile_order). */
 typedef struct {

@@ -207,15 +207,19 @@ extern "C" int sk_plan_estimate_us(const sk_plan_t* plan, double* microseconds) 
     return SK_OK;
 }
 
-extern "C" int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, int32_t* out_blk) {
-    if (!out_blk || M < 1 || N < 1 || K < 1 || !dtype_in_ok(in_dtype)) return SK_ERR_INVALID_ARG;
-    // Dispatcher: the tile shape whose best schedule - whole tiles in waves, the remainder wave split, or every
-    // tile split - the cost model estimates the cheapest.
+namespace {
+
+// Dispatcher: the tile shape whose best schedule - whole tiles in waves, the remainder wave split, or every
+// tile split - the cost model estimates the cheapest.  given: blk_m, blk_n, blk_k that the caller fixes (0 = free);
+// then only shapes that agree with them and, with the given blk_k, have a kernel count.  False if there is none.
+bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* given, int32_t* out_blk) {
     // 8 bits: the tiles of 128 columns only where the LDS-DMA path serves them (they are slower than the large ones
     // on the register-staged path), and not where fewer than 8 k-iterations meet a quarter of the grid or more of
     // 128 x 256 tiles: there the answer has always been one of the two large shapes, and callers build on it.
-    int n;
-    const TileCost* costs = model_costs(in_dtype, &n);
+    int n_all;
+    const TileCost* costs = model_costs(in_dtype, &n_all);
+    const bool free = !given[0] && !given[1] && !given[2];
+    int n = n_all;
     if (in_dtype == SK_FP8_E4M3) {
         const bool shallow = K < 1024 && ceil_div(M, 128) * (double)ceil_div(N, 256) >= MODEL_GRID / 4;
         if (K % 16 != 0 || N % 16 != 0 || shallow) n = 2;
@@ -224,19 +228,32 @@ extern "C" int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, in
     const int64_t most = std::numeric_limits<int32_t>::max();
     double best_t = 0;
     int best = -1;
-    for (int i = 0; i < n; i++) {
+    auto bk_of = [&](const TileCost& c) { return given[2] ? given[2] : c.bk; };
+    for (int i = 0; i < (best < 0 ? n_all : n); i++) {          // (the shapes from n on only if none before them will do)
         const TileCost& c = costs[i];
-        const int64_t ipt = ceil_div(K, c.bk), tiles_m = ceil_div(M, c.bm), tiles_n = ceil_div(N, c.bn);
+        const int bk = bk_of(c);
+        if (!free && ((given[0] && given[0] != c.bm) || (given[1] && given[1] != c.bn) || !sk_kernel_available(in_dtype, c.bm, c.bn, bk))) continue;
+        const int64_t ipt = ceil_div(K, bk), tiles_m = ceil_div(M, c.bm), tiles_n = ceil_div(N, c.bn);
         // beyond what sk_plan accepts: any answer will do, the first (largest) shape
         if (ipt > most || tiles_m > most || tiles_n > most || tiles_m * tiles_n > most || tiles_m * tiles_n > std::numeric_limits<int64_t>::max() / ipt) continue;
         const int64_t tiles = tiles_m * tiles_n;
-        double t = model_us(c, c.bk, ipt, tiles, 0, MODEL_GRID, staged);
-        t = std::min(t, model_us(c, c.bk, ipt, tiles, tiles, MODEL_GRID, staged));
-        t = std::min(t, model_us(c, c.bk, ipt, tiles, tiles % MODEL_GRID, MODEL_GRID, staged));
+        double t = model_us(c, bk, ipt, tiles, 0, MODEL_GRID, staged);
+        t = std::min(t, model_us(c, bk, ipt, tiles, tiles, MODEL_GRID, staged));
+        t = std::min(t, model_us(c, bk, ipt, tiles, tiles % MODEL_GRID, MODEL_GRID, staged));
         if (best < 0 || t < best_t) { best = i; best_t = t; }
     }
+    if (best < 0 && !free) return false;
     if (best < 0) best = 0;
-    out_blk[0] = costs[best].bm; out_blk[1] = costs[best].bn; out_blk[2] = costs[best].bk;
+    out_blk[0] = costs[best].bm; out_blk[1] = costs[best].bn; out_blk[2] = bk_of(costs[best]);
+    return true;
+}
+
+}  // namespace
+
+extern "C" int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, int32_t* out_blk) {
+    if (!out_blk || M < 1 || N < 1 || K < 1 || !dtype_in_ok(in_dtype)) return SK_ERR_INVALID_ARG;
+    const int32_t none[3] = {0, 0, 0};
+    pick_tile(M, N, K, in_dtype, none, out_blk);
     return SK_OK;
 }
 
@@ -254,8 +271,9 @@ extern "C" int sk_plan(int64_t M, int64_t N, int64_t K, int policy, const sk_con
     if (order != -1 && order != SK_ORDER_ROW_MAJOR && order != SK_ORDER_GROUPED) return SK_ERR_INVALID_ARG;
     int32_t blk[3] = {c.blk_m, c.blk_n, c.blk_k};
     if (!blk[0] || !blk[1] || !blk[2]) {
+        // the rest of a partly given shape: from a shape that has a kernel with the given fields, else from the default
         int32_t def[3];
-        sk_default_tile(M, N, K, in_dtype, def);
+        if (!pick_tile(M, N, K, in_dtype, blk, def)) sk_default_tile(M, N, K, in_dtype, def);
         for (int i = 0; i < 3; i++) if (!blk[i]) blk[i] = def[i];
     }
     const int grid = c.grid ? c.grid : 256;

@@ -139,6 +139,31 @@ def test_plan_defaults_and_errors():
     assert sk.sk_status_str(sk.SK_ERR_WORKSPACE).startswith("workspace")
 
 
+def test_partly_given_tile_is_completed_to_one_with_a_kernel():
+    # every field value that some kernel of the type has: the rest comes from a shape that fits it, whatever the size
+    shapes = {sk.SK_BF16: [(256, 256, 64), (256, 256, 32), (256, 128, 64), (128, 128, 64), (128, 128, 32), (64, 128, 64), (64, 64, 128),
+                           (32, 128, 64), (32, 64, 64), (16, 128, 64)],
+              sk.SK_FP8_E4M3: [(256, 256, 128), (128, 256, 128), (128, 128, 128), (64, 128, 128), (32, 128, 128)]}
+    shapes[sk.SK_F16] = shapes[sk.SK_BF16]
+    rng = random.Random(8)
+    sizes = [(1, 1, 1), (16, 3712, 1648), (122, 78, 557), (1760, 176, 4208), (4976, 6896, 352), (5237, 3683, 134), (8192, 8192, 8192)]
+    sizes += [tuple(int(2 ** rng.uniform(0, 13)) for _ in range(3)) for _ in range(60)]
+    for dtype, known in shapes.items():
+        for M, N, K in sizes:
+            for mask in range(1, 7):
+                for given_blk in {tuple(v if mask >> i & 1 else 0 for i, v in enumerate(t)) for t in known}:
+                    plan = sk.sk_plan(M, N, K, sk.SK_POLICY_ALL_SK, given_blk, 0, dtype)
+                    info = sk.sk_plan_info(plan)
+                    sk.sk_plan_destroy(plan)
+                    blk = tuple(info["blk_" + c] for c in "mnk")
+                    assert info["has_kernel"] and all(g in (0, b) for g, b in zip(given_blk, blk)), (dtype, M, N, K, given_blk, blk)
+    # a value no kernel has is kept for planning, as any tile shape is
+    plan = sk.sk_plan(300, 300, 300, sk.SK_POLICY_DP, (48, 0, 0))
+    info = sk.sk_plan_info(plan)
+    sk.sk_plan_destroy(plan)
+    assert info["blk_m"] == 48 and not info["has_kernel"]
+
+
 def test_gemm_rejects_bad_arguments_without_touching_the_gpu():
     p = sk.sk_plan(512, 512, 512, sk.SK_POLICY_ALL_SK, (128, 128, 32))
     assert sk.sk_gemm_status(0, 256, 512, p) == sk.SK_ERR_INVALID_ARG
