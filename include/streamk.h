@@ -343,10 +343,9 @@ int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, int32_t* out_
  * the policies of one problem when no tuning record knows it (the selector's
  * fall-back when the Bloom filters of Sec. 4.2 return no candidate), not for
  * predicting times.  microseconds: host double.
- * fp8 tiles are modelled as the 16-bit shape of the same byte footprint with half
- * the blk_k (same bytes and same matrix-core time per K-iteration).
  * Errors: INVALID_ARG (NULL), UNSUPPORTED (a tile shape the model has no constants
- * for: anything but the shapes sk_default_tile picks from). */
+ * for: anything but the shapes sk_default_tile picks from - the tiles of at least 128
+ * columns, with 8-bit inputs of at least 128 rows, at any blk_k - and 8-bit 256 x 128). */
 int sk_plan_estimate_us(const sk_plan_t* plan, double* microseconds);
 
 /* ---- Bloom-filter policy selector (Sec. 4.2) --------------------------------

@@ -151,13 +151,16 @@ const TileCost* model_costs(int in_dtype, int* count) {
     *count = fp8 ? N_COSTS8 : N_COSTS16;
     return fp8 ? tile_costs8 : tile_costs16;
 }
-// The constants of a tile shape: the entry with its blk_k, or - for 16 bits, where blk_k 32 and 64 share the rate -
-// one with at least as deep a k-iteration as the shape's.
+// The constants of a tile shape: the entry with its blk_m and blk_n.  A tile's rate hardly depends on blk_k, so the
+// tiles of 128 columns (8 bits: of 128 rows) and more answer for any; the smaller ones for their own and, where that
+// is 64, for less.  8 bits: 256 x 128, which has no kernel, as 128 x 256.
 const TileCost* model_constants(int bm, int bn, int bk, int in_dtype) {
     int n;
     const TileCost* t = model_costs(in_dtype, &n);
+    const bool fp8 = in_dtype == SK_FP8_E4M3;
+    if (fp8 && bm == 256 && bn == 128) std::swap(bm, bn);
     for (int i = 0; i < n; i++)
-        if (t[i].bm == bm && t[i].bn == bn && (t[i].bk == bk || (t[i].bk == 64 && bk < 64))) return &t[i];
+        if (t[i].bm == bm && t[i].bn == bn && ((fp8 ? bm : bn) >= 128 || t[i].bk == bk || (t[i].bk == 64 && bk < 64))) return &t[i];
     return nullptr;
 }
 

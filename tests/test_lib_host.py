@@ -403,6 +403,22 @@ def test_plan_estimate_properties():
     sk.sk_plan_destroy(p)
 
 
+def test_plan_estimate_of_every_modelled_tile():
+    any_k = (16, 32, 64, 128, 256)
+    tiles16 = [(256, 256, any_k), (256, 128, any_k), (128, 128, any_k), (64, 128, any_k), (32, 128, any_k), (16, 128, any_k),
+               (64, 64, (128,)), (32, 64, (64, 32, 16))]
+    tiles8 = [(256, 256, any_k), (256, 128, any_k), (128, 256, any_k), (128, 128, any_k), (64, 128, (128,)), (32, 128, (128,))]
+    for dtype, tiles in ((sk.SK_BF16, tiles16), (sk.SK_F16, tiles16), (sk.SK_FP8_E4M3, tiles8)):
+        for bm, bn, depths in tiles:
+            for bk in depths:
+                for policy in (sk.SK_POLICY_DP, sk.SK_POLICY_ALL_SK):
+                    plan = sk.sk_plan(1000, 2000, 4096, policy, (bm, bn, bk), 256, dtype)
+                    try:
+                        assert 1.0 < sk.sk_plan_estimate_us(plan) < 1e4, (dtype, bm, bn, bk, policy)
+                    finally:
+                        sk.sk_plan_destroy(plan)
+
+
 def test_seeded_suites_are_reproducible_and_in_range():
     from paper_2408_11417_amd import inputs
     a, b = inputs.sweep_shapes(500, 4), inputs.sweep_shapes(500, 4)
