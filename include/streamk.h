@@ -120,8 +120,9 @@ typedef enum { SK_ORDER_ROW_MAJOR = 0, SK_ORDER_GROUPED = 1 } sk_tile_order;
 
 /* Tile shape, grid and types.  A zero field means "library default": the tile
  * is then chosen from (M, N, K) - where blk_m, blk_n or blk_k is given, among the
- * tiles that fit it and have a kernel, if there are any -, grid = 256 (one
- * workgroup per compute unit),
+ * tiles that fit it and have a kernel, if there are any; on a grid of more than
+ * 256 workgroups a tile that sk_gemm can run there goes before a somewhat faster
+ * one that it would refuse -, grid = 256 (one workgroup per compute unit),
  * in_dtype = SK_BF16, out_dtype = in_dtype (SK_BF16 for fp8 inputs),
  * tile_order = chosen per plan (see sk_tile_order). */
 typedef struct {
@@ -333,7 +334,7 @@ size_t sk_mfma_peak_operand_bytes(void);
 int sk_mfma_peak_launch(int in_dtype, const void* operands, float* sink, int workgroups, int iters, void* stream, double* flops);
 
 /* The tile shape the library picks for (M, N, K, in_dtype) when sk_config leaves
- * it zero.  out_blk: host int32[3] = blk_m, blk_n, blk_k. */
+ * tile and grid zero.  out_blk: host int32[3] = blk_m, blk_n, blk_k. */
 int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, int32_t* out_blk);
 
 /* The dispatcher's cost model applied to this plan: a rough time estimate in

@@ -23,6 +23,18 @@ int batches_of(int policy) {
     }
 }
 
+// Tiles of a policy's Stream-K region (Sec. 3.2, Sec. 4.1).
+int64_t sk_tile_count(int policy, int64_t tiles, int64_t grid) {
+    const int b = batches_of(policy);
+    if (b < 0) return tiles;
+    if (b == 0) return 0;
+    return std::min(tiles % grid + (int64_t)(b - 1) * grid, tiles);
+}
+// Is a tile split, i.e. does some workgroup's range end strictly inside one?
+bool splits_tiles(int64_t sk_iters, int64_t iters_per_wg, int64_t iters_per_tile) {
+    return sk_iters > iters_per_wg && iters_per_wg % iters_per_tile != 0;
+}
+
 bool dtype_in_ok(int d) { return d == SK_F16 || d == SK_BF16 || d == SK_FP8_E4M3; }
 bool dtype_out_ok(int d) { return d == SK_F16 || d == SK_BF16 || d == SK_F32; }
 
@@ -93,13 +105,14 @@ void expand_wg(const sk_plan_header& h, int x, std::vector<sk_segment>* out, sk_
 // fit optimises the dispatcher's pick of tile and policy, not the predicted times).  Time of the pick over the
 // fastest of all tiles and schedules, geometric mean: 16 bits 1.016 / 1.028 / 1.027 on the three sets (the six
 // shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.009 / 1.007 / 1.015 (two shapes: 1.59 / 2.29 / 2.44).
-struct TileCost { int bm, bn, bk; double tflops, tile_us; };
-const TileCost tile_costs16[] = {{256, 256, 64, 1590., 10.40}, {256, 128, 64, 1307., 5.61}, {128, 128, 64, 1062., 4.33},
-                                 {64, 128, 64, 745., 2.91}, {32, 128, 64, 478., 2.73}, {16, 128, 64, 287., 2.68},
-                                 {64, 64, 128, 500., 3.08}, {32, 64, 64, 364., 2.76}};
+// (per_cu: workgroups of the tile's kernel that fit a compute unit side by side - 160 KB of LDS)
+struct TileCost { int bm, bn, bk; double tflops, tile_us; int per_cu; };
+const TileCost tile_costs16[] = {{256, 256, 64, 1590., 10.40, 1}, {256, 128, 64, 1307., 5.61, 1}, {128, 128, 64, 1062., 4.33, 1},
+                                 {64, 128, 64, 745., 2.91, 1}, {32, 128, 64, 478., 2.73, 2}, {16, 128, 64, 287., 2.68, 2},
+                                 {64, 64, 128, 500., 3.08, 1}, {32, 64, 64, 364., 2.76, 3}};
 // (the large 8-bit tile moves the bytes of the large 16-bit one with twice the k at twice the rate: its constants)
-const TileCost tile_costs8[] = {{256, 256, 128, 3180., 10.40}, {128, 256, 128, 2821., 4.75}, {128, 128, 128, 1919., 2.61},
-                                {64, 128, 128, 1467., 2.45},  {32, 128, 128, 915., 2.48}};
+const TileCost tile_costs8[] = {{256, 256, 128, 3180., 10.40, 1}, {128, 256, 128, 2821., 4.75, 1}, {128, 128, 128, 1919., 2.61, 1},
+                                {64, 128, 128, 1467., 2.45, 1},  {32, 128, 128, 915., 2.48, 2}};
 constexpr int N_COSTS16 = 8, N_COSTS8 = 5;
 constexpr int MODEL_GRID = 256;
 constexpr double MODEL_LEVEL_US = 1.68, MODEL_FETCH_BYTES_PER_US = 107e3, MODEL_TRAFFIC_BYTES_PER_US = 6.953e6;
@@ -215,7 +228,10 @@ namespace {
 // Dispatcher: the tile shape whose best schedule - whole tiles in waves, the remainder wave split, or every
 // tile split - the cost model estimates the cheapest.  given: blk_m, blk_n, blk_k that the caller fixes (0 = free);
 // then only shapes that agree with them and, with the given blk_k, have a kernel count.  False if there is none.
-bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* given, int32_t* out_blk) {
+// policy, grid: those of the plan the tile is for.  On more workgroups than CUs a plan that splits tiles can only be
+// launched if several workgroups fit a CU, so there a shape that can run goes before one that cannot, unless the
+// model has it 1.4 times slower or more (a plan may also be meant for the atomic fix-up, which runs any grid).
+bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* given, int policy, int64_t grid, int32_t* out_blk) {
     // 8 bits: the tiles of 128 columns only where the LDS-DMA path serves them (they are slower than the large ones
     // on the register-staged path), and not where fewer than 8 k-iterations meet a quarter of the grid or more of
     // 128 x 256 tiles: there the answer has always been one of the two large shapes, and callers build on it.
@@ -229,8 +245,8 @@ bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* giv
     }
     const bool staged = model_staged(N, K, in_dtype);
     const int64_t most = std::numeric_limits<int32_t>::max();
-    double best_t = 0;
-    int best = -1;
+    double best_t = 0, runs_t = 0;
+    int best = -1, runs = -1;
     auto bk_of = [&](const TileCost& c) { return given[2] ? given[2] : c.bk; };
     for (int i = 0; i < (best < 0 ? n_all : n); i++) {          // (the shapes from n on only if none before them will do)
         const TileCost& c = costs[i];
@@ -244,9 +260,12 @@ bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* giv
         t = std::min(t, model_us(c, bk, ipt, tiles, tiles, MODEL_GRID, staged));
         t = std::min(t, model_us(c, bk, ipt, tiles, tiles % MODEL_GRID, MODEL_GRID, staged));
         if (best < 0 || t < best_t) { best = i; best_t = t; }
+        const int64_t iters = sk_tile_count(policy, tiles, grid) * ipt;
+        if ((grid <= MODEL_GRID * c.per_cu || !splits_tiles(iters, ceil_div(iters, grid), ipt)) && (runs < 0 || t < runs_t)) { runs = i; runs_t = t; }
     }
     if (best < 0 && !free) return false;
     if (best < 0) best = 0;
+    else if (runs >= 0 && runs_t < 1.4 * best_t) best = runs;
     out_blk[0] = costs[best].bm; out_blk[1] = costs[best].bn; out_blk[2] = bk_of(costs[best]);
     return true;
 }
@@ -256,7 +275,7 @@ bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* giv
 extern "C" int sk_default_tile(int64_t M, int64_t N, int64_t K, int in_dtype, int32_t* out_blk) {
     if (!out_blk || M < 1 || N < 1 || K < 1 || !dtype_in_ok(in_dtype)) return SK_ERR_INVALID_ARG;
     const int32_t none[3] = {0, 0, 0};
-    pick_tile(M, N, K, in_dtype, none, out_blk);
+    pick_tile(M, N, K, in_dtype, none, SK_POLICY_DP, MODEL_GRID, out_blk);
     return SK_OK;
 }
 
@@ -273,13 +292,13 @@ extern "C" int sk_plan(int64_t M, int64_t N, int64_t K, int policy, const sk_con
     int order = c.tile_order ? c.tile_order - 1 : -1;   // -1: decided below, once the split is known
     if (order != -1 && order != SK_ORDER_ROW_MAJOR && order != SK_ORDER_GROUPED) return SK_ERR_INVALID_ARG;
     int32_t blk[3] = {c.blk_m, c.blk_n, c.blk_k};
+    const int grid = c.grid ? c.grid : 256;
     if (!blk[0] || !blk[1] || !blk[2]) {
         // the rest of a partly given shape: from a shape that has a kernel with the given fields, else from the default
         int32_t def[3];
-        if (!pick_tile(M, N, K, in_dtype, blk, def)) sk_default_tile(M, N, K, in_dtype, def);
+        if (!pick_tile(M, N, K, in_dtype, blk, policy, grid, def)) sk_default_tile(M, N, K, in_dtype, def);
         for (int i = 0; i < 3; i++) if (!blk[i]) blk[i] = def[i];
     }
-    const int grid = c.grid ? c.grid : 256;
 
     sk_plan_header h{};
     h.M = M; h.N = N; h.K = K; h.policy = policy;
@@ -295,15 +314,7 @@ extern "C" int sk_plan(int64_t M, int64_t N, int64_t K, int policy, const sk_con
     h.tiles_m = (int32_t)tiles_m; h.tiles_n = (int32_t)tiles_n; h.tiles = (int32_t)tiles;
     h.iters_per_tile = (int32_t)ipt;
     h.total_iters = tiles * ipt;
-    // Stream-K / data-parallel split (Sec. 3.2, Sec. 4.1)
-    const int b = batches_of(policy);
-    int64_t sk_tiles;
-    if (b < 0) sk_tiles = tiles;
-    else if (b == 0) sk_tiles = 0;
-    else {
-        sk_tiles = tiles % grid + (int64_t)(b - 1) * grid;
-        if (sk_tiles > tiles) sk_tiles = tiles;
-    }
+    const int64_t sk_tiles = sk_tile_count(policy, tiles, grid);     // Stream-K / data-parallel split
     // Default tile order: the one under which the tiles that an XCD's workgroups hold at the same
     // time touch fewer operand rows and columns (A row-blocks x blk_m + B column-blocks x blk_n,
     // averaged over the XCDs): that is what the XCD's L2 has to keep per k-iteration.  The
@@ -361,8 +372,7 @@ extern "C" int sk_plan(int64_t M, int64_t N, int64_t K, int policy, const sk_con
     sk_plan_t* p = new (std::nothrow) sk_plan_t;
     if (!p) return SK_ERR_NOMEM;
     p->h = h;
-    // a tile is split iff some workgroup range ends strictly inside it
-    p->needs_fixup = (h.sk_iters > ipw && ipw % ipt != 0) ? 1 : 0;
+    p->needs_fixup = splits_tiles(h.sk_iters, ipw, ipt) ? 1 : 0;
     *out = p;
     return SK_OK;
 }

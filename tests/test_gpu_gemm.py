@@ -210,6 +210,13 @@ def test_low_tiles_integer_exact(blk, dtype):
     _run_and_compare(A, B, dtype, sk.SK_POLICY_SK2_DP, blk, grid=8, launches=2)
 
 
+@pytest.mark.parametrize("shape,grid", [((57, 14784, 1920), 304), ((496, 256, 11152), 512), ((6528, 96, 1904), 512)])
+def test_default_tile_on_a_larger_grid(shape, grid):
+    M, N, K = shape
+    A, B = inputs.small_int_pair(M, N, K, inputs.BF16, 81, lo=-1, hi=1)
+    _run_and_compare(A, B, inputs.BF16, sk.SK_POLICY_ALL_SK, None, grid=grid, out_dtype=sk.SK_F32, ref=G.gemm_fp64(A, B, G.BF16), exact=True)
+
+
 @pytest.mark.parametrize("shape,blk", [((64, 256, 52000), (32, 64, 64)), ((96, 512, 16384), (32, 64, 64)), ((112, 400, 30016), (64, 128, 64)),
                                        ((33, 777, 40000), (16, 128, 64))])
 def test_workgroups_sorted_by_k_slice_integer_exact(shape, blk):

@@ -164,6 +164,17 @@ def test_partly_given_tile_is_completed_to_one_with_a_kernel():
     assert info["blk_m"] == 48 and not info["has_kernel"]
 
 
+@pytest.mark.parametrize("M,N,K,policy,grid", [(57, 14784, 1920, 6, 304), (57, 14784, 1920, 6, 512), (496, 256, 11152, 6, 512), (6528, 96, 1904, 6, 512),
+                                               (3296, 11504, 656, 6, 304), (4656, 3520, 176, 6, 512), (2368, 5072, 96, 6, 768)])
+def test_default_tile_on_a_larger_grid_can_be_launched(M, N, K, policy, grid):
+    # more workgroups than CUs: either no tile is split, or as many workgroups as that takes fit a CU (160 KB of LDS)
+    plan = sk.sk_plan(M, N, K, policy, None, grid, sk.SK_BF16)
+    info, kernel = sk.sk_plan_info(plan), sk.sk_plan_kernel_info(plan)
+    sk.sk_plan_destroy(plan)
+    split = info["sk_iters"] > info["iters_per_wg"] and info["iters_per_wg"] % info["iters_per_tile"] != 0
+    assert not split or grid <= 256 * min(160 * 1024 // kernel["lds_bytes"], 2048 // kernel["threads"]), (info, kernel)
+
+
 def test_gemm_rejects_bad_arguments_without_touching_the_gpu():
     p = sk.sk_plan(512, 512, 512, sk.SK_POLICY_ALL_SK, (128, 128, 32))
     assert sk.sk_gemm_status(0, 256, 512, p) == sk.SK_ERR_INVALID_ARG
