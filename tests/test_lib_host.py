@@ -25,6 +25,25 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, name), name
 
 
+def test_package_shows_the_binding_as_it_stands(monkeypatch):
+    import importlib
+    import sys
+    assert sk.SK_OK == 0 and sk.sk_plan is sk.binding.sk_plan
+    monkeypatch.setattr(sk.binding, "sk_plan", "replaced")
+    assert sk.sk_plan == "replaced"
+    monkeypatch.setattr(sk.binding, "a_new_name", 7, raising=False)
+    assert sk.a_new_name == 7
+    monkeypatch.undo()
+    assert sk.sk_plan is sk.binding.sk_plan and not hasattr(sk, "a_new_name")
+    # a binding loaded anew, as after a rebuild of the library
+    name, loaded = sk.__name__ + ".binding", sk.binding
+    monkeypatch.delitem(sys.modules, name)
+    monkeypatch.setattr(sk, "binding", importlib.import_module(name))
+    assert sys.modules[name] is not loaded and sk.sk_plan is sys.modules[name].sk_plan
+    with pytest.raises(AttributeError):
+        sk.no_such_name
+
+
 def test_public_header_is_plain_c_and_links(tmp_path):
     import shutil
     import subprocess
