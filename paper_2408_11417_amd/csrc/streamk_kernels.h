@@ -170,6 +170,13 @@ struct Cfg {
     // vector stores one wave issues in the epilogue of an unsplit interior tile with 16-bit output (an fp32
     // output issues more): what may still be in flight when the next tile's first stage is waited for
     static constexpr int EPILOGUE_STORES = MI * NI * (MF == 32 ? ACC / 8 : ACC / 4);
+    // 16-byte stores from the lanes as the blocks lie, 32 rows of 32 bytes per instruction, instead of store_blocks'
+    // exchange, where that costs more than the better pattern gives: the lowest tiles (bound by the length of the chain
+    // at the end of the kernel: 23 x 4096 x 8128 to fp32 16.5 us, 16.6 with it) and the four-wave 256 x 256 kernels
+    // (nothing runs beside a wave's exchange, 500 instructions or 1 us, and they only take tiles of 48 k-iterations and
+    // more: 3840 x 4224 x 4096 109.4 us, 110.0 with it, 4096 x 4032 x 3072 83.4 / 84.9, 8 bits 3840 x 4224 x 8192
+    // 100.9 / 104.1, 8192^3 no difference).  The other four-wave kernels gain from it at every depth tried.
+    static constexpr bool DIRECT_STORES = BM <= 32 || (FINE && NW == 4 && BM == 256 && BN == 256);
     static_assert(WTM % MF == 0 && WTN % MF == 0 && BK % KM == 0, "tile does not divide");
     static_assert(CPA == 4 || CPA == 8 || CPA == 16, "A swizzle assumes 64/128/256-byte rows");
     static_assert(CPB >= 8, "B swizzle assumes rows of at least 128 bytes");
@@ -1066,9 +1073,7 @@ __device__ __forceinline__ void store_blocks(const GemmArgs& g, int row, int col
             }
         }
         const int lane = threadIdx.x % 64;
-        if constexpr (C::BM <= 32) {
-            // the lowest tiles are bound by the length of the chain at the end of the kernel, not by the store rate: no
-            // exchange (23 x 4096 x 8128 to fp32: 16.6 us with it, 16.5 without)
+        if constexpr (C::DIRECT_STORES) {
 #pragma unroll
             for (int i = 0; i < G; i++) {
                 const int col = col0 - 4 * (lane / 32) + COLS * (lane / 32 + 2 * i);
