@@ -254,8 +254,8 @@ __device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
     const int q = (hw % 8) * (g.grid / 8) + hw / 8;
     if (g.xcd_remap == 1) return q;
     // workgroups ceil(t * grid / tiles) .. ceil((t + 1) * grid / tiles) - 1 share tile t, about: `each` or
-    // one more; the tiles with one more are t = floor(i * tiles / extra), i = 0 .. extra - 1.
-    const int each = (int)fast_div((uint32_t)g.grid, g.div_tiles), extra = g.grid - each * g.tiles;
+    // one more; the tiles with one more are t = floor(i * tiles / extra), i = 0 .. extra - 1, extra = grid mod tiles.
+    const int each = (int)fast_div((uint32_t)g.grid, g.div_tiles);
     int t, j;
     if (q < each * g.tiles) {
         j = (int)fast_div((uint32_t)q, g.div_tiles);

@@ -183,7 +183,7 @@ const TileCost* model_constants(int bm, int bn, int bk, int in_dtype) {
 //    inside one L2 (64 x 128 tiles of 8 workgroups, 512 x 512 x 8192: 14.4 us against 18.3 with either other map);
 //  - with at least 4 workgroups per tile each XCD reads the whole K range of its few tiles, so operand blocks
 //    shared with other XCDs' tiles are fetched once per XCD; sorted by K slice (2) they are fetched once.
-//    Where that saves 20 MB or more it pays for the longer exchange: 3 % at 20 - 40 MB, 8 - 12 % above, up to
+//    Where that saves 20 MB or more in all it pays for the longer exchange: 3 % at 20 - 40 MB, 8 - 12 % above, up to
 //    1.5x (384 x 240 x 52832, 64 x 128 tiles: 48.1 -> 31.6 us); below 20 MB it loses 3 - 9 %;
 //  - a single row of low 16-bit tiles over a large B streams B once and shares only the small A: the hardware
 //    order (0), neighbouring column blocks on different XCDs, gains 2 - 6 % from 48 MB of B on (32 rows and
@@ -194,7 +194,7 @@ int choose_remap(const sk_plan_header& h) {
         const double b_bytes = (double)h.K * (double)h.N * es;
         if (b_bytes >= (h.blk_m <= 32 ? 16e6 : 48e6)) return 0;
     }
-    if (h.dp_tiles == 0 && h.tiles <= h.grid && h.grid <= 4096 && 4ll * h.iters_per_wg <= h.iters_per_tile) {
+    if (h.dp_tiles == 0 && h.tiles <= h.grid && h.grid <= 4096 && h.grid % 8 == 0 && 4ll * h.iters_per_wg <= h.iters_per_tile) {
         const double per_xcd = h.grid / 8.0 * h.iters_per_wg / h.iters_per_tile;   // tiles of one XCD under the contiguous map
         const double all = (double)h.tiles_m * h.blk_m + (double)h.tiles_n * h.blk_n;      // operand rows and columns
         double fetched;

@@ -194,6 +194,13 @@ def test_default_tile_on_a_larger_grid_can_be_launched(M, N, K, policy, grid):
     assert not split or grid <= 256 * min(160 * 1024 // kernel["lds_bytes"], 2048 // kernel["threads"]), (info, kernel)
 
 
+def test_workgroup_numbering_by_k_slice_only_where_the_kernel_does_it():
+    for grid, remap in ((256, 2), (248, 2), (250, 1), (255, 1)):
+        plan = sk.sk_plan(384, 240, 52832, sk.SK_POLICY_ALL_SK, (64, 128, 64), grid)
+        assert sk.sk_plan_info(plan)["xcd_remap"] == remap, grid
+        sk.sk_plan_destroy(plan)
+
+
 def test_gemm_rejects_bad_arguments_without_touching_the_gpu():
     p = sk.sk_plan(512, 512, 512, sk.SK_POLICY_ALL_SK, (128, 128, 32))
     assert sk.sk_gemm_status(0, 256, 512, p) == sk.SK_ERR_INVALID_ARG
