@@ -104,7 +104,7 @@ void expand_wg(const sk_plan_header& h, int x, std::vector<sk_segment>* out, sk_
 // MI355X; sizes 400 .. 499 are the selector's held-out split and stay out of the fit (fit_tile_model.py; the
 // fit optimises the dispatcher's pick of tile and policy, not the predicted times).  Time of the pick over the
 // fastest of all tiles and schedules, geometric mean: 16 bits 1.016 / 1.028 / 1.027 on the three sets (the six
-// shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.009 / 1.007 / 1.015 (two shapes: 1.59 / 2.29 / 2.44).
+// shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.011 / 1.007 / 1.015 (two shapes: 1.59 / 2.29 / 2.44).
 // (per_cu: workgroups of the tile's kernel that fit a compute unit side by side - 160 KB of LDS)
 struct TileCost { int bm, bn, bk; double tflops, tile_us; int per_cu; };
 const TileCost tile_costs16[] = {{256, 256, 64, 1590., 10.40, 1}, {256, 128, 64, 1307., 5.61, 1}, {128, 128, 64, 1062., 4.33, 1},
@@ -233,16 +233,11 @@ namespace {
 // model has it 1.4 times slower or more (a plan may also be meant for the atomic fix-up, which runs any grid).
 bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* given, int policy, int64_t grid, int32_t* out_blk) {
     // 8 bits: the tiles of 128 columns only where the LDS-DMA path serves them (they are slower than the large ones
-    // on the register-staged path), and not where fewer than 8 k-iterations meet a quarter of the grid or more of
-    // 128 x 256 tiles: there the answer has always been one of the two large shapes, and callers build on it.
+    // on the register-staged path).
     int n_all;
     const TileCost* costs = model_costs(in_dtype, &n_all);
     const bool free = !given[0] && !given[1] && !given[2];
-    int n = n_all;
-    if (in_dtype == SK_FP8_E4M3) {
-        const bool shallow = K < 1024 && ceil_div(M, 128) * (double)ceil_div(N, 256) >= MODEL_GRID / 4;
-        if (K % 16 != 0 || N % 16 != 0 || shallow) n = 2;
-    }
+    const int n = in_dtype == SK_FP8_E4M3 && (K % 16 != 0 || N % 16 != 0) ? 2 : n_all;
     const bool staged = model_staged(N, K, in_dtype);
     const int64_t most = std::numeric_limits<int32_t>::max();
     double best_t = 0, runs_t = 0;

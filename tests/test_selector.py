@@ -137,15 +137,21 @@ def test_fit_tool_formula_is_the_library_cost_model():
         blk = sk.sk_default_tile(M, N, K, sk.SK_BF16)
         est = {t: F.predict(F.LIBRARY, t, M, N, K) for t in F.LIBRARY["tflops"]}
         assert tuple(blk[:2]) == pick or abs(est[tuple(blk[:2])] - est[pick]) <= 1e-9 * est[pick], (M, N, K, blk, pick)
-    # fp8: a modelled pick between the two 8-bit shapes, and an estimate for every policy
-    for M, N, K in [(8192, 8192, 8192), (300, 700, 4096), (2048, 1024, 512)]:
-        blk = sk.sk_default_tile(M, N, K, sk.SK_FP8_E4M3)
-        assert tuple(blk) in ((256, 256, 128), (128, 256, 128))
-        plan = sk.sk_plan(M, N, K, sk.SK_POLICY_ALL_SK, None, 256, sk.SK_FP8_E4M3)
+    # fp8: the cheapest of the five 8-bit shapes by the library's own estimate (best of whole tiles, the remainder wave
+    # split and everything split), for few and many k-iterations and tiles; and an estimate for every policy
+    def estimate(M, N, K, policy, blk):
+        plan = sk.sk_plan(M, N, K, policy, blk, 256, sk.SK_FP8_E4M3)
         try:
-            assert sk.sk_plan_estimate_us(plan) > 0
+            return sk.sk_plan_estimate_us(plan)
         finally:
             sk.sk_plan_destroy(plan)
+    for M, N, K in [(8192, 8192, 8192), (2048, 1024, 512), (1968, 1024, 128), (2032, 1024, 1040), (1920, 1024, 512), (4512, 288, 656),
+                    (64, 8192, 8192), (10640, 64, 96)] + inputs.sweep_shapes(100, 4):
+        blk = tuple(sk.sk_default_tile(M, N, K, sk.SK_FP8_E4M3))
+        cost = {t: min(estimate(M, N, K, p, t) for p in (sk.SK_POLICY_DP, sk.SK_POLICY_SK1_DP, sk.SK_POLICY_ALL_SK))
+                for t in ((256, 256, 128), (128, 256, 128), (128, 128, 128), (64, 128, 128), (32, 128, 128))}
+        assert cost[blk] <= min(cost.values()) * (1 + 1e-9), (M, N, K, blk, cost)
+    assert tuple(sk.sk_default_tile(300, 700, 4096, sk.SK_FP8_E4M3)) in ((256, 256, 128), (128, 256, 128))      # N off the 16-byte grid
     assert tuple(sk.sk_default_tile(8192, 8192, 8192, sk.SK_FP8_E4M3)) == (256, 256, 128)
 
 
