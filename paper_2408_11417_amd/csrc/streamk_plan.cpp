@@ -130,8 +130,10 @@ int64_t model_contributors(int64_t workgroups, int64_t ipt, int64_t ipw) {
 }
 
 // Rows of A or B off the 16-byte grid: the register-staged kernels, whose first two stages arrive one after the other and
-// whose D leaves element by element.  Counting 1.6 times the microseconds outside the loop takes the picks on 69 odd
-// sizes from 1.050 of the fastest (worst 1.52) to 1.035 (1.21); scaling the loop as well did not help.
+// whose D leaves element by element.  Counting 1.6 times the microseconds outside the loop took the 16-bit picks on 69 odd
+// sizes from 1.050 of the fastest to 1.035; scaling the loop as well did not help.  With the kernels as they are, time of
+// the picked tile and schedule over the fastest of all on 69 odd sizes, 40 of at most 128 rows and 40 of short K: 16 bits
+// 1.023 / 1.072 / 1.005, 8 bits 1.016 / 1.071 / 1.006 (8-bit problems on the two large shapes only: 1.88 / 2.52 / 1.52).
 constexpr double MODEL_STAGED_TILE = 1.6;
 bool model_staged(int64_t N, int64_t K, int in_dtype) {
     const int piece = in_dtype == SK_FP8_E4M3 ? 16 : 8;
@@ -232,18 +234,15 @@ namespace {
 // launched if several workgroups fit a CU, so there a shape that can run goes before one that cannot, unless the
 // model has it 1.4 times slower or more (a plan may also be meant for the atomic fix-up, which runs any grid).
 bool pick_tile(int64_t M, int64_t N, int64_t K, int in_dtype, const int32_t* given, int policy, int64_t grid, int32_t* out_blk) {
-    // 8 bits: the tiles of 128 columns only where the LDS-DMA path serves them (they are slower than the large ones
-    // on the register-staged path).
-    int n_all;
-    const TileCost* costs = model_costs(in_dtype, &n_all);
+    int n;
+    const TileCost* costs = model_costs(in_dtype, &n);
     const bool free = !given[0] && !given[1] && !given[2];
-    const int n = in_dtype == SK_FP8_E4M3 && (K % 16 != 0 || N % 16 != 0) ? 2 : n_all;
     const bool staged = model_staged(N, K, in_dtype);
     const int64_t most = std::numeric_limits<int32_t>::max();
     double best_t = 0, runs_t = 0;
     int best = -1, runs = -1;
     auto bk_of = [&](const TileCost& c) { return given[2] ? given[2] : c.bk; };
-    for (int i = 0; i < (best < 0 ? n_all : n); i++) {          // (the shapes from n on only if none before them will do)
+    for (int i = 0; i < n; i++) {
         const TileCost& c = costs[i];
         const int bk = bk_of(c);
         if (!free && ((given[0] && given[0] != c.bm) || (given[1] && given[1] != c.bn) || !sk_kernel_available(in_dtype, c.bm, c.bn, bk))) continue;

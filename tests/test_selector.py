@@ -146,12 +146,11 @@ def test_fit_tool_formula_is_the_library_cost_model():
         finally:
             sk.sk_plan_destroy(plan)
     for M, N, K in [(8192, 8192, 8192), (2048, 1024, 512), (1968, 1024, 128), (2032, 1024, 1040), (1920, 1024, 512), (4512, 288, 656),
-                    (64, 8192, 8192), (10640, 64, 96)] + inputs.sweep_shapes(100, 4):
+                    (64, 8192, 8192), (10640, 64, 96), (300, 700, 4096), (33, 1438, 1155), (3841, 4225, 4097)] + inputs.sweep_shapes(100, 4):
         blk = tuple(sk.sk_default_tile(M, N, K, sk.SK_FP8_E4M3))
         cost = {t: min(estimate(M, N, K, p, t) for p in (sk.SK_POLICY_DP, sk.SK_POLICY_SK1_DP, sk.SK_POLICY_ALL_SK))
                 for t in ((256, 256, 128), (128, 256, 128), (128, 128, 128), (64, 128, 128), (32, 128, 128))}
         assert cost[blk] <= min(cost.values()) * (1 + 1e-9), (M, N, K, blk, cost)
-    assert tuple(sk.sk_default_tile(300, 700, 4096, sk.SK_FP8_E4M3)) in ((256, 256, 128), (128, 256, 128))      # N off the 16-byte grid
     assert tuple(sk.sk_default_tile(8192, 8192, 8192, sk.SK_FP8_E4M3)) == (256, 256, 128)
 
 
