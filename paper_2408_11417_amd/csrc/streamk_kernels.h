@@ -157,8 +157,9 @@ struct Cfg {
     // queue up (needs the two operand sets of PIN_ORDER).
     static constexpr bool FINE = FINE_ != 0;
     // the tiles of at most 64 rows (HBM-bound shapes) and the eight-wave 128 x 128 tile can request B non-temporally,
-    // decided per launch (GemmArgs::stream_b; 128 x 8192 x 8192: 38.5 -> 37.6 us, 128 x 16384 x 4096: 34.9 -> 33.6); the
-    // larger tiles re-use B blocks through the L2 caches, so they carry no such switch
+    // decided per launch (GemmArgs::stream_b).  128 x 128 tile, fourteen problems of 65 - 128 rows, B of 128 - 512 MiB:
+    // 1.6 - 5 % faster, one without effect (128 x 8192 x 8192: 37.9 -> 37.2 us, 128 x 16384 x 16384: 104.4 -> 99.8).
+    // The larger tiles re-use B blocks through the L2 caches, so they carry no such switch
     static constexpr bool MAY_STREAM_B = BM <= 64 || (BM == 128 && BK == 64 && NW == 8);
     static_assert(!FINE || PIN_ORDER, "the instruction-by-instruction order needs two operand sets");
     // register-staged path: a stage's pieces (4 registers each).  STAGED_FINE: the instruction-by-instruction

@@ -210,6 +210,19 @@ def test_low_tiles_integer_exact(blk, dtype):
     _run_and_compare(A, B, dtype, sk.SK_POLICY_SK2_DP, blk, grid=8, launches=2)
 
 
+@pytest.mark.parametrize("dtype,K,blks", [(inputs.BF16, 8192, ((128, 128, 64), (64, 128, 64), (64, 64, 128), (32, 64, 64))),
+                                          (inputs.E4M3, 16384, ((64, 128, 128), (32, 128, 128)))])
+def test_large_b_of_a_single_row_of_tiles(dtype, K, blks):
+    # 128 MiB of B read once: requested non-temporally by the 16-bit 128 x 128 tile and by every tile of at most 64 rows
+    N = 8192
+    A, B = inputs.small_int_pair(61, N, K, dtype, 82, lo=-1, hi=1)
+    for blk in blks:
+        M = min(blk[0] - 3, 61)
+        rows = [0, M // 2, M - 1]
+        ref = G.gemm_fp64(A[:M], B, ODT[dtype], rows=rows)
+        _run_and_compare(A[:M], B, dtype, sk.SK_POLICY_ALL_SK, blk, out_dtype=sk.SK_F32, rows=rows, ref=ref, exact=True)
+
+
 @pytest.mark.parametrize("shape,grid", [((57, 14784, 1920), 304), ((496, 256, 11152), 512), ((6528, 96, 1904), 512)])
 def test_default_tile_on_a_larger_grid(shape, grid):
     M, N, K = shape
