@@ -264,9 +264,10 @@ int sk_plan_set_spin_limit(sk_plan_t* plan, uint32_t polls);
  * (SK_ERR_TIMEOUT from sk_plan_check, D invalid).  Plans without split tiles and
  * SK_FIXUP_ATOMIC launches never wait and may overlap freely.
  * Cache policy: a plan with a single row of tiles (at most 64 rows high, or the
- * 16-bit 128 x 128 x 64 tile on eight waves) reads B exactly once; if B is also 128 MiB or more (too large to be found in the
- * memory-side cache by a later launch), its loads carry the non-temporal hint.
- * All other operand loads use the default policy.
+ * 16-bit 128 x 128 x 64 tile on eight waves) reads B exactly once; if B is also
+ * 128 MiB or more (too large to be found in the memory-side cache by a later
+ * launch) and K and N are multiples of 16 bytes, its loads carry the non-temporal
+ * hint.  All other operand loads use the default policy.
  * Errors: INVALID_ARG, UNSUPPORTED (no kernel for tile + dtype + fix-up mode,
  * sizes beyond the kernels' 32-bit index range: M*K or K*N >= 2^31 elements,
  * M*N >= 2^32, or the grid cannot be co-resident while the plan has split
@@ -305,8 +306,8 @@ int sk_plan_check(const sk_plan_t* plan, void* stream);
 /* Ask for another compiled wave layout of the plan's tile (a tuning knob of the dispatcher,
  * Sec. 4.1: one kernel instance per tile configuration).  Variant 0 (the default) leaves the choice
  * to the library: the tile's standard kernel, except that the 256 x 256, 256 x 128 and 128 x 128 x 64
- * tiles run a four-wave kernel when the plan has no split tile (and, for the 256-row tiles, enough
- * K-iterations per tile: 48 and 16) and the eight-wave one otherwise.
+ * tiles run a four-wave kernel when the plan has no split tile, enough K-iterations per tile (256-row
+ * tiles: 48 and 16) and, with 16-bit inputs, K and N that are multiples of 8; the eight-wave one otherwise.
  * Where a tile has further layouts compiled in they are numbered from 1 (for those three tiles: 1 = four
  * waves, 3 = eight waves, whatever the plan; 256 x 256 also 2 = eight waves with the coarser MAC loop);
  * a tile without the requested variant keeps variant 0.  The results are the same under every variant.

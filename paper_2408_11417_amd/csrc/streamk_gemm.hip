@@ -29,9 +29,11 @@ KernelEntry** kernel_table(int* count) {
 // else the shape's variant 0.  want = 0 leaves the choice to the library: variant 0, except that a plan
 // without split tiles (whole_tile_iters = its k-iterations per tile, 0 for plans with split tiles) gets
 // the variant marked for such plans where the shape has one and the tiles are deep enough.
-// whole_tile_iters is also 0 for problems on the register-staged path: its loads are bound by the vector L1,
+// whole_tile_iters is also 0 for 16-bit problems on the register-staged path: its loads are bound by the vector L1,
 // and two waves per SIMD hide that better (3841 x 4225 x 4097, data-parallel, eight waves / four waves:
-// 224 / 252 us with 256 x 256, 232 / 258 us with 256 x 128, 238 / 262 us with 128 x 128).
+// 211 / 254 us with 256 x 256, 230 / 249 us with 256 x 128, 228 / 250 us with 128 x 128; 2001 x 2003 x 2005 65 / 85,
+// 42 / 50, 27 / 33).  Not so in 8 bits, where the eight-wave 256 x 256 kernel has no registers for a stage in flight:
+// 4097 x 4097 x 6145 256 / 236 us, 4097 x 4097 x 8193 341 / 291, 2049 x 4097 x 16385 372 / 267.
 KernelEntry* find_kernel(int dtype, int bm, int bn, int bk, int fixup = SK_FIXUP_FLAGS, int want = 0, int whole_tile_iters = 0) {
     int n;
     KernelEntry** t = kernel_table(&n);
@@ -52,7 +54,7 @@ int whole_tile_iters(const sk_plan_t* plan) {
     const sk_plan_header& h = plan->h;
     const int piece = h.in_dtype == SK_FP8_E4M3 ? 16 : 8;          // elements of a 16-byte piece
     const bool staged = h.K % piece != 0 || h.N % piece != 0;
-    return plan->needs_fixup || staged ? 0 : h.iters_per_tile;
+    return plan->needs_fixup || (staged && h.in_dtype != SK_FP8_E4M3) ? 0 : h.iters_per_tile;
 }
 
 // Helpers of the atomic fix-up: clear the fp32 image, and turn it into a 16-bit D afterwards.

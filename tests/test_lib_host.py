@@ -287,6 +287,11 @@ def test_kernel_info_names_the_kernel_of_a_launch():
         p = sk.sk_plan(1000, 1000, 1000, sk.SK_POLICY_ALL_SK, blk, 256, dt)     # split tiles: eight waves
         assert sk.sk_plan_kernel_info(p)["threads"] == 512
         sk.sk_plan_destroy(p)
+    # rows off the 16-byte grid: four waves in 8 bits only
+    for dt, blk, threads in ((sk.SK_BF16, (256, 256, 64), 512), (sk.SK_FP8_E4M3, (256, 256, 128), 256)):
+        p = sk.sk_plan(1025, 1025, 6145, sk.SK_POLICY_DP, blk, 256, dt)
+        assert sk.sk_plan_kernel_info(p)["threads"] == threads
+        sk.sk_plan_destroy(p)
     p = sk.sk_plan(1000, 1000, 1000, sk.SK_POLICY_DP, (64, 64, 64), 256, sk.SK_BF16)   # a tile without a kernel
     assert lib.sk_plan_kernel_info(p, None, None, None) == sk.SK_ERR_UNSUPPORTED
     sk.sk_plan_destroy(p)
