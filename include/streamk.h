@@ -155,8 +155,9 @@ typedef struct {
                                              share operand blocks and exchange partial tiles); 2: the workgroups sorted by
                                              their slice of the tiles' K range, in eight consecutive parts - chosen when
                                              at least 4 workgroups share every tile and the XCDs would otherwise fetch
-                                             20 MB or more in all of operand blocks that another XCD fetches too; 0: hardware
-                                             order, consecutive workgroups on different XCDs - chosen when the tile grid is
+                                             20 MB or more in all of operand blocks that another XCD fetches too (where an
+                                             XCD's consecutive workgroups hold whole tiles: also twice the bytes of the
+                                             partial tiles written and fetched); 0: hardware order, consecutive workgroups on different XCDs - chosen when the tile grid is
                                              a single row of 16-bit tiles at most 64 (32) rows high and B is at least
                                              48 (16) MB, which is then streamed once in narrow column blocks.  A grid
                                              that is not a multiple of 8 runs in hardware order (and has 0 or 1 here) */

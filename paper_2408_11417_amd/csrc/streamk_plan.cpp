@@ -180,13 +180,17 @@ const TileCost* model_constants(int bm, int bn, int bk, int in_dtype) {
 }
 
 // Which logical workgroups an XCD runs (sk_plan_header.xcd_remap; the three maps are logical_wg's).  Measured on
-// 1667 (size, tile) pairs whose tiles are all split, 16 and 8 bits, under each map:
+// 1667 (size, tile) pairs whose tiles are all split, 16 and 8 bits, under each map, and on 2408 + 2901 more under 1 and 2:
 //  - the contiguous map (1) is the fastest in general: the workgroups of a tile then exchange their partials
 //    inside one L2 (64 x 128 tiles of 8 workgroups, 512 x 512 x 8192: 14.4 us against 18.3 with either other map);
 //  - with at least 4 workgroups per tile each XCD reads the whole K range of its few tiles, so operand blocks
 //    shared with other XCDs' tiles are fetched once per XCD; sorted by K slice (2) they are fetched once.
 //    Where that saves 20 MB or more in all it pays for the longer exchange: 3 % at 20 - 40 MB, 8 - 12 % above, up to
-//    1.5x (384 x 240 x 52832, 64 x 128 tiles: 48.1 -> 31.6 us); below 20 MB it loses 3 - 9 %;
+//    1.5x (384 x 240 x 52832, 64 x 128 tiles: 48.1 -> 31.6 us); below 20 MB it loses 3 - 9 %.  Where the contiguous map
+//    gives every XCD whole tiles, it keeps the exchange inside one L2 altogether, and what is saved has to be twice the
+//    bytes of the partials (written and fetched) as well.  On 1939 such (size, tile) pairs the contiguous map is 10 %
+//    faster up to once those bytes, 4 % up to twice, level up to three times, and the sorted one 6 - 20 % beyond
+//    (1024 x 1024 x 8192, 128 x 256 8-bit tiles: 29.0 us, sorted 41.3);
 //  - a single row of low 16-bit tiles over a large B streams B once and shares only the small A: the hardware
 //    order (0), neighbouring column blocks on different XCDs, gains 2 - 6 % from 48 MB of B on (32 rows and
 //    less: from 16 MB on) and loses 2 - 20 % below.  8-bit tiles lose 3 - 20 % with it at any size.
@@ -209,7 +213,11 @@ int choose_remap(const sk_plan_header& h) {
         } else {
             fetched = (double)h.tiles * (h.blk_m + h.blk_n);
         }
-        if ((fetched - all) * (double)h.K * es >= 20e6) return 2;
+        const double saved = (fetched - all) * (double)h.K * es;
+        // (tiles * ipt == grid * ipw: the ranges fill the tiles evenly; then an XCD's grid / 8 ranges may be whole tiles)
+        const bool exchange_inside = h.total_iters == (int64_t)h.grid * h.iters_per_wg && h.grid / 8 * h.iters_per_wg % h.iters_per_tile == 0;
+        const double partials = (double)(h.grid - h.tiles) * h.blk_m * h.blk_n * 8;
+        if (saved >= 20e6 && !(exchange_inside && saved < 2 * partials)) return 2;
     }
     return 1;
 }

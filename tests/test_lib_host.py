@@ -201,6 +201,16 @@ def test_workgroup_numbering_by_k_slice_only_where_the_kernel_does_it():
         sk.sk_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("shape,blk,dtype,remap", [((1024, 1024, 8192), (128, 256, 128), sk.SK_FP8_E4M3, 1), ((2048, 2048, 8192), (256, 256, 128), sk.SK_FP8_E4M3, 1),
+                                                   ((256, 512, 16384), (64, 64, 128), sk.SK_F16, 2), ((1024, 1024, 65536), (128, 128, 64), sk.SK_BF16, 2),
+                                                   ((1024, 1040, 8320), (128, 256, 128), sk.SK_FP8_E4M3, 2)])
+def test_numbering_of_plans_whose_xcds_hold_whole_tiles(shape, blk, dtype, remap):
+    # by K slice only where that saves twice the bytes of the partial tiles; the last plan's XCDs do not hold whole tiles
+    plan = sk.sk_plan(*shape, sk.SK_POLICY_ALL_SK, blk, 256, dtype)
+    assert sk.sk_plan_info(plan)["xcd_remap"] == remap
+    sk.sk_plan_destroy(plan)
+
+
 def test_gemm_rejects_bad_arguments_without_touching_the_gpu():
     p = sk.sk_plan(512, 512, 512, sk.SK_POLICY_ALL_SK, (128, 128, 32))
     assert sk.sk_gemm_status(0, 256, 512, p) == sk.SK_ERR_INVALID_ARG
