@@ -103,8 +103,8 @@ void expand_wg(const sk_plan_header& h, int x, std::vector<sk_segment>* out, sk_
 // of the first 400 of 500 seeded problem sizes, 72 with at most 128 rows and 40 with few tiles and deep K on
 // MI355X; sizes 400 .. 499 are the selector's held-out split and stay out of the fit (fit_tile_model.py; the
 // fit optimises the dispatcher's pick of tile and policy, not the predicted times).  Time of the pick over the
-// fastest of all tiles and schedules, geometric mean: 16 bits 1.016 / 1.028 / 1.027 on the three sets (the six
-// shapes and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.011 / 1.007 / 1.015 (two shapes: 1.59 / 2.29 / 2.44).
+// fastest of all tiles and schedules, geometric mean: 16 bits 1.015 / 1.020 / 1.028 on the three sets (the six shapes
+// and constants of before: 1.047 / 1.110 / 1.097), 8 bits 1.011 / 1.008 / 1.016 (two shapes: 1.59 / 2.29 / 2.44).
 // (per_cu: workgroups of the tile's kernel that fit a compute unit side by side - 160 KB of LDS)
 struct TileCost { int bm, bn, bk; double tflops, tile_us; int per_cu; };
 const TileCost tile_costs16[] = {{256, 256, 64, 1590., 10.40, 1}, {256, 128, 64, 1307., 5.61, 1}, {128, 128, 64, 1062., 4.33, 1},
@@ -132,8 +132,8 @@ int64_t model_contributors(int64_t workgroups, int64_t ipt, int64_t ipw) {
 // Rows of A or B off the 16-byte grid: the register-staged kernels, whose first two stages arrive one after the other and
 // whose D leaves element by element.  Counting 1.6 times the microseconds outside the loop took the 16-bit picks on 69 odd
 // sizes from 1.050 of the fastest to 1.035; scaling the loop as well did not help.  With the kernels as they are, time of
-// the picked tile and schedule over the fastest of all on 69 odd sizes, 40 of at most 128 rows and 40 of short K: 16 bits
-// 1.023 / 1.072 / 1.005, 8 bits 1.016 / 1.071 / 1.006 (8-bit problems on the two large shapes only: 1.88 / 2.52 / 1.52).
+// the picked tile and schedule over the fastest of all on 70 odd sizes, 40 of at most 128 rows and 40 of short K: 16 bits
+// 1.023 / 1.069 / 1.002, 8 bits 1.016 / 1.073 / 1.002 (8-bit problems on the two large shapes only: 1.88 / 2.52 / 1.52).
 constexpr double MODEL_STAGED_TILE = 1.6;
 bool model_staged(int64_t N, int64_t K, int in_dtype) {
     const int piece = in_dtype == SK_FP8_E4M3 ? 16 : 8;

@@ -10,6 +10,9 @@ same bits.
 The shapes and value distributions stand in for the paper's FP16 benchmark
 suite (Sec. 5.1), whose member list is not published.
 """
+import math
+import random
+
 import numpy as np
 
 F16, BF16, E4M3 = 0, 1, 2
@@ -130,6 +133,33 @@ def paper_suite(n=923, seed=5):
     rng = np.random.default_rng(seed)
     pick = rng.permutation(len(grid))[:n]
     return [grid[i] for i in pick]
+
+
+def model_sizes(seed=11):
+    """The sizes that the tile dispatcher's cost model is fitted and judged on, by family: "sweep" - the first 400
+    sizes of sweep_shapes(500, 4) (the others are the selector's held-out split) but for the three largest -, "skinny" -
+    at most 128 rows against a weight matrix -, "deep" - few tiles, long K -, "odd" - any sizes at all -,
+    "odd skinny" and "odd short" - off the 16-byte grid with few rows or few k-iterations."""
+    rng = random.Random(seed)
+
+    def log_uniform(lo, hi):
+        return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+    def multiple(lo, hi, step):
+        return max(step, log_uniform(lo, hi) // step * step)
+
+    sweep = [(M, N, K) for M, N, K in sweep_shapes(500, 4)[:400]
+             if 2 * M * N * K <= 1.1e12 and (M * K + N * K + M * N) * 2 < 4e8]
+    skinny = [(M, N, K) for M in (16, 32, 64, 128) for N, K in ((8192, 8192), (4096, 4096), (16384, 4096))]
+    while len(skinny) < 72:
+        size = rng.randint(1, 128), multiple(1024, 16384, 64), multiple(1024, 16384, 64)
+        if size[1] * size[2] <= 8192 * 8192:
+            skinny.append(size)
+    deep = [(multiple(64, 1024, 16), multiple(64, 1024, 16), multiple(8192, 65536, 16)) for _ in range(40)]
+    odd = [tuple(log_uniform(64, 4400) for _ in range(3)) for _ in range(70)]
+    odd_skinny = [(rng.randint(1, 128), log_uniform(1024, 9000) | 1, log_uniform(1024, 9000) | 1) for _ in range(40)]
+    odd_short = [(log_uniform(300, 6000), log_uniform(300, 6000), log_uniform(16, 600) | 1) for _ in range(40)]
+    return {"sweep": sweep, "skinny": skinny, "deep": deep, "odd": odd, "odd skinny": odd_skinny, "odd short": odd_short}
 
 
 def sample_rows(M, n, seed):

@@ -7,8 +7,8 @@ Bloom filters (Sec. 4.2) from the winners and evaluates them on held-out shapes.
 
     python -m paper_2408_11417_amd.sweep --shapes 500 --seed 4 --out sweep_bf16.json
 
-Needs a GPU.  Inputs are seeded synthetic bf16 matrices, uniform in [-1, 1], carved out of two
-device pools that are filled once.
+Needs a GPU.  Inputs are seeded synthetic matrices (bf16 unless --dtype says otherwise; 8-bit inputs give bf16
+results), uniform in [-1, 1], carved out of two device pools that are filled once.
 """
 import argparse
 import json
@@ -70,7 +70,9 @@ def run(shapes, out_path, dtype_code=1, verbose=True, check_every=25, fixup=0, t
 
     torch.cuda.set_device(0)
     stream = torch.cuda.current_stream().cuda_stream
-    tdt = torch.bfloat16 if dtype_code == sk.SK_BF16 else torch.float16
+    tdt = {sk.SK_BF16: torch.bfloat16, sk.SK_F16: torch.float16, sk.SK_FP8_E4M3: torch.float8_e4m3fn}[dtype_code]
+    es = 1 if dtype_code == sk.SK_FP8_E4M3 else 2                       # bytes of an input element
+    out_code, out_tdt = (sk.SK_BF16, torch.bfloat16) if es == 1 else (dtype_code, tdt)
     max_a = max(M * K for M, N, K in shapes)
     max_b = max(K * N for M, N, K in shapes)
     max_d = max(M * N for M, N, K in shapes)
@@ -90,8 +92,8 @@ def run(shapes, out_path, dtype_code=1, verbose=True, check_every=25, fixup=0, t
     # memory-side cache holds for every operand above 64 MB, which is where that cache would matter)
     slack = 4 * 256
     pa, pb = pool(4 * max_a + slack), pool(4 * max_b + slack)
-    pd = torch.empty(4 * max_d + slack, dtype=tdt, device="cuda")
-    pd2 = torch.empty(max_d, dtype=tdt, device="cuda")
+    pd = torch.empty(4 * max_d + slack, dtype=out_tdt, device="cuda")
+    pd2 = torch.empty(max_d, dtype=out_tdt, device="cuda")
     ws_bytes = 256 * 256 * 256 * 4 + (1 << 16)
     if fixup:                                  # the atomic fix-up keeps an fp32 image of D in the workspace
         ws_bytes = max(ws_bytes, max_d * 4 + (1 << 16))
@@ -102,7 +104,7 @@ def run(shapes, out_path, dtype_code=1, verbose=True, check_every=25, fixup=0, t
     for idx, (M, N, K) in enumerate(shapes):
         plans, infos = [], []
         for p in range(sk.SK_NUM_POLICIES):
-            plan = sk.sk_plan(M, N, K, p, tile, 256, dtype_code, dtype_code, tile_order)
+            plan = sk.sk_plan(M, N, K, p, tile, 256, dtype_code, out_code, tile_order)
             sk.sk_plan_set_fixup(plan, fixup)
             if dp_first:
                 sk.sk_plan_set_batch_order(plan, sk.SK_DATA_PARALLEL_FIRST)
@@ -117,9 +119,9 @@ def run(shapes, out_path, dtype_code=1, verbose=True, check_every=25, fixup=0, t
         dA, dB, dD = pa.data_ptr(), pb.data_ptr(), pd.data_ptr()
         # four operand sets carved out of the pools at 256-byte aligned offsets
         copies = 4
-        step = lambda n: (n * 2 + 255) // 256 * 256
-        assert step(M * K) * copies <= pa.numel() * 2 and step(K * N) * copies <= pb.numel() * 2 and step(M * N) * copies <= pd.numel() * 2
-        sets = [(dA + c * step(M * K), dB + c * step(K * N), dD + c * step(M * N)) for c in range(copies)]
+        step = lambda n, size: (n * size + 255) // 256 * 256
+        assert step(M * K, es) * copies <= pa.numel() * es and step(K * N, es) * copies <= pb.numel() * es and step(M * N, 2) * copies <= pd.numel() * 2
+        sets = [(dA + c * step(M * K, es), dB + c * step(K * N, es), dD + c * step(M * N, 2)) for c in range(copies)]
         for p in range(sk.SK_NUM_POLICIES):
             key = infos[p]["sk_tiles"]
             if key not in by_sched:
@@ -159,7 +161,7 @@ def run(shapes, out_path, dtype_code=1, verbose=True, check_every=25, fixup=0, t
                 sk.POLICY_NAMES[times.index(best)], 2.0 * M * N * K / best / 1e9, times[0]), flush=True)
         if out_path and (idx % 50 == 49 or idx == len(shapes) - 1):
             with open(out_path, "w") as f:
-                json.dump({"dtype": "bf16" if dtype_code == 1 else "f16", "grid": 256,
+                json.dump({"dtype": {1: "bf16", 0: "f16", 2: "e4m3"}[dtype_code], "grid": 256,
                            "fixup": "atomic" if fixup else "flags", "dp_first": bool(dp_first),
                            "segment_order": "ascending" if ascending else "k_aligned",
                            "tile_order": {None: "default", 0: "row_major", 1: "grouped"}[tile_order],
@@ -178,10 +180,10 @@ def main():
                     help="append the skinny family (M in 16..128, N = K in 4096, 8192; N = 16384, K = 4096) to the shapes")
     ap.add_argument("--dp-first", action="store_true",
                     help="data-parallel batches before the Stream-K work (the earlier hybrid of Sec. 3.2)")
-    ap.add_argument("--suite", choices=("random", "paper"), default="random",
+    ap.add_argument("--suite", choices=("random", "paper", "model"), default="random",
                     help="random: log-uniform sizes (inputs.sweep_shapes); paper: a seeded sample of the power-of-two grid "
-                         "of Sec. 5.1 (inputs.paper_suite)")
-    ap.add_argument("--dtype", choices=("bf16", "f16"), default="bf16")
+                         "of Sec. 5.1 (inputs.paper_suite); model: the sizes of the tile dispatcher's fit (inputs.model_sizes)")
+    ap.add_argument("--dtype", choices=("bf16", "f16", "e4m3"), default="bf16")
     ap.add_argument("--tile-order", choices=("default", "row_major", "grouped"), default="default",
                     help="tile index -> tile grid position for every plan (default: the library's choice per schedule)")
     ap.add_argument("--graph", action="store_true",
@@ -192,13 +194,16 @@ def main():
                     help="how split tiles are combined (atomic = Algorithm 1's accumulation into C)")
     args = ap.parse_args()
     from paper_2408_11417_amd import inputs
-    shapes = inputs.paper_suite(args.shapes, args.seed) if args.suite == "paper" else inputs.sweep_shapes(args.shapes, args.seed)
+    if args.suite == "model":
+        shapes = [size for family in inputs.model_sizes().values() for size in family]
+    else:
+        shapes = inputs.paper_suite(args.shapes, args.seed) if args.suite == "paper" else inputs.sweep_shapes(args.shapes, args.seed)
     if args.first:
         shapes = shapes[:args.first]
     if args.skinny:
         shapes += [(M, N, K) for M in (16, 32, 64, 128) for N, K in ((8192, 8192), (4096, 4096), (16384, 4096))]
     tile = tuple(int(v) for v in args.tile.split(",")) if args.tile else None
-    run(shapes, args.out, dtype_code=1 if args.dtype == "bf16" else 0, fixup=1 if args.fixup == "atomic" else 0, tile=tile, dp_first=args.dp_first, ascending=args.ascending,
+    run(shapes, args.out, dtype_code={"bf16": 1, "f16": 0, "e4m3": 2}[args.dtype], fixup=1 if args.fixup == "atomic" else 0, tile=tile, dp_first=args.dp_first, ascending=args.ascending,
         tile_order={"default": None, "row_major": 0, "grouped": 1}[args.tile_order], graph=args.graph)
     return 0
 

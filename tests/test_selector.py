@@ -154,6 +154,22 @@ def test_fit_tool_formula_is_the_library_cost_model():
     assert tuple(sk.sk_default_tile(8192, 8192, 8192, sk.SK_FP8_E4M3)) == (256, 256, 128)
 
 
+def test_fit_tool_formula_covers_8_bits_and_rows_off_the_16_byte_grid():
+    from paper_2408_11417_amd import fit_tile_model as F, inputs
+    families = inputs.model_sizes()
+    odd = families["odd"] + families["odd skinny"] + families["odd short"]
+    for P, dtype, sizes in ((F.LIBRARY, sk.SK_F16, odd), (F.LIBRARY8, sk.SK_FP8_E4M3, odd + families["skinny"] + families["deep"] + inputs.sweep_shapes(300, 4))):
+        for M, N, K in sizes:
+            blk = sk.sk_default_tile(M, N, K, dtype)
+            est = {t: F.predict(P, t, M, N, K) for t in P["bk"]}
+            assert blk[2] == P["bk"][tuple(blk[:2])] and est[tuple(blk[:2])] <= min(est.values()) * (1 + 1e-9), (M, N, K, blk, est)
+            for policy in (sk.SK_POLICY_DP, sk.SK_POLICY_SK2_DP, sk.SK_POLICY_ALL_SK):
+                plan = sk.sk_plan(M, N, K, policy, tuple(blk), 256, dtype)
+                t = F.schedule_us(P, tuple(blk[:2]), M, N, K, sk.sk_plan_info(plan)["sk_tiles"])
+                assert abs(sk.sk_plan_estimate_us(plan) - t) <= 1e-9 * t, (M, N, K, policy)
+                sk.sk_plan_destroy(plan)
+
+
 def test_winner_mask_error_paths_and_hand_values():
     import ctypes
     lib = sk.binding._lib
