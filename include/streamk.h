@@ -266,9 +266,10 @@ int sk_plan_set_spin_limit(sk_plan_t* plan, uint32_t polls);
  * SK_FIXUP_ATOMIC launches never wait and may overlap freely.
  * Cache policy: a plan with a single row of tiles (at most 64 rows high, or the
  * 16-bit 128 x 128 x 64 tile on eight waves) reads B exactly once; if B is also
- * 128 MiB or more (too large to be found in the memory-side cache by a later
- * launch) and K and N are multiples of 16 bytes, its loads carry the non-temporal
- * hint.  All other operand loads use the default policy.
+ * 128 MiB or more and K and N are multiples of 16 bytes, its loads carry the
+ * non-temporal hint: B is then not kept for a later launch, which the 256 MB
+ * memory-side cache could only do if no other large operand came in between.
+ * All other operand loads use the default policy.
  * Errors: INVALID_ARG, UNSUPPORTED (no kernel for tile + dtype + fix-up mode,
  * sizes beyond the kernels' 32-bit index range: M*K or K*N >= 2^31 elements,
  * M*N >= 2^32, or the grid cannot be co-resident while the plan has split

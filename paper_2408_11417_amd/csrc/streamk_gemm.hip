@@ -172,10 +172,13 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
     g.dp_first = plan->dp_first;
     g.k_aligned = plan->k_aligned;
     g.xcd_remap = h.xcd_remap;
-    // B is requested non-temporally when it is read exactly once (one row of tiles) and is too large to be
-    // found in the 256 MB memory-side cache by a later launch anyway (at least half of it: 128 MiB).  Measured:
-    // 16 x 8192 x 8192 and 16 x 16384 x 4096 (128 MiB) 5 - 6 % faster, 16 x 4096 x 4096 and 32 x 8192 x 2048
-    // (32 MiB, served by the caches from launch to launch) 10 - 25 % slower with the hint.
+    // B is requested non-temporally when it is read exactly once (one row of tiles) and is so large that a later
+    // launch hardly finds it in the 256 MB memory-side cache: from 128 MiB, half of it, on, a launch with another B in
+    // between is enough.  Measured on four operand sets in turn, 128 - 512 MiB: 1 - 9 % faster on every tile that may
+    // (16 x 8192 x 8192 26.8 -> 25.4 us, 128 x 8192 x 8192 41.1 -> 38.7 with other work in between); 16 x 4096 x 4096 and
+    // 32 x 8192 x 2048 (32 MiB, served by the cache from launch to launch) 10 - 25 % slower with the hint.  The price: one
+    // and the same B of 128 - 260 MiB launched over and over, which the cache would serve in part, is 5 - 16 % slower
+    // (128 x 8192 x 8192 32.2 -> 37.7 us); from 288 MiB on that is faster too.
     g.stream_b = h.tiles_m == 1 && (size_t)h.K * (size_t)h.N * (h.in_dtype == SK_FP8_E4M3 ? 1 : 2) >= ((size_t)128 << 20);
     g.div_ipt = sk_make_fast_div((uint32_t)h.iters_per_tile);
     g.div_ipw = sk_make_fast_div((uint32_t)h.iters_per_wg);

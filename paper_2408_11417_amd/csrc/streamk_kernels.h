@@ -164,7 +164,9 @@ struct Cfg {
     static_assert(!FINE || PIN_ORDER, "the instruction-by-instruction order needs two operand sets");
     // register-staged path: a stage's pieces (4 registers each).  STAGED_FINE: the instruction-by-instruction
     // MAC loop with one stage in registers, where the two operand sets leave room for it; the other tiles hold
-    // STAGES_HELD stages in registers, about 64 registers of loads in flight.
+    // STAGES_HELD stages in registers, about 64 registers of loads in flight.  (The count is an estimate: the compiler
+    // spills 8 registers of the eight-wave 256 x 256 kernel, 52 of the four-wave one and 136 of the 8-bit four-wave one.
+    // No steady trip holds a spill; the checked trips of the last one do.)
     static constexpr int PIECES = CA + CB;
     static constexpr bool STAGED_FINE = FINE && KK % 2 == 0 && 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 5 * PIECES + 32 <= 256;
     static constexpr int STAGES_HELD = 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 4 * PIECES + 64 > 256 ? 0 : PIECES <= 5 ? 4 : PIECES <= 8 ? 2 : 1;
@@ -639,7 +641,9 @@ __device__ __forceinline__ void mac_prefetch(const GemmArgs& g, int m0, int n0, 
 // k-step's LDS reads, and one piece parked (stage i+2, into the slot that the barrier has freed) whose
 // registers then take the same piece of stage i+3.  A load therefore has a whole trip to land.
 // What bounds it is the vector L1: under-aligned 16-byte loads move about 25 bytes per clock and CU where
-// aligned ones move 52 (a microbenchmark of this access pattern), and a 256 x 256 x 64 stage is 64 KB.
+// aligned ones move 52 (a microbenchmark of this access pattern), and a 256 x 256 x 64 stage is 64 KB: 2600 clocks,
+// against 2050 of matrix-core work.  3841 x 4225 x 4097 looks up 63 million cache lines where the aligned neighbour
+// looks up 19 (counters); its matrix cores are busy a third of the time, 0.63 there.
 template <class C, bool TR>
 __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n0, int k_begin, int k_end, unsigned char* smem,
                                                 const FragMap<C>& fm, typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI]) {
@@ -1460,8 +1464,9 @@ template <int DT, bool ATOMIC = false> void add_16bit_tiles(KernelEntry** t, int
 
 // The tiles of at most 64 rows.  What bounds them outside the HBM-bound shapes is the rate at which a CU
 // takes operand bytes into LDS (about 90 bytes per ns with rows on 128-byte boundaries, 60 off them), so they
-// matter where the larger tiles leave CUs idle: 1024^3 on 256 tiles of 64 x 64 6.6 us (128 of 64 x 128: 8.2,
-// 256 of 32 x 128: 7.2), 1 x 4096 x 4096 on 32 x 64 9.3 us (32 x 128: 11.4, 16 x 128: 9.8).
+// matter where the larger tiles leave CUs idle: 1024^3 on 256 tiles of 64 x 64 7.0 us (128 of 64 x 128: 8.2,
+// 256 of 32 x 128: 7.2), 1 x 4096 x 4096 on 16 x 128 9.8 us (32 x 128: 11.4; 32 x 64: 9.4, which the cost model
+// has behind it).
 template <int DT, bool ATOMIC = false> void add_16bit_low_tiles(KernelEntry** t, int* n) {
     t[(*n)++] = make_entry<Cfg<DT, 64, 128, 64, 2, 4, 32, 4>, ATOMIC>();
     t[(*n)++] = make_entry<Cfg<DT, 32, 128, 64, 1, 4, 32, 4>, ATOMIC>();

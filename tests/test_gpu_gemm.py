@@ -1,6 +1,6 @@
 """Parity of the HIP Stream-K GEMM (through the C ABI) with the CPU oracle, on a real MI355X.
 
-Tolerances (the benchmark spec): max relative error <= 1e-2 with fp16 / bf16 output and
+Tolerances: max relative error <= 1e-2 with fp16 / bf16 output and
 <= 1e-4 on the fp32-accumulator output, with err = max |d - ref| / max(|ref|, rms(ref)).
 Integer-valued inputs are exact in fp32 under every schedule, so they are compared bit-exactly.
 """
