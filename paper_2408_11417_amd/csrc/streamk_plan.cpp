@@ -215,7 +215,7 @@ int choose_remap(const sk_plan_header& h) {
         }
         const double saved = (fetched - all) * (double)h.K * es;
         // (tiles * ipt == grid * ipw: the ranges fill the tiles evenly; then an XCD's grid / 8 ranges may be whole tiles)
-        const bool exchange_inside = h.total_iters == (int64_t)h.grid * h.iters_per_wg && h.grid / 8 * h.iters_per_wg % h.iters_per_tile == 0;
+        const bool exchange_inside = h.total_iters == (int64_t)h.grid * h.iters_per_wg && (int64_t)(h.grid / 8) * h.iters_per_wg % h.iters_per_tile == 0;
         const double partials = (double)(h.grid - h.tiles) * h.blk_m * h.blk_n * 8;
         if (saved >= 20e6 && !(exchange_inside && saved < 2 * partials)) return 2;
     }
