@@ -186,7 +186,7 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
     g.div_band = sk_make_fast_div((uint32_t)(SK_GROUP_ROWS * h.tiles_n));
     g.div_last_rows = sk_make_fast_div((uint32_t)(h.tiles_m % SK_GROUP_ROWS));
     g.div_tiles = sk_make_fast_div((uint32_t)h.tiles);
-    g.div_extra = sk_make_fast_div((uint32_t)(h.grid % h.tiles));
+    g.div_extra = sk_make_fast_div(h.iters_per_wg ? (uint32_t)(h.iters_per_tile % h.iters_per_wg) : 0u);
     if (atomic) {
         // Algorithm 1's atomic accumulation needs C to start at zero: clear the image in-stream, accumulate, convert
         const size_t n = (size_t)h.M * (size_t)h.N;

@@ -58,7 +58,7 @@ struct GemmArgs {
     int stream_b;          // 1: B is read exactly once (one row of tiles) and is large: MAY_STREAM_B tiles request it non-temporally
     // divisors of the index arithmetic: ipt, ipw, tiles_n, SK_GROUP_ROWS * tiles_n, rows of the last (short) band
     sk_fast_div div_ipt, div_ipw, div_tiles_n, div_band, div_last_rows;
-    sk_fast_div div_tiles, div_extra;   // of logical_wg: tiles, grid mod tiles
+    sk_fast_div div_tiles, div_extra;   // of logical_wg: tiles, ipt mod ipw
 };
 
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, sk_fast_div f) { return (uint32_t)(((uint64_t)n * f.mul) >> f.shift); }
@@ -256,18 +256,20 @@ __device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
     if (g.xcd_remap == 0 || g.grid % 8 != 0) return hw;
     const int q = (hw % 8) * (g.grid / 8) + hw / 8;
     if (g.xcd_remap == 1) return q;
-    // workgroups ceil(t * grid / tiles) .. ceil((t + 1) * grid / tiles) - 1 share tile t, about: `each` or
-    // one more; the tiles with one more are t = floor(i * tiles / extra), i = 0 .. extra - 1, extra = grid mod tiles.
-    const int each = (int)fast_div((uint32_t)g.grid, g.div_tiles);
+    // The ranges of workgroups ceil(t * ipt / ipw) .. ceil((t + 1) * ipt / ipw) - 1 start in tile t: `each` of them or
+    // one more; the tiles with one more are t = floor(i * ipw / extra), i = 0, 1, ..., extra = ipt mod ipw.  (By the
+    // ranges themselves, not by grid / tiles: ipw is rounded up, and over the tiles that adds up to a slice or more.)
+    const int each = (int)fast_div((uint32_t)g.ipt, g.div_ipw);
+    if (q >= (int)fast_div((uint32_t)(g.sk_iters + g.ipw - 1), g.div_ipw)) return q;       // an empty range
     int t, j;
     if (q < each * g.tiles) {
         j = (int)fast_div((uint32_t)q, g.div_tiles);
         t = q - j * g.tiles;
     } else {
         j = each;
-        t = (int)fast_div((uint32_t)((q - each * g.tiles) * g.tiles), g.div_extra);
+        t = (int)fast_div((uint32_t)((q - each * g.tiles) * g.ipw), g.div_extra);
     }
-    return (int)fast_div((uint32_t)(t * g.grid + g.tiles - 1), g.div_tiles) + j;
+    return (int)fast_div((uint32_t)(t * g.ipt + g.ipw - 1), g.div_ipw) + j;
 }
 
 // 16 bytes whose address is only known to be a multiple of the element size (rows of a matrix whose

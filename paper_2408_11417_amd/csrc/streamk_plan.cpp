@@ -180,13 +180,15 @@ const TileCost* model_constants(int bm, int bn, int bk, int in_dtype) {
 }
 
 // Which logical workgroups an XCD runs (sk_plan_header.xcd_remap; the three maps are logical_wg's).  Measured on
-// 1667 (size, tile) pairs whose tiles are all split, 16 and 8 bits, under each map, and on 2408 + 2901 more under 1 and 2:
+// 1667 (size, tile) pairs whose tiles are all split, 16 and 8 bits, under each map, and on more under 1 and 2:
 //  - the contiguous map (1) is the fastest in general: the workgroups of a tile then exchange their partials
 //    inside one L2 (64 x 128 tiles of 8 workgroups, 512 x 512 x 8192: 14.4 us against 18.3 with either other map);
 //  - with at least 4 workgroups per tile each XCD reads the whole K range of its few tiles, so operand blocks
 //    shared with other XCDs' tiles are fetched once per XCD; sorted by K slice (2) they are fetched once.
-//    Where that saves 20 MB or more in all it pays for the longer exchange: 3 % at 20 - 40 MB, 8 - 12 % above, up to
-//    1.5x (384 x 240 x 52832, 64 x 128 tiles: 48.1 -> 31.6 us); below 20 MB it loses 3 - 9 %.  Where the contiguous map
+//    Where that saves 20 MB or more in all it pays for the longer exchange: 2408 pairs under 1 and 2, tiles of at most
+//    64 rows 4 - 18 % at 20 - 40 MB, 17 - 36 % above, larger tiles level at 20 - 40 MB, 3 - 17 % above (384 x 240 x
+//    52832, 64 x 128 tiles: 48.1 -> 31.6 us; 512 x 240 x 63792, 64 x 128 8-bit tiles: 51.2 -> 26.8); below 20 MB it
+//    loses 2 - 13 %.  Where the contiguous map
 //    gives every XCD whole tiles, it keeps the exchange inside one L2 altogether, and what is saved has to be twice the
 //    bytes of the partials (written and fetched) as well.  On 1939 such (size, tile) pairs the contiguous map is 10 %
 //    faster up to once those bytes, 4 % up to twice, level up to three times, and the sorted one 6 - 20 % beyond
