@@ -1,4 +1,5 @@
 // Host side of the Stream-K GEMM: kernel table, workspace handling and the sk_gemm launcher.
+#include <algorithm>
 #include <mutex>
 #include "streamk_kernels.h"
 
@@ -20,6 +21,9 @@ KernelEntry** kernel_table(int* count) {
         register_bf16_atomic(table, &n);
         register_f16_atomic(table, &n);
         register_fp8_atomic(table, &n);
+        add_across_bf16(table, n);
+        add_across_f16(table, n);
+        add_across_fp8(table, n);
     });
     *count = n;
     return table;
@@ -34,27 +38,43 @@ KernelEntry** kernel_table(int* count) {
 // 211 / 254 us with 256 x 256, 230 / 249 us with 256 x 128, 228 / 250 us with 128 x 128; 2001 x 2003 x 2005 65 / 85,
 // 42 / 50, 27 / 33).  Not so in 8 bits, where the eight-wave 256 x 256 kernel has no registers for a stage in flight:
 // 4097 x 4097 x 6145 256 / 236 us, 4097 x 4097 x 8193 341 / 291, 2049 x 4097 x 16385 372 / 267.
-KernelEntry* find_kernel(int dtype, int bm, int bn, int bk, int fixup = SK_FIXUP_FLAGS, int want = 0, int whole_tile_iters = 0) {
+// across_iters: least k-iterations per tile from which a kernel whose MAC loop can run on across this plan's tiles is the
+// choice (0: the plan cannot use that loop).
+KernelEntry* find_kernel(int dtype, int bm, int bn, int bk, int fixup = SK_FIXUP_FLAGS, int want = 0, int whole_tile_iters = 0, int across_iters = 0) {
     int n;
     KernelEntry** t = kernel_table(&n);
     KernelEntry* fallback = nullptr;
     KernelEntry* exact = nullptr;
     for (int i = 0; i < n; i++)
         if (t[i]->dtype == dtype && t[i]->bm == bm && t[i]->bn == bn && t[i]->bk == bk && t[i]->fixup == fixup) {
-            if (want == 0 && t[i]->whole_tiles_choice && whole_tile_iters >= t[i]->whole_tiles_choice) return t[i];
+            const int from = t[i]->across && across_iters ? std::max(t[i]->across_iters, across_iters) : t[i]->whole_tiles_choice;
+            if (want == 0 && t[i]->whole_tiles_choice && whole_tile_iters >= from) return t[i];
             if (t[i]->variant == want) exact = t[i];
             if (t[i]->variant == 0) fallback = t[i];
         }
     return exact ? exact : fallback;
 }
 
-
-// k-iterations per tile as find_kernel wants them.
-int whole_tile_iters(const sk_plan_t* plan) {
+// The kernel that a launch of the plan runs; `across`: its MAC loop that runs on across the tiles of a workgroup.
+// That loop keeps the requests and the stores going from one tile to the next.  Measured against the eight-wave kernel
+// (16 bits, which takes the shallow tiles) and the four-wave one (8 bits):
+//  - 16 bits, three tiles or more per workgroup, from 8 k-iterations on: 8192 x 8192 x 512 77.2 -> 69.7 us, x 1024 121.3 -> 115.0,
+//    16384 x 16384 x 1024 491.9 -> 457.1, 12288 x 12288 x 520 195.2 -> 170.2;
+//  - 16 bits, two tiles: from 32 on (6000 x 4104 x 2056 109.2 -> 107.3; 6000 x 4096 x 512 33.9 -> 34.9);
+//  - 16 bits, one tile, where only the first and the last tile's code counts: from 56 on (3840 x 4224 x 4096 102.9 -> 101.3,
+//    4096 x 4096 x 16384 398 -> 378, four waves without it 382; x 3072 77.6 -> 78.9);
+//  - 8 bits always (4096 x 4096 x 640 20.3 -> 16.4, 8192 x 8192 x 1024 88.8 -> 65.0, 8192^3 377.6 -> 355.8).
+KernelEntry* kernel_of(const sk_plan_t* plan, bool* across = nullptr) {
     const sk_plan_header& h = plan->h;
-    const int piece = h.in_dtype == SK_FP8_E4M3 ? 16 : 8;          // elements of a 16-byte piece
+    const bool atomic = plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup, fp8 = h.in_dtype == SK_FP8_E4M3;
+    const int piece = fp8 ? 16 : 8;                                // elements of a 16-byte piece
     const bool staged = h.K % piece != 0 || h.N % piece != 0;
-    return plan->needs_fixup || (staged && h.in_dtype != SK_FP8_E4M3) ? 0 : h.iters_per_tile;
+    const int whole_iters = plan->needs_fixup || (staged && !fp8) ? 0 : h.iters_per_tile;
+    const bool can = !plan->needs_fixup && !staged && h.out_dtype != SK_F32 && h.N < SK_ACROSS_MAX_N;
+    const int from = !can ? 0 : fp8 || h.tiles > 2ll * h.grid ? 1 : h.tiles > h.grid ? 32 : 56;
+    KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, whole_iters, from);
+    if (across) *across = e && can && e->across && h.iters_per_tile >= e->across_iters;
+    return e;
 }
 
 // Helpers of the atomic fix-up: clear the fp32 image, and turn it into a 16-bit D afterwards.
@@ -112,9 +132,7 @@ extern "C" int sk_plan_check(const sk_plan_t* plan, void* stream) {
 
 extern "C" int sk_plan_kernel_info(const sk_plan_t* plan, int32_t* threads, int32_t* lds_bytes, int32_t* variant) {
     if (!plan) return SK_ERR_INVALID_ARG;
-    const sk_plan_header& h = plan->h;
-    const bool atomic = plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup;
-    const KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, whole_tile_iters(plan));
+    const KernelEntry* e = kernel_of(plan);
     if (!e) return SK_ERR_UNSUPPORTED;
     if (threads) *threads = e->threads;
     if (lds_bytes) *lds_bytes = e->lds_bytes;
@@ -136,16 +154,17 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
         return SK_ERR_UNSUPPORTED;
     // plans without split tiles run the plain kernel under either fix-up mode
     const bool atomic = plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup;
-    KernelEntry* e = find_kernel(h.in_dtype, h.blk_m, h.blk_n, h.blk_k, atomic ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS, plan->kernel_variant, whole_tile_iters(plan));
+    bool across;
+    KernelEntry* e = kernel_of(plan, &across);
     if (!e) return SK_ERR_UNSUPPORTED;
     if (plan->needs_fixup && !workspace && !(atomic && h.out_dtype == SK_F32)) return SK_ERR_WORKSPACE;
     const bool aligned = (h.K % e->piece_elems == 0) && (h.N % e->piece_elems == 0);   // whole 16-byte pieces per row
-    kernel_fn fn = aligned ? e->aligned : e->generic;
+    kernel_fn fn = across ? e->across : aligned ? e->aligned : e->generic;
 
     if (e->max_resident.load() < 0) {
         // first use on this process: allow the large LDS footprint and ask how many workgroups fit at once
-        for (kernel_fn f : {e->aligned, e->generic})
-            if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, e->lds_bytes)))
+        for (kernel_fn f : {e->aligned, e->generic, e->across})
+            if (f && !hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, e->lds_bytes)))
                 return SK_ERR_HIP;
         int dev = 0, cus = 0, per_cu = 0;
         if (!hip_ok(hipGetDevice(&dev)) || !hip_ok(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)))

@@ -272,6 +272,21 @@ __device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
     return (int)fast_div((uint32_t)(t * g.ipt + g.ipw - 1), g.div_ipw) + j;
 }
 
+// Position of a tile index in the tile grid under the plan's tile order.
+__device__ __forceinline__ void tile_position(const GemmArgs& g, int tile, int& tm, int& tn) {
+    if (g.tile_order == SK_ORDER_ROW_MAJOR) {
+        tm = (int)fast_div((uint32_t)tile, g.div_tiles_n);
+        tn = tile - tm * g.tiles_n;
+    } else {                                     // bands of 8 tile rows, walked column by column
+        const uint32_t per_band = (uint32_t)(SK_GROUP_ROWS * g.tiles_n);
+        const uint32_t band = fast_div((uint32_t)tile, g.div_band), within = (uint32_t)tile - band * per_band;
+        const int left = g.tiles_m - (int)band * SK_GROUP_ROWS;
+        const uint32_t rows = (uint32_t)(left < SK_GROUP_ROWS ? left : SK_GROUP_ROWS);
+        tn = (int)(left < SK_GROUP_ROWS ? fast_div(within, g.div_last_rows) : within / (uint32_t)SK_GROUP_ROWS);
+        tm = (int)band * SK_GROUP_ROWS + (int)(within - (uint32_t)tn * rows);
+    }
+}
+
 // 16 bytes whose address is only known to be a multiple of the element size (rows of a matrix whose
 // leading dimension is not a multiple of 8 elements start anywhere); the compiler picks the access.
 struct __attribute__((packed, aligned(1))) Piece1 { u32x4 v; };
@@ -1265,17 +1280,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
             return false;
         }
         int tm, tn;
-        if (g.tile_order == SK_ORDER_ROW_MAJOR) {
-            tm = (int)fast_div((uint32_t)tile, g.div_tiles_n);
-            tn = tile - tm * g.tiles_n;
-        } else {                                 // bands of 8 tile rows, walked column by column
-            const uint32_t per_band = (uint32_t)(SK_GROUP_ROWS * g.tiles_n);
-            const uint32_t band = fast_div((uint32_t)tile, g.div_band), within = (uint32_t)tile - band * per_band;
-            const int left = g.tiles_m - (int)band * SK_GROUP_ROWS;
-            const uint32_t rows = (uint32_t)(left < SK_GROUP_ROWS ? left : SK_GROUP_ROWS);
-            tn = (int)(left < SK_GROUP_ROWS ? fast_div(within, g.div_last_rows) : within / (uint32_t)SK_GROUP_ROWS);
-            tm = (int)band * SK_GROUP_ROWS + (int)(within - (uint32_t)tn * rows);
-        }
+        tile_position(g, tile, tm, tn);
         m0 = tm * C::BM;
         n0 = tn * C::BN;
         return true;
@@ -1419,6 +1424,8 @@ struct KernelEntry {
     int whole_tiles_choice = 0;          // > 0: the library launches this variant instead of variant 0 for plans without split
                                          // tiles whose tiles have at least this many k-iterations
     kernel_fn aligned, generic;
+    kernel_fn across = nullptr;          // the MAC loop that runs on across the tiles of a workgroup (streamk_whole_tiles.h), and the fewest
+    int across_iters = 0;                // k-iterations per tile that it takes; for plans without split tiles, aligned, with 16-bit output
     int threads, lds_bytes, piece_elems;
     std::atomic<int> max_resident{-1};   // co-resident workgroups on the device, -1 = not yet asked
     KernelEntry(int d, int m, int n, int k, int v, int fx, kernel_fn a, kernel_fn g, int t, int l, int pe)
@@ -1488,6 +1495,12 @@ void register_fp8(KernelEntry** t, int* n);
 void register_bf16_low(KernelEntry** t, int* n);
 void register_f16_low(KernelEntry** t, int* n);
 void register_fp8_low(KernelEntry** t, int* n);
+// ... and these add the MAC loop that runs on across tiles to the kernels it belongs to.
+void add_across_bf16(KernelEntry** t, int n);
+void add_across_f16(KernelEntry** t, int n);
+void add_across_fp8(KernelEntry** t, int n);
+// 256 rows of N 16-bit values have to stay below 2^31 bytes there (32-bit offsets inside a tile's rows).
+constexpr int64_t SK_ACROSS_MAX_N = 1 << 22;
 void register_bf16_atomic(KernelEntry** t, int* n);
 void register_f16_atomic(KernelEntry** t, int* n);
 void register_fp8_atomic(KernelEntry** t, int* n);

@@ -125,6 +125,54 @@ def test_many_interior_tiles_per_workgroup_short_k_fp8(blk, variant):
         _run_and_compare(A, B, inputs.E4M3, sk.SK_POLICY_SK1_DP, blk, grid=8, ref=ref, variant=variant)        # bf16 output
 
 
+@pytest.mark.parametrize("dtype,out_dtype,iters,cut", [
+    (inputs.BF16, sk.SK_BF16, 8, 0), (inputs.BF16, sk.SK_F16, 8, 56), (inputs.F16, sk.SK_F16, 9, 8), (inputs.F16, sk.SK_BF16, 17, 16),
+    (inputs.E4M3, sk.SK_BF16, 5, 0), (inputs.E4M3, sk.SK_F16, 5, 112), (inputs.E4M3, sk.SK_BF16, 6, 16), (inputs.E4M3, sk.SK_BF16, 9, 64)])
+@pytest.mark.parametrize("tiles_m,tiles_n,grid", [(3, 3, 2), (2, 3, 3), (1, 9, 4), (5, 1, 3)])
+def test_mac_loop_running_on_across_tiles(dtype, out_dtype, iters, cut, tiles_m, tiles_n, grid):
+    # one to five tiles per workgroup, from the fewest k-iterations that the kernel takes, whole and ragged in K, the last
+    # row and column of tiles cut short: the same sums in the same order as the eight-wave kernel, so the same bits
+    blk = (256, 256, 128 if dtype == inputs.E4M3 else 64)
+    piece = 16 if dtype == inputs.E4M3 else 8
+    K = iters * blk[2] - cut
+    for short_m, short_n in ((0, 0), (1, piece), (255, 256 - piece), (130, 128)):
+        M, N = tiles_m * 256 - short_m, tiles_n * 256 - short_n
+        A, B = inputs.uniform_pair(M, N, K, dtype, 60 + iters)
+        dA, dB = to_device(A), to_device(B)
+        got = {}
+        for variant in (1, 3):                                 # 1: plans of whole tiles run that loop
+            for policy in (sk.SK_POLICY_DP, sk.SK_POLICY_ALL_SK):
+                r = Runner(M, N, K, policy, blk, grid, dtype, out_dtype, variant=variant)
+                whole = all(s[4] == sk.SK_ROLE_FULL for s in sk.sk_plan_segments(r.plan))
+                if whole:
+                    print("case M=%d N=%d K=%d dtype=%d policy=%d grid=%d variant=%d" % (M, N, K, dtype, policy, grid, variant), flush=True)
+                    for _ in range(2):
+                        r.D.fill_(-1)
+                        r.run(dA, dB)
+                    got.setdefault(variant, []).append(r.result())
+                r.close()
+        assert len(got[1]) == len(got[3]) and all(np.array_equal(d, got[3][0]) for d in got[1])
+        rows = np.unique(np.array([0, M - 1, M // 2, min(M - 1, 255), min(M - 1, 256)]))
+        assert G.rel_error(got[1][0][rows], G.gemm_fp64(A, B, ODT[dtype], rows=rows)) <= TOL_16
+
+
+def test_what_lies_beyond_a_ragged_k_stays_out_of_the_sums():
+    # the pieces beyond K of a last k-iteration hold other elements of A and B until they are cleared: an infinity in the
+    # last row of B reaches its own column as an infinity, and no other
+    M, N, K = 512, 512, 8 * 64 - 24
+    A, B = inputs.small_int_pair(M, N, K, inputs.BF16, 61)
+    A = np.where(A & 0x7FFF, A & 0x7FFF, 0x3F80).astype(A.dtype)           # positive, no zero
+    ref = G.gemm_fp64(A, B, G.BF16)
+    B[K - 1, 3] = 0x7F80
+    r = Runner(M, N, K, sk.SK_POLICY_DP, (256, 256, 64), 2, inputs.BF16, variant=1)
+    r.run(to_device(A), to_device(B))
+    d = r.result()
+    r.close()
+    assert np.all(np.isposinf(d[:, 3]))
+    others = np.delete(np.arange(N), 3)
+    assert G.rel_error(d[:, others], ref[:, others]) <= TOL_16
+
+
 @pytest.mark.parametrize("shape", [(77, 101, 203), (1, 64, 16), (5, 7, 3), (130, 129, 1), (300, 8, 2049), (16, 264, 520)])
 def test_ragged_and_unaligned_shapes(shape):
     M, N, K = shape
