@@ -37,6 +37,8 @@ typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
+typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
+constexpr int BUFFER_RAW = 0x00020000;               // word 3 of a buffer descriptor: raw 32-bit data, no swizzle
 
 struct GemmArgs {
     const void* A;
@@ -959,58 +961,101 @@ __device__ __forceinline__ void for_each_below_impl(F&& f, std::integer_sequence
 template <int N, class F>
 __device__ __forceinline__ void for_each_below(F&& f) { for_each_below_impl<N>(f, std::make_integer_sequence<int, N>()); }
 
-// blk += this block's share of the parked partial tiles src, src + stride, ... (`count` of them), in
-// that order, GB contributors per round trip (GB * ACC registers of loads in flight).
-template <class C, int GB>
-__device__ __forceinline__ void add_block_partials(typename Mfma<C::DT, C::MF>::Acc& blk, const float* src, int count, ptrdiff_t stride) {
-    int c = 0;
-    for (; c + GB <= count; c += GB, src += GB * stride) {
-        float v[GB][C::ACC];
+// A workgroup's slot of the workspace: the partial tile in register order, 16 bytes per lane side by side: registers 4q .. 4q + 3
+// of block b of all lanes are at ((b * ACC / 4 + q) * THREADS + thread) * 16.  Accessed at device scope (sc1), as the flags
+// are: coherent across the XCDs' L2 caches without a write-back or an invalidation.  The slot is addressed by a descriptor
+// in scalar registers (64-bit addresses per lane do not fit beside the accumulators of the large tiles).
+// WIDE: as above; otherwise register r of block b at ((b * ACC + r) * THREADS + thread) * 4 (the register-staged four-wave
+// 256 x 256 kernels, whose accumulators fill the accumulation registers: in groups of four they spilled 510 registers, in 8 bits 940).
+template <class C, bool WIDE> struct Slot {
+    static constexpr int DEVICE_SCOPE = 16;      // sc1, among the cache policy bits of the instruction
+    buffer_rsrc rsrc;
+    __device__ __forceinline__ explicit Slot(const float* start)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(start), 0, C::BM * C::BN * 4, BUFFER_RAW)) {}
+    template <class Acc> __device__ __forceinline__ void park(int block, const Acc& acc) const {
+        if constexpr (WIDE) {
 #pragma unroll
-        for (int j = 0; j < GB; j++)
+            for (int q = 0; q < C::ACC / 4; q++)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]}),
+                                                       rsrc, (int)threadIdx.x * 16, (block * (C::ACC / 4) + q) * C::THREADS * 16, DEVICE_SCOPE);
+        } else {
 #pragma unroll
             for (int r = 0; r < C::ACC; r++)
-                v[j][r] = __hip_atomic_load(src + j * stride + r * C::THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[r]), rsrc, (int)threadIdx.x * 4, (block * C::ACC + r) * C::THREADS * 4, DEVICE_SCOPE);
+        }
+    }
+    template <class Acc> __device__ __forceinline__ void fetch(int block, Acc& v) const {
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int q = 0; q < C::ACC / 4; q++) {
+                const f32x4 w = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)threadIdx.x * 16, (block * (C::ACC / 4) + q) * C::THREADS * 16, DEVICE_SCOPE));
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[4 * q + e] = w[e];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < C::ACC; r++)
+                v[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)threadIdx.x * 4, (block * C::ACC + r) * C::THREADS * 4, DEVICE_SCOPE));
+        }
+    }
+};
+
+template <class C, bool TR> constexpr bool WIDE_SLOT = TR || C::ACC_REGS < 256;
+
+// Blocks FIRST .. FIRST + N - 1 of a wave tile: blks += their share of the parked partial tiles src, src + stride, ...
+// (`count` of them), in that order, one contributor per round trip.
+template <class C, bool WIDE, int FIRST, int N>
+__device__ __forceinline__ void add_block_partials(typename Mfma<C::DT, C::MF>::Acc (&blks)[N], const float* src, int count, ptrdiff_t stride) {
+#pragma unroll 1
+    for (int c = 0; c < count; c++, src += stride) {
+        typename Mfma<C::DT, C::MF>::Acc v[N];
+        const Slot<C, WIDE> slot(src);
+#pragma unroll
+        for (int b = 0; b < N; b++) slot.fetch(FIRST + b, v[b]);
         __builtin_amdgcn_sched_barrier(0);     // all loads of the round trip in flight before the first addition waits for one
 #pragma unroll
-        for (int j = 0; j < GB; j++)
+        for (int b = 0; b < N; b++)
 #pragma unroll
-            for (int r = 0; r < C::ACC; r++) blk[r] += v[j][r];
-    }
-    for (; c < count; c++, src += stride) {
-        float v[C::ACC];
-#pragma unroll
-        for (int r = 0; r < C::ACC; r++)
-            v[r] = __hip_atomic_load(src + r * C::THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int r = 0; r < C::ACC; r++) blk[r] += v[r];
+            for (int r = 0; r < C::ACC; r++) blks[b][r] += v[b][r];
     }
 }
 
 // sum += the parked partial tiles src, src + stride, ... (`count` of them, this lane's share), in
 // that order.  Tiles with at most 64 accumulators per lane: a contributor's whole share is
 // fetched at once and G contributors per round trip (about 64 registers of loads in flight).
-// Bigger tiles: block by block, the shares of two contributors per round trip.
-template <class C>
+// The 256 x 256 tile: what bounds an owner is the chain of its round trips, each of which fetches what the registers beside the
+// accumulators hold.  SUM_BLOCKS blocks of one contributor each, four round trips for a tile with one contributor, the commonest
+// case where the tiles are deep; one block of two contributors each were eight of them.  With that and 16 bytes per lane and
+// access instead of 4 (all tiles), us, before -> two blocks -> and 16 bytes: 4608 x 4608 x 1024 65.6 -> 54.3 -> 52.9 (all tiles split),
+// 256 x 512 x 16384 101 -> 84 -> 76 (127 contributors), 3848 x 4232 x 4104 136 -> 126 -> 125, 6144 x 4096 x 2048 105 -> 93 -> 93;
+// 128 x 8192 x 8192 with 128 x 128 tiles 37.0 -> 36.1, 1 x 4096 x 4096 9.81 -> 9.69.  Four blocks spill 46 registers and more.
+template <class C> constexpr int SUM_BLOCKS = 2;
+template <class C, bool WIDE>
 __device__ __forceinline__ void add_partials(typename Mfma<C::DT, C::MF>::Acc (&sum)[C::MI][C::NI], const float* src, int count, ptrdiff_t stride) {
+    typedef typename Mfma<C::DT, C::MF>::Acc Acc;
     if constexpr (C::ACC_REGS > 64) {
+        constexpr int N = SUM_BLOCKS<C>;
+        for_each_below<C::MI * C::NI / N>([&](auto chunk) {
+            constexpr int first = decltype(chunk)::value * N;
+            Acc blks[N];
 #pragma unroll
-        for (int mi = 0; mi < C::MI; mi++)
+            for (int b = 0; b < N; b++) blks[b] = sum[(first + b) / C::NI][(first + b) % C::NI];
+            add_block_partials<C, WIDE, first, N>(blks, src, count, stride);
 #pragma unroll
-            for (int ni = 0; ni < C::NI; ni++) {
-                add_block_partials<C, 32 / C::ACC>(sum[mi][ni], src + ((mi * C::NI + ni) * C::ACC) * C::THREADS, count, stride);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int b = 0; b < N; b++) sum[(first + b) / C::NI][(first + b) % C::NI] = blks[b];
+            __builtin_amdgcn_sched_barrier(0);
+        });
     } else {
     constexpr int G = 64 / C::ACC_REGS < 8 ? 64 / C::ACC_REGS : 8;
     auto add_group = [&](const float* p, auto cnt) {
         constexpr int CNT = decltype(cnt)::value;
-        float v[CNT][C::ACC_REGS];
+        Acc v[CNT][C::MI * C::NI];
 #pragma unroll
-        for (int j = 0; j < CNT; j++)
+        for (int j = 0; j < CNT; j++) {
+            const Slot<C, WIDE> slot(p + j * stride);
 #pragma unroll
-            for (int i = 0; i < C::ACC_REGS; i++)
-                v[j][i] = __hip_atomic_load(p + j * stride + i * C::THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int b = 0; b < C::MI * C::NI; b++) slot.fetch(b, v[j][b]);
+        }
         __builtin_amdgcn_sched_barrier(0);     // all loads of the round trip in flight before the first addition waits for one
 #pragma unroll
         for (int j = 0; j < CNT; j++)
@@ -1019,7 +1064,7 @@ __device__ __forceinline__ void add_partials(typename Mfma<C::DT, C::MF>::Acc (&
 #pragma unroll
                 for (int ni = 0; ni < C::NI; ni++)
 #pragma unroll
-                    for (int r = 0; r < C::ACC; r++) sum[mi][ni][r] += v[j][(mi * C::NI + ni) * C::ACC + r];
+                    for (int r = 0; r < C::ACC; r++) sum[mi][ni][r] += v[j][mi * C::NI + ni][r];
     };
     int c = 0;
     for (; c + G <= count; c += G, src += G * stride) add_group(src, std::integral_constant<int, G>());
@@ -1170,35 +1215,45 @@ __device__ __forceinline__ void reduce_and_store(const GemmArgs& g, int row0, in
     constexpr int NB = STORE_BLOCKS<C, OUT, TR>;
     // Tiles with few accumulators per lane fetch a contributor's whole share at once (one round trip
     // per contributor instead of one per block and contributor); the big tiles have no registers for that.
-    constexpr bool WHOLE = C::ACC_REGS <= 64;
+    constexpr bool WHOLE = C::ACC_REGS <= 64, WIDE = WIDE_SLOT<C, TR>;
     Acc sum[WHOLE ? C::MI : 1][WHOLE ? C::NI : 1];
     if constexpr (WHOLE) {
 #pragma unroll
         for (int mi = 0; mi < C::MI; mi++)
 #pragma unroll
             for (int ni = 0; ni < C::NI; ni++) sum[mi][ni] = acc[mi][ni];
-        add_partials<C>(sum, part0, n_contrib, part_stride);
+        add_partials<C, WIDE>(sum, part0, n_contrib, part_stride);
     }
     // (unrolled by instantiation: written as loops the four-wave kernels' bodies exceed the compiler's limit for
     // unrolling, and accumulators indexed at run time would live in memory)
-    for_each_below<C::MI * C::NI / NB>([&](auto index) {
-        constexpr int mi = decltype(index)::value * NB / C::NI, ni = decltype(index)::value * NB % C::NI;
-        Acc blks[NB];
+    if constexpr (WHOLE) {
+        for_each_below<C::MI * C::NI / NB>([&](auto index) {
+            constexpr int mi = decltype(index)::value * NB / C::NI, ni = decltype(index)::value * NB % C::NI;
+            Acc blks[NB];
 #pragma unroll
-        for (int b = 0; b < NB; b++) {
-            if constexpr (WHOLE) {
-                blks[b] = sum[mi][ni + b];
-            } else {
-                blks[b] = acc[mi][ni + b];
-                const float* src = part0 + ((mi * C::NI + ni + b) * C::ACC) * C::THREADS;
-                // two contributors' shares of this block per round trip (all the registers allow), added in
-                // the same fixed order as one by one
-                add_block_partials<C, 32 / C::ACC>(blks[b], src, n_contrib, part_stride);
-            }
-        }
-        store_blocks<C, OUT, EDGE, TR, NB>(g, row0 + mi * C::MF, col0 + ni * C::MF, blks);
-        __builtin_amdgcn_sched_barrier(0);
-    });
+            for (int b = 0; b < NB; b++) blks[b] = sum[mi][ni + b];
+            store_blocks<C, OUT, EDGE, TR, NB>(g, row0 + mi * C::MF, col0 + ni * C::MF, blks);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    } else {
+        constexpr int N = SUM_BLOCKS<C>;
+        static_assert(N % NB == 0 && C::MI * C::NI % N == 0, "whole chunks of blocks, of whole pairs");
+        for_each_below<C::MI * C::NI / N>([&](auto chunk) {
+            constexpr int first = decltype(chunk)::value * N;
+            Acc sums[N];
+#pragma unroll
+            for (int b = 0; b < N; b++) sums[b] = acc[(first + b) / C::NI][(first + b) % C::NI];
+            add_block_partials<C, WIDE, first, N>(sums, part0, n_contrib, part_stride);
+            for_each_below<N / NB>([&](auto index) {
+                constexpr int b0 = decltype(index)::value * NB, mi = (first + b0) / C::NI, ni = (first + b0) % C::NI;
+                Acc blks[NB];
+#pragma unroll
+                for (int b = 0; b < NB; b++) blks[b] = sums[b0 + b];
+                store_blocks<C, OUT, EDGE, TR, NB>(g, row0 + mi * C::MF, col0 + ni * C::MF, blks);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+    }
 }
 
 // Atomic fix-up (the accumulation step of Algorithm 1): a segment that covers only part of the tile's
@@ -1323,26 +1378,15 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
                 const int members = (j + SK_TREE_GROUP - 1 <= n_all ? j + SK_TREE_GROUP - 1 : n_all) - j;
                 if (wave == 0) wait_flags(g, x + dir, members, dir);
                 __syncthreads();
-                const float* mp = g.partials + (ptrdiff_t)(x + dir) * (C::BM * C::BN) + tid;
-                asm volatile("" : "+v"(mp));
-                add_partials<C>(acc, mp, members, slot_stride);
+                add_partials<C, WIDE_SLOT<C, TR>>(acc, g.partials + (ptrdiff_t)(x + dir) * (C::BM * C::BN), members, slot_stride);
             }
-            // park the accumulators (register order, coalesced), then signal.
-            // Partial tiles are stored and loaded with device-scope atomic accesses (one dword
-            // per lane, lanes contiguous): these are coherent across the XCDs' L2 caches by
-            // themselves, so no L2 write-back / invalidate is needed around the exchange.
-            // (the empty asm statements keep the per-block addresses from being computed once, ahead
-            // of the persistent loop, where they would occupy registers for the whole kernel)
-            float* slot = g.partials + (size_t)x * (C::BM * C::BN) + tid;
-            asm volatile("" : "+v"(slot));
+            // park the accumulators, then signal
+            const Slot<C, WIDE_SLOT<C, TR>> slot(g.partials + (size_t)x * (C::BM * C::BN));
 #pragma unroll
             for (int mi = 0; mi < C::MI; mi++)
 #pragma unroll
                 for (int ni = 0; ni < C::NI; ni++) {
-#pragma unroll
-                    for (int r = 0; r < C::ACC; r++)
-                        __hip_atomic_store(slot + ((mi * C::NI + ni) * C::ACC + r) * C::THREADS, acc[mi][ni][r],
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    slot.park(mi * C::NI + ni, acc[mi][ni]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             wait_vmcnt<0>();                      // every lane's part of the partial tile has reached memory
@@ -1368,8 +1412,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         int row0 = m0 + wm * C::WTM + (TR ? lane % C::MF : 4 * (lane / C::MF));
         int col0 = n0 + wn * C::WTN + (TR ? 4 * (lane / C::MF) : lane % C::MF);
         asm volatile("" : "+v"(row0), "+v"(col0));
-        const float* part0 = g.partials + (ptrdiff_t)(x + dir) * (C::BM * C::BN) + tid;
-        asm volatile("" : "+v"(part0));
+        const float* part0 = g.partials + (ptrdiff_t)(x + dir) * (C::BM * C::BN);
         const bool edge = m0 + C::BM > g.M || n0 + C::BN > g.N;
         if (g.out_dtype == SK_BF16) {
             if (edge) reduce_and_store<C, SK_BF16, true, TR>(g, row0, col0, part0, n_contrib, part_stride, acc);

@@ -22,9 +22,6 @@
 
 namespace streamk_detail {
 
-// Stores that lie beyond the end of the buffer are dropped by the hardware: edge tiles need no branches.
-typedef __amdgpu_buffer_rsrc_t buffer_rsrc;
-constexpr int BUFFER_RAW = 0x00020000;               // word 3 of a descriptor: raw 32-bit data, no swizzle
 
 template <class C> struct WholeTiles {
     static_assert(C::FINE && C::NSA == C::NSB + 1 && C::MF == 32 && C::NI % 2 == 0 && C::KK % 2 == 0 && C::A_WAVES == C::NW, "layout of the kernel");
@@ -156,7 +153,8 @@ __device__ __forceinline__ void whole_tiles(const GemmArgs& g, unsigned char* sm
         }
     };
 
-    // ---- results: the blocks of the previous tile, packed, and where they go
+    // ---- results: the blocks of the previous tile, packed, and where they go (stores that lie beyond the end of the buffer
+    // are dropped by the hardware: edge tiles need no branches)
     u32x4 out[W::KEPT][2][2];
     buffer_rsrc d_rsrc;
     uint32_t d_off[2];                                 // byte offset of this lane's first store of an even / odd pair of blocks

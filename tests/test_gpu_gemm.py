@@ -4,6 +4,8 @@ Tolerances: max relative error <= 1e-2 with fp16 / bf16 output and
 <= 1e-4 on the fp32-accumulator output, with err = max |d - ref| / max(|ref|, rms(ref)).
 Integer-valued inputs are exact in fp32 under every schedule, so they are compared bit-exactly.
 """
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -564,8 +566,8 @@ def test_paper_suite_shapes_fp16_sampled_rows(shape):
 @pytest.mark.parametrize("blk,shape", [((32, 128, 64), (64, 208, 7872)), ((16, 128, 64), (48, 256, 6208)),
                                        ((64, 128, 64), (128, 128, 16448)), ((128, 128, 64), (128, 256, 8256)),
                                        ((32, 128, 64), (32, 1024, 4160)), (None, (112, 128, 3552)),
-                                       # 128 accumulators per lane: reduced block by block, two contributors per
-                                       # round trip; 32 - 33 contributors per tile, then 67 (an odd one left over)
+                                       # 128 accumulators per lane: reduced two blocks at a time; 32 - 33 contributors
+                                       # per tile, then 67
                                        ((256, 256, 64), (300, 512, 4160)), ((256, 256, 64), (256, 256, 4352))])
 def test_tiles_shared_by_many_workgroups(blk, shape):
     # few tiles, long K: 16 ... 120 contributors per tile, reduced in two levels (groups of 8 behind a leader)
@@ -601,6 +603,22 @@ def test_every_small_contributor_count(blk):
         _run_and_compare(A, B, inputs.BF16, sk.SK_POLICY_ALL_SK, blk, grid=2 * (c + 1), out_dtype=sk.SK_F32, ref=ref, exact=True, launches=2)
         _run_and_compare(A, B, inputs.BF16, sk.SK_POLICY_ALL_SK, blk, grid=2 * (c + 1), out_dtype=sk.SK_BF16, ref=ref)     # sums beyond 256 round in bf16
         _run_and_compare(A, B, inputs.BF16, sk.SK_POLICY_ALL_SK, blk, grid=2 * (c + 1), out_dtype=sk.SK_F32, ref=ref, exact=True, k_aligned=False)
+
+
+@pytest.mark.parametrize("blk,dtype,variant", [((256, 256, 64), inputs.BF16, 3), ((256, 256, 64), inputs.BF16, 1), ((256, 256, 32), inputs.F16, 0),
+                                               ((256, 128, 64), inputs.F16, 1), ((256, 256, 128), inputs.E4M3, 0), ((256, 256, 128), inputs.E4M3, 1),
+                                               ((128, 256, 128), inputs.E4M3, 0)])
+def test_partial_tiles_of_the_large_tiles(blk, dtype, variant):
+    # 1, 2, 3 and 17 contributors per tile (17: two levels), rows on the 16-byte grid and off it (slots in groups of four registers
+    # or register by register), an edge tile
+    bm, bn, bk = blk
+    for c, off in itertools.product((1, 2, 3, 17), (0, 3)):
+        M, N, K = bm - 5, 2 * bn - off, bk * 2 * (c + 1) - off
+        A, B = inputs.small_int_pair(M, N, K, dtype, 90 + c)
+        ref = G.gemm_fp64(A, B, ODT[dtype])
+        for k_aligned in (True, False):
+            _run_and_compare(A, B, dtype, sk.SK_POLICY_ALL_SK, blk, grid=2 * (c + 1), out_dtype=sk.SK_F32, ref=ref, exact=True, launches=2,
+                             k_aligned=k_aligned, variant=variant)
 
 
 @pytest.mark.parametrize("blk", [(128, 128, 64), (256, 128, 64), (256, 256, 64), (32, 128, 64)])
