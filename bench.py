@@ -15,7 +15,7 @@ Default run, all on seeded synthetic inputs resident in HBM:
 Prints ONE JSON line.  `roofline` belongs to the GEMM kernel of the headline workload: kernel time from
 HIP events on the launch stream around back-to-back launches; `traffic` = measured HBM bytes per launch
 from profiles/hbm_traffic_streamk_gemm_kernel.txt (written by paper_2408_11417_amd/hbm_traffic.py from
-rocprofv3 counter runs of this file), null if the file has no row for the workload and policy.
+rocprofv3 counter runs of this file), null if the file has no row for the workload, policy and kernel.
 """
 import argparse
 import json
@@ -57,12 +57,13 @@ def workload(name):
     return c
 
 
-def measured_traffic(name, policy):
-    """HBM bytes per launch (reads + writes) of a workload under a policy, from the tracked summary."""
+def measured_traffic(name, policy, kernel):
+    """HBM bytes per launch (reads + writes) of a workload under a policy, from the tracked summary; None unless
+    they were measured on the kernel that the plan runs."""
     try:
         for line in open(TRAFFIC_FILE):
             f = line.split()
-            if len(f) >= 4 and f[0] == name and f[1] == policy:
+            if len(f) == 5 and f[:2] == [name, policy] and f[4] == kernel:
                 return float(f[2]) + float(f[3])
     except OSError:
         pass
@@ -212,8 +213,9 @@ class Bench:
             roof = {"bound": "mfma", "achieved": round(self.flops / (kernel_ms * 1e-3) / 1e12, 2), "peak": PEAK_TFLOPS[dtype_name],
                     "unit": "TFLOP/s"}
         roof["frac"] = round(roof["achieved"] / roof["peak"], 4)
-        roof.update(traffic=None if args.ascending else measured_traffic(self.name, sk.POLICY_NAMES[sel]),
-                    algorithmic_bytes=alg_bytes, kernel="streamk_gemm_kernel", kernel_ms=round(kernel_ms, 5),
+        kernel = sk.sk_plan_kernel_name(self.plans[sel])
+        roof.update(traffic=None if args.ascending else measured_traffic(self.name, sk.POLICY_NAMES[sel], kernel),
+                    algorithmic_bytes=alg_bytes, kernel=kernel, kernel_ms=round(kernel_ms, 5),
                     step_event_ms=round(step_ms, 5))
         if self.hbm_bound:
             # reported apart: the same launches on one operand set, which the 256 MB memory-side cache then serves

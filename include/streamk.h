@@ -327,6 +327,12 @@ int sk_plan_set_kernel_variant(sk_plan_t* plan, int variant);
  * the plan's tile, input type and fix-up mode). */
 int sk_plan_kernel_info(const sk_plan_t* plan, int32_t* threads, int32_t* lds_bytes, int32_t* variant);
 
+/* Name of the kernel function behind that launch, as a profiler's kernel trace shows it before the template
+ * arguments (host only, no GPU call): "streamk_whole_tiles_kernel" for the second form of the four-wave
+ * 256 x 256 kernel (see sk_plan_set_kernel_variant), "streamk_gemm_kernel" otherwise.  The string is static.
+ * NULL where sk_plan_kernel_info returns an error. */
+const char* sk_plan_kernel_name(const sk_plan_t* plan);
+
 void sk_plan_destroy(sk_plan_t* plan);
 
 /* Measurement aid: the rate of the matrix-core instructions of the MAC loop (Sec. 2: the GEMM runs on

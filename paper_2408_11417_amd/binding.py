@@ -34,7 +34,7 @@ SK_STREAMK_FIRST, SK_DATA_PARALLEL_FIRST = 0, 1
 SK_SEGMENTS_ASCENDING, SK_SEGMENTS_K_ALIGNED = 0, 1
 
 EXPORTS = ("sk_plan", "sk_plan_info", "sk_plan_ranges", "sk_plan_segments", "sk_plan_tile_coords", "sk_workspace_bytes",
-           "sk_plan_set_fixup", "sk_plan_set_batch_order", "sk_plan_set_segment_order", "sk_plan_set_workspace", "sk_plan_set_spin_limit", "sk_plan_set_kernel_variant", "sk_gemm", "sk_gemm_static", "sk_plan_check", "sk_plan_kernel_info",
+           "sk_plan_set_fixup", "sk_plan_set_batch_order", "sk_plan_set_segment_order", "sk_plan_set_workspace", "sk_plan_set_spin_limit", "sk_plan_set_kernel_variant", "sk_gemm", "sk_gemm_static", "sk_plan_check", "sk_plan_kernel_info", "sk_plan_kernel_name",
            "sk_plan_destroy", "sk_mfma_peak_operand_bytes", "sk_mfma_peak_launch", "sk_default_tile", "sk_plan_estimate_us", "bloom_winner_mask", "bloom_build", "bloom_insert", "bloom_query",
            "bloom_query_many", "bloom_bits", "bloom_serialize", "bloom_deserialize", "bloom_shape_key", "bloom_murmur3_32", "bloom_destroy", "sk_status_str", "sk_last_hip_error")
 
@@ -94,6 +94,8 @@ _lib.sk_mfma_peak_launch.argtypes = [_int, _vp, _vp, _int, _int, _vp, ctypes.POI
 _lib.sk_gemm_static.argtypes = [_vp, _vp, _vp, _vp, _vp]
 _lib.sk_plan_check.argtypes = [_vp, _vp]
 _lib.sk_plan_kernel_info.argtypes = [_vp] + [ctypes.POINTER(ctypes.c_int32)] * 3
+_lib.sk_plan_kernel_name.argtypes = [_vp]
+_lib.sk_plan_kernel_name.restype = ctypes.c_char_p
 _lib.sk_plan_destroy.argtypes = [_vp]
 _lib.sk_plan_destroy.restype = None
 _lib.sk_default_tile.argtypes = [_i64, _i64, _i64, _int, ctypes.POINTER(ctypes.c_int32)]
@@ -255,6 +257,14 @@ def sk_plan_kernel_info(plan):
     p = [ctypes.cast(ctypes.byref(v, 4 * i), ctypes.POINTER(ctypes.c_int32)) for i in range(3)]
     _check(_lib.sk_plan_kernel_info(plan, *p), "sk_plan_kernel_info")
     return {"threads": v[0], "lds_bytes": v[1], "variant": v[2]}
+
+
+def sk_plan_kernel_name(plan):
+    """Name of the kernel function a launch of this plan would run now, as a kernel trace shows it."""
+    name = _lib.sk_plan_kernel_name(plan)
+    if name is None:
+        raise StreamKError(SK_ERR_UNSUPPORTED if plan else SK_ERR_INVALID_ARG, "sk_plan_kernel_name")
+    return name.decode()
 
 
 def sk_plan_destroy(plan):

@@ -140,6 +140,12 @@ extern "C" int sk_plan_kernel_info(const sk_plan_t* plan, int32_t* threads, int3
     return SK_OK;
 }
 
+extern "C" const char* sk_plan_kernel_name(const sk_plan_t* plan) {
+    bool across;
+    if (!plan || !kernel_of(plan, &across)) return nullptr;
+    return across ? "streamk_whole_tiles_kernel" : "streamk_gemm_kernel";
+}
+
 namespace {
 
 // The launch behind sk_gemm and sk_gemm_static: `workspace` is the device memory that holds the flag

@@ -13,7 +13,8 @@ of each counter is worth in bytes:
         --entry cfg5:DP --out profiles/hbm_traffic_streamk_gemm_kernel.txt
 
 Each --entry NAME:POLICY[,POLICY...] reads out/fetch_NAME and out/write_NAME (several policy names for one
-run: policies that are the same schedule on that workload, e.g. all seven on whole waves of tiles).  The counters are in KiB per dispatch.
+run: policies that are the same schedule on that workload, e.g. all seven on whole waves of tiles) and names the
+GEMM kernel that ran.  The counters are in KiB per dispatch.
 The calibration factor is (bytes the copy moves) / (bytes the counter reports for the copy kernel).
 CPU only; reads CSV files, nothing else.
 """
@@ -21,33 +22,39 @@ import argparse
 import csv
 import glob
 import os
+import re
 import sys
 
 COPY_BYTES = float(1 << 30)     # bench.py --calibrate-copy reads 1 GiB and writes 1 GiB per copy kernel
+GEMM_KERNEL = re.compile(r"\b(streamk_gemm_kernel|streamk_whole_tiles_kernel)\b")     # the names sk_plan_kernel_name gives
 
 
-def counter_per_dispatch(run_dir, counter, kernel_substr, biggest=False):
-    """Mean counter value over the dispatches of the kernels whose name contains kernel_substr (the
-    first such dispatch dropped when there are several: it runs cold); with biggest=True over the
-    dispatches whose value is within 10 % of the largest one of any kernel (the copy kernel)."""
+def counter_per_dispatch(run_dir, counter, biggest=False):
+    """(kernel, value): mean counter value over the dispatches of the GEMM kernel that the run launched (the
+    first one dropped when there are several: it runs cold); with biggest=True over the dispatches whose
+    value is within 10 % of the largest one of any kernel (the copy kernel)."""
     files = glob.glob(os.path.join(run_dir, "**", "*counter_collection.csv"), recursive=True)
     if not files:
         raise SystemExit("no counter_collection.csv under %s" % run_dir)
-    vals = []
+    vals, kernels = [], set()
     for f in files:
         for row in csv.DictReader(open(f)):
             if row["Counter_Name"] != counter:
                 continue
-            if biggest or kernel_substr in row["Kernel_Name"]:
+            name = GEMM_KERNEL.search(row["Kernel_Name"])
+            if biggest or name:
                 vals.append(float(row["Counter_Value"]))
+                kernels.add(name.group(1) if name else "")
     if not vals:
-        raise SystemExit("counter %s / kernel %s not found under %s" % (counter, kernel_substr, run_dir))
+        raise SystemExit("counter %s of a GEMM kernel not found under %s" % (counter, run_dir))
+    if not biggest and len(kernels) > 1:
+        raise SystemExit("the run under %s launched several GEMM kernels: %s" % (run_dir, ", ".join(sorted(kernels))))
     if biggest:
         top = max(vals)
         vals = [v for v in vals if v >= 0.9 * top]
     elif len(vals) > 1:
         vals = vals[1:]
-    return sum(vals) / len(vals)
+    return min(kernels), sum(vals) / len(vals)
 
 
 def main():
@@ -58,19 +65,21 @@ def main():
     ap.add_argument("--out", required=True)
     args = ap.parse_args()
     kib = 1024.0
-    f_copy = counter_per_dispatch(os.path.join(args.runs, "fetch_copy"), "FETCH_SIZE", "", biggest=True) * kib
-    w_copy = counter_per_dispatch(os.path.join(args.runs, "write_copy"), "WRITE_SIZE", "", biggest=True) * kib
+    f_copy = counter_per_dispatch(os.path.join(args.runs, "fetch_copy"), "FETCH_SIZE", biggest=True)[1] * kib
+    w_copy = counter_per_dispatch(os.path.join(args.runs, "write_copy"), "WRITE_SIZE", biggest=True)[1] * kib
     f_scale, w_scale = COPY_BYTES / f_copy, COPY_BYTES / w_copy
-    lines = ["# HBM bytes per launch of streamk_gemm_kernel (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, KiB per dispatch,",
+    lines = ["# HBM bytes per launch of the GEMM kernel (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, KiB per dispatch,",
              "# scaled by what the same counter reads for a plain 1 GiB device copy: fetch x %.3f, write x %.3f);" % (f_scale, w_scale),
              "# written by paper_2408_11417_amd/hbm_traffic.py; library commit %s" % args.library_commit,
-             "# workload policy fetch_bytes write_bytes"]
+             "# workload policy fetch_bytes write_bytes kernel"]
     for e in args.entry:
         name, _, policy = e.partition(":")
-        f = counter_per_dispatch(os.path.join(args.runs, "fetch_" + name), "FETCH_SIZE", "streamk_gemm_kernel") * kib * f_scale
-        w = counter_per_dispatch(os.path.join(args.runs, "write_" + name), "WRITE_SIZE", "streamk_gemm_kernel") * kib * w_scale
+        kernel, f = counter_per_dispatch(os.path.join(args.runs, "fetch_" + name), "FETCH_SIZE")
+        wrote, w = counter_per_dispatch(os.path.join(args.runs, "write_" + name), "WRITE_SIZE")
+        if kernel != wrote:
+            raise SystemExit("%s: the two runs launched different kernels, %s and %s" % (name, kernel, wrote))
         for pol in policy.split(","):
-            lines.append("%s %s %.4g %.4g" % (name, pol, f, w))
+            lines.append("%s %s %.4g %.4g %s" % (name, pol, f * kib * f_scale, w * kib * w_scale, kernel))
     with open(args.out, "w") as fh:
         fh.write("\n".join(lines) + "\n")
     print("\n".join(lines))

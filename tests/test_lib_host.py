@@ -307,6 +307,63 @@ def test_kernel_info_names_the_kernel_of_a_launch():
     sk.sk_plan_destroy(p)
 
 
+def test_kernel_name_is_that_of_the_launch():
+    lib = sk.binding._lib
+    assert lib.sk_plan_kernel_name(None) is None
+    whole, plain = "streamk_whole_tiles_kernel", "streamk_gemm_kernel"
+    for shape, policy, blk, dt, out, variant, name in [
+            ((8192, 8192, 8192), sk.SK_POLICY_DP, None, sk.SK_BF16, None, 0, whole),            # whole waves of 256 x 256 tiles
+            ((8192, 8192, 8192), sk.SK_POLICY_ALL_SK, None, sk.SK_FP8_E4M3, None, 0, whole),
+            ((8192, 8192, 8192), sk.SK_POLICY_DP, None, sk.SK_BF16, sk.SK_F32, 0, plain),       # fp32 output
+            ((8192, 8192, 8192), sk.SK_POLICY_DP, None, sk.SK_BF16, None, 3, plain),            # eight waves asked for
+            ((8192, 8192, 8193), sk.SK_POLICY_DP, None, sk.SK_BF16, None, 0, plain),            # rows off the 16-byte grid
+            ((4096, 4352, 8192), sk.SK_POLICY_SK1_DP, (256, 256, 64), sk.SK_BF16, None, 0, plain),   # split tiles
+            ((4096, 4096, 8192), sk.SK_POLICY_DP, (256, 128, 64), sk.SK_BF16, None, 0, plain)]:      # another tile
+        p = sk.sk_plan(*shape, policy, blk, 256, dt, out)
+        sk.sk_plan_set_kernel_variant(p, variant)
+        assert sk.sk_plan_kernel_name(p) == name, (shape, policy, blk, dt, out, variant)
+        sk.sk_plan_destroy(p)
+    p = sk.sk_plan(1000, 1000, 1000, sk.SK_POLICY_DP, (64, 64, 64), 256, sk.SK_BF16)   # a tile without a kernel
+    assert lib.sk_plan_kernel_name(p) is None
+    with pytest.raises(sk.StreamKError):
+        sk.sk_plan_kernel_name(p)
+    sk.sk_plan_destroy(p)
+
+
+def _counter_run(folder, counter, rows):
+    folder.mkdir()
+    lines = ["Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value"]
+    lines += ['%d,"%s",%s,%f' % (i, name, counter, value) for i, (name, value) in enumerate(rows)]
+    (folder / "out_counter_collection.csv").write_text("\n".join(lines) + "\n")
+
+
+def test_traffic_table_names_the_kernel_that_ran(tmp_path, monkeypatch):
+    import sys
+    import bench
+    from paper_2408_11417_amd import hbm_traffic
+    kib = 1 << 10
+    gemm, whole = "void streamk_detail::streamk_gemm_kernel<streamk_detail::Cfg<1> >(G)", "void streamk_detail::streamk_whole_tiles_kernel<streamk_detail::Cfg<1> >(G)"
+    for counter, prefix, scale in (("FETCH_SIZE", "fetch_", 2), ("WRITE_SIZE", "write_", 1)):
+        _counter_run(tmp_path / (prefix + "copy"), counter, [("copy", kib * kib / scale), ("fill", 3)])
+        _counter_run(tmp_path / (prefix + "cfg5"), counter, [("fill", 7 * kib), (whole, 9 * kib), (whole, 4 * kib), (whole, 2 * kib)])
+        _counter_run(tmp_path / (prefix + "cfg2"), counter, [(gemm, 5 * kib)])
+        _counter_run(tmp_path / (prefix + "mixed"), counter, [(gemm, 5 * kib), (whole, 5 * kib)])
+    table = tmp_path / "table.txt"
+    args = ["hbm_traffic", "--runs", str(tmp_path), "--out", str(table)]
+    monkeypatch.setattr(sys, "argv", args + ["--entry", "cfg5:DP,ALL_SK", "--entry", "cfg2:DP"])
+    assert hbm_traffic.main() == 0
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(table))
+    mib = float(kib * kib)
+    # the first of several dispatches is dropped; reads are worth twice what the counter says here
+    assert bench.measured_traffic("cfg5", "ALL_SK", "streamk_whole_tiles_kernel") == pytest.approx((2 + 1) * 3 * mib, rel=1e-3)
+    assert bench.measured_traffic("cfg2", "DP", "streamk_gemm_kernel") == pytest.approx((2 + 1) * 5 * mib, rel=1e-3)
+    assert bench.measured_traffic("cfg5", "DP", "streamk_gemm_kernel") is None          # measured on another kernel
+    assert bench.measured_traffic("cfg2", "ALL_SK", "streamk_gemm_kernel") is None
+    monkeypatch.setattr(sys, "argv", args + ["--entry", "mixed:DP"])
+    with pytest.raises(SystemExit):
+        hbm_traffic.main()
+
+
 # ---- Bloom -----------------------------------------------------------------------------------
 
 def test_hash_bit_exact_with_oracle():
