@@ -1390,9 +1390,12 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         // worked out at the kernel's start and kept, 40 instructions and 10 to 15 spilled scalars of the 400 and 25 ahead of the
         // first request.  With the offsets above, us: 512^3 4.80 -> 4.77, 1 x 4096 x 4096 9.80 -> 9.67, 16 x 8192 x 8192 25.3 -> 25.2,
         // 1008 x 1200 x 1040 9.68 -> 9.63, 256 x 512 x 16384 to fp32 14.86 -> 14.73.  Issuing the first requests ahead of the lanes' LDS
-        // addresses as well, another 90 instructions, made 512^3 4.92.)
+        // addresses as well, another 90 instructions, made 512^3 4.92.  Not on the register-staged path of the 64 x 64 x 128 tile, eight k-steps
+        // of one block: the reads of its MAC loop, whose order is the compiler's, then run no longer ahead of the matrix-core work,
+        // 1083 x 1021 x 4093 53.2 us, 50.7 without, 500 x 700 x 5001 30.5 / 28.6; below five k-iterations 0.1 us the other way.  The
+        // staged path of the other tiles gains from it, 32 x 128 4 %.)
         int wg = x, from_end = g.k_aligned, thread = tid;
-        asm volatile("" : "+s"(wg), "+s"(from_end), "+v"(thread));
+        if constexpr (ALIGNED || C::MI * C::NI > 1 || C::KK < 8) asm volatile("" : "+s"(wg), "+s"(from_end), "+v"(thread));
         const bool split = k_begin > 0 || k_end < g.ipt;
         const bool contributor = from_end ? k_end < g.ipt : k_begin > 0;
         const int dir = from_end ? -1 : 1;
