@@ -147,6 +147,7 @@ def test_mac_loop_running_on_across_tiles(dtype, out_dtype, iters, cut, tiles_m,
                 r = Runner(M, N, K, policy, blk, grid, dtype, out_dtype, variant=variant)
                 whole = all(s[4] == sk.SK_ROLE_FULL for s in sk.sk_plan_segments(r.plan))
                 if whole:
+                    assert sk.sk_plan_kernel_name(r.plan) == ("streamk_whole_tiles_kernel" if variant == 1 else "streamk_gemm_kernel")
                     print("case M=%d N=%d K=%d dtype=%d policy=%d grid=%d variant=%d" % (M, N, K, dtype, policy, grid, variant), flush=True)
                     for _ in range(2):
                         r.D.fill_(-1)
@@ -173,6 +174,61 @@ def test_what_lies_beyond_a_ragged_k_stays_out_of_the_sums():
     assert np.all(np.isposinf(d[:, 3]))
     others = np.delete(np.arange(N), 3)
     assert G.rel_error(d[:, others], ref[:, others]) <= TOL_16
+
+
+@pytest.mark.parametrize("dtype,special,cut", [(inputs.BF16, 0x7F80, 24), (inputs.F16, 0x7C00, 8), (inputs.F16, 0x7E00, 56), (inputs.E4M3, 0x7F, 16), (inputs.E4M3, 0x7F, 112)])
+@pytest.mark.parametrize("operand", ["A", "B"])
+def test_stand_ins_for_a_ragged_k_stay_out_of_the_sums(dtype, special, cut, operand):
+    # beyond K a last k-iteration holds its own first columns of A and the last row of B until both are cleared: an infinity
+    # (in 8 bits, which have none, and in one case of 16 the NaN) there reaches its own row or column as it is and no other, in
+    # each of a workgroup's three tiles (a piece of A left over meets B's zeros and the other way round: 0 * inf would be NaN)
+    blk = (256, 256, 128 if dtype == inputs.E4M3 else 64)
+    M, N, K = 768, 512, 8 * blk[2] - cut
+    sign, one = {inputs.BF16: (0x7FFF, 0x3F80), inputs.F16: (0x7FFF, 0x3C00), inputs.E4M3: (0x7F, 0x38)}[dtype]
+    A, B = ((np.where(X & sign, X & sign, one)).astype(X.dtype) for X in inputs.small_int_pair(M, N, K, dtype, 62))    # positive, no zero
+    ref = G.gemm_fp64(A, B, ODT[dtype])
+    at = [5, 300, 767] if operand == "A" else [3, 400, 511]
+    if operand == "A":
+        A[at, K // blk[2] * blk[2]] = special
+    else:
+        B[K - 1, at] = special
+    r = Runner(M, N, K, sk.SK_POLICY_DP, blk, 2, dtype, sk.SK_F16 if dtype == inputs.F16 else sk.SK_BF16, variant=1)
+    assert sk.sk_plan_kernel_name(r.plan) == "streamk_whole_tiles_kernel"
+    print("case operand=%s dtype=%d K=%d" % (operand, dtype, K), flush=True)
+    for _ in range(2):
+        r.D.fill_(-1)
+        r.run(to_device(A), to_device(B))
+    d = r.result()
+    r.close()
+    if operand == "B":
+        d, ref = d.T, ref.T
+    assert np.all(np.isposinf(d[at]) if special in (0x7F80, 0x7C00) else np.isnan(d[at]))
+    rest = np.delete(np.arange(len(d)), at)
+    assert G.rel_error(d[rest], ref[rest]) <= TOL_16
+
+
+def test_loop_across_tiles_at_its_largest_row():
+    # the last N that its 32-bit offsets take: 256 rows of D end 2^12 bytes below 2^31.  The same bits as from the eight-wave kernel, and
+    # integers up to 4 * 456 = 1824 whose sums an f16 result holds exactly to 2048
+    M, N, K = 256, 2 ** 22 - 8, 456
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(63)
+    A = torch.randint(-2, 3, (M, K), generator=gen, device="cuda", dtype=torch.int8).to(torch.float16)
+    B = torch.randint(-2, 3, (K, N), generator=gen, device="cuda", dtype=torch.int8).to(torch.float16)
+    got = []
+    for variant in (0, 3):
+        r = Runner(M, N, K, sk.SK_POLICY_DP, (256, 256, 64), 256, inputs.F16, variant=variant)
+        assert sk.sk_plan_kernel_name(r.plan) == ("streamk_gemm_kernel" if variant else "streamk_whole_tiles_kernel")
+        print("case M=%d N=%d K=%d variant=%d" % (M, N, K, variant), flush=True)
+        r.D.fill_(-1)
+        r.run(A, B)
+        torch.cuda.synchronize()
+        got.append(r.D)
+        r.close()
+    assert torch.equal(got[0], got[1])
+    for cols in (slice(0, 300), slice(N // 2 - 300, N // 2 + 300), slice(N - 300, N)):
+        ref = A.cpu().double() @ B[:, cols].cpu().double()
+        assert torch.equal(got[0][:, cols].cpu().view(torch.float16).double(), ref)
 
 
 @pytest.mark.parametrize("shape", [(77, 101, 203), (1, 64, 16), (5, 7, 3), (130, 129, 1), (300, 8, 2049), (16, 264, 520)])

@@ -330,6 +330,46 @@ def test_kernel_name_is_that_of_the_launch():
     sk.sk_plan_destroy(p)
 
 
+@pytest.mark.parametrize("tiles,grid,from_iters", [(2, 2, 56), (3, 2, 32), (4, 2, 32), (5, 2, 8), (9, 2, 8)])
+@pytest.mark.parametrize("dtype,out", [(sk.SK_BF16, sk.SK_F16), (sk.SK_F16, sk.SK_F16)])
+def test_loop_across_tiles_is_taken_from_its_threshold_on_16_bits(tiles, grid, from_iters, dtype, out):
+    # one, two, and three or more tiles per workgroup; below it the eight-wave kernel, also from 48 on
+    for iters in (from_iters - 1, from_iters):
+        for K in (64 * iters, 64 * iters - 56):
+            for out_dtype, variant in ((out, 0), (sk.SK_F32, 0), (out, 1), (out, 3)):
+                p = sk.sk_plan(256, 256 * tiles, K, sk.SK_POLICY_DP, (256, 256, 64), grid, dtype, out_dtype)
+                sk.sk_plan_set_kernel_variant(p, variant)
+                name, threads = sk.sk_plan_kernel_name(p), sk.sk_plan_kernel_info(p)["threads"]
+                sk.sk_plan_destroy(p)
+                if variant == 0 and out_dtype == sk.SK_F32:          # fp32 output: never; four waves from 48 iterations on
+                    assert (name, threads) == ("streamk_gemm_kernel", 256 if iters >= 48 else 512)
+                elif variant == 3 or (variant == 0 and iters < from_iters):
+                    assert (name, threads) == ("streamk_gemm_kernel", 512)
+                else:                                                # asked for: from the fewest iterations that it can take, 8
+                    assert (name, threads) == ("streamk_whole_tiles_kernel" if iters >= 8 else "streamk_gemm_kernel", 256)
+
+
+@pytest.mark.parametrize("tiles", [1, 2, 3, 5])
+def test_loop_across_tiles_is_taken_from_its_threshold_on_8_bits(tiles):
+    for K, name, threads in ((512, "streamk_gemm_kernel", 512), (528, "streamk_whole_tiles_kernel", 256), (640, "streamk_whole_tiles_kernel", 256),
+                             (648, "streamk_gemm_kernel", 512)):     # (648: rows off the 16-byte grid)
+        p = sk.sk_plan(256, 256 * tiles, K, sk.SK_POLICY_DP, (256, 256, 128), 2, sk.SK_FP8_E4M3)
+        assert (sk.sk_plan_kernel_name(p), sk.sk_plan_kernel_info(p)["threads"]) == (name, threads), K
+        sk.sk_plan_destroy(p)
+
+
+def test_loop_across_tiles_ends_at_its_largest_row():
+    # 256 rows of 16-bit results have to stay below 2^31 bytes
+    for N, name in ((2 ** 22 - 16, "streamk_whole_tiles_kernel"), (2 ** 22, "streamk_gemm_kernel")):
+        for dt, blk in ((sk.SK_BF16, (256, 256, 64)), (sk.SK_FP8_E4M3, (256, 256, 128))):
+            p = sk.sk_plan(256, N, 480, sk.SK_POLICY_DP, blk, 256, dt)       # 8 (4) iterations; 8 bits: one too few
+            assert sk.sk_plan_kernel_name(p) == (name if dt == sk.SK_BF16 else "streamk_gemm_kernel")
+            sk.sk_plan_destroy(p)
+        p = sk.sk_plan(256, N, 528, sk.SK_POLICY_DP, (256, 256, 128), 256, sk.SK_FP8_E4M3)
+        assert sk.sk_plan_kernel_name(p) == name
+        sk.sk_plan_destroy(p)
+
+
 def _counter_run(folder, counter, rows):
     folder.mkdir()
     lines = ["Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value"]
