@@ -311,9 +311,10 @@ int sk_plan_check(const sk_plan_t* plan, void* stream);
  * tiles run a four-wave kernel when the plan has no split tile, enough K-iterations per tile (256-row
  * tiles: 48 and 16) and, with 16-bit inputs, K and N that are multiples of 8; the eight-wave one otherwise.
  * The four-wave 256 x 256 kernel has a second form for such plans with 16-bit output and K and N that are
- * multiples of 16 bytes, which runs on from one tile of a workgroup to the next without a break; where that
- * applies it is taken from 5 K-iterations per tile on with 8-bit inputs, and with 16-bit inputs from 8 on
- * (three tiles or more per workgroup), 32 (two) or 56 (one).
+ * multiples of 16 bytes (and N below 2^22), which runs on from one tile of a workgroup to the next without a
+ * break; where it applies it takes the place of the first form, from 5 K-iterations per tile on with 8-bit
+ * inputs, and with 16-bit inputs from 8 on (three tiles or more per workgroup), 32 (two) or 56 (one).  Below
+ * that the eight-wave kernel runs, also from 48 to 55.
  * Where a tile has further layouts compiled in they are numbered from 1 (for those three tiles: 1 = four
  * waves, 3 = eight waves, whatever the plan; 256 x 256 also 2 = eight waves with the coarser MAC loop);
  * a tile without the requested variant keeps variant 0.  The results are the same under every variant.

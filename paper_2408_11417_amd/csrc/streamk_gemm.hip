@@ -33,8 +33,8 @@ KernelEntry** kernel_table(int* count) {
 // else the shape's variant 0.  want = 0 leaves the choice to the library: variant 0, except that a plan
 // without split tiles (whole_tile_iters = its k-iterations per tile, 0 for plans with split tiles) gets
 // the variant marked for such plans where the shape has one and the tiles are deep enough.
-// whole_tile_iters is also 0 for 16-bit problems on the register-staged path: its loads are bound by the vector L1,
-// and two waves per SIMD hide that better (3841 x 4225 x 4097, data-parallel, eight waves / four waves:
+// whole_tile_iters is also 0 for 16-bit problems on the register-staged path: under-aligned loads and
+// the parking of what they bring take longer, and two waves per SIMD hide that better (3841 x 4225 x 4097, data-parallel, eight waves / four waves:
 // 211 / 254 us with 256 x 256, 230 / 249 us with 256 x 128, 228 / 250 us with 128 x 128; 2001 x 2003 x 2005 65 / 85,
 // 42 / 50, 27 / 33).  Not so in 8 bits, where the eight-wave 256 x 256 kernel has no registers for a stage in flight:
 // 4097 x 4097 x 6145 256 / 236 us, 4097 x 4097 x 8193 341 / 291, 2049 x 4097 x 16385 372 / 267.
@@ -56,14 +56,18 @@ KernelEntry* find_kernel(int dtype, int bm, int bn, int bk, int fixup = SK_FIXUP
 }
 
 // The kernel that a launch of the plan runs; `across`: its MAC loop that runs on across the tiles of a workgroup.
-// That loop keeps the requests and the stores going from one tile to the next.  Measured against the eight-wave kernel
-// (16 bits, which takes the shallow tiles) and the four-wave one (8 bits):
-//  - 16 bits, three tiles or more per workgroup, from 8 k-iterations on: 8192 x 8192 x 512 77.2 -> 69.7 us, x 1024 121.3 -> 115.0,
-//    16384 x 16384 x 1024 491.9 -> 457.1, 12288 x 12288 x 520 195.2 -> 170.2;
-//  - 16 bits, two tiles: from 32 on (6000 x 4104 x 2056 109.2 -> 107.3; 6000 x 4096 x 512 33.9 -> 34.9);
-//  - 16 bits, one tile, where only the first and the last tile's code counts: from 56 on (3840 x 4224 x 4096 102.9 -> 101.3,
-//    4096 x 4096 x 16384 398 -> 378, four waves without it 382; x 3072 77.6 -> 78.9);
-//  - 8 bits always (4096 x 4096 x 640 20.3 -> 16.4, 8192 x 8192 x 1024 88.8 -> 65.0, 8192^3 377.6 -> 355.8).
+// That loop keeps the requests and the stores going from one tile to the next.  Below its threshold the eight-wave kernel
+// runs, also where the four-wave kernel without it (which takes other plans from 48 on) is the slower one.  256 x 256 tiles,
+// three sets of N(0, 1/K) operands in turn, us, eight waves / that loop / four waves without it:
+//  - 16 bits, three tiles or more per workgroup, from 8 k-iterations on, the fewest it takes: 8192 x 8192 x 512 81.0 / 77.8 / 87.0,
+//    x 1024 126.9 / 123.8 / 132.0, 12288 x 12288 x 520 206.9 / 187.0 / 223.8, x 4096 945 / 919 / 939;
+//  - 16 bits, two tiles, from 32 on: 6000 x 4096 x 512 37.0 / 37.8 / 45.2, x 1536 83.2 / 82.1 / 91.5, x 2048 106.3 / 104.9 / 114.3,
+//    x 4096 205.4 / 198.9 / 207.2 (8192 x 4096, all of them full: 42.4 / 40.5 / 48.7, 87.2 / 86.5 / 93.4, 113.4 / 113.6 / 117.0);
+//  - 16 bits, one tile, where only the first and the last tile's code counts, from 56 on: 4096 x 4096 x 3072 81.7 / 83.0 / 85.0,
+//    x 3520 92.5 / 93.2 / 95.3, x 4096 105.6 / 106.3 / 108.7; 3840 x 4224 x 3584 93.2 / 93.0 / 95.6, x 4096 105.9 / 104.5 / 107.5;
+//    4096 x 4096 x 16384 (one operand set) 398 / 378 / 382;
+//  - 8 bits always, from 5 on, the fewest it takes: 4096 x 4096 x 640 24.7 / 18.2 / 22.4 (a size whose own tile is 128 x 256),
+//    8192 x 8192 x 1024 98.0 / 73.7 / 93.4, 4096 x 4096 x 6016 78.8 / 73.4 / 77.0, 8192 x 8192 x 6144 321 / 288 / 307.
 KernelEntry* kernel_of(const sk_plan_t* plan, bool* across = nullptr) {
     const sk_plan_header& h = plan->h;
     const bool atomic = plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup, fp8 = h.in_dtype == SK_FP8_E4M3;

@@ -167,7 +167,7 @@ struct Cfg {
     // register-staged path: a stage's pieces (4 registers each).  STAGED_FINE: the instruction-by-instruction
     // MAC loop with one stage in registers, where the two operand sets leave room for it; the other tiles hold
     // STAGES_HELD stages in registers, about 64 registers of loads in flight.  (The count is an estimate: the compiler
-    // spills 8 registers of the eight-wave 256 x 256 kernel, 52 of the four-wave one and 136 of the 8-bit four-wave one.
+    // spills 9 registers of the eight-wave 256 x 256 kernel, 49 of the four-wave one and 133 of the 8-bit four-wave one.
     // No steady trip holds a spill; the checked trips of the last one do.)
     static constexpr int PIECES = CA + CB;
     static constexpr bool STAGED_FINE = FINE && KK % 2 == 0 && 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 5 * PIECES + 32 <= 256;
@@ -178,9 +178,10 @@ struct Cfg {
     // 16-byte stores from the lanes as the blocks lie, 32 rows of 32 bytes per instruction, instead of store_blocks'
     // exchange, where that costs more than the better pattern gives: the lowest tiles (bound by the length of the chain
     // at the end of the kernel: 23 x 4096 x 8128 to fp32 16.5 us, 16.6 with it) and the four-wave 256 x 256 kernels
-    // (nothing runs beside a wave's exchange, 500 instructions or 1 us, and they only take tiles of 48 k-iterations and
-    // more: 3840 x 4224 x 4096 109.4 us, 110.0 with it, 4096 x 4032 x 3072 83.4 / 84.9, 8 bits 3840 x 4224 x 8192
-    // 100.9 / 104.1, 8192^3 no difference).  The other four-wave kernels gain from it at every depth tried.
+    // (nothing runs beside a wave's exchange, 500 instructions or 1 us; the library takes them from 48 k-iterations on, where
+    // streamk_whole_tiles_kernel does not apply: fp32 output, 8-bit rows off the 16-byte grid, the longest rows.  Measured with
+    // bf16 output before that kernel took those plans: 3840 x 4224 x 4096 109.4 us, 110.0 with it, 4096 x 4032 x 3072 83.4 / 84.9, 8
+    // bits 3840 x 4224 x 8192 100.9 / 104.1, 8192^3 no difference).  The other four-wave kernels gain from it at every depth tried.
     static constexpr bool DIRECT_STORES = BM <= 32 || (FINE && NW == 4 && BM == 256 && BN == 256);
     static_assert(WTM % MF == 0 && WTN % MF == 0 && BK % KM == 0, "tile does not divide");
     static_assert(CPA == 4 || CPA == 8 || CPA == 16, "A swizzle assumes 64/128/256-byte rows");
@@ -659,10 +660,12 @@ __device__ __forceinline__ void mac_prefetch(const GemmArgs& g, int m0, int n0, 
 // 0 .. KK-2 of stage i+1], written out slot by slot: one matrix-core instruction, its share of the next
 // k-step's LDS reads, and one piece parked (stage i+2, into the slot that the barrier has freed) whose
 // registers then take the same piece of stage i+3.  A load therefore has a whole trip to land.
-// What bounds it is the vector L1: under-aligned 16-byte loads move about 25 bytes per clock and CU where
+// What bounds it is not settled: under-aligned 16-byte loads move about 25 bytes per clock and CU where
 // aligned ones move 52 (a microbenchmark of this access pattern), and a 256 x 256 x 64 stage is 64 KB: 2600 clocks,
-// against 2050 of matrix-core work.  3841 x 4225 x 4097 looks up 63 million cache lines where the aligned neighbour
-// looks up 19 (counters); its matrix cores are busy a third of the time, 0.63 there.
+// against 2050 of matrix-core work.  3841 x 4225 x 4097 looks up 63 million cache lines in the vector L1 where the aligned
+// neighbour looks up 19 (counters); its matrix cores are busy a third of the time, 0.63 there.  But loads widened to aligned
+// ones, with half the look-ups, took longer (174 -> 187 us), and loads that wait for less changed nothing; a row's 128 bytes
+// of A straddle two lines, so a stage fills 106 KB from L2.
 template <class C, bool TR>
 __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n0, int k_begin, int k_end, unsigned char* smem,
                                                 const FragMap<C>& fm, typename Mfma<C::DT, C::MF>::Acc (&acc)[C::MI][C::NI]) {
@@ -1552,8 +1555,8 @@ template <int DT, bool ATOMIC = false> void add_16bit_tiles(KernelEntry** t, int
 // The tiles of at most 64 rows.  What bounds them outside the HBM-bound shapes is the rate at which a CU
 // takes operand bytes into LDS (about 90 bytes per ns with rows on 128-byte boundaries, 60 off them), so they
 // matter where the larger tiles leave CUs idle: 1024^3 on 256 tiles of 64 x 64 7.0 us (128 of 64 x 128: 8.2,
-// 256 of 32 x 128: 7.2), 1 x 4096 x 4096 on 16 x 128 9.8 us (32 x 128: 11.4; 32 x 64: 9.4, which the cost model
-// has behind it).
+// 256 of 32 x 128: 7.2), 1 x 4096 x 4096 on 16 x 128 10.9 us from cold
+// operands (32 x 128: 12.4; 32 x 64: 10.7, and at 1 x 4096 x 8192 16.3 against 18.2, which the cost model has behind it).
 template <int DT, bool ATOMIC = false> void add_16bit_low_tiles(KernelEntry** t, int* n) {
     t[(*n)++] = make_entry<Cfg<DT, 64, 128, 64, 2, 4, 32, 4>, ATOMIC>();
     t[(*n)++] = make_entry<Cfg<DT, 32, 128, 64, 1, 4, 32, 4>, ATOMIC>();

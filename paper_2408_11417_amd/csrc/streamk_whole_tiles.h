@@ -9,14 +9,20 @@
 //    accumulators start from zero with the next one's first k-step;
 //  - the packed blocks stay in registers (128 per lane with 16-bit operands) and leave in the following trips, one pair of
 //    blocks per trip, their lane exchange and their stores in the shadow of the matrix-core work.
-// 8192 x 8192 x 512 bf16 77.2 -> 69.7 us, 16384 x 16384 x 1024 491.9 -> 457.1, 8192^3 774 -> 764; 8 bits 8192 x 8192 x
-// 1024 88.8 -> 65.0 us, 8192^3 383 -> 364.  One tile per workgroup gains from the trips alone (one offset per operand and
-// lane, 5 instructions per request): 4096 x 4096 x 16384 bf16 382 -> 378, 8 bits x 640 20.3 -> 16.4.
-// A long K is bound by the power limit, a short one by that and the stores' share of it.
+// With operands in turn, against what ran before it, us: 8192 x 8192 x 512 bf16 82.0 -> 77.8 (N(0, 1/K) values; uniform ones 79 - 81 -> 76 - 80
+// on five boxes, one of which showed no gain), 12288 x 12288 x 1024 283.5 -> 269.2, 8192^3 750 -> 737; 8 bits 8192 x 8192 x 1024
+// 103.2 -> 73.7, 8192^3 374 -> 357.  One tile per workgroup gains from the trips alone (one offset per operand and lane, 5
+// instructions per request): 3840 x 4224 x 4096 bf16 104.8 -> 102.8, 8 bits 4096 x 4096 x 640 26.5 -> 18.2 (tile forced).
+// Counters, before -> now: 8192 x 8192 x 512 172 -> 156 thousand cycles at 2.08 -> 2.16 GHz, matrix cores busy 0.38 -> 0.42 (they need 65.5:
+// the rest is not the clock); 8192^3 1.306 -> 1.265 million at 1.61 -> 1.58 GHz, busy 0.80 -> 0.83; 8 bits 0.719 -> 0.644
+// at 1.78 -> 1.67, 0.73 -> 0.81.
+// A long K is bound by the power limit: most of the cycles saved come back as a lower clock.
 //
 // The accumulators fill the 256 accumulation registers, so the code is laid out for a register allocation in place: one
 // loop nest that makes and ends them once per tile (a second copy of a tile's end, or packing beside the next tile's
-// first instructions, spilled 600 registers).
+// first instructions, spilled 600 registers).  The 16-bit kernels spill 3 vector registers (12 bytes of scratch per lane) and 94 scalar ones,
+// the 8-bit kernel 54 scalar ones.  The steady trip holds none of them, but the trip that hands over a ragged k-iteration reloads one
+// from scratch and so waits for all requests, once per tile whose K is not a multiple of BK.
 #pragma once
 #include "streamk_kernels.h"
 
@@ -42,7 +48,7 @@ template <class C> struct WholeTiles {
     static constexpr int CHECKED = C::NSA + 2;                         // a tile's last trips: requests cross into a ragged k-iteration and the next tile
     static constexpr int MIN_ITERS = KEPT < CHECKED ? CHECKED : KEPT;                        // the kept pairs leave in as many trips before the next turn
     static_assert((C::LPS * 8) % SLOTS == 0 || SLOTS % C::LPS == 0, "requests spread over the slots");
-    static_assert(SLOTS % 16 == 0, "eight store phases in the second half of a trip");
+    static_assert(SLOTS % 16 == 0, "eight places for stores in the second half of a trip, of which the six phases take six");
 };
 
 template <class C, int OUT>
