@@ -152,7 +152,8 @@ typedef struct {
                                              defaults, or what the sk_plan_set_* calls chose */
     int32_t xcd_remap;                    /* which workgroups of the schedule share one of the 8 XCDs (and its L2).
                                              1: each XCD runs grid/8 consecutive ones (neighbours in the schedule, which
-                                             share operand blocks and exchange partial tiles); 2: the workgroups sorted by
+                                             share operand blocks and exchange partial tiles; those with work in a
+                                             last, partly filled wave of tiles may be dealt to the XCDs evenly); 2: the workgroups sorted by
                                              their slice of the tiles' K range, in eight consecutive parts - chosen when
                                              at least 4 workgroups share every tile and the XCDs would otherwise fetch
                                              20 MB or more in all of operand blocks that another XCD fetches too (where an

@@ -54,6 +54,7 @@ struct GemmArgs {
     int out_dtype;
     int dp_first;          // 1: a workgroup runs its data-parallel tiles before its Stream-K iterations
     int xcd_remap;         // which logical workgroup ids share an XCD (see logical_wg)
+    int first_ids, other_ids;  // map 1: how many of the first logical ids, and of the others, an XCD runs; together grid / 8
     int k_aligned;         // 1: a workgroup runs the whole tiles of its Stream-K range first, then the head of its last
                            //    tile (k from 0), then the tail of its first one, and the workgroup holding a tile's
                            //    last iteration reduces and stores it
@@ -250,15 +251,17 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 
 // Hardware workgroup ids go round-robin over the 8 XCDs.  Which logical ids (positions in the schedule) an
 // XCD runs decides what its L2 can share (sk_plan chooses, see there):
-//   1  a contiguous block of logical ids: neighbours in the schedule share tiles and A row-blocks;
+//   1  a contiguous block of logical ids: neighbours in the schedule share tiles and A row-blocks; where only the
+//      first ids have work in the last wave of tiles (or at all), a block of those and a block of the others;
 //   2  for plans in which several workgroups share every tile: the ids sorted by their piece of the
 //      tile's K range, then by tile, and a contiguous block of that - an XCD then reads one slice of K of
 //      every tile it touches, and the tiles that share an A row-block or B column-block share its slice in L2;
 //   0  the hardware order.
-__device__ __forceinline__ int logical_wg(int hw, const GemmArgs& g) {
-    if (g.xcd_remap == 0 || g.grid % 8 != 0) return hw;
-    const int q = (hw % 8) * (g.grid / 8) + hw / 8;
-    if (g.xcd_remap == 1) return q;
+__device__ __forceinline__ int logical_wg(uint32_t hw, const GemmArgs& g) {
+    if (g.xcd_remap == 0) return (int)hw;
+    const int xcd = (int)(hw % 8), i = (int)(hw / 8);
+    if (g.xcd_remap == 1) return i < g.first_ids ? xcd * g.first_ids + i : 7 * g.first_ids + xcd * g.other_ids + i;
+    const int q = xcd * (g.grid / 8) + i;
     // The ranges of workgroups ceil(t * ipt / ipw) .. ceil((t + 1) * ipt / ipw) - 1 start in tile t: `each` of them or
     // one more; the tiles with one more are t = floor(i * ipw / extra), i = 0, 1, ..., extra = ipt mod ipw.  (By the
     // ranges themselves, not by grid / tiles: ipw is rounded up, and over the tiles that adds up to a slice or more.)
