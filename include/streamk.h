@@ -225,13 +225,18 @@ int sk_plan_set_batch_order(sk_plan_t* plan, int batch_order);
 int sk_plan_set_segment_order(sk_plan_t* plan, int segment_order);
 
 /* Device bytes sk_gemm needs for this plan.  FLAGS: one flag line per workgroup,
- * a status word, and one fp32 partial tile (blk_m * blk_n) per workgroup.
+ * a status word, and one fp32 partial tile (blk_m * blk_n) per workgroup; plans
+ * of which many workgroups share every tile may add one per tile (see
+ * sk_plan_set_workspace).
  * ATOMIC: the flag and status lines, plus an fp32 image of D (M * N * 4 bytes)
  * unless the plan's output type is SK_F32 (then D itself is accumulated into).
  * Returns 0 for a NULL plan. */
 size_t sk_workspace_bytes(const sk_plan_t* plan);
 
-/* Attach caller-owned device memory (>= sk_workspace_bytes, 256-byte aligned).
+/* Attach caller-owned device memory (>= sk_workspace_bytes, 256-byte aligned; at
+ * the least without the partial tiles per tile, then the owner of a tile adds up
+ * all its partial tiles instead of every workgroup a share of them: the same
+ * results, later).
  * Clears the flag and status area with a blocking memset on the null stream.
  * One workspace must not serve two launches that are in flight at once; it may
  * be shared by plans that run one after another on one stream.
@@ -285,7 +290,7 @@ int sk_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, void* 
  * ignored.  The call allocates nothing and frees nothing.  Before the GEMM kernel it enqueues a small
  * fill kernel that takes the flag and status lines down (the array keeps the previous call's
  * contents), so a launch with split tiles is two kernels; a plan without split tiles is one.
- * Limit: sk_workspace_bytes(plan) <= SK_STATIC_WORKSPACE_MAX_BYTES - enough for every tile shape on
+ * Limit: what sk_plan_set_workspace needs at the least <= SK_STATIC_WORKSPACE_MAX_BYTES - enough for every tile shape on
  * the default grid of 256 workgroups; larger grids with the largest tiles are refused.
  * All calls on one GPU share that GPU's array: two calls whose kernels may run at the same time
  * (different streams, or replays of graphs that hold them) race on it; calls on one stream do not.

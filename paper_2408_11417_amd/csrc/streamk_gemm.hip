@@ -145,7 +145,7 @@ bool sk_kernel_available(int in_dtype, int blk_m, int blk_n, int blk_k) {
 
 extern "C" int sk_plan_set_workspace(sk_plan_t* plan, void* dev_ptr, size_t bytes) {
     if (!plan || !dev_ptr) return SK_ERR_INVALID_ARG;
-    if (bytes < sk_workspace_bytes(plan) || (reinterpret_cast<uintptr_t>(dev_ptr) & 255)) return SK_ERR_WORKSPACE;
+    if (bytes < sk_ws_least_bytes(plan) || (reinterpret_cast<uintptr_t>(dev_ptr) & 255)) return SK_ERR_WORKSPACE;
     if (!hip_ok(hipMemset(dev_ptr, 0, sk_ws_partials_offset(plan->h.grid)))) return SK_ERR_HIP;
     if (!hip_ok(hipDeviceSynchronize())) return SK_ERR_HIP;
     plan->workspace = dev_ptr;
@@ -188,7 +188,7 @@ namespace {
 
 // The launch behind sk_gemm and sk_gemm_static: `workspace` is the device memory that holds the flag
 // lines, the status line and the partial tiles (or the fp32 image of the atomic fix-up).
-int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, void* stream, void* workspace) {
+int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, void* stream, void* workspace, size_t workspace_bytes) {
     if (!A || !B || !D || !plan) return SK_ERR_INVALID_ARG;
     const sk_plan_header& h = plan->h;
     const uintptr_t align = reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(D);
@@ -207,7 +207,7 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
 
     if (e->max_resident.load() < 0) {
         // first use on this process: allow the large LDS footprint and ask how many workgroups fit at once
-        for (kernel_fn f : {e->aligned, e->generic, e->across})
+        for (kernel_fn f : {e->aligned, e->generic, e->across, e->shared_aligned, e->shared_generic})
             if (f && !hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, e->lds_bytes)))
                 return SK_ERR_HIP;
         int dev = 0, cus = 0, per_cu = 0;
@@ -215,10 +215,21 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
             return SK_ERR_HIP;
         if (!hip_ok(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(e->generic), e->threads, e->lds_bytes)))
             return SK_ERR_HIP;
+        if (e->shared_generic) {
+            int most = per_cu;
+            for (kernel_fn f : {e->shared_aligned, e->shared_generic}) {
+                int n = 0;
+                if (!hip_ok(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(f), e->threads, e->lds_bytes))) return SK_ERR_HIP;
+                most = std::min(most, n);
+            }
+            e->max_shared.store(most * cus);
+        }
         e->max_resident.store(per_cu * cus);
     }
     // an owner spins on flags of other workgroups: all of them must be on the machine at once
     if (plan->needs_fixup && !atomic && h.grid > e->max_resident.load()) return SK_ERR_UNSUPPORTED;
+    if (e->shared_generic && sk_shared_reduction(plan) && workspace_bytes >= sk_workspace_bytes(plan) && h.grid <= e->max_shared.load())
+        fn = aligned ? e->shared_aligned : e->shared_generic;
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     GemmArgs g{};
@@ -310,15 +321,15 @@ int static_scratch(void** out) {
 
 extern "C" int sk_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, void* stream) {
     if (!plan) return SK_ERR_INVALID_ARG;
-    return launch_gemm(A, B, D, plan, stream, plan->workspace);
+    return launch_gemm(A, B, D, plan, stream, plan->workspace, plan->workspace_bytes);
 }
 
 extern "C" int sk_gemm_static(const void* A, const void* B, void* D, const sk_plan_t* plan, void* stream) {
     if (!A || !B || !D || !plan) return SK_ERR_INVALID_ARG;
     // the atomic fix-up accumulates into an fp32 image of D, whose size has no bound: caller-owned memory only
     if (plan->fixup == SK_FIXUP_ATOMIC && plan->needs_fixup && plan->h.out_dtype != SK_F32) return SK_ERR_UNSUPPORTED;
-    if (!plan->needs_fixup) return launch_gemm(A, B, D, plan, stream, nullptr);    // no split tile: nothing to exchange
-    if (sk_workspace_bytes(plan) > SK_STATIC_SCRATCH_BYTES) return SK_ERR_WORKSPACE;
+    if (!plan->needs_fixup) return launch_gemm(A, B, D, plan, stream, nullptr, 0);    // no split tile: nothing to exchange
+    if (sk_ws_least_bytes(plan) > SK_STATIC_SCRATCH_BYTES) return SK_ERR_WORKSPACE;
     void* ws = nullptr;
     const int rc = static_scratch(&ws);
     if (rc != SK_OK) return rc;
@@ -327,5 +338,5 @@ extern "C" int sk_gemm_static(const void* A, const void* B, void* D, const sk_pl
     hipLaunchKernelGGL(clear_words_kernel, dim3((words + 255) / 256), dim3(256), 0, static_cast<hipStream_t>(stream),
                        static_cast<uint32_t*>(ws), words);
     if (!hip_ok(hipGetLastError())) return SK_ERR_HIP;
-    return launch_gemm(A, B, D, plan, stream, ws);
+    return launch_gemm(A, B, D, plan, stream, ws, SK_STATIC_SCRATCH_BYTES);
 }

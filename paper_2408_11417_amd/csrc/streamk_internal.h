@@ -42,6 +42,10 @@ inline sk_fast_div sk_make_fast_div(uint32_t d) {
 }
 inline uint32_t sk_fast_div_apply(uint32_t n, sk_fast_div f) { return (uint32_t)(((uint64_t)n * f.mul) >> f.shift); }
 
+// Does the plan's fix-up share the reduction of a tile among all its workgroups (where its kernel can and the workspace suffices)?
+bool sk_shared_reduction(const sk_plan_t* plan);
+// The workspace that a plan cannot do without; sk_workspace_bytes adds what the shared reduction needs.
+size_t sk_ws_least_bytes(const sk_plan_t* plan);
 // Does the GEMM launcher hold a kernel for this configuration?
 bool sk_kernel_available(int in_dtype, int blk_m, int blk_n, int blk_k);
 // Bytes of the fp32 image of D that the atomic fix-up accumulates into (0 if D itself serves).

@@ -184,6 +184,9 @@ struct Cfg {
     // bf16 output before that kernel took those plans: 3840 x 4224 x 4096 109.4 us, 110.0 with it, 4096 x 4032 x 3072 83.4 / 84.9, 8
     // bits 3840 x 4224 x 8192 100.9 / 104.1, 8192^3 no difference).  The other four-wave kernels gain from it at every depth tried.
     static constexpr bool DIRECT_STORES = BM <= 32 || (FINE && NW == 4 && BM == 256 && BN == 256);
+    // has a kernel with the shared reduction: slots of 16 bytes per lane (the four-wave 256 x 256 kernels' may be others), and
+    // where sk_shared_reduction may ask for it
+    static constexpr bool MAY_SHARE = ACC_REGS < 256 && BM * BN >= 4096;
     static_assert(WTM % MF == 0 && WTN % MF == 0 && BK % KM == 0, "tile does not divide");
     static_assert(CPA == 4 || CPA == 8 || CPA == 16, "A swizzle assumes 64/128/256-byte rows");
     static_assert(CPB >= 8, "B swizzle assumes rows of at least 128 bytes");
@@ -1287,6 +1290,146 @@ __device__ __forceinline__ void reduce_and_store(const GemmArgs& g, int row0, in
     }
 }
 
+// ---- shared reduction -----------------------------------------------------------------------
+// Fix-up of plans in which many workgroups share every tile and nothing follows the Stream-K work (sk_shared_reduction): each
+// workgroup of a tile, its owner too, parks its piece and counts itself in; once all have, each fetches the same share
+// of all pieces, adds them up and stores that share of D.  What bounds the exchange otherwise is the owner's CU, which takes the
+// partial tiles of all contributors through one port (about 107 bytes per ns); here a tile's pieces go to as many CUs as made
+// them.  The order of the additions is the owner's (and, from 2 * SK_TREE_GROUP contributors on, the group leaders'): the
+// results are the same bit for bit.
+//
+// Count of a tile: arrivals in the lower half of its flag line's word, in the upper half those who need not look at
+// it any more.  The last of these takes it down.
+__device__ __forceinline__ uint32_t* tile_count(const GemmArgs& g, int tile) { return g.flags + (size_t)tile * (SK_FLAG_STRIDE / 4); }
+// Where a workgroup's piece of a tile is parked: in the workgroup's slot - but the owner's, whose slot holds its piece of
+// the next tile if its range goes on there, then behind the workgroups' slots.
+__device__ __forceinline__ int owner_slot(const GemmArgs& g, int tile, int wg) {
+    const int end = (wg + 1) * g.ipw < g.sk_iters ? (wg + 1) * g.ipw : g.sk_iters;
+    return end > (tile + 1) * g.ipt ? g.grid + tile : wg;
+}
+
+// Four consecutive values of a lane: of a row (TR) or of a column (see store_blocks).
+template <int OUT, bool TR>
+__device__ __forceinline__ void store_four(const GemmArgs& g, int row, int col, f32x4 v) {
+    if (col >= g.N) return;
+    if constexpr (TR) {
+        if (row >= g.M) return;
+        const size_t o = (size_t)((uint32_t)row * (uint32_t)g.N + (uint32_t)col);
+        if constexpr (OUT == SK_F32) *reinterpret_cast<f32x4*>(static_cast<float*>(g.D) + o) = v;
+        else if constexpr (OUT == SK_BF16) *reinterpret_cast<u32x2*>(static_cast<u16*>(g.D) + o) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        else *reinterpret_cast<u32x2*>(static_cast<u16*>(g.D) + o) = u32x2{pack_f16(v[0], v[1]), pack_f16(v[2], v[3])};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            if (row + e >= g.M) return;
+            const size_t o = (size_t)((uint32_t)(row + e) * (uint32_t)g.N + (uint32_t)col);
+            if constexpr (OUT == SK_F32) static_cast<float*>(g.D)[o] = v[e];
+            else if constexpr (OUT == SK_BF16) static_cast<u16*>(g.D)[o] = to_bf16_bits(v[e]);
+            else static_cast<_Float16*>(g.D)[o] = (_Float16)v[e];
+        }
+    }
+}
+
+// A workgroup's share of one split tile: units [begin, end) of the tile's pieces.  A unit is the 1 KB that one register group
+// of one wave takes in a slot.
+template <class C> struct Share {
+    static constexpr int Q = C::ACC / 4, BLOCKS = C::MI * C::NI, UNITS = C::NW * BLOCKS * Q;
+    int tile, last_wg, n_all, begin, end;        // the tile, its owner, the number of its contributors
+    __device__ __forceinline__ void init(const GemmArgs& g, int x, int t) {
+        tile = t;
+        const int first_wg = (int)fast_div((uint32_t)(t * g.ipt), g.div_ipw);
+        last_wg = (int)fast_div((uint32_t)(t * g.ipt + g.ipt - 1), g.div_ipw);
+        n_all = last_wg - first_wg;
+        const uint32_t j = (uint32_t)(last_wg - x), n = (uint32_t)n_all + 1;
+        begin = (int)(UNITS * j / n);
+        end = (int)(UNITS * (j + 1) / n);
+    }
+};
+
+// One unit of a tile: all its pieces added up, 16 contributors per round trip, and stored.
+template <class C, bool TR>
+__device__ __forceinline__ void store_unit(const GemmArgs& g, const buffer_rsrc& rsrc, const Share<C>& share, int unit) {
+    constexpr int Q = Share<C>::Q, BLOCKS = Share<C>::BLOCKS, AT_ONCE = 2 * SK_TREE_GROUP;
+    constexpr uint32_t SLOT_BYTES = C::BM * C::BN * 4;
+    const int lane = threadIdx.x % 64, n_all = share.n_all;
+    const int w = unit / (BLOCKS * Q), b = unit / Q % BLOCKS, q = unit % Q;
+    const int at = ((b * Q + q) * C::NW + w) * 1024 + lane * 16;
+    auto fetch = [&](int slot) {
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (int)((uint32_t)slot * SLOT_BYTES), 16 /* sc1 */));
+    };
+    f32x4 sum = fetch(owner_slot(g, share.tile, share.last_wg));
+    for (int c = 1; c <= n_all; c += AT_ONCE) {
+        f32x4 part[AT_ONCE];
+#pragma unroll
+        for (int e = 0; e < AT_ONCE; e++) {
+            part[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (c + e <= n_all) part[e] = fetch(share.last_wg - c - e);
+        }
+        if (n_all >= AT_ONCE) {                  // the order of the two-level reduction
+#pragma unroll
+            for (int h = 0; h < AT_ONCE; h += SK_TREE_GROUP) {
+                f32x4 group = part[h];
+#pragma unroll
+                for (int e = 1; e < SK_TREE_GROUP; e++) group += part[h + e];
+                sum += group;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < AT_ONCE; e++) sum += part[e];
+        }
+    }
+    int tm, tn;
+    tile_position(g, share.tile, tm, tn);
+    const int wm = w / C::WN, wn = w % C::WN, mi = b / C::NI, ni = b % C::NI;
+    const int row = tm * C::BM + wm * C::WTM + mi * C::MF + (TR ? lane % C::MF : 4 * (lane / C::MF) + q * 4 * C::KG);
+    const int col = tn * C::BN + wn * C::WTN + ni * C::MF + (TR ? 4 * (lane / C::MF) + q * 4 * C::KG : lane % C::MF);
+    if (g.out_dtype == SK_BF16) store_four<SK_BF16, TR>(g, row, col, sum);
+    else if (g.out_dtype == SK_F16) store_four<SK_F16, TR>(g, row, col, sum);
+    else store_four<SK_F32, TR>(g, row, col, sum);
+}
+
+// This workgroup's shares of the one or two tiles of its range, all of them split (the range is shorter than a tile): both
+// counts are waited for at once, and a wave takes every NW-th unit of the two shares together.
+template <class C, bool TR>
+__device__ __forceinline__ void store_shares(const GemmArgs& g, int x) {
+    const int begin = x * g.ipw, end = begin + g.ipw < g.sk_iters ? begin + g.ipw : g.sk_iters;
+    if (begin >= end) return;
+    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    Share<C> s0, s1;
+    s0.init(g, x, (int)fast_div((uint32_t)begin, g.div_ipt));
+    const int last = (int)fast_div((uint32_t)end - 1, g.div_ipt);
+    s1 = s0;
+    if (last > s0.tile) s1.init(g, x, last);
+    else s1.end = s1.begin;
+    const int len0 = s0.end - s0.begin, len1 = s1.end - s1.begin;
+    // lane i of the first wave watches and leaves tile i
+    const bool mine = wave == 0 && lane <= last - s0.tile;
+    uint32_t* count = tile_count(g, lane == 1 ? s1.tile : s0.tile);
+    const uint32_t n_all = (uint32_t)(lane == 1 ? s1.n_all : s0.n_all);
+    if (wave == 0) {
+        bool seen = !mine || (lane == 1 ? len1 : len0) == 0;
+        uint32_t polls = 0;
+        while (true) {
+            if (!seen) seen = (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffffu) > n_all;
+            if (__all(seen)) break;
+            if (polls++ >= g.spin_limit) {
+                if (lane == 0) __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    __syncthreads();
+    uint32_t left = 0;
+    if (mine) left = __hip_atomic_fetch_add(count, 0x10000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const buffer_rsrc rsrc = __builtin_amdgcn_make_buffer_rsrc(g.partials, 0, (uint32_t)(g.grid + g.tiles) * (uint32_t)(C::BM * C::BN * 4), BUFFER_RAW);
+    for (int i = wave; i < len0 + len1; i += C::NW) {
+        const bool second = i >= len0;
+        store_unit<C, TR>(g, rsrc, second ? s1 : s0, second ? s1.begin + i - len0 : s0.begin + i);
+    }
+    if (mine && (left >> 16) == n_all) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Atomic fix-up (the accumulation step of Algorithm 1): a segment that covers only part of the tile's
 // K-iterations adds its accumulators into the zero-initialised fp32 image with atomic adds; a
 // segment that covers the whole tile stores them.  Blocks are not transposed here: the lanes of
@@ -1313,7 +1456,11 @@ __device__ __forceinline__ void add_to_image(const GemmArgs& g, int row0, int co
         }
 }
 
-template <class C, bool ALIGNED, bool ATOMIC = false>
+// How the pieces of a split tile come together: OWNER: one of its workgroups waits for the partial tiles of the others and adds them
+// up; SHARED: all of them, a share each, which a kernel of its own does (in one kernel the two cost the small problems 0.1 - 0.2 us:
+// 512^3 4.74 -> 4.85), all of whose segments are pieces of split tiles; ATOMIC: atomic adds into an image of D.
+enum FixUp { OWNER, SHARED, ATOMIC_ADDS };
+template <class C, bool ALIGNED, FixUp FIXUP = OWNER>
 __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
     extern __shared__ __align__(1024) unsigned char smem[];
     typedef typename Mfma<C::DT, C::MF>::Acc Acc;
@@ -1322,7 +1469,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
     const int x = logical_wg(blockIdx.x, g);
     // transposed accumulator blocks (vector stores) where D's rows are 16-byte aligned; the atomic
     // fix-up and the element-wise stores of unaligned problems want the lanes side by side in a row
-    constexpr bool TR = ALIGNED && !ATOMIC;
+    constexpr bool ATOMIC = FIXUP == ATOMIC_ADDS, TR = ALIGNED && !ATOMIC;
     FragMap<C> fm;
     fm.init();
 
@@ -1382,6 +1529,22 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
             const bool partial = k_begin > 0 || k_end < g.ipt;
             if (m0 + C::BM > g.M || n0 + C::BN > g.N) add_to_image<C, true>(g, row0, col0, partial, acc);
             else add_to_image<C, false>(g, row0, col0, partial, acc);
+            return false;
+        }
+        if constexpr (FIXUP == SHARED) {
+            int wg = x;
+            asm volatile("" : "+s"(wg));
+            const Slot<C, true> slot(g.partials + (size_t)(k_end < g.ipt ? wg : owner_slot(g, tile, wg)) * (C::BM * C::BN));
+#pragma unroll
+            for (int mi = 0; mi < C::MI; mi++)
+#pragma unroll
+                for (int ni = 0; ni < C::NI; ni++) {
+                    slot.park(mi * C::NI + ni, acc[mi][ni]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            wait_vmcnt<0>();                      // every lane's part of the piece has reached memory
+            __syncthreads();
+            if (tid == 0) __hip_atomic_fetch_add(tile_count(g, tile), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
 
@@ -1499,6 +1662,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         }
         stores_in_flight = finish_segment(cur_tile, cur_k_begin, cur_k_end, cur_m0, cur_n0, acc) && prefetched;
     }
+    if constexpr (FIXUP == SHARED) store_shares<C, TR>(g, x);
 }
 
 // ---- kernel table entries --------------------------------------------------------------------
@@ -1509,18 +1673,24 @@ struct KernelEntry {
                                          // tiles whose tiles have at least this many k-iterations
     kernel_fn aligned, generic;
     kernel_fn across = nullptr;          // the MAC loop that runs on across the tiles of a workgroup (streamk_whole_tiles.h), and the fewest
+    kernel_fn shared_aligned = nullptr, shared_generic = nullptr;    // with the shared reduction
     int across_iters = 0;                // k-iterations per tile that it takes; for plans without split tiles, aligned, with 16-bit output
     int threads, lds_bytes, piece_elems;
     std::atomic<int> max_resident{-1};   // co-resident workgroups on the device, -1 = not yet asked
+    std::atomic<int> max_shared{0};      // ... of the kernels with the shared reduction
     KernelEntry(int d, int m, int n, int k, int v, int fx, kernel_fn a, kernel_fn g, int t, int l, int pe)
         : dtype(d), bm(m), bn(n), bk(k), variant(v), fixup(fx), aligned(a), generic(g), threads(t), lds_bytes(l), piece_elems(pe) {}
 };
 
 template <class C, bool ATOMIC = false> KernelEntry* make_entry(int variant = 0, int whole_tiles_choice = 0) {
     KernelEntry* e = new KernelEntry(C::DT, C::BM, C::BN, C::BK, variant, ATOMIC ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS,
-                                     streamk_gemm_kernel<C, true, ATOMIC>, streamk_gemm_kernel<C, false, ATOMIC>,
+                                     streamk_gemm_kernel<C, true, ATOMIC ? ATOMIC_ADDS : OWNER>, streamk_gemm_kernel<C, false, ATOMIC ? ATOMIC_ADDS : OWNER>,
                                      C::THREADS, C::LDS_BYTES, C::PE);
     e->whole_tiles_choice = whole_tiles_choice;
+    if constexpr (C::MAY_SHARE && !ATOMIC) {
+        e->shared_aligned = streamk_gemm_kernel<C, true, SHARED>;
+        e->shared_generic = streamk_gemm_kernel<C, false, SHARED>;
+    }
     return e;
 }
 

@@ -441,11 +441,35 @@ extern "C" int bloom_shape_key(const sk_plan_t* plan, uint32_t* key) {
     return SK_OK;
 }
 
-extern "C" size_t sk_workspace_bytes(const sk_plan_t* plan) {
-    if (!plan) return 0;
+// Where the shared reduction (store_shares in streamk_kernels.h) is the faster fix-up: the owner's chain of fetches, n - 1 partial
+// tiles through one CU, has to be longer than what sharing adds: the owner's own piece is parked and waited for too, and a range that
+// goes on into the next tile ends with shares of two tiles.  Owner alone -> shared, bf16 unless said, us:
+//  - n = 3: 512 x 10752 x 3136 on 256 x 256 tiles 55 -> 70, 384 x 3584 x 1536 on 128 x 128 12.1 -> 13.6; n = 4: 128 x 8192 x 8192 level;
+//  - n = 5: 512 x 6656 x 2496 on 256 x 256 57 -> 44, 768 x 2176 x 5120 on 256 x 128 35 -> 27, 256 x 3328 x 2496 on 128 x 128 15.9 -> 16.8 (8 bits, 384 x 2176 x
+//    10240, 20.0 -> 16.2), 192 x 2176 x 2560 on 64 x 128 level, 120 x 2688 x 6400 (n = 6) 16.4 -> 16.7;
+//  - n = 8 - 20: 256 x 256 21 - 43 % faster, 256 x 128 19 - 38 %, 128 x 128 18 - 32 %, 64 x 128 5 - 14 %, 32 x 128 and 64 x 64 level to 12 %
+//    (256 x 512 x 16384 to fp32 14.5 -> 12.9);
+//  - more workgroups than 1 KB units of the tile: 64 x 128, n = 57: 3 % slower, 32 x 128, n = 40: 3 %; tiles of 8 KB, 16 x 128 and 32 x 64, 2 - 25 % at any n.
+// Only where nothing follows the Stream-K work, whose workgroups would otherwise wait with tiles of their own left to do.
+bool sk_shared_reduction(const sk_plan_t* plan) {
+    const sk_plan_header& h = plan->h;
+    if (plan->fixup != SK_FIXUP_FLAGS || !plan->needs_fixup || !plan->k_aligned || h.dp_tiles > 0 || h.grid > 4096) return false;
+    const int64_t tile_kb = (int64_t)h.blk_m * h.blk_n / 256, ipt = h.iters_per_tile, ipw = h.iters_per_wg;
+    return tile_kb >= 16 && 2 * ipt >= (tile_kb >= 64 ? 9 : 14) * ipw && 4 * ipt <= 5 * tile_kb * ipw;
+}
+
+size_t sk_ws_least_bytes(const sk_plan_t* plan) {
     const sk_plan_header& h = plan->h;
     if (plan->fixup == SK_FIXUP_ATOMIC) return sk_ws_partials_offset(h.grid) + sk_ws_image_bytes(plan);
     return sk_ws_partials_offset(h.grid) + (size_t)h.grid * h.blk_m * h.blk_n * sizeof(float);
+}
+
+extern "C" size_t sk_workspace_bytes(const sk_plan_t* plan) {
+    if (!plan) return 0;
+    // a slot per tile for owners whose range goes on into the next tile
+    const sk_plan_header& h = plan->h;
+    const bool more = sk_shared_reduction(plan) && h.iters_per_tile % h.iters_per_wg != 0;
+    return sk_ws_least_bytes(plan) + (more ? (size_t)h.tiles * h.blk_m * h.blk_n * sizeof(float) : 0);
 }
 
 extern "C" int sk_plan_set_fixup(sk_plan_t* plan, int fixup) {

@@ -94,7 +94,7 @@ def run(shapes, out_path, dtype_code=1, verbose=True, check_every=25, fixup=0, t
     pa, pb = pool(4 * max_a + slack), pool(4 * max_b + slack)
     pd = torch.empty(4 * max_d + slack, dtype=out_tdt, device="cuda")
     pd2 = torch.empty(max_d, dtype=out_tdt, device="cuda")
-    ws_bytes = 256 * 256 * 256 * 4 + (1 << 16)
+    ws_bytes = (256 + 64) * 256 * 256 * 4 + (1 << 16)      # 256 workgroups' partial tiles, and owners' where at least 4.5 share a tile
     if fixup:                                  # the atomic fix-up keeps an fp32 image of D in the workspace
         ws_bytes = max(ws_bytes, max_d * 4 + (1 << 16))
     ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device="cuda")

@@ -369,6 +369,49 @@ def test_workgroups_with_work_in_the_last_wave_spread_over_the_xcds(shape, blk, 
         _run_and_compare(A, B, inputs.BF16, policy, blk, grid=grid, out_dtype=out, ref=ref, exact=out == sk.SK_F32, launches=2)
 
 
+# Shared reduction (every workgroup of a tile adds up a share of it): sizes at which it applies, with ranges that end with the
+# tiles and that straddle them, edge tiles, one and two round trips of 16 contributors, tiles of one and of eight units per workgroup.
+SHARED = [((256, 512, 4096), (64, 64, 128), sk.SK_BF16, sk.SK_BF16), ((700, 256, 2000), (64, 128, 64), sk.SK_BF16, sk.SK_F16),
+          ((511, 777, 3203), (256, 256, 64), sk.SK_BF16, sk.SK_F32), ((700, 1000, 1600), (256, 128, 64), sk.SK_F16, sk.SK_F16),
+          ((64, 1280, 3201), (32, 128, 64), sk.SK_F16, sk.SK_BF16), ((300, 500, 4100), (128, 128, 64), sk.SK_BF16, sk.SK_F32),
+          ((384, 640, 4700), (128, 128, 128), sk.SK_FP8_E4M3, sk.SK_BF16), ((500, 1504, 2112), (128, 256, 128), sk.SK_FP8_E4M3, sk.SK_F32)]
+
+
+@pytest.mark.parametrize("shape,blk,dtype,out", SHARED)
+def test_shared_reduction_same_bits_as_the_owners_and_counts_back_at_zero(shape, blk, dtype, out):
+    M, N, K = shape
+    A, B = inputs.uniform_pair(M, N, K, dtype, 76)
+    dA, dB = to_device(A), to_device(B)
+    print("shared reduction", shape, blk, dtype, out, flush=True)
+    r = Runner(M, N, K, sk.SK_POLICY_ALL_SK, blk, 256, dtype, out)
+    try:
+        shared = [r.run(dA, dB).clone() for _ in range(3)]
+        assert r.check() == sk.SK_OK
+        flags = r.ws[(-r.ws.data_ptr()) % 256:][:256 * 128]
+        assert not flags.any()                   # the next launch, and another plan on this workspace, find the counts at zero
+        err = G.rel_error(r.result(shared[0]), G.gemm_fp64(A, B, ODT[dtype]))
+        assert err <= (TOL_32 if out == sk.SK_F32 else TOL_16), err
+        # the same plan with the least workspace: the owner's reduction, in the same order; and a time-out of the wait is survived
+        info, slots = r.info, 256 * r.info["blk_m"] * r.info["blk_n"] * 4
+        least = 257 * 128 + 384 + slots
+        needs_more = info["iters_per_tile"] % info["iters_per_wg"] != 0
+        assert sk.sk_workspace_bytes(r.plan) == least + needs_more * info["tiles"] * info["blk_m"] * info["blk_n"] * 4
+        base = (r.ws.data_ptr() + 255) // 256 * 256
+        if needs_more:
+            sk.sk_plan_set_workspace(r.plan, base, least)
+            owners = r.run(dA, dB)
+            assert r.check() == sk.SK_OK
+            assert all(torch.equal(d.view(torch.uint8), owners.view(torch.uint8)) for d in shared)
+            sk.sk_plan_set_workspace(r.plan, base, sk.sk_workspace_bytes(r.plan))
+        sk.sk_plan_set_spin_limit(r.plan, 0)
+        r.run(dA, dB)
+        assert r.check() in (sk.SK_OK, sk.SK_ERR_TIMEOUT)
+        sk.sk_plan_set_spin_limit(r.plan, 1 << 24)
+        assert torch.equal(r.run(dA, dB).view(torch.uint8), shared[0].view(torch.uint8)) and r.check() == sk.SK_OK
+    finally:
+        r.close()
+
+
 def test_bit_identical_run_to_run_and_flag_reuse():
     c = inputs.config1()
     dA, dB = to_device(c["A"]), to_device(c["B"])
