@@ -192,6 +192,10 @@ struct Cfg {
     static_assert(CPB >= 8, "B swizzle assumes rows of at least 128 bytes");
     static_assert(NSB >= 2 && (NSA == NSB || NSA == NSB + 1) && LDS_BYTES <= 160 * 1024, "LDS budget / ring depths");
     static_assert((NSA - 1) * LPS <= 63, "vmcnt range");
+    // Stages requested before the first one is waited for, at the kernel's start; the others of the ring follow once that has
+    // landed (the requests of early workgroups delay the first stage of late ones: two instead of three of the ring of four
+    // 0.05 - 0.08 us at 512^3 and 640 x 2048 x 512; one, whose successor then comes too late, 0.1 us slower).
+    static constexpr int START = NSA == NSB && NSA > 3 ? 2 : NSA - 1;
     // LDS-DMA loads that may still be in flight when iteration i starts, if `later` more
     // iterations follow it.  Issue order inside an iteration: B tile of iteration +NSB-1, then A
     // tile of iteration +NSA-1; loads complete in order.
@@ -644,17 +648,17 @@ __device__ __forceinline__ void issue_requests(const GemmArgs& g, const DmaMap<C
     }
 }
 
-// The first requests of a segment on the LDS-DMA path: the batches that stages before the first would have
-// requested, all but the last (that one goes out in the MAC loop's first trip).  The ring must be free: no
-// wave may still read operands of the previous segment.  Called either at the start of the MAC loop or -
-// for the segment after the current one - before the current tile's fix-up and epilogue, so that the
-// first loads travel while the tile is stored.
-template <class C, bool NT>
-__device__ __forceinline__ void mac_prefetch(const GemmArgs& g, int m0, int n0, int k_begin, int k_end, unsigned char* smem, const DmaMap<C>& dm) {
+// The first requests of a segment on the LDS-DMA path: of the batches that NSA stages before the first would have
+// requested, numbers FIRST .. LAST - 1.  The ring must be free: no
+// wave may still read operands of the previous segment.  All but the last batch are called for either at the start of the MAC loop
+// (in two parts, see Cfg::START) or - for the segment after the current one - before the current tile's fix-up and epilogue, so that
+// the first loads travel while the tile is stored; the last one once the first stage has landed.
+template <class C, bool NT, int FIRST = 0, int LAST = C::NSA - 1>
+__device__ __forceinline__ void mac_prefetch(const GemmArgs& g, int k_begin, int k_end, unsigned char* smem, const DmaMap<C>& dm) {
     const uint32_t lds0 = (uint32_t)(size_t)(lds_byte*)smem;
     const int nk = k_end - k_begin, full_k = g.K / C::BK;
 #pragma unroll
-    for (int j = -C::NSA; j <= -2; j++)
+    for (int j = FIRST - C::NSA; j < LAST - C::NSA; j++)
         issue_requests<C, false, NT>(g, dm, lds0, k_begin, nk, full_k, j, (j + C::NSA) % C::NSA, (j + 2 * C::NSB) % C::NSB, 0, 1);
 }
 
@@ -819,11 +823,12 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
         const int full_k = g.K / C::BK;             // iterations below this index are entirely inside K
         DmaMap<C> dm;
         dm.init(g, m0, n0);
-        if (!prefetched) mac_prefetch<C, NT>(g, m0, n0, k_begin, k_end, smem, dm);
+        if (!prefetched) mac_prefetch<C, NT, 0, C::START>(g, k_begin, k_end, smem, dm);
         // request batch j (issued after the barrier of stage j): B tile of stage j+NSB, then A tile of
         // stage j+NSA, into the slots of stage j; step / steps select a slice of the batch
+        // (steady: 1, nothing to check; 0: see issue_requests; -1: a trip that requests nothing)
         auto issue_batch = [&](int j, int slot_a, int slot_b, int step, int steps, auto steady) {
-            issue_requests<C, decltype(steady)::value, NT>(g, dm, lds0, k_begin, nk, full_k, j, slot_a, slot_b, step, steps);
+            if (decltype(steady)::value >= 0) issue_requests<C, decltype(steady)::value == 1, NT>(g, dm, lds0, k_begin, nk, full_k, j, slot_a, slot_b, step, steps);
         };
         Frags<C> f[2];
         int ca = C::NSA - 1, cb = C::NSB - 1;        // ring slots of stage i (i = -1: the slots batch -1 fills)
@@ -859,9 +864,21 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
+        // Wait for the segment's first stage and request the rest of the ring, all of which is free.
+        auto wait_first = [&]() {
+            if (!prefetched) {
+                wait_stage<C, C::START - 1>(nk - 1);
+                mac_prefetch<C, NT, C::START, C::NSA - 1>(g, k_begin, k_end, smem, dm);
+            } else if (stores_in_flight) {
+                wait_stage<C, C::NSA - 1, C::EPILOGUE_STORES>(nk - 1);
+            } else {
+                wait_stage<C, C::NSA - 1>(nk - 1);
+            }
+            mac_prefetch<C, NT, C::NSA - 1, C::NSA>(g, k_begin, k_end, smem, dm);
+        };
         auto trip = [&](int i, auto first, auto next, auto steady) {
             constexpr bool FIRST = decltype(first)::value;
-            constexpr bool STEADY = decltype(steady)::value;     // batch i's stages exist and need no K-tail handling, and at least NSA - 1 stages follow stage i + 1
+            constexpr bool STEADY = decltype(steady)::value == 1;   // batch i's stages exist and need no K-tail handling, and at least NSA - 1 stages follow stage i + 1
             constexpr int NEXT = decltype(next)::value;          // 1 / 0: known, -1: decided at run time
             const bool has_next = NEXT < 0 ? i + 1 < nk : NEXT == 1;
             const int na = ca + 1 == C::NSA ? 0 : ca + 1, nb = cb + 1 == C::NSB ? 0 : cb + 1;   // slots of stage i+1
@@ -871,7 +888,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
                 static_assert(!C::FINE || NEXT >= 0, "known at compile time under PIN_ORDER");
                 if (NEXT) {
                     if (STEADY) wait_vmcnt<C::in_flight(C::NSA - 1)>();
-                    else if (FIRST && stores_in_flight) wait_stage<C, C::NSA - 1, C::EPILOGUE_STORES>(nk - 2 - i);
+                    else if (FIRST) wait_first();
                     else wait_stage<C, C::NSA - 1>(nk - 2 - i);
                     __syncthreads();
                 }
@@ -889,7 +906,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
             }
             if (has_next) {
                 if (STEADY) wait_vmcnt<C::in_flight(C::NSA - 1)>();
-                else if (FIRST && stores_in_flight) wait_stage<C, C::NSA - 1, C::EPILOGUE_STORES>(nk - 2 - i);
+                else if (FIRST) wait_first();
                 else wait_stage<C, C::NSA - 1>(nk - 2 - i);   // stage i+1 has landed (this wave's share)
                 __syncthreads();                         // ... and everybody's; stage i's slots are free
                 f[0].load(a_next, b_next, fm, 0);
@@ -914,20 +931,26 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
         typedef std::integral_constant<int, 0> No;
         typedef std::integral_constant<int, -1> AtRunTime;
         // Trips 0 .. n_steady-1 request stages that exist and lie inside K: their body carries neither
-        // range checks nor the K-tail variant of the requests, and waits with a constant count.
+        // range checks nor the K-tail variant of the requests, and waits with a constant count.  The first trip (wait_first
+        // has filled the ring) and those from nk - NSB on request nothing, and a copy of the trip without requests serves them: slot by
+        // slot the checks cost 0.05 - 0.2 us a trip, NSA of them per segment.  With START, us: 512^3 f16 4.71 -> 4.42, 1280 x 2048 x 256
+        // on 128 x 128 6.36 -> 5.89, 640 x 1024 x 512 on 64 x 64 5.49 -> 5.01, 1472 x 1936 x 144 6.26 -> 5.64, 1008 x 1200 x 1040 9.43 -> 9.19.
         int n_steady = (full_k - k_begin < nk ? full_k - k_begin : nk) - C::NSA;
         if (n_steady < 0) n_steady = 0;
+        typedef std::integral_constant<int, -1> Quiet;
         if constexpr (C::PIN_ORDER) {
-            trip(-1, std::true_type(), Yes(), std::false_type());
+            trip(-1, std::true_type(), Yes(), Quiet());
             int i = 0;
-            for (; i < n_steady; i++) trip(i, std::false_type(), Yes(), std::true_type());
-            for (; i < nk - 1; i++) trip(i, std::false_type(), Yes(), std::false_type());
-            trip(nk - 1, std::false_type(), No(), std::false_type());
+            for (; i < n_steady; i++) trip(i, std::false_type(), Yes(), Yes());
+            for (; i < nk - C::NSB; i++) trip(i, std::false_type(), Yes(), No());
+            for (; i < nk - 1; i++) trip(i, std::false_type(), Yes(), Quiet());
+            trip(nk - 1, std::false_type(), No(), Quiet());
         } else {
-            trip(-1, std::true_type(), AtRunTime(), std::false_type());
+            trip(-1, std::true_type(), AtRunTime(), Quiet());
             int i = 0;
-            for (; i < n_steady; i++) trip(i, std::false_type(), Yes(), std::true_type());
-            for (; i < nk; i++) trip(i, std::false_type(), AtRunTime(), std::false_type());
+            for (; i < n_steady; i++) trip(i, std::false_type(), Yes(), Yes());
+            for (; i < nk - C::NSB; i++) trip(i, std::false_type(), Yes(), No());
+            for (; i < nk; i++) trip(i, std::false_type(), AtRunTime(), Quiet());
         }
         __syncthreads();                             // all reads done before the next segment refills
     } else {
@@ -1657,8 +1680,8 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         if (prefetched) {
             DmaMap<C> ahead;
             ahead.init(g, m0, n0);
-            if (MAY_NT && g.stream_b) mac_prefetch<C, MAY_NT>(g, m0, n0, k_begin, k_end, smem, ahead);
-            else mac_prefetch<C, false>(g, m0, n0, k_begin, k_end, smem, ahead);
+            if (MAY_NT && g.stream_b) mac_prefetch<C, MAY_NT>(g, k_begin, k_end, smem, ahead);
+            else mac_prefetch<C, false>(g, k_begin, k_end, smem, ahead);
         }
         stores_in_flight = finish_segment(cur_tile, cur_k_begin, cur_k_end, cur_m0, cur_n0, acc) && prefetched;
     }

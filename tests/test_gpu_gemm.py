@@ -369,6 +369,18 @@ def test_workgroups_with_work_in_the_last_wave_spread_over_the_xcds(shape, blk, 
         _run_and_compare(A, B, inputs.BF16, policy, blk, grid=grid, out_dtype=out, ref=ref, exact=out == sk.SK_F32, launches=2)
 
 
+@pytest.mark.parametrize("dtype,blk", [(inputs.BF16, b) for b in ((256, 256, 64), (256, 128, 64), (128, 128, 64), (128, 128, 32), (64, 128, 64),
+                                                                  (32, 128, 64), (16, 128, 64), (64, 64, 128), (32, 64, 64), (256, 256, 32))] +
+                         [(inputs.E4M3, b) for b in ((256, 256, 128), (128, 256, 128), (128, 128, 128), (64, 128, 128), (32, 128, 128))])
+def test_segments_shorter_and_longer_than_the_ring(dtype, blk):
+    """One to seven k-iterations, whole and ragged: the trips that fill the ring, find it filled, and request nothing."""
+    piece = 16 if dtype == inputs.E4M3 else 8
+    for iters in range(1, 8):
+        for K in (iters * blk[2], iters * blk[2] - blk[2] + piece):
+            A, B = inputs.small_int_pair(blk[0] + 8, blk[1], K, dtype, 78, lo=-1, hi=1)
+            _run_and_compare(A, B, dtype, sk.SK_POLICY_DP, blk, grid=1 if iters % 2 else 256, out_dtype=sk.SK_F32, exact=True)
+
+
 # Shared reduction (every workgroup of a tile adds up a share of it): sizes at which it applies, with ranges that end with the
 # tiles and that straddle them, edge tiles, one and two round trips of 16 contributors, tiles of one and of eight units per workgroup.
 SHARED = [((256, 512, 4096), (64, 64, 128), sk.SK_BF16, sk.SK_BF16), ((700, 256, 2000), (64, 128, 64), sk.SK_BF16, sk.SK_F16),
