@@ -173,6 +173,12 @@ struct Cfg {
     static constexpr int PIECES = CA + CB;
     static constexpr bool STAGED_FINE = FINE && KK % 2 == 0 && 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 5 * PIECES + 32 <= 256;
     static constexpr int STAGES_HELD = 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 4 * PIECES + 64 > 256 ? 0 : PIECES <= 5 ? 4 : PIECES <= 8 ? 2 : 1;
+    // The other tiles' stages in whole rounds of STAGES_HELD (see mac_loop_staged), but for the tiles of 16 and 32 rows on four waves,
+    // which are 1 - 8 % slower with them.  us: 319 x 1021 on 32 x 64, K = 125 / 253 / 1021 / 2043, 4.62 -> 4.33, 5.44 -> 5.15, 10.2 -> 8.8,
+    // 16.2 -> 12.8 (between five and thirteen iterations on a few dozen tiles 0.2 us slower: 103 x 334 x 479 6.01 -> 6.24); 639 x 1021 on
+    // 64 x 64 2 - 7 %; 639 x 2045 on 64 x 128, K = 61, 4.52 -> 4.24, longer ones level to 2 % slower; 8 bits 2 - 8 % up to K = 509,
+    // 1 - 2 % slower from 2043 on.
+    static constexpr bool STAGED_ROUNDS = STAGES_HELD > 0 && PIECES != 5;
     // vector stores one wave issues in the epilogue of an unsplit interior tile with 16-bit output (an fp32
     // output issues more): what may still be in flight when the next tile's first stage is waited for
     static constexpr int EPILOGUE_STORES = MI * NI * (MF == 32 ? ACC / 8 : ACC / 4);
@@ -707,9 +713,13 @@ __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n
             for (int q = 0; q < C::PIECES; q++) st[q] = sf.template fetch<true>(g, k_begin + 1, q);
         }
         Frags<C> f[2];
-        auto step = [&](int i, int k_step, auto read, const Frags<C>& cur, Frags<C>& nxt, int kk_next, auto steady) {
-            constexpr int R = Frags<C>::READS, NRS = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1;
-            constexpr bool STEADY = decltype(steady)::value;
+        // Kinds of trips: STEADY parks a stage and fetches one that is inside, CHECKED any, PARK has none left to fetch, QUIET none to park.
+        // (Which it is is known at compile time: behind a branch the compiler waits for every load in flight, not only for
+        // the piece that is parked, and the first and last trips of a segment took twice a steady one's time.  us: 1279 x 2045 on 128 x 128,
+        // K = 253 / 509 / 2043, 8.7 -> 7.4, 11.4 -> 9.8, 25.6 -> 24.1; 256 x 128, 1535 x 2045 x 509 16.3 -> 14.1; 3841 x 4225 x 4097 161 -> 156.)
+        enum { STEADY, CHECKED, PARK, QUIET };
+        auto step = [&](int i, int k_step, auto read, const Frags<C>& cur, Frags<C>& nxt, int kk_next, auto kind) {
+            constexpr int R = Frags<C>::READS, NRS = NM * 3 / 4 > 0 ? NM * 3 / 4 : 1, KIND = decltype(kind)::value;
 #pragma unroll
             for (int s = 0; s < NM; s++) {
                 const int mi = s / C::NI, ni = s % C::NI, slot = k_step * NM + s;
@@ -718,38 +728,40 @@ __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n
 #pragma unroll
                     for (int r = s * R / NRS; r < (s + 1) * R / NRS; r++) nxt.load_one(a_slot(i + 1), b_slot(i + 1), fm, kk_next, r);
                 }
-                if (slot < PS) {
+                if (KIND != QUIET && slot < PS) {
 #pragma unroll
                     for (int q = slot * C::PIECES / PS; q < (slot + 1) * C::PIECES / PS; q++) {
-                        if (STEADY || i + 2 < nk) sf.park(a_slot(i), b_slot(i), q, st[q]);
-                        if (STEADY || i + 3 < nk) st[q] = sf.template fetch<!STEADY>(g, k_begin + i + 3, q);
+                        sf.park(a_slot(i), b_slot(i), q, st[q]);
+                        if (KIND != PARK) st[q] = sf.template fetch<KIND != STEADY>(g, k_begin + i + 3, q);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        auto trip = [&](int i, auto next, auto steady) {
+        auto trip = [&](int i, auto next, auto kind) {
             constexpr bool NEXT = decltype(next)::value;
+            constexpr int KIND = decltype(kind)::value;
             if (NEXT) __syncthreads();
-            if (NEXT && !decltype(steady)::value && i + 2 < nk) sf.cut(g, k_begin + i + 2, st);
+            if (KIND == CHECKED || KIND == PARK) sf.cut(g, k_begin + i + 2, st);
             __builtin_amdgcn_sched_barrier(0);
-            step(i, 0, std::integral_constant<bool, NEXT>(), f[1], f[0], 0, steady);
+            step(i, 0, std::integral_constant<bool, NEXT>(), f[1], f[0], 0, kind);
             if (NEXT) {
 #pragma unroll
-                for (int kk = 0; kk < C::KK - 1; kk++) step(i, kk + 1, std::true_type(), f[kk & 1], f[(kk + 1) & 1], kk + 1, steady);
+                for (int kk = 0; kk < C::KK - 1; kk++) step(i, kk + 1, std::true_type(), f[kk & 1], f[(kk + 1) & 1], kk + 1, kind);
             }
         };
         // trips 0 .. n_steady-1 fetch a stage that exists and is inside: no checks in their body
         const int n_steady = (inside - k_begin < nk ? inside - k_begin : nk) - 3;
-        // trip -1 multiplies zeros: it runs the checked trips' code, which a short segment then fetches once
-        f[1] = Frags<C>{};
+        f[1] = Frags<C>{};                       // trip -1 multiplies zeros: the other checked trips run its code
         int i = -1;
-        do {
-            trip(i, std::true_type(), std::false_type());
+        while (i < nk - 3) {
+            trip(i, std::true_type(), std::integral_constant<int, CHECKED>());
             i++;
-            for (; i < n_steady; i++) trip(i, std::true_type(), std::true_type());
-        } while (i < nk - 1);
-        trip(nk - 1, std::false_type(), std::false_type());
+            for (; i < n_steady; i++) trip(i, std::true_type(), std::integral_constant<int, STEADY>());
+        }
+        if (nk > 1) trip(nk - 3, std::true_type(), std::integral_constant<int, PARK>());
+        trip(nk - 2, std::true_type(), std::integral_constant<int, QUIET>());
+        trip(nk - 1, std::false_type(), std::integral_constant<int, QUIET>());
     } else {
         // The other tiles: HELD stages in registers, requested HELD k-iterations ahead of their use (HELD = 0: the
         // two operand sets leave no room, a stage is requested right before it is parked).
@@ -759,6 +771,7 @@ __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n
 #pragma unroll
             for (int q = 0; q < C::PIECES; q++) dst[q] = sf.template fetch<true>(g, kit, q);
         };
+        // whole rounds of H stages whose requests are all inside, then the rest
         auto consume = [&](int s, uint4 (&src)[C::PIECES], auto steady) {
             constexpr bool STEADY = decltype(steady)::value;
             if (HELD == 0) fetch_stage(k_begin + s, src);
@@ -776,22 +789,60 @@ __device__ __forceinline__ void mac_loop_staged(const GemmArgs& g, int m0, int n
             __syncthreads();      // also: every wave is done with the other slot (stage s-1)
             mac_stage<C, TR>(a_slot(s), b_slot(s), fm, acc);
         };
-        if (HELD > 0) {
+        if constexpr (!C::STAGED_ROUNDS) {
+            if (HELD > 0) {
+#pragma unroll
+                for (int h = 0; h < H; h++)
+                    if (h < nk) fetch_stage(k_begin + h, st[h]);
+            }
+            const int n_steady = HELD == 0 ? 0 : (inside - k_begin < nk ? inside - k_begin : nk) - H;
+            int s = 0;
+            for (; s + H <= n_steady; s += H) {
+#pragma unroll
+                for (int h = 0; h < H; h++) consume(s + h, st[h], std::true_type());
+            }
+            for (; s < nk; s += H) {
+#pragma unroll
+                for (int h = 0; h < H; h++)
+                    if (s + h < nk) consume(s + h, st[h], std::false_type());
+            }
+        } else {
+            // The first round filled up with `pad` stages in front that do not exist; each round fetches the next one's stages, the
+            // last one none.  Padding in front, and fetching in the first round where nothing is multiplied, leaves the same loads in
+            // flight behind a stage's own whatever the number of stages: where that depends on a branch the compiler waits
+            // for every load in flight before a stage is parked.
+            const int rounds = (nk + H - 1) / H, pad = rounds * H - nk;
+            auto round = [&](int r, int skip, auto checked, auto more) {
+#pragma unroll
+                for (int h = 0; h < H; h++) {
+                    const int s = r * H + h - pad;
+                    if (!decltype(checked)::value || h >= skip) {
+                        if (decltype(checked)::value) sf.cut(g, k_begin + s, st[h]);
+#pragma unroll
+                        for (int q = 0; q < C::PIECES; q++) sf.park(a_slot(s), b_slot(s), q, st[h][q]);
+                    }
+                    if (decltype(more)::value) {
+#pragma unroll
+                        for (int q = 0; q < C::PIECES; q++) st[h][q] = sf.template fetch<decltype(checked)::value>(g, k_begin + s + H, q);
+                    }
+                    if (!decltype(checked)::value || h >= skip) {
+                        __syncthreads();
+                        mac_stage<C, TR>(a_slot(s), b_slot(s), fm, acc);
+                    }
+                }
+            };
 #pragma unroll
             for (int h = 0; h < H; h++)
-                if (h < nk) fetch_stage(k_begin + h, st[h]);
-        }
-        // whole rounds of H stages whose requests are all inside, then the rest
-        const int n_steady = HELD == 0 ? 0 : (inside - k_begin < nk ? inside - k_begin : nk) - H;
-        int s = 0;
-        for (; s + H <= n_steady; s += H) {
-#pragma unroll
-            for (int h = 0; h < H; h++) consume(s + h, st[h], std::true_type());
-        }
-        for (; s < nk; s += H) {
-#pragma unroll
-            for (int h = 0; h < H; h++)
-                if (s + h < nk) consume(s + h, st[h], std::false_type());
+                if (h >= pad) fetch_stage(k_begin + h - pad, st[h]);
+            // rounds 1 .. n_steady-1 multiply and fetch stages that are inside
+            const int n_steady = ((inside - k_begin < nk ? inside - k_begin : nk) + pad) / H - 1;
+            int r = 0;
+            while (r < rounds - 1) {
+                round(r, r == 0 ? pad : 0, std::true_type(), std::true_type());
+                r++;
+                for (; r < n_steady; r++) round(r, 0, std::false_type(), std::true_type());
+            }
+            round(r, r == 0 ? pad : 0, std::true_type(), std::false_type());
         }
     }
     __syncthreads();                             // all reads done before the next segment refills

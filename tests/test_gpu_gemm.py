@@ -381,6 +381,19 @@ def test_segments_shorter_and_longer_than_the_ring(dtype, blk):
             _run_and_compare(A, B, dtype, sk.SK_POLICY_DP, blk, grid=1 if iters % 2 else 256, out_dtype=sk.SK_F32, exact=True)
 
 
+@pytest.mark.parametrize("dtype,blk", [(inputs.F16, b) for b in ((256, 256, 64), (256, 128, 64), (128, 128, 64), (128, 128, 32), (64, 128, 64),
+                                                                 (32, 128, 64), (16, 128, 64), (64, 64, 128), (32, 64, 64), (256, 256, 32))] +
+                         [(inputs.E4M3, b) for b in ((256, 256, 128), (128, 256, 128), (128, 128, 128), (64, 128, 128), (32, 128, 128))])
+def test_register_staged_segments_of_every_length(dtype, blk):
+    """One to eleven k-iterations off the 16-byte grid: whole tiles, and pieces of tiles that end inside K."""
+    for iters in range(1, 12):
+        M, N, K = blk[0] + 3, blk[1] - 3, (iters - 1) * blk[2] + (5, blk[2] - 1)[iters % 2]
+        A, B = inputs.small_int_pair(M, N, K, dtype, 79, lo=-1, hi=1)
+        ref = G.gemm_fp64(A, B, ODT[dtype])
+        _run_and_compare(A, B, dtype, sk.SK_POLICY_DP, blk, grid=1, out_dtype=sk.SK_F32, ref=ref, exact=True)
+        _run_and_compare(A, B, dtype, sk.SK_POLICY_ALL_SK, blk, grid=3, out_dtype=sk.SK_F32, ref=ref, exact=True)
+
+
 # Shared reduction (every workgroup of a tile adds up a share of it): sizes at which it applies, with ranges that end with the
 # tiles and that straddle them, edge tiles, one and two round trips of 16 contributors, tiles of one and of eight units per workgroup.
 SHARED = [((256, 512, 4096), (64, 64, 128), sk.SK_BF16, sk.SK_BF16), ((700, 256, 2000), (64, 128, 64), sk.SK_BF16, sk.SK_F16),
