@@ -915,7 +915,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // Wait for the segment's first stage and request the rest of the ring, all of which is free.
+        // Wait for the segment's first stage and request the rest of the ring, all of which is free (PIN_ORDER; otherwise the trip does that).
         auto wait_first = [&]() {
             if (!prefetched) {
                 wait_stage<C, C::START - 1>(nk - 1);
@@ -925,7 +925,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
             } else {
                 wait_stage<C, C::NSA - 1>(nk - 1);
             }
-            mac_prefetch<C, NT, C::NSA - 1, C::NSA>(g, k_begin, k_end, smem, dm);
+            if (C::PIN_ORDER) mac_prefetch<C, NT, C::NSA - 1, C::NSA>(g, k_begin, k_end, smem, dm);
         };
         auto trip = [&](int i, auto first, auto next, auto steady) {
             constexpr bool FIRST = decltype(first)::value;
@@ -997,11 +997,13 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
             for (; i < nk - 1; i++) trip(i, std::false_type(), Yes(), Quiet());
             trip(nk - 1, std::false_type(), No(), Quiet());
         } else {
-            trip(-1, std::true_type(), AtRunTime(), Quiet());
+            // (The one tile whose accumulators leave no room for a second operand set, 8-bit 256 x 256 on eight waves, has no
+            // copy of the trip without requests: with one the compiler keeps accumulators in scratch, 14464 x 1632 x 6432 172 us ->
+            // 1595.)
+            trip(-1, std::true_type(), AtRunTime(), No());
             int i = 0;
             for (; i < n_steady; i++) trip(i, std::false_type(), Yes(), Yes());
-            for (; i < nk - C::NSB; i++) trip(i, std::false_type(), Yes(), No());
-            for (; i < nk; i++) trip(i, std::false_type(), AtRunTime(), Quiet());
+            for (; i < nk; i++) trip(i, std::false_type(), AtRunTime(), No());
         }
         __syncthreads();                             // all reads done before the next segment refills
     } else {
