@@ -246,7 +246,10 @@ int sk_plan_set_workspace(sk_plan_t* plan, void* dev_ptr, size_t bytes);
 /* Number of flag polls after which a waiting tile owner gives up, records a
  * time-out in the workspace status word and goes on (so that every wave exits
  * even if a partial never arrives).  Default 1 << 24.  0 = give up on the first
- * unsuccessful poll (for tests of the error path). */
+ * unsuccessful poll (for tests of the error path).  Where all workgroups of a tile
+ * reduce it together (see sk_plan_set_workspace) nobody has to wait: a workgroup
+ * polls at most this often, and at most a few hundred times, and then leaves its
+ * share to the last one, with the same results and no time-out. */
 int sk_plan_set_spin_limit(sk_plan_t* plan, uint32_t polls);
 
 /* D = A * B under the plan (Algorithm 1 with its MAC loop on the matrix cores;
@@ -264,7 +267,9 @@ int sk_plan_set_spin_limit(sk_plan_t* plan, uint32_t polls);
  * capture does not allow).
  * Co-residency: under SK_FIXUP_FLAGS a tile owner waits inside the kernel for
  * workgroups of the same launch, so all `grid` workgroups must be on the device
- * at once.  sk_gemm checks that against an otherwise idle device; the caller
+ * at once (not where all workgroups of a tile reduce it together, see
+ * sk_plan_set_workspace: such a launch ends, later, with any part of the device).
+ * sk_gemm checks that against an otherwise idle device; the caller
  * must not let such a launch overlap with other kernels that occupy compute
  * units (e.g. a second sk_gemm on another stream): two launches that each hold
  * part of the device can wait for each other until the bounded wait gives up

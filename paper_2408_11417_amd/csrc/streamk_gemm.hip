@@ -228,8 +228,9 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
     }
     // an owner spins on flags of other workgroups: all of them must be on the machine at once
     if (plan->needs_fixup && !atomic && h.grid > e->max_resident.load()) return SK_ERR_UNSUPPORTED;
-    if (e->shared_generic && sk_shared_reduction(plan) && workspace_bytes >= sk_workspace_bytes(plan) && h.grid <= e->max_shared.load())
-        fn = aligned ? e->shared_aligned : e->shared_generic;
+    // (a larger grid's shared reduction would end too, but its first workgroups would wait in vain: the owner's is faster)
+    const bool shared = e->shared_generic && sk_shared_reduction(plan) && workspace_bytes >= sk_workspace_bytes(plan) && h.grid <= e->max_shared.load();
+    if (shared) fn = aligned ? e->shared_aligned : e->shared_generic;
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     GemmArgs g{};
@@ -241,7 +242,7 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
     g.M = (int)h.M; g.N = (int)h.N; g.K = (int)h.K;
     g.tiles_m = h.tiles_m; g.tiles_n = h.tiles_n; g.tiles = h.tiles; g.ipt = h.iters_per_tile; g.tile_order = h.tile_order;
     g.sk_tiles = h.sk_tiles; g.ipw = h.iters_per_wg; g.grid = h.grid; g.sk_iters = (int)h.sk_iters;
-    g.spin_limit = plan->spin_limit;
+    g.spin_limit = shared ? std::min(plan->spin_limit, sk_share_polls(h)) : plan->spin_limit;
     g.out_dtype = h.out_dtype;
     g.dp_first = plan->dp_first;
     g.k_aligned = plan->k_aligned;

@@ -42,6 +42,40 @@ inline sk_fast_div sk_make_fast_div(uint32_t d) {
 }
 inline uint32_t sk_fast_div_apply(uint32_t n, sk_fast_div f) { return (uint32_t)(((uint64_t)n * f.mul) >> f.shift); }
 
+// ---- shared reduction: who adds up and stores which part of a split tile, and when -----------------
+// The n workgroups of a tile park their pieces and count themselves in at the tile's flag line.  Then each waits for the others, for a
+// bounded time, and leaves: with its share of the tile where all have arrived by then, and otherwise giving the share up, which it
+// notes in the line's other words.  The last one to leave, by whose time all have arrived, takes what was given up.  So nobody
+// depends on a workgroup that has not started: the launch ends whatever part of the device it gets, and only the split of the
+// work depends on it.  (tests/host/shared_reduction.cpp runs these functions on threads.)
+#ifdef __HIPCC__
+#define SK_HOST_DEVICE __host__ __device__
+#else
+#define SK_HOST_DEVICE
+#endif
+// The line's first word: three counts of ten bits, of the workgroups that have arrived, have left, have given their share up.
+constexpr uint32_t SK_ARRIVES = 1, SK_LEAVES = 1u << 10, SK_GIVES_UP = 1u << 20;
+SK_HOST_DEVICE inline uint32_t sk_arrived(uint32_t word) { return word & 1023; }
+SK_HOST_DEVICE inline uint32_t sk_left(uint32_t word) { return word >> 10 & 1023; }
+SK_HOST_DEVICE inline uint32_t sk_given_up(uint32_t word) { return word >> 20; }
+// ... and a bit per workgroup in the other words.
+constexpr int SK_LINE_WORDS = (int)(SK_FLAG_STRIDE / 4), SK_MAX_SHARERS = 32 * (SK_LINE_WORDS - 1);
+// How often a workgroup polls for the others: a little longer than they are apart on an idle device, which is a part of the time that
+// their iterations take.  Least number without a loss, 256 x 256 tiles: 8 iterations 64, 12 of 8 bits 112, 118 about 800;
+// 64 x 128: 34 64, 54 - 94 about 100; smaller ones 2 - 32.
+inline uint32_t sk_share_polls(const sk_plan_header& h) {
+    return 64 + (uint32_t)h.iters_per_wg * (2 + (uint32_t)(h.blk_m * h.blk_n) / 8192);
+}
+// Leave the tile, with share j or giving it up.  Returns the first word as it is then.
+// Line: add(v), the word before it; give_up(j), which is done when it returns.
+template <class Line> SK_HOST_DEVICE inline uint32_t sk_leave_tile(const Line& line, int j, bool with_share) {
+    if (!with_share) line.give_up(j);
+    const uint32_t step = with_share ? SK_LEAVES : SK_LEAVES + SK_GIVES_UP;
+    return line.add(step) + step;
+}
+// Share j of n of a tile of `units` units.
+SK_HOST_DEVICE inline int sk_share_begin(int units, int j, int n) { return (int)((uint32_t)units * (uint32_t)j / (uint32_t)n); }
+
 // Does the plan's fix-up share the reduction of a tile among all its workgroups (where its kernel can and the workspace suffices)?
 bool sk_shared_reduction(const sk_plan_t* plan);
 // The workspace that a plan cannot do without; sk_workspace_bytes adds what the shared reduction needs.

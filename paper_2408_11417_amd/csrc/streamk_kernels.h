@@ -1372,11 +1372,19 @@ __device__ __forceinline__ void reduce_and_store(const GemmArgs& g, int row0, in
 // of all pieces, adds them up and stores that share of D.  What bounds the exchange otherwise is the owner's CU, which takes the
 // partial tiles of all contributors through one port (about 107 bytes per ns); here a tile's pieces go to as many CUs as made
 // them.  The order of the additions is the owner's (and, from 2 * SK_TREE_GROUP contributors on, the group leaders'): the
-// results are the same bit for bit.
-//
-// Count of a tile: arrivals in the lower half of its flag line's word, in the upper half those who need not look at
-// it any more.  The last of these takes it down.
-__device__ __forceinline__ uint32_t* tile_count(const GemmArgs& g, int tile) { return g.flags + (size_t)tile * (SK_FLAG_STRIDE / 4); }
+// results are the same bit for bit, whoever takes a share (see sk_leave_tile).
+struct TileLine {
+    uint32_t* word;
+    __device__ __forceinline__ TileLine(const GemmArgs& g, int tile) : word(g.flags + (size_t)tile * SK_LINE_WORDS) {}
+    __device__ __forceinline__ uint32_t load(int i = 0) const { return __hip_atomic_load(word + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ uint32_t add(uint32_t v) const { return __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void give_up(int j) const {
+        uint32_t before = __hip_atomic_fetch_or(word + 1 + j / 32, 1u << j % 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("" : "+v"(before) : : "memory");      // waits for the answer: the bit is there before the count says so
+    }
+    __device__ __forceinline__ bool is_given_up(int j) const { return load(1 + j / 32) >> j % 32 & 1; }
+    __device__ __forceinline__ void clear(int i = 0) const { __hip_atomic_store(word + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
 // Where a workgroup's piece of a tile is parked: in the workgroup's slot - but the owner's, whose slot holds its piece of
 // the next tile if its range goes on there, then behind the workgroups' slots.
 __device__ __forceinline__ int owner_slot(const GemmArgs& g, int tile, int wg) {
@@ -1410,24 +1418,27 @@ __device__ __forceinline__ void store_four(const GemmArgs& g, int row, int col, 
 // of one wave takes in a slot.
 template <class C> struct Share {
     static constexpr int Q = C::ACC / 4, BLOCKS = C::MI * C::NI, UNITS = C::NW * BLOCKS * Q;
-    int tile, last_wg, n_all, begin, end;        // the tile, its owner, the number of its contributors
+    int tile, last_wg, n_all, j, begin, end;     // the tile, its owner, the number of its contributors, which share
     __device__ __forceinline__ void init(const GemmArgs& g, int x, int t) {
         tile = t;
         const int first_wg = (int)fast_div((uint32_t)(t * g.ipt), g.div_ipw);
         last_wg = (int)fast_div((uint32_t)(t * g.ipt + g.ipt - 1), g.div_ipw);
         n_all = last_wg - first_wg;
-        const uint32_t j = (uint32_t)(last_wg - x), n = (uint32_t)n_all + 1;
-        begin = (int)(UNITS * j / n);
-        end = (int)(UNITS * (j + 1) / n);
+        take(last_wg - x);
+    }
+    __device__ __forceinline__ void take(int share) {
+        j = share;
+        begin = sk_share_begin(UNITS, j, n_all + 1);
+        end = sk_share_begin(UNITS, j + 1, n_all + 1);
     }
 };
 
 // One unit of a tile: all its pieces added up, 16 contributors per round trip, and stored.
 template <class C, bool TR>
-__device__ __forceinline__ void store_unit(const GemmArgs& g, const buffer_rsrc& rsrc, const Share<C>& share, int unit) {
+__device__ __forceinline__ void store_unit(const GemmArgs& g, const buffer_rsrc& rsrc, const Share<C>& share, int unit, int lane) {
     constexpr int Q = Share<C>::Q, BLOCKS = Share<C>::BLOCKS, AT_ONCE = 2 * SK_TREE_GROUP;
     constexpr uint32_t SLOT_BYTES = C::BM * C::BN * 4;
-    const int lane = threadIdx.x % 64, n_all = share.n_all;
+    const int n_all = share.n_all;
     const int w = unit / (BLOCKS * Q), b = unit / Q % BLOCKS, q = unit % Q;
     const int at = ((b * Q + q) * C::NW + w) * 1024 + lane * 16;
     auto fetch = [&](int slot) {
@@ -1467,43 +1478,92 @@ __device__ __forceinline__ void store_unit(const GemmArgs& g, const buffer_rsrc&
 // This workgroup's shares of the one or two tiles of its range, all of them split (the range is shorter than a tile): both
 // counts are waited for at once, and a wave takes every NW-th unit of the two shares together.
 template <class C, bool TR>
-__device__ __forceinline__ void store_shares(const GemmArgs& g, int x) {
+__device__ __forceinline__ void store_shares(const GemmArgs& g, int x, unsigned char* smem) {
+    int thread = threadIdx.x;
+    asm volatile("" : "+s"(x), "+v"(thread));        // (what follows from them is worked out here and not ahead of the MAC loop)
     const int begin = x * g.ipw, end = begin + g.ipw < g.sk_iters ? begin + g.ipw : g.sk_iters;
     if (begin >= end) return;
-    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const int lane = thread % 64, wave = __builtin_amdgcn_readfirstlane(thread / 64);
     Share<C> s0, s1;
     s0.init(g, x, (int)fast_div((uint32_t)begin, g.div_ipt));
     const int last = (int)fast_div((uint32_t)end - 1, g.div_ipt);
     s1 = s0;
     if (last > s0.tile) s1.init(g, x, last);
     else s1.end = s1.begin;
-    const int len0 = s0.end - s0.begin, len1 = s1.end - s1.begin;
-    // lane i of the first wave watches and leaves tile i
-    const bool mine = wave == 0 && lane <= last - s0.tile;
-    uint32_t* count = tile_count(g, lane == 1 ? s1.tile : s0.tile);
-    const uint32_t n_all = (uint32_t)(lane == 1 ? s1.n_all : s0.n_all);
+    // lane i of the first wave watches and leaves tile i; the other waves learn through LDS, which is free by now, which shares
+    // are taken (bits 0 and 1), and whether some were given up (bit 2); what it mostly says is there before the wait
+    const bool mine = wave == 0 && lane <= last - s0.tile, second_lane = lane == 1;
+    const TileLine line(g, second_lane ? s1.tile : s0.tile);
+    const uint32_t n = (uint32_t)(second_lane ? s1.n_all : s0.n_all) + 1;
+    volatile int* told = reinterpret_cast<volatile int*>(smem);
+    bool with_share = true;
+    uint32_t word = 0;
     if (wave == 0) {
-        bool seen = !mine || (lane == 1 ? len1 : len0) == 0;
-        uint32_t polls = 0;
-        while (true) {
-            if (!seen) seen = (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffffu) > n_all;
-            if (__all(seen)) break;
-            if (polls++ >= g.spin_limit) {
-                if (lane == 0) __hip_atomic_store(g.status, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
+        if (lane == 0) told[0] = 3;
+        with_share = !mine || (second_lane ? s1.end - s1.begin : s0.end - s0.begin) == 0;
+        for (uint32_t polls = 0;; polls++) {
+            if (!with_share) {
+                word = line.load();
+                with_share = sk_arrived(word) == n;
             }
+            if (__all(with_share) || polls >= g.spin_limit) break;
             __builtin_amdgcn_s_sleep(1);
+        }
+        if (__any(!with_share || sk_given_up(word) > 0)) {
+            const int taken = (int)(__ballot(with_share) & 3);
+            if (lane == 0) told[0] = taken | 4;
         }
     }
     __syncthreads();
-    uint32_t left = 0;
-    if (mine) left = __hip_atomic_fetch_add(count, 0x10000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word = 0;
+    if (mine) word = sk_leave_tile(line, second_lane ? s1.j : s0.j, with_share);
+    const int state = __builtin_amdgcn_readfirstlane(told[0]);
     const buffer_rsrc rsrc = __builtin_amdgcn_make_buffer_rsrc(g.partials, 0, (uint32_t)(g.grid + g.tiles) * (uint32_t)(C::BM * C::BN * 4), BUFFER_RAW);
-    for (int i = wave; i < len0 + len1; i += C::NW) {
-        const bool second = i >= len0;
-        store_unit<C, TR>(g, rsrc, second ? s1 : s0, second ? s1.begin + i - len0 : s0.begin + i);
+    int len0 = state & 1 ? s0.end - s0.begin : 0, len1 = state & 2 ? s1.end - s1.begin : 0;
+    // The last one to leave a tile takes its line down, after the shares that others gave up.  All waves work at these where the first one
+    // knew of some before it left; of those given up right then it alone learns.  (One loop for them and the workgroup's own: with a copy of
+    // the unit's code for each the 8-bit 256 x 256 kernel spilled 11 registers instead of 7 and took 3 % longer.)
+    const bool all_waves = (state & 4) != 0;
+    int rest = 0, stride = C::NW, j = 0;
+    for (int t = -1;;) {
+        for (int i = wave; i < len0 + len1; i += stride) {
+            const bool second = i >= len0;
+            store_unit<C, TR>(g, rsrc, second ? s1 : s0, second ? s1.begin + i - len0 : s0.begin + i, lane);
+        }
+        if (t < 0) {
+            const bool last_out = mine && sk_left(word) == n;
+            if (last_out && sk_given_up(word) == 0) line.clear();
+            rest = (int)(__ballot(last_out && sk_given_up(word) > 0) & 3);
+            if (all_waves) {
+                if (thread == 0) told[1] = rest;
+                __syncthreads();
+                rest = __builtin_amdgcn_readfirstlane(told[1]);
+            } else {
+                stride = 1;
+            }
+            if (rest == 0) return;
+            t = 0;
+        }
+        // the next share given up, of tile t or the one after it
+        for (; t < 2; t++, j = 0) {
+            if (!(rest >> t & 1)) continue;
+            const TileLine left(g, t == 0 ? s0.tile : s1.tile);
+            const int n_all = t == 0 ? s0.n_all : s1.n_all;
+            while (j <= n_all && !__builtin_amdgcn_readfirstlane((int)left.is_given_up(j))) j++;
+            if (j <= n_all) break;
+            if (all_waves) __syncthreads();
+            if (wave == 0 && lane < SK_LINE_WORDS) left.clear(lane);
+        }
+        if (t == 2) return;
+        len0 = len1 = 0;
+        if (t == 0) {
+            s0.take(j++);
+            len0 = s0.end - s0.begin;
+        } else {
+            s1.take(j++);
+            len1 = s1.end - s1.begin;
+        }
     }
-    if (mine && (left >> 16) == n_all) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Atomic fix-up (the accumulation step of Algorithm 1): a segment that covers only part of the tile's
@@ -1620,7 +1680,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
                 }
             wait_vmcnt<0>();                      // every lane's part of the piece has reached memory
             __syncthreads();
-            if (tid == 0) __hip_atomic_fetch_add(tile_count(g, tile), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) TileLine(g, tile).add(SK_ARRIVES);
             return false;
         }
 
@@ -1738,7 +1798,7 @@ __global__ __launch_bounds__(C::THREADS) void streamk_gemm_kernel(GemmArgs g) {
         }
         stores_in_flight = finish_segment(cur_tile, cur_k_begin, cur_k_end, cur_m0, cur_n0, acc) && prefetched;
     }
-    if constexpr (FIXUP == SHARED) store_shares<C, TR>(g, x);
+    if constexpr (FIXUP == SHARED) store_shares<C, TR>(g, x, smem);
 }
 
 // ---- kernel table entries --------------------------------------------------------------------

@@ -455,6 +455,7 @@ bool sk_shared_reduction(const sk_plan_t* plan) {
     const sk_plan_header& h = plan->h;
     if (plan->fixup != SK_FIXUP_FLAGS || !plan->needs_fixup || !plan->k_aligned || h.dp_tiles > 0 || h.grid > 4096) return false;
     const int64_t tile_kb = (int64_t)h.blk_m * h.blk_n / 256, ipt = h.iters_per_tile, ipw = h.iters_per_wg;
+    if (ipt > (SK_MAX_SHARERS - 2) * ipw) return false;      // at most ceil(ipt / ipw) + 1 workgroups
     return tile_kb >= 16 && 2 * ipt >= (tile_kb >= 64 ? 9 : 14) * ipw && 4 * ipt <= 5 * tile_kb * ipw;
 }
 

@@ -437,6 +437,46 @@ def test_shared_reduction_same_bits_as_the_owners_and_counts_back_at_zero(shape,
         r.close()
 
 
+def _shared_reduction_ran(r, dA, dB):
+    """Does a launch of the plan park the piece of the first tile's owner, as only the shared reduction does?"""
+    i = r.info
+    owner = (i["iters_per_tile"] - 1) // i["iters_per_wg"]
+    slot = owner if i["iters_per_tile"] % i["iters_per_wg"] == 0 else i["grid"]
+    base = (-r.ws.data_ptr()) % 256 + (i["grid"] + 1) * 128 + 384 + slot * i["blk_m"] * i["blk_n"] * 4
+    if base + 16 > r.ws.numel():
+        return False
+    r.ws[base:base + 16] = 255
+    r.run(dA, dB)
+    return not bool((r.ws[base:base + 16] == 255).all())
+
+
+# ... and with more workgroups of a tile than units, some of whose shares are empty, with and without ranges that straddle tiles
+@pytest.mark.parametrize("shape,blk,dtype,out", SHARED + [((128, 448, 2304), (64, 64, 128), sk.SK_BF16, sk.SK_F32),
+                                                          ((64, 896, 4672), (64, 128, 64), sk.SK_BF16, sk.SK_BF16)])
+def test_shares_given_up_are_taken_by_the_last_workgroup(shape, blk, dtype, out):
+    """Workgroups that poll for the others 0, 1 or 5 times: most or some leave without their share, and every bit is as before."""
+    M, N, K = shape
+    A, B = inputs.uniform_pair(M, N, K, dtype, 80)
+    dA, dB = to_device(A), to_device(B)
+    print("shares given up", shape, blk, dtype, out, flush=True)
+    r = Runner(M, N, K, sk.SK_POLICY_ALL_SK, blk, 256, dtype, out)
+    try:
+        assert _shared_reduction_ran(r, dA, dB)
+        want = r.run(dA, dB).clone()
+        assert r.check() == sk.SK_OK
+        err = G.rel_error(r.result(want), G.gemm_fp64(A, B, ODT[dtype]))
+        assert err <= (TOL_32 if out == sk.SK_F32 else TOL_16), err
+        lines = r.ws[(-r.ws.data_ptr()) % 256:][:257 * 128]
+        for polls in (0, 1, 5, 0):
+            sk.sk_plan_set_spin_limit(r.plan, polls)
+            for _ in range(3):
+                r.D.view(torch.uint8).fill_(0xA5)
+                assert torch.equal(r.run(dA, dB).view(torch.uint8), want.view(torch.uint8)), polls
+            assert r.check() == sk.SK_OK and not lines.any()
+    finally:
+        r.close()
+
+
 def test_bit_identical_run_to_run_and_flag_reuse():
     c = inputs.config1()
     dA, dB = to_device(c["A"]), to_device(c["B"])
