@@ -442,21 +442,31 @@ extern "C" int bloom_shape_key(const sk_plan_t* plan, uint32_t* key) {
 }
 
 // Where the shared reduction (store_shares in streamk_kernels.h) is the faster fix-up: the owner's chain of fetches, n - 1 partial
-// tiles through one CU, has to be longer than what sharing adds: the owner's own piece is parked and waited for too, and a range that
-// goes on into the next tile ends with shares of two tiles.  Owner alone -> shared, bf16 unless said, us:
-//  - n = 3: 512 x 10752 x 3136 on 256 x 256 tiles 55 -> 70, 384 x 3584 x 1536 on 128 x 128 12.1 -> 13.6; n = 4: 128 x 8192 x 8192 level;
-//  - n = 5: 512 x 6656 x 2496 on 256 x 256 57 -> 44, 768 x 2176 x 5120 on 256 x 128 35 -> 27, 256 x 3328 x 2496 on 128 x 128 15.9 -> 16.8 (8 bits, 384 x 2176 x
-//    10240, 20.0 -> 16.2), 192 x 2176 x 2560 on 64 x 128 level, 120 x 2688 x 6400 (n = 6) 16.4 -> 16.7;
-//  - n = 8 - 20: 256 x 256 21 - 43 % faster, 256 x 128 19 - 38 %, 128 x 128 18 - 32 %, 64 x 128 5 - 14 %, 32 x 128 and 64 x 64 level to 12 %
-//    (256 x 512 x 16384 to fp32 14.5 -> 12.9);
-//  - more workgroups than 1 KB units of the tile: 64 x 128, n = 57: 3 % slower, 32 x 128, n = 40: 3 %; tiles of 8 KB, 16 x 128 and 32 x 64, 2 - 25 % at any n.
+// tiles through one CU, has to be longer than what sharing adds: the owner's own piece is parked and waited for too.  A range that goes
+// on into the next tile ends with shares of two tiles, and the piece parked first is fetched last; that costs most where neighbours
+// share an XCD, whose L2 then serves the owner (map 1 or 0 of the workgroups; sorted by K slice, map 2, the owner fetches from
+// all XCDs).  n = ipt / ipw, owner alone -> shared, same build, 16 bits unless said; 450 plans, per cent of the time:
+//  - ranges that end with the tiles, or map 2: from n = 4.5 on 256 x 256 -7 .. -42, 256 x 128 and 128 x 256 -5 .. -44, 128 x 128 -3 .. -25, and
+//    below 4.5 level to slower (n = 3: 384 x 3584 x 1536 on 128 x 128 12.1 -> 13.6 us); 64 x 128 from 7 on -7 .. -21; 32 x 128 and 64 x 64 from
+//    7.6 on -1 .. -24 (one plan at 7.1 and one at 7.3 +4, +2);
+//  - straddling ranges otherwise: 128 x 128 (8 bits too) n = 4.5 .. 6.4 +1 .. +18, from 7.4 on -8 .. -27; 256 x 128 4.7 .. 6.4 +9 .. -4, from
+//    7.4 on -6 .. -36; 8-bit 128 x 256 4.5 .. 5.5 +4 .. +15, 5.6 .. 6.4 +2 .. -6; 256 x 256 4.7 .. 5.4 +1 .. +6, 6.2 -3, 6.4 -7, in 8 bits -2 .. -14 from
+//    4.7 on; 64 x 128 (8 bits too) from 7.3 on -1 .. -19; 32 x 128 (8 bits too) and 64 x 64 7.3 .. 8.4 +7 .. 0, 9.1 .. 10.4 +2 .. -3, 11.5 .. 16.3 0 .. -7,
+//    18 .. 20 +6 .. -4;
+//  - more than 1.25 workgroups per 1 KB unit of the tile: 64 x 128, n = 57: +3, 32 x 128, n = 40: +3; tiles of 8 KB, 16 x 128 and 32 x 64, +2 .. +25 at any n.
 // Only where nothing follows the Stream-K work, whose workgroups would otherwise wait with tiles of their own left to do.
 bool sk_shared_reduction(const sk_plan_t* plan) {
     const sk_plan_header& h = plan->h;
     if (plan->fixup != SK_FIXUP_FLAGS || !plan->needs_fixup || !plan->k_aligned || h.dp_tiles > 0 || h.grid > 4096) return false;
     const int64_t tile_kb = (int64_t)h.blk_m * h.blk_n / 256, ipt = h.iters_per_tile, ipw = h.iters_per_wg;
     if (ipt > (SK_MAX_SHARERS - 2) * ipw) return false;      // at most ceil(ipt / ipw) + 1 workgroups
-    return tile_kb >= 16 && 2 * ipt >= (tile_kb >= 64 ? 9 : 14) * ipw && 4 * ipt <= 5 * tile_kb * ipw;
+    int64_t least = tile_kb >= 64 ? 18 : 28, most = 5 * tile_kb;   // workgroups per tile, in quarters
+    if (ipt % ipw != 0 && h.xcd_remap != 2) {
+        if (tile_kb >= 256) least = h.in_dtype == SK_FP8_E4M3 ? 18 : 24;
+        else if (tile_kb >= 64) least = 26;
+        else if (tile_kb < 32) least = 36, most = 4 * (tile_kb + 1);
+    }
+    return tile_kb >= 16 && 4 * ipt >= least * ipw && 4 * ipt <= most * ipw;
 }
 
 size_t sk_ws_least_bytes(const sk_plan_t* plan) {

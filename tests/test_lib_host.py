@@ -211,6 +211,25 @@ def test_numbering_of_plans_whose_xcds_hold_whole_tiles(shape, blk, dtype, remap
     sk.sk_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("shape,blk,dtype,remap,shared", [
+    ((256, 3328, 2496), (128, 128, 64), sk.SK_BF16, 1, False), ((128, 5504, 4544), (128, 128, 64), sk.SK_BF16, 1, False),
+    ((128, 4736, 5312), (128, 128, 64), sk.SK_BF16, 1, True), ((128, 6016, 8320), (128, 128, 128), sk.SK_FP8_E4M3, 1, False),
+    ((256, 5504, 2304), (256, 128, 64), sk.SK_BF16, 1, False), ((256, 5504, 4544), (256, 128, 64), sk.SK_BF16, 2, True),
+    ((256, 12032, 2112), (256, 256, 64), sk.SK_BF16, 1, False), ((256, 12032, 4224), (256, 256, 128), sk.SK_FP8_E4M3, 1, True),
+    ((256, 11008, 2304), (256, 256, 64), sk.SK_BF16, 2, True), ((64, 896, 4672), (64, 128, 64), sk.SK_BF16, 1, True),
+    ((64, 1280, 3201), (32, 128, 64), sk.SK_F16, 1, True), ((96, 1408, 2368), (32, 128, 64), sk.SK_F16, 1, False)])
+def test_straddling_ranges_share_the_reduction_only_where_it_is_faster(shape, blk, dtype, remap, shared):
+    """Workspace need of plans whose ranges straddle tiles: with the shared reduction a slot per tile more."""
+    plan = sk.sk_plan(*shape, sk.SK_POLICY_ALL_SK, blk, 256, dtype)
+    try:
+        i = sk.sk_plan_info(plan)
+        assert i["iters_per_tile"] % i["iters_per_wg"] != 0 and i["xcd_remap"] == remap
+        slot = blk[0] * blk[1] * 4
+        assert sk.sk_workspace_bytes(plan) == 257 * 128 + 384 + (256 + (i["tiles"] if shared else 0)) * slot
+    finally:
+        sk.sk_plan_destroy(plan)
+
+
 def test_gemm_rejects_bad_arguments_without_touching_the_gpu():
     p = sk.sk_plan(512, 512, 512, sk.SK_POLICY_ALL_SK, (128, 128, 32))
     assert sk.sk_gemm_status(0, 256, 512, p) == sk.SK_ERR_INVALID_ARG
