@@ -199,9 +199,12 @@ struct Cfg {
     static_assert(NSB >= 2 && (NSA == NSB || NSA == NSB + 1) && LDS_BYTES <= 160 * 1024, "LDS budget / ring depths");
     static_assert((NSA - 1) * LPS <= 63, "vmcnt range");
     // Stages requested before the first one is waited for, at the kernel's start; the others of the ring follow once that has
-    // landed (the requests of early workgroups delay the first stage of late ones: two instead of three of the ring of four
-    // 0.05 - 0.08 us at 512^3 and 640 x 2048 x 512; one, whose successor then comes too late, 0.1 us slower).
-    static constexpr int START = NSA == NSB && NSA > 3 ? 2 : NSA - 1;
+    // landed.  The requests of early workgroups delay the first stage of late ones; a stage that is requested late comes late.  Two instead
+    // of three of the ring of four, segments of 2 to 12 k-iterations, operands in caches and not: 64 x 128 in 8 bits 0 - 3 % faster (four
+    // iterations, 640 x 2048 x 512 from memory 5.90 us, three 6.04), 32 x 128 in 8 bits 0 - 6 %, the others 2 % faster to 2 % slower.  Not
+    // with the small stages (12 KB) of 32 x 64, where three are as fast from caches and faster from memory: 512 x 512 x 256 / 384 / 512 / 768 3.97 / 4.76 / 5.28 /
+    // 6.43 -> 3.85 / 4.60 / 5.15 / 6.27.  One, whose successor then comes too late, is 0.1 us slower.
+    static constexpr int START = NSA == NSB && NSA > 3 && A_BYTES + B_BYTES >= 16 * 1024 ? 2 : NSA - 1;
     // LDS-DMA loads that may still be in flight when iteration i starts, if `later` more
     // iterations follow it.  Issue order inside an iteration: B tile of iteration +NSB-1, then A
     // tile of iteration +NSA-1; loads complete in order.
