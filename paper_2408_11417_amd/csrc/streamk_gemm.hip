@@ -204,10 +204,11 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
     if (plan->needs_fixup && !workspace && !(atomic && h.out_dtype == SK_F32)) return SK_ERR_WORKSPACE;
     const bool aligned = (h.K % e->piece_elems == 0) && (h.N % e->piece_elems == 0);   // whole 16-byte pieces per row
     kernel_fn fn = across ? e->across : aligned ? e->aligned : e->generic;
+    if (!aligned && e->generic_one_by_one && !plan->needs_fixup && takes_one_by_one(h)) fn = e->generic_one_by_one;
 
     if (e->max_resident.load() < 0) {
         // first use on this process: allow the large LDS footprint and ask how many workgroups fit at once
-        for (kernel_fn f : {e->aligned, e->generic, e->across, e->shared_aligned, e->shared_generic})
+        for (kernel_fn f : {e->aligned, e->generic, e->across, e->shared_aligned, e->shared_generic, e->generic_one_by_one})
             if (f && !hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, e->lds_bytes)))
                 return SK_ERR_HIP;
         int dev = 0, cus = 0, per_cu = 0;

@@ -174,10 +174,10 @@ struct Cfg {
     static constexpr bool STAGED_FINE = FINE && KK % 2 == 0 && 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 5 * PIECES + 32 <= 256;
     static constexpr int STAGES_HELD = 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 4 * PIECES + 64 > 256 ? 0 : PIECES <= 5 ? 4 : PIECES <= 8 ? 2 : 1;
     // The other tiles' stages in whole rounds of STAGES_HELD (see mac_loop_staged), but for the tiles of 16 and 32 rows on four waves,
-    // which are 1 - 8 % slower with them.  us: 319 x 1021 on 32 x 64, K = 125 / 253 / 1021 / 2043, 4.62 -> 4.33, 5.44 -> 5.15, 10.2 -> 8.8,
-    // 16.2 -> 12.8 (between five and thirteen iterations on a few dozen tiles 0.2 us slower: 103 x 334 x 479 6.01 -> 6.24); 639 x 1021 on
-    // 64 x 64 2 - 7 %; 639 x 2045 on 64 x 128, K = 61, 4.52 -> 4.24, longer ones level to 2 % slower; 8 bits 2 - 8 % up to K = 509,
-    // 1 - 2 % slower from 2043 on.
+    // which are 1 - 8 % slower with them.  Stage by stage -> rounds, whole tiles, us: 319 x 1021 on 32 x 64, K = 125 / 253 / 1021 / 2043, 4.60 -> 4.30, 5.41 -> 5.12,
+    // 10.2 -> 8.8, 16.2 -> 12.8 (five to nine iterations are slower: OneByOne below); 639 x 1021 on 64 x 64, K = 509 / 2043, 7.69 -> 7.29, 16.4 -> 16.0; 639 x 2045
+    // on 64 x 128, K = 509 / 4093, 9.11 -> 8.85, 33.8 -> 33.0; 8 bits 4 - 10 % up to K = 509, 0 - 1 % from 4093 on.  (On a dozen tiles, for which the
+    // library takes smaller ones, up to 3 % slower.)
     static constexpr bool STAGED_ROUNDS = STAGES_HELD > 0 && PIECES != 5;
     // vector stores one wave issues in the epilogue of an unsplit interior tile with 16-bit output (an fp32
     // output issues more): what may still be in flight when the next tile's first stage is waited for
@@ -1812,14 +1812,28 @@ struct KernelEntry {
                                          // tiles whose tiles have at least this many k-iterations
     kernel_fn aligned, generic;
     kernel_fn across = nullptr;          // the MAC loop that runs on across the tiles of a workgroup (streamk_whole_tiles.h), and the fewest
-    kernel_fn shared_aligned = nullptr, shared_generic = nullptr;    // with the shared reduction
     int across_iters = 0;                // k-iterations per tile that it takes; for plans without split tiles, aligned, with 16-bit output
+    kernel_fn shared_aligned = nullptr, shared_generic = nullptr;    // with the shared reduction
+    kernel_fn generic_one_by_one = nullptr;                          // for plans without split tiles, see takes_one_by_one
     int threads, lds_bytes, piece_elems;
     std::atomic<int> max_resident{-1};   // co-resident workgroups on the device, -1 = not yet asked
     std::atomic<int> max_shared{0};      // ... of the kernels with the shared reduction
     KernelEntry(int d, int m, int n, int k, int v, int fx, kernel_fn a, kernel_fn g, int t, int l, int pe)
         : dtype(d), bm(m), bn(n), bk(k), variant(v), fixup(fx), aligned(a), generic(g), threads(t), lds_bytes(l), piece_elems(pe) {}
 };
+
+// A tile whose register-staged path takes its stages one by one instead of in rounds: 32 x 64 on whole tiles of few iterations.  A round
+// that is not inside in all its stages pays for the checks of all, and the first one counts as such; in return no load is waited for
+// early, which is worth more the longer the loads take and the more of them there are.  Rounds -> one by one, us: 5 - 8 iterations, N up to 1021,
+// 4 to 512 tiles: 1 - 5 % faster (319 x 1021, 6 iterations, 6.04 -> 5.93, 103 x 334 5.85 -> 5.62, 1022 x 1020 10.35 -> 9.98); a wider B,
+// less of which is read twice, 5 - 7 to N = 2630 2 - 3 % faster, 31 x 1533 with 8 6 % slower, 32 x 8191 2 - 8 %; up to 48 tiles 9 iterations level to 1 %
+// faster, with even N, whose rows of B are 4-byte aligned, 9 - 14 3 - 5 % (103 x 334, 12, 7.17 -> 6.92; 95 x 508 with 17 10 %
+// slower); otherwise slower: 3 and 4 iterations 3 - 4 %, 160 tiles of 10 / 12 / 20 5 / 10 / 19 %, split plans 2 - 6 %.
+template <class C> struct OneByOne : C { static constexpr bool STAGED_ROUNDS = false; };
+inline bool takes_one_by_one(const sk_plan_header& h) {
+    const int most = h.tiles_n > 64 ? 0 : h.tiles_n > 16 ? 7 : h.tiles > 48 ? 8 : h.N % 2 ? 9 : 14;
+    return h.iters_per_tile >= 5 && h.iters_per_tile <= most;
+}
 
 template <class C, bool ATOMIC = false> KernelEntry* make_entry(int variant = 0, int whole_tiles_choice = 0) {
     KernelEntry* e = new KernelEntry(C::DT, C::BM, C::BN, C::BK, variant, ATOMIC ? SK_FIXUP_ATOMIC : SK_FIXUP_FLAGS,
@@ -1830,6 +1844,7 @@ template <class C, bool ATOMIC = false> KernelEntry* make_entry(int variant = 0,
         e->shared_aligned = streamk_gemm_kernel<C, true, SHARED>;
         e->shared_generic = streamk_gemm_kernel<C, false, SHARED>;
     }
+    if constexpr (C::BM == 32 && C::BN == 64 && !ATOMIC) e->generic_one_by_one = streamk_gemm_kernel<OneByOne<C>, false>;
     return e;
 }
 

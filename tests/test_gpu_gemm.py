@@ -394,6 +394,15 @@ def test_register_staged_segments_of_every_length(dtype, blk):
         _run_and_compare(A, B, dtype, sk.SK_POLICY_ALL_SK, blk, grid=3, out_dtype=sk.SK_F32, ref=ref, exact=True)
 
 
+@pytest.mark.parametrize("N", [61, 126, 1021])
+def test_short_register_staged_segments_stage_by_stage(N):
+    """32 x 64 tiles on both sides of the numbers of iterations, and of tiles, that are taken stage by stage."""
+    for iters in (4, 5, 9, 10, 14, 15):
+        for M, K in ((35, iters * 64 - 61), (509 if N > 999 else 33, iters * 64)):
+            A, B = inputs.small_int_pair(M, N, K, inputs.F16, 81, lo=-1, hi=1)
+            _run_and_compare(A, B, inputs.F16, sk.SK_POLICY_DP, (32, 64, 64), out_dtype=sk.SK_F32, exact=True)
+
+
 # Shared reduction (every workgroup of a tile adds up a share of it): sizes at which it applies, with ranges that end with the
 # tiles and that straddle them, edge tiles, one and two round trips of 16 contributors, tiles of one and of eight units per workgroup.
 SHARED = [((256, 512, 4096), (64, 64, 128), sk.SK_BF16, sk.SK_BF16), ((700, 256, 2000), (64, 128, 64), sk.SK_BF16, sk.SK_F16),
