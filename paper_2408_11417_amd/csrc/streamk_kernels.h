@@ -205,6 +205,12 @@ struct Cfg {
     // with the small stages (12 KB) of 32 x 64, where three are as fast from caches and faster from memory: 512 x 512 x 256 / 384 / 512 / 768 3.97 / 4.76 / 5.28 /
     // 6.43 -> 3.85 / 4.60 / 5.15 / 6.27.  One, whose successor then comes too late, is 0.1 us slower.
     static constexpr int START = NSA == NSB && NSA > 3 && A_BYTES + B_BYTES >= 16 * 1024 ? 2 : NSA - 1;
+    // The last stage of the ring is requested in one go behind the first wait, or slot by slot in the first trip.  In one go is faster by what the
+    // slots' checks cost (128 x 128, 4096 x 4096 x 128 .. 832 3 - 6 %; 256 x 128 1 % either way), but not in the tiles of 256 columns, where the
+    // burst, 24 - 32 KB, meets the stores of the tile before.  In one go -> slot by slot, us: 256 x 256, 10656 x 8752 x 192 / 256 / 448 f16 84.8 / 94.7 / 124.2 -> 80.0 /
+    // 90.3 / 119.7, 14416 x 5728 x 1008 194.5 -> 183.1, 5120 x 4096 x 256 24.2 -> 24.0; 8 bits 128 x 256, 9000 x 9008 x 256 / 384 70.7 / 80.1 -> 67.4 / 77.5,
+    // 1040 x 15376 x 368 24.0 -> 23.4, and a single iteration 0.7 % slower (4096 x 8192 x 128 17.54 -> 17.66).
+    static constexpr bool FILL_FIRST = PIN_ORDER && BN < 256;
     // LDS-DMA loads that may still be in flight when iteration i starts, if `later` more
     // iterations follow it.  Issue order inside an iteration: B tile of iteration +NSB-1, then A
     // tile of iteration +NSA-1; loads complete in order.
@@ -918,7 +924,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        // Wait for the segment's first stage and request the rest of the ring, all of which is free (PIN_ORDER; otherwise the trip does that).
+        // Wait for the segment's first stage and request the rest of the ring, all of which is free (the last one: FILL_FIRST).
         auto wait_first = [&]() {
             if (!prefetched) {
                 wait_stage<C, C::START - 1>(nk - 1);
@@ -928,7 +934,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
             } else {
                 wait_stage<C, C::NSA - 1>(nk - 1);
             }
-            if (C::PIN_ORDER) mac_prefetch<C, NT, C::NSA - 1, C::NSA>(g, k_begin, k_end, smem, dm);
+            if (C::FILL_FIRST) mac_prefetch<C, NT, C::NSA - 1, C::NSA>(g, k_begin, k_end, smem, dm);
         };
         auto trip = [&](int i, auto first, auto next, auto steady) {
             constexpr bool FIRST = decltype(first)::value;
@@ -985,7 +991,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
         typedef std::integral_constant<int, 0> No;
         typedef std::integral_constant<int, -1> AtRunTime;
         // Trips 0 .. n_steady-1 request stages that exist and lie inside K: their body carries neither
-        // range checks nor the K-tail variant of the requests, and waits with a constant count.  The first trip (wait_first
+        // range checks nor the K-tail variant of the requests, and waits with a constant count.  The first trip (where wait_first
         // has filled the ring) and those from nk - NSB on request nothing, and a copy of the trip without requests serves them: slot by
         // slot the checks cost 0.05 - 0.2 us a trip, NSA of them per segment.  With START, us: 512^3 f16 4.71 -> 4.42, 1280 x 2048 x 256
         // on 128 x 128 6.36 -> 5.89, 640 x 1024 x 512 on 64 x 64 5.49 -> 5.01, 1472 x 1936 x 144 6.26 -> 5.64, 1008 x 1200 x 1040 9.43 -> 9.19.
@@ -993,7 +999,7 @@ __device__ __forceinline__ void mac_loop(const GemmArgs& g, int m0, int n0, int 
         if (n_steady < 0) n_steady = 0;
         typedef std::integral_constant<int, -1> Quiet;
         if constexpr (C::PIN_ORDER) {
-            trip(-1, std::true_type(), Yes(), Quiet());
+            trip(-1, std::true_type(), Yes(), std::conditional_t<C::FILL_FIRST, Quiet, No>());
             int i = 0;
             for (; i < n_steady; i++) trip(i, std::false_type(), Yes(), Yes());
             for (; i < nk - C::NSB; i++) trip(i, std::false_type(), Yes(), No());
