@@ -81,40 +81,6 @@ KernelEntry* kernel_of(const sk_plan_t* plan, bool* across = nullptr) {
     return e;
 }
 
-// Map 1 of logical_wg: how many logical ids, the first ones, are dealt to the XCDs evenly because the others have no work
-// in the last wave of tiles, or none at all (0: no such two kinds).  Contiguous blocks would leave whole XCDs idle there and crowd the
-// others, which costs what their CUs share: an L2's bandwidth, the fabric port and, most of all, the clock of an XCD
-// whose 32 CUs all run the matrix cores.  Contiguous -> spread, bf16 unless said, us:
-//  - less than one wave of whole tiles: 256 x 256 tiles, 64 / 128 / 160 / 200 / 224 of them, K = 2048: 54.8 -> 39.9 / 40.3 / 41.8 / 47.0 / 50.1, K =
-//    512: 19.3 -> 16.4 / 17.4 / 17.5 / 18.1 / 18.4; 256 x 128 tiles, 128, K = 2048: 30.7 -> 24.0; 128 x 128, 128, K = 2048: 17.8 -> 15.5;
-//    64 x 128, 128, K = 2048: 12.5 -> 12.1; 32 x 128 and 16 x 128
-//    0 - 12 % at K = 2048, 4 % slower to level at K = 128, as are fewer than a dozen tiles of any shape; 8 bits 256 x 256, 128, K = 4096: 62.5 -> 49.4.  Tiles of 64
-//    columns lose as often as they gain (32 x 64: 0 - 1 % slower, 64 x 64: 15 % faster to 7 % slower);
-//  - the last of several waves, where the full ones then hold two blocks of tiles per XCD: 256 x 256, 320 tiles, K = 2048:
-//    104.5 -> 87.6, 576 tiles, K = 896 / 4096: 74.8 -> 68.6 / 285 -> 260, 900 tiles, K = 4096: 378 -> 362; after three waves of a short K 3 % faster to 4 %
-//    slower (6624 x 11584 x 896, 1196 tiles, 127.6 -> 132.4), and a last wave of 164 after two 3 % slower at K = 512, from K = 2048 on faster.  256 x
-//    128, 320 tiles, K = 2048: 58.1 -> 51.5; 128 x 128, 288 - 464 tiles, K = 1024: 6 % faster to level; after two waves, or with a last wave
-//    nearly full, these lose up to 4 % as often as they gain; tiles of at most 64 rows up to 4 % anywhere.
-//    Not where nearly all workgroups have work: 3840 x 4224 x 4096, 255 tiles, 107.1 -> 107.9;
-//  - Stream-K plans with empty ranges (iterations per workgroup are rounded up): 256 x 256 tiles 0 - 12 % faster, 128 x 128 2 - 8 %, 64 x 128
-//    level to 5 %; a dozen busy workgroups, all of one tile, are 1 - 5 % slower apart.
-int first_ids_of(const sk_plan_header& h) {
-    if (h.xcd_remap != 1 || h.blk_n < 128) return 0;
-    const int most = h.grid - h.grid / 16;
-    if (h.sk_tiles > 0) {
-        if (h.dp_tiles > 0) return 0;
-        const int busy = (int)((h.sk_iters + h.iters_per_wg - 1) / h.iters_per_wg);
-        return busy >= 32 && busy <= most ? busy : 0;
-    }
-    const int last = h.tiles % h.grid, full = h.tiles / h.grid;
-    if (last > most) return 0;
-    if (full == 0) return last >= 16 && (h.blk_m >= 64 || h.blk_m * (int64_t)h.iters_per_tile >= 512) ? last : 0;
-    const int area = h.blk_m * h.blk_n;
-    const bool few = 8ll * last <= 5ll * h.grid;
-    if (area >= 256 * 256) return (full <= 2 && few) || h.iters_per_tile >= 32 ? last : 0;
-    return area >= 128 * 128 && full == 1 && few ? last : 0;
-}
-
 // Helpers of the atomic fix-up: clear the fp32 image, and turn it into a 16-bit D afterwards.
 __global__ void zero_image_kernel(float4* p, size_t n4, float* tail, int n_tail) {
     const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -248,7 +214,7 @@ int launch_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, vo
     g.dp_first = plan->dp_first;
     g.k_aligned = plan->k_aligned;
     g.xcd_remap = h.grid % 8 == 0 ? h.xcd_remap : 0;
-    g.first_ids = (first_ids_of(h) + 7) / 8;
+    g.first_ids = (sk_first_ids(h) + 7) / 8;
     g.other_ids = h.grid / 8 - g.first_ids;
     // B is requested non-temporally when it is read exactly once (one row of tiles) and is so large that a later
     // launch hardly finds it in the 256 MB memory-side cache: from 128 MiB, half of it, on, a launch with another B in

@@ -42,17 +42,26 @@ inline sk_fast_div sk_make_fast_div(uint32_t d) {
 }
 inline uint32_t sk_fast_div_apply(uint32_t n, sk_fast_div f) { return (uint32_t)(((uint64_t)n * f.mul) >> f.shift); }
 
+#ifdef __HIPCC__
+#define SK_HOST_DEVICE __host__ __device__
+#else
+#define SK_HOST_DEVICE
+#endif
+
+// Map 1 of the workgroups: the logical id that workgroup i of an XCD runs, where the first 8 * first_ids ids and the 8 * other_ids others are
+// dealt out in a block of each per XCD.
+SK_HOST_DEVICE inline int sk_spread_id(int xcd, int i, int first_ids, int other_ids) {
+    return i < first_ids ? xcd * first_ids + i : 7 * first_ids + xcd * other_ids + i;
+}
+// How many of the first ids are dealt out so (0: one contiguous block per XCD).
+int sk_first_ids(const sk_plan_header& h);
+
 // ---- shared reduction: who adds up and stores which part of a split tile, and when -----------------
 // The n workgroups of a tile park their pieces and count themselves in at the tile's flag line.  Then each waits for the others, for a
 // bounded time, and leaves: with its share of the tile where all have arrived by then, and otherwise giving the share up, which it
 // notes in the line's other words.  The last one to leave, by whose time all have arrived, takes what was given up.  So nobody
 // depends on a workgroup that has not started: the launch ends whatever part of the device it gets, and only the split of the
 // work depends on it.  (tests/host/shared_reduction.cpp runs these functions on threads.)
-#ifdef __HIPCC__
-#define SK_HOST_DEVICE __host__ __device__
-#else
-#define SK_HOST_DEVICE
-#endif
 // The line's first word: three counts of ten bits, of the workgroups that have arrived, have left, have given their share up.
 constexpr uint32_t SK_ARRIVES = 1, SK_LEAVES = 1u << 10, SK_GIVES_UP = 1u << 20;
 SK_HOST_DEVICE inline uint32_t sk_arrived(uint32_t word) { return word & 1023; }

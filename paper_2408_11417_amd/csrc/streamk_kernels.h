@@ -282,7 +282,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 __device__ __forceinline__ int logical_wg(uint32_t hw, const GemmArgs& g) {
     if (g.xcd_remap == 0) return (int)hw;
     const int xcd = (int)(hw % 8), i = (int)(hw / 8);
-    if (g.xcd_remap == 1) return i < g.first_ids ? xcd * g.first_ids + i : 7 * g.first_ids + xcd * g.other_ids + i;
+    if (g.xcd_remap == 1) return sk_spread_id(xcd, i, g.first_ids, g.other_ids);
     const int q = xcd * (g.grid / 8) + i;
     // The ranges of workgroups ceil(t * ipt / ipw) .. ceil((t + 1) * ipt / ipw) - 1 start in tile t: `each` of them or
     // one more; the tiles with one more are t = floor(i * ipw / extra), i = 0, 1, ..., extra = ipt mod ipw.  (By the

@@ -441,6 +441,40 @@ extern "C" int bloom_shape_key(const sk_plan_t* plan, uint32_t* key) {
     return SK_OK;
 }
 
+// Map 1 of logical_wg (streamk_kernels.h): how many logical ids, the first ones, are dealt to the XCDs evenly because the others have no work
+// in the last wave of tiles, or none at all (0: no such two kinds).  Contiguous blocks would leave whole XCDs idle there and crowd the
+// others, which costs what their CUs share: an L2's bandwidth, the fabric port and, most of all, the clock of an XCD
+// whose 32 CUs all run the matrix cores.  Neighbours that an XCD's L2 served together are taken apart, which costs something where few
+// are left.  Contiguous -> spread, 256 workgroups, per cent of the time; 1200 plans, 4 to 40 iterations per tile, 16 bits unless said:
+//  - less than one wave of whole tiles.  256 x 256 (8 bits too), 20 - 160 tiles -5 .. -26 (K = 2048, 128 tiles, 54.7 -> 40.3 us), 190 - 232 -1 .. -14; 256 x 128 and 8-bit
+//    128 x 256 -4 .. -21 to 190 tiles, 0 .. -7 above (one of 32 plans +2.5); 128 x 128 -2 .. -12 to 190, 0 .. -3 above (20 tiles of 40 iterations
+//    +2 .. +4); 64 x 128 -1 .. -11 to 17 iterations, +4 .. -6 at 40, nearly a wave of 16 and more +1 .. -2; 32 x 128 at 17 iterations 0 .. -19, below 16
+//    level, at 40 +3 .. -14; 16 x 128 from 32 iterations on +1 .. -13, below level; fewer than 16 tiles of any shape are level to slower, tiles of
+//    64 columns lose as often as they gain;
+//  - the last of several waves, where the full ones then hold two blocks of tiles per XCD.  Behind one wave, a last one of 4 - 8 tiles: 256 x 256 +1 .. +4, 256 x 128 and
+//    8-bit 128 x 256 +2 .. +7, 128 x 128 +1 .. +5; of 16 - 24 +4 .. -3; of 32 - 154 256 x 256 0 .. -13, 256 x 128 0 .. -8, 8-bit 128 x 256 0 .. -7, 128 x 128 of 32 - 52 +3 .. -5,
+//    64 - 154 +2 .. -4; 256 x 256 behind two waves, 8 tiles +1 .. +5, 28 - 148 from 8 iterations on 0 .. -11, below +6 .. -2, behind any number from 32
+//    iterations on -1 .. -7; the others behind two, and tiles of at most 64 rows anywhere, lose up to 4 as often as they gain;
+//  - Stream-K plans with empty ranges: all tiles 0 .. -26 (182 plans, four of them +1 .. +4) while 32 to 240 workgroups are busy; fewer, all of one
+//    tile, +1 .. +5, as are 16-row tiles that more than 16 workgroups share (70 x 119 x 4092 7.4 -> 7.75 us);
+//  - not where nearly all workgroups have work: 3840 x 4224 x 4096, 255 tiles, 107.1 -> 107.9 us.
+int sk_first_ids(const sk_plan_header& h) {
+    if (h.xcd_remap != 1 || h.blk_n < 128) return 0;
+    const int most = h.grid - h.grid / 16;
+    if (h.sk_tiles > 0) {
+        if (h.dp_tiles > 0 || (h.blk_m < 32 && h.iters_per_tile > 16ll * h.iters_per_wg)) return 0;
+        const int busy = (int)((h.sk_iters + h.iters_per_wg - 1) / h.iters_per_wg);
+        return busy >= 32 && busy <= most ? busy : 0;
+    }
+    const int last = h.tiles % h.grid, full = h.tiles / h.grid, ipt = h.iters_per_tile, area = h.blk_m * h.blk_n;
+    if (last > most) return 0;
+    if (full == 0) return last >= 16 && (h.blk_m >= 64 || h.blk_m * (int64_t)ipt >= 512) ? last : 0;
+    if (area < 128 * 128 || 8ll * last < (area >= 256 * 128 ? 1 : 2) * h.grid) return 0;
+    const bool few = 8ll * last <= 5ll * h.grid;
+    if (area >= 256 * 256) return (few && (full == 1 || (full == 2 && ipt >= 8))) || ipt >= 32 ? last : 0;
+    return full == 1 && few ? last : 0;
+}
+
 // Where the shared reduction (store_shares in streamk_kernels.h) is the faster fix-up: the owner's chain of fetches, n - 1 partial
 // tiles through one CU, has to be longer than what sharing adds: the owner's own piece is parked and waited for too.  A range that goes
 // on into the next tile ends with shares of two tiles, and the piece parked first is fetched last; that costs most where neighbours

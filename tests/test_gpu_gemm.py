@@ -350,14 +350,22 @@ def test_workgroups_sorted_by_k_slice_integer_exact(shape, blk):
         _run_and_compare(A, B, inputs.BF16, sk.SK_POLICY_ALL_SK, blk, out_dtype=sk.SK_F32, ref=ref, exact=True, launches=3, k_aligned=k_aligned)
 
 
-@pytest.mark.parametrize("shape,blk,grid,policy", [((16 * 5, 128 * 7, 64), (16, 128, 64), 256, sk.SK_POLICY_DP),            # 35 tiles: 4 or 5 per XCD
-                                                   ((256, 256, 512), (256, 256, 64), 256, sk.SK_POLICY_DP),                  # a single tile
-                                                   ((64 * 15, 128 * 17 - 3, 70), (64, 128, 64), 256, sk.SK_POLICY_DP),       # 255, off the 16-byte grid
-                                                   ((64 * 9, 128 * 8, 128), (64, 128, 64), 80, sk.SK_POLICY_DP),             # 72 tiles on 80 workgroups
-                                                   ((128 * 10, 128 * 27, 64), (128, 128, 64), 256, sk.SK_POLICY_DP),         # one full wave and 14
-                                                   ((256 * 5, 256 * 7, 1024), (256, 256, 64), 16, sk.SK_POLICY_DP),          # two full waves and 3, the loop across tiles
-                                                   ((64 * 10, 128 * 5, 384), (64, 128, 64), 256, sk.SK_POLICY_ALL_SK),       # 150 of 256 ranges
-                                                   ((128 * 5, 128 * 9, 768), (128, 128, 64), 256, sk.SK_POLICY_ALL_SK)])     # 180, three iterations each
+# ... and how many logical ids are dealt to the XCDs (tests/test_numbering.py)
+SPREAD = [((16 * 5, 128 * 7, 64), (16, 128, 64), 256, sk.SK_POLICY_DP, 0),                   # 35 tiles too short to be dealt
+          ((16 * 5, 128 * 7, 64 * 40), (16, 128, 64), 256, sk.SK_POLICY_DP, 35),             # 4 or 5 tiles per XCD
+          ((256, 256, 512), (256, 256, 64), 256, sk.SK_POLICY_DP, 0),                        # a single tile
+          ((64 * 15, 128 * 17 - 3, 70), (64, 128, 64), 256, sk.SK_POLICY_DP, 0),             # 255 tiles, nearly a full wave
+          ((64 * 9 - 1, 128 * 11 - 3, 70), (64, 128, 64), 256, sk.SK_POLICY_DP, 99),         # off the 16-byte grid: the register-staged kernel
+          ((64 * 9, 128 * 8, 128), (64, 128, 64), 80, sk.SK_POLICY_DP, 72),                  # 72 tiles on 80 workgroups
+          ((128 * 10, 128 * 27, 64), (128, 128, 64), 256, sk.SK_POLICY_DP, 0),               # one full wave and 14
+          ((128 * 12, 128 * 31, 64), (128, 128, 64), 256, sk.SK_POLICY_DP, 116),             # one full wave and 116
+          ((256 * 5, 256 * 7, 1024), (256, 256, 64), 16, sk.SK_POLICY_DP, 3),                # two full waves and 3, the loop across tiles
+          ((64 * 10, 128 * 5, 384), (64, 128, 64), 256, sk.SK_POLICY_ALL_SK, 150),           # 150 of 256 ranges
+          ((128 * 5, 128 * 9, 768), (128, 128, 64), 256, sk.SK_POLICY_ALL_SK, 180),          # 180, three iterations each
+          ((70, 119, 4092), (16, 128, 64), 256, sk.SK_POLICY_ALL_SK, 0)]                     # 160 ranges of five tiles
+
+
+@pytest.mark.parametrize("shape,blk,grid,policy", [s[:4] for s in SPREAD])
 def test_workgroups_with_work_in_the_last_wave_spread_over_the_xcds(shape, blk, grid, policy):
     M, N, K = shape
     A, B = inputs.small_int_pair(M, N, K, inputs.BF16, 75, lo=-1, hi=1)
@@ -365,7 +373,7 @@ def test_workgroups_with_work_in_the_last_wave_spread_over_the_xcds(shape, blk, 
     assert sk.sk_plan_info(plan)["xcd_remap"] == 1
     sk.sk_plan_destroy(plan)
     ref = G.gemm_fp64(A, B, G.BF16)
-    for out in (sk.SK_BF16, sk.SK_F32):      # sums of at most 1024 products of -1, 0, 1: exact in fp32, and rounded in bf16
+    for out in (sk.SK_BF16, sk.SK_F32):      # sums of at most 4092 products of -1, 0, 1: exact in fp32, and rounded in bf16
         _run_and_compare(A, B, inputs.BF16, policy, blk, grid=grid, out_dtype=out, ref=ref, exact=out == sk.SK_F32, launches=2)
 
 
