@@ -175,9 +175,9 @@ struct Cfg {
     static constexpr int STAGES_HELD = 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 4 * PIECES + 64 > 256 ? 0 : PIECES <= 5 ? 4 : PIECES <= 8 ? 2 : 1;
     // The other tiles' stages in whole rounds of STAGES_HELD (see mac_loop_staged), but for the tiles of 16 and 32 rows on four waves,
     // which are 1 - 8 % slower with them.  Stage by stage -> rounds, whole tiles, us: 319 x 1021 on 32 x 64, K = 125 / 253 / 1021 / 2043, 4.60 -> 4.30, 5.41 -> 5.12,
-    // 10.2 -> 8.8, 16.2 -> 12.8 (five to nine iterations are slower: OneByOne below); 639 x 1021 on 64 x 64, K = 509 / 2043, 7.69 -> 7.29, 16.4 -> 16.0; 639 x 2045
-    // on 64 x 128, K = 509 / 4093, 9.11 -> 8.85, 33.8 -> 33.0; 8 bits 4 - 10 % up to K = 509, 0 - 1 % from 4093 on.  (On a dozen tiles, for which the
-    // library takes smaller ones, up to 3 % slower.)
+    // 10.2 -> 8.8, 16.2 -> 12.8; 639 x 1021 on 64 x 64, K = 509 / 2043, 7.69 -> 7.29, 16.4 -> 16.0 (17 plans 3 % in the mean); 64 x 128 up to eight iterations 1 - 4 %, in
+    // 8 bits 2 % in the mean; 8-bit 128 x 128 and 128 x 128 x 32 4 % faster to 3 % slower.  Where whole tiles are slower with them they are taken one
+    // by one, see OneByOne; split plans are 6 % faster to 2 % slower.
     static constexpr bool STAGED_ROUNDS = STAGES_HELD > 0 && PIECES != 5;
     // vector stores one wave issues in the epilogue of an unsplit interior tile with 16-bit output (an fp32
     // output issues more): what may still be in flight when the next tile's first stage is waited for
@@ -1828,17 +1828,25 @@ struct KernelEntry {
         : dtype(d), bm(m), bn(n), bk(k), variant(v), fixup(fx), aligned(a), generic(g), threads(t), lds_bytes(l), piece_elems(pe) {}
 };
 
-// A tile whose register-staged path takes its stages one by one instead of in rounds: 32 x 64 on whole tiles of few iterations.  A round
+// A tile whose register-staged path takes its stages one by one instead of in rounds, for plans of whole tiles.  A round
 // that is not inside in all its stages pays for the checks of all, and the first one counts as such; in return no load is waited for
-// early, which is worth more the longer the loads take and the more of them there are.  Rounds -> one by one, us: 5 - 8 iterations, N up to 1021,
-// 4 to 512 tiles: 1 - 5 % faster (319 x 1021, 6 iterations, 6.04 -> 5.93, 103 x 334 5.85 -> 5.62, 1022 x 1020 10.35 -> 9.98); a wider B,
-// less of which is read twice, 5 - 7 to N = 2630 2 - 3 % faster, 31 x 1533 with 8 6 % slower, 32 x 8191 2 - 8 %; up to 48 tiles 9 iterations level to 1 %
-// faster, with even N, whose rows of B are 4-byte aligned, 9 - 14 3 - 5 % (103 x 334, 12, 7.17 -> 6.92; 95 x 508 with 17 10 %
-// slower); otherwise slower: 3 and 4 iterations 3 - 4 %, 160 tiles of 10 / 12 / 20 5 / 10 / 19 %, split plans 2 - 6 %.
+// early, which is worth more the longer the loads take and the more of them there are.  Rounds -> one by one, us:
+//  - 32 x 64: 5 - 8 iterations, N up to 1022, 4 to 512 tiles, 1 - 5 % faster (319 x 1021, 6 iterations, 6.04 -> 5.93, 103 x 334 5.85 -> 5.62, 1022 x 1020
+//    10.35 -> 9.98); a wider B, less of which is read twice, 5 - 7 to N = 2630 2 - 3 % faster, 31 x 1533 with 8 6 % slower, 32 x 8191 2 - 8 %; up to 48
+//    tiles, or N = 510, 9 iterations level to 2 % faster, and with the rows of A or of B 4-byte aligned, which arrive sooner, 9 - 14 1 - 5 % (103 x 334, 12, 7.17 ->
+//    6.92; 1302 x 273 x 610 6.81 -> 6.55; 690 x 244 with 16 4 % faster, 95 x 508 with 17 10 % slower); otherwise slower: 3 and 4 iterations 3 - 4 %, 160
+//    tiles, N = 1021, of 10 / 12 / 20 5 / 10 / 19 %, split plans 2 - 6 %;
+//  - 64 x 128, 12 to 400 tiles: 9 - 16 iterations 4 % faster to level (191 x 509, 10 / 12 / 16, 8.65 / 10.32 / 11.57 -> 8.37 / 10.04 / 11.22), 17 - 40
+//    2 % faster to level, 7 1 - 2 % slower, above 43 level to slower;
+//  - 8-bit 128 x 256, 12 to 400 tiles: from 8 iterations on 2 % faster to level (767 x 2045, 8 / 18, 17.43 / 29.30 -> 17.17 / 28.80), from 44 on level, below 8 1 - 4 % slower.
 template <class C> struct OneByOne : C { static constexpr bool STAGED_ROUNDS = false; };
+template <class C> constexpr bool MAY_TAKE_ONE_BY_ONE = C::FP8 ? C::BM == 128 && C::BN == 256 : (C::BM == 32 && C::BN == 64) || (C::BM == 64 && C::BN == 128 && C::NW == 8);
 inline bool takes_one_by_one(const sk_plan_header& h) {
-    const int most = h.tiles_n > 64 ? 0 : h.tiles_n > 16 ? 7 : h.tiles > 48 ? 8 : h.N % 2 ? 9 : 14;
-    return h.iters_per_tile >= 5 && h.iters_per_tile <= most;
+    const int ipt = h.iters_per_tile;
+    if (h.blk_n == 256) return ipt >= 8 && ipt < 44;
+    if (h.blk_n == 128) return ipt >= 9 && ipt <= 40;
+    const int near = h.tiles > 48 && h.tiles_n > 8 ? 8 : h.N % 2 && h.K % 2 ? 9 : 14;
+    return ipt >= 5 && ipt <= (h.tiles_n > 64 ? 0 : h.tiles_n > 16 ? 7 : near);
 }
 
 template <class C, bool ATOMIC = false> KernelEntry* make_entry(int variant = 0, int whole_tiles_choice = 0) {
@@ -1850,7 +1858,7 @@ template <class C, bool ATOMIC = false> KernelEntry* make_entry(int variant = 0,
         e->shared_aligned = streamk_gemm_kernel<C, true, SHARED>;
         e->shared_generic = streamk_gemm_kernel<C, false, SHARED>;
     }
-    if constexpr (C::BM == 32 && C::BN == 64 && !ATOMIC) e->generic_one_by_one = streamk_gemm_kernel<OneByOne<C>, false>;
+    if constexpr (MAY_TAKE_ONE_BY_ONE<C> && !ATOMIC) e->generic_one_by_one = streamk_gemm_kernel<OneByOne<C>, false>;
     return e;
 }
 
