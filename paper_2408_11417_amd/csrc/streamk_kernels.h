@@ -206,11 +206,12 @@ struct Cfg {
     // 6.43 -> 3.85 / 4.60 / 5.15 / 6.27.  One, whose successor then comes too late, is 0.1 us slower.
     static constexpr int START = NSA == NSB && NSA > 3 && A_BYTES + B_BYTES >= 16 * 1024 ? 2 : NSA - 1;
     // The last stage of the ring is requested in one go behind the first wait, or slot by slot in the first trip.  In one go is faster by what the
-    // slots' checks cost (128 x 128, 4096 x 4096 x 128 .. 832 3 - 6 %; 256 x 128 1 % either way), but not in the tiles of 256 columns, where the
-    // burst, 24 - 32 KB, meets the stores of the tile before.  In one go -> slot by slot, us: 256 x 256, 10656 x 8752 x 192 / 256 / 448 f16 84.8 / 94.7 / 124.2 -> 80.0 /
-    // 90.3 / 119.7, 14416 x 5728 x 1008 194.5 -> 183.1, 5120 x 4096 x 256 24.2 -> 24.0; 8 bits 128 x 256, 9000 x 9008 x 256 / 384 70.7 / 80.1 -> 67.4 / 77.5,
-    // 1040 x 15376 x 368 24.0 -> 23.4, and a single iteration 0.7 % slower (4096 x 8192 x 128 17.54 -> 17.66).
-    static constexpr bool FILL_FIRST = PIN_ORDER && BN < 256;
+    // slots' checks cost (128 x 128, 4096 x 4096 x 128 .. 832 3 - 6 %), but not in the larger tiles, where the burst, 24 - 32 KB, meets
+    // the stores of the tile before.  In one go -> slot by slot, us: 256 x 256, 10656 x 8752 x 192 / 256 / 448 f16 84.8 / 94.7 / 124.2 -> 80.0 /
+    // 90.3 / 119.7, 14416 x 5728 x 1008 194.5 -> 183.1, 5120 x 4096 x 256 24.2 -> 24.0; 256 x 128, 2432 x 13424 x 240 to fp32 58.2 -> 55.2, 9248 x 3104 x 320 / 720
+    // 35.4 / 62.9 -> 34.2 / 61.2, 11520 x 640 x 624 16.7 -> 16.2, two iterations 1 - 3 % slower (4096 x 4096 x 128 13.8 -> 14.0); 8-bit 128 x 256, 9000 x 9008 x
+    // 256 / 384 70.7 / 80.1 -> 67.4 / 77.5, 1040 x 15376 x 368 24.0 -> 23.4, a single iteration 0.7 % slower (4096 x 8192 x 128 17.54 -> 17.66).
+    static constexpr bool FILL_FIRST = PIN_ORDER && BM * BN < 256 * 128;
     // LDS-DMA loads that may still be in flight when iteration i starts, if `later` more
     // iterations follow it.  Issue order inside an iteration: B tile of iteration +NSB-1, then A
     // tile of iteration +NSA-1; loads complete in order.
