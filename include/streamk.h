@@ -234,9 +234,10 @@ int sk_plan_set_segment_order(sk_plan_t* plan, int segment_order);
 size_t sk_workspace_bytes(const sk_plan_t* plan);
 
 /* Attach caller-owned device memory (>= sk_workspace_bytes, 256-byte aligned; at
- * the least without the partial tiles per tile, then the owner of a tile adds up
- * all its partial tiles instead of every workgroup a share of them: the same
- * results, later).
+ * the least without the partial tiles per tile, which is
+ * (grid + 1) * 128 + 384 + grid * blk_m * blk_n * 4 bytes under FLAGS: then the
+ * owner of a tile adds up all its partial tiles instead of every workgroup a
+ * share of them, with the same results, later).
  * Clears the flag and status area with a blocking memset on the null stream.
  * One workspace must not serve two launches that are in flight at once; it may
  * be shared by plans that run one after another on one stream.
@@ -295,7 +296,7 @@ int sk_gemm(const void* A, const void* B, void* D, const sk_plan_t* plan, void* 
  * ignored.  The call allocates nothing and frees nothing.  Before the GEMM kernel it enqueues a small
  * fill kernel that takes the flag and status lines down (the array keeps the previous call's
  * contents), so a launch with split tiles is two kernels; a plan without split tiles is one.
- * Limit: what sk_plan_set_workspace needs at the least <= SK_STATIC_WORKSPACE_MAX_BYTES - enough for every tile shape on
+ * Limit: what sk_plan_set_workspace needs at the least (its formula) <= SK_STATIC_WORKSPACE_MAX_BYTES - enough for every tile shape on
  * the default grid of 256 workgroups; larger grids with the largest tiles are refused.
  * All calls on one GPU share that GPU's array: two calls whose kernels may run at the same time
  * (different streams, or replays of graphs that hold them) race on it; calls on one stream do not.

@@ -168,8 +168,8 @@ struct Cfg {
     // register-staged path: a stage's pieces (4 registers each).  STAGED_FINE: the instruction-by-instruction
     // MAC loop with one stage in registers, where the two operand sets leave room for it; the other tiles hold
     // STAGES_HELD stages in registers, about 64 registers of loads in flight.  (The count is an estimate: the compiler
-    // spills 9 registers of the eight-wave 256 x 256 kernel, 49 of the four-wave one and 133 of the 8-bit four-wave one.
-    // No steady trip holds a spill; the checked trips of the last one do.)
+    // spills 6 registers of the eight-wave 256 x 256 kernel, of the one with the shared reduction too, 49 of the four-wave one and 88 of
+    // the 8-bit four-wave one.  No trip of a loop holds a spill: they are stored once and reloaded around a segment's loops.)
     static constexpr int PIECES = CA + CB;
     static constexpr bool STAGED_FINE = FINE && KK % 2 == 0 && 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 5 * PIECES + 32 <= 256;
     static constexpr int STAGES_HELD = 2 * FRAG_REGS + (NW >= 8 ? ACC_REGS : 0) + 4 * PIECES + 64 > 256 ? 0 : PIECES <= 5 ? 4 : PIECES <= 8 ? 2 : 1;

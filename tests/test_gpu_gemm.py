@@ -411,6 +411,19 @@ def test_short_register_staged_segments_stage_by_stage(N):
             _run_and_compare(A, B, inputs.F16, sk.SK_POLICY_DP, (32, 64, 64), out_dtype=sk.SK_F32, exact=True)
 
 
+def _shared_reduction_ran(r, dA, dB):
+    """Does a launch of the plan park the piece of the first tile's owner, as only the shared reduction does?"""
+    i = r.info
+    owner = (i["iters_per_tile"] - 1) // i["iters_per_wg"]
+    slot = owner if i["iters_per_tile"] % i["iters_per_wg"] == 0 else i["grid"]
+    base = (-r.ws.data_ptr()) % 256 + (i["grid"] + 1) * 128 + 384 + slot * i["blk_m"] * i["blk_n"] * 4
+    if base + 16 > r.ws.numel():
+        return False
+    r.ws[base:base + 16] = 255
+    r.run(dA, dB)
+    return not bool((r.ws[base:base + 16] == 255).all())
+
+
 # Shared reduction (every workgroup of a tile adds up a share of it): sizes at which it applies, with ranges that end with the
 # tiles and that straddle them, edge tiles, one and two round trips of 16 contributors, tiles of one and of eight units per workgroup.
 SHARED = [((256, 512, 4096), (64, 64, 128), sk.SK_BF16, sk.SK_BF16), ((700, 256, 2000), (64, 128, 64), sk.SK_BF16, sk.SK_F16),
@@ -433,7 +446,8 @@ def test_shared_reduction_same_bits_as_the_owners_and_counts_back_at_zero(shape,
         assert not flags.any()                   # the next launch, and another plan on this workspace, find the counts at zero
         err = G.rel_error(r.result(shared[0]), G.gemm_fp64(A, B, ODT[dtype]))
         assert err <= (TOL_32 if out == sk.SK_F32 else TOL_16), err
-        # the same plan with the least workspace: the owner's reduction, in the same order; and a time-out of the wait is survived
+        assert _shared_reduction_ran(r, dA, dB)
+        # the same plan with the least workspace: the owner's reduction, in the same order; and no wait that could time out
         info, slots = r.info, 256 * r.info["blk_m"] * r.info["blk_n"] * 4
         least = 257 * 128 + 384 + slots
         needs_more = info["iters_per_tile"] % info["iters_per_wg"] != 0
@@ -441,30 +455,17 @@ def test_shared_reduction_same_bits_as_the_owners_and_counts_back_at_zero(shape,
         base = (r.ws.data_ptr() + 255) // 256 * 256
         if needs_more:
             sk.sk_plan_set_workspace(r.plan, base, least)
+            assert not _shared_reduction_ran(r, dA, dB)
             owners = r.run(dA, dB)
             assert r.check() == sk.SK_OK
             assert all(torch.equal(d.view(torch.uint8), owners.view(torch.uint8)) for d in shared)
             sk.sk_plan_set_workspace(r.plan, base, sk.sk_workspace_bytes(r.plan))
         sk.sk_plan_set_spin_limit(r.plan, 0)
-        r.run(dA, dB)
-        assert r.check() in (sk.SK_OK, sk.SK_ERR_TIMEOUT)
+        assert torch.equal(r.run(dA, dB).view(torch.uint8), shared[0].view(torch.uint8)) and r.check() == sk.SK_OK
         sk.sk_plan_set_spin_limit(r.plan, 1 << 24)
         assert torch.equal(r.run(dA, dB).view(torch.uint8), shared[0].view(torch.uint8)) and r.check() == sk.SK_OK
     finally:
         r.close()
-
-
-def _shared_reduction_ran(r, dA, dB):
-    """Does a launch of the plan park the piece of the first tile's owner, as only the shared reduction does?"""
-    i = r.info
-    owner = (i["iters_per_tile"] - 1) // i["iters_per_wg"]
-    slot = owner if i["iters_per_tile"] % i["iters_per_wg"] == 0 else i["grid"]
-    base = (-r.ws.data_ptr()) % 256 + (i["grid"] + 1) * 128 + 384 + slot * i["blk_m"] * i["blk_n"] * 4
-    if base + 16 > r.ws.numel():
-        return False
-    r.ws[base:base + 16] = 255
-    r.run(dA, dB)
-    return not bool((r.ws[base:base + 16] == 255).all())
 
 
 # ... and with more workgroups of a tile than units, some of whose shares are empty, with and without ranges that straddle tiles

@@ -45,6 +45,26 @@ def test_static_scratch_entry_matches_sk_gemm_two_calls_second_smaller():
     _both(300, 512, 1040, sk.SK_POLICY_DP, None, 73)                      # no split tile: no scratch use at all
 
 
+def test_static_scratch_entry_without_room_for_the_slots_per_tile():
+    """264 slots of 256 x 256 with the shared reduction, 256 at the least: sk_gemm shares it, the static entry's owners reduce alone."""
+    M, N, K = 511, 777, 3203
+    A, B = inputs.uniform_pair(M, N, K, inputs.BF16, 74)
+    dA, dB = to_device(A), to_device(B)
+    r = Runner(M, N, K, sk.SK_POLICY_ALL_SK, (256, 256, 64), 256, inputs.BF16, sk.SK_F32)
+    try:
+        slot, most = 256 * 256 * 4, 257 * 128 + 384 + 256 * 256 * 256 * 4
+        assert sk.sk_workspace_bytes(r.plan) == most + 8 * slot
+        want = r.run(dA, dB).clone()
+        assert r.check() == sk.SK_OK
+        got = torch.full_like(want, -1)
+        sk.sk_gemm_static(dA.data_ptr(), dB.data_ptr(), got.data_ptr(), r.plan, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        assert G.rel_error(r.result(got), G.gemm_fp64(A, B, G.BF16)) <= 1e-4
+    finally:
+        r.close()
+
+
 def test_static_scratch_entry_refuses_what_does_not_fit():
     a = torch.zeros(1 << 20, dtype=torch.int16, device="cuda")
     stream = torch.cuda.current_stream().cuda_stream
