@@ -456,13 +456,13 @@ extern "C" int bloom_shape_key(const sk_plan_t* plan, uint32_t* key) {
 //    64 - 154 +2 .. -4; 256 x 256 behind two waves, 8 tiles +1 .. +5, 28 - 148 from 8 iterations on 0 .. -11, below +6 .. -2, behind any number from 32
 //    iterations on -1 .. -7; the others behind two, and tiles of at most 64 rows anywhere, lose up to 4 as often as they gain;
 //  - Stream-K plans with empty ranges: all tiles 0 .. -26 (182 plans, four of them +1 .. +4) while 32 to 240 workgroups are busy; fewer, all of one
-//    tile, +1 .. +5, as are 16-row tiles that more than 16 workgroups share (70 x 119 x 4092 7.4 -> 7.75 us);
+//    tile, +1 .. +5; 16-row tiles that 17 to 36 workgroups share -6 .. +8 (5 x 893 x 3328 8.4 -> 7.9 us, 70 x 120 x 4096 6.6 -> 7.0);
 //  - not where nearly all workgroups have work: 3840 x 4224 x 4096, 255 tiles, 107.1 -> 107.9 us.
 int sk_first_ids(const sk_plan_header& h) {
     if (h.xcd_remap != 1 || h.blk_n < 128) return 0;
     const int most = h.grid - h.grid / 16;
     if (h.sk_tiles > 0) {
-        if (h.dp_tiles > 0 || (h.blk_m < 32 && h.iters_per_tile > 16ll * h.iters_per_wg)) return 0;
+        if (h.dp_tiles > 0) return 0;
         const int busy = (int)((h.sk_iters + h.iters_per_wg - 1) / h.iters_per_wg);
         return busy >= 32 && busy <= most ? busy : 0;
     }

@@ -362,7 +362,8 @@ SPREAD = [((16 * 5, 128 * 7, 64), (16, 128, 64), 256, sk.SK_POLICY_DP, 0),      
           ((256 * 5, 256 * 7, 1024), (256, 256, 64), 16, sk.SK_POLICY_DP, 3),                # two full waves and 3, the loop across tiles
           ((64 * 10, 128 * 5, 384), (64, 128, 64), 256, sk.SK_POLICY_ALL_SK, 150),           # 150 of 256 ranges
           ((128 * 5, 128 * 9, 768), (128, 128, 64), 256, sk.SK_POLICY_ALL_SK, 180),          # 180, three iterations each
-          ((70, 119, 4092), (16, 128, 64), 256, sk.SK_POLICY_ALL_SK, 0)]                     # 160 ranges of five tiles
+          ((70, 119, 4092), (16, 128, 64), 256, sk.SK_POLICY_ALL_SK, 160),                   # 160, of five tiles, off the 16-byte grid
+          ((16, 128, 1984), (16, 128, 64), 256, sk.SK_POLICY_ALL_SK, 0)]                     # 31, all of one tile
 
 
 @pytest.mark.parametrize("shape,blk,grid,policy", [s[:4] for s in SPREAD])

@@ -48,7 +48,7 @@ def test_plans_that_run_the_spread_numbering_on_the_gpu_do_so(numbering, shape, 
     # less than one wave
     ((256 * 11, 256 * 20, 576), (256, 256, 64), DP, BF16, 220), ((64 * 115, 128 * 2, 576), (64, 128, 64), DP, BF16, 230), ((256 * 15, 256 * 17, 576), (256, 256, 64), DP, BF16, 0),
     ((32 * 8, 128 * 8, 1024), (32, 128, 64), DP, BF16, 64), ((32 * 8, 128 * 8, 960), (32, 128, 64), DP, BF16, 0), ((256 * 3, 256 * 5, 576), (256, 256, 64), DP, BF16, 0),
-    # Stream-K ranges of the lowest tile shared by more than 16 workgroups
-    ((70, 119, 4092), (16, 128, 64), SK, BF16, 0), ((112, 256, 896), (16, 128, 64), SK, BF16, 196)])
+    # Stream-K plans with empty ranges: by how many workgroups are busy
+    ((70, 119, 4092), (16, 128, 64), SK, BF16, 160), ((112, 256, 896), (16, 128, 64), SK, BF16, 196), ((16, 128, 1984), (16, 128, 64), SK, BF16, 0)])
 def test_where_the_numbering_is_spread(numbering, shape, blk, policy, dtype, dealt):
     assert int(numbering(*shape, policy, *blk, 256, dtype)) == dealt
