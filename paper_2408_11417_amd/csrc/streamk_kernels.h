@@ -1837,15 +1837,15 @@ struct KernelEntry {
 //    tiles, or N = 510, 9 iterations level to 2 % faster, and with the rows of A or of B 4-byte aligned, which arrive sooner, 9 - 14 1 - 5 % (103 x 334, 12, 7.17 ->
 //    6.92; 1302 x 273 x 610 6.81 -> 6.55; 690 x 244 with 16 4 % faster, 95 x 508 with 17 10 % slower); otherwise slower: 3 and 4 iterations 3 - 4 %, 160
 //    tiles, N = 1021, of 10 / 12 / 20 5 / 10 / 19 %, split plans 2 - 6 %;
-//  - 64 x 128, 12 to 400 tiles: 9 - 16 iterations 4 % faster to level (191 x 509, 10 / 12 / 16, 8.65 / 10.32 / 11.57 -> 8.37 / 10.04 / 11.22), 17 - 40
-//    2 % faster to level, 7 1 - 2 % slower, above 43 level to slower;
+//  - 64 x 128, 12 to 400 tiles: 9 - 24 iterations 5 % faster to 2 % slower (383 x 1021, 10 / 12 / 16, 8.79 / 10.45 / 11.69 -> 8.56 / 10.19 / 11.37; 288 plans of all
+//    alignments 0.9 % in the mean), 7 and from 33 on level to 2 % slower;
 //  - 8-bit 128 x 256, 12 to 400 tiles: from 8 iterations on 2 % faster to level (767 x 2045, 8 / 18, 17.43 / 29.30 -> 17.17 / 28.80), from 44 on level, below 8 1 - 4 % slower.
 template <class C> struct OneByOne : C { static constexpr bool STAGED_ROUNDS = false; };
 template <class C> constexpr bool MAY_TAKE_ONE_BY_ONE = C::FP8 ? C::BM == 128 && C::BN == 256 : (C::BM == 32 && C::BN == 64) || (C::BM == 64 && C::BN == 128 && C::NW == 8);
 inline bool takes_one_by_one(const sk_plan_header& h) {
     const int ipt = h.iters_per_tile;
     if (h.blk_n == 256) return ipt >= 8 && ipt < 44;
-    if (h.blk_n == 128) return ipt >= 9 && ipt <= 40;
+    if (h.blk_n == 128) return ipt >= 9 && ipt <= 24;
     const int near = h.tiles > 48 && h.tiles_n > 8 ? 8 : h.N % 2 && h.K % 2 ? 9 : 14;
     return ipt >= 5 && ipt <= (h.tiles_n > 64 ? 0 : h.tiles_n > 16 ? 7 : near);
 }
