@@ -1835,10 +1835,10 @@ struct KernelEntry {
 //  - 32 x 64: 5 - 8 iterations, N up to 1022, 4 to 512 tiles, 1 - 5 % faster (319 x 1021, 6 iterations, 6.04 -> 5.93, 103 x 334 5.85 -> 5.62, 1022 x 1020
 //    10.35 -> 9.98); a wider B, less of which is read twice, 5 - 7 to N = 2630 2 - 3 % faster, 31 x 1533 with 8 6 % slower, 32 x 8191 2 - 8 %; up to 48
 //    tiles, or N = 510, 9 iterations level to 2 % faster, and with the rows of A or of B 4-byte aligned, which arrive sooner, 9 - 14 1 - 5 % (103 x 334, 12, 7.17 ->
-//    6.92; 1302 x 273 x 610 6.81 -> 6.55; 690 x 244 with 16 4 % faster, 95 x 508 with 17 10 % slower); otherwise slower: 3 and 4 iterations 3 - 4 %, 160
+//    6.92; 1302 x 273 x 610 6.87 -> 6.68; 690 x 244 with 16 2 - 4 % faster, 95 x 508 with 17 10 % slower); otherwise slower: 3 and 4 iterations 3 - 4 %, 160
 //    tiles, N = 1021, of 10 / 12 / 20 5 / 10 / 19 %, split plans 2 - 6 %;
-//  - 64 x 128, 12 to 400 tiles: 9 - 24 iterations 5 % faster to 2 % slower (383 x 1021, 10 / 12 / 16, 8.79 / 10.45 / 11.69 -> 8.56 / 10.19 / 11.37; 288 plans of all
-//    alignments 0.9 % in the mean), 7 and from 33 on level to 2 % slower;
+//  - 64 x 128, 12 to 400 tiles: 9 - 24 iterations 5 % faster to 2 % slower (383 x 1021, 10 / 12 / 16, 8.81 / 10.43 / 11.70 -> 8.56 / 10.16 / 11.41; 288 plans of all
+//    alignments 0.9 % in the mean), 7 and from 33 on level to 2 % slower (379 x 1022 x 2110 17.0 -> 17.3);
 //  - 8-bit 128 x 256, 12 to 400 tiles: from 8 iterations on 2 % faster to level (767 x 2045, 8 / 18, 17.43 / 29.30 -> 17.17 / 28.80), from 44 on level, below 8 1 - 4 % slower.
 template <class C> struct OneByOne : C { static constexpr bool STAGED_ROUNDS = false; };
 template <class C> constexpr bool MAY_TAKE_ONE_BY_ONE = C::FP8 ? C::BM == 128 && C::BN == 256 : (C::BM == 32 && C::BN == 64) || (C::BM == 64 && C::BN == 128 && C::NW == 8);
